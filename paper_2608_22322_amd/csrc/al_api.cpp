@@ -129,13 +129,23 @@ al_status check_ws(void* ws, size_t ws_bytes, size_t need, const char* who) {
 struct FacPlan {
     std::vector<al::FacDesc> desc;  // 2-D tensors first, then 1-D
     int n2 = 0, n1 = 0;
-    int64_t total_units = 0, total_chunks = 0, whole_units = 0;
+    int64_t total_units = 0, total_ach = 0, total_mt = 0, rows_ach = 0;
+    int32_t ur = 256, any_whole = 0, any_edge = 0;
     int64_t total_blk[2] = {0, 0};
     size_t bytes = 0;
-    size_t rms_off = 0;
+    size_t index_off = 0, rms_off = 0;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Two wavefronts per SIMD. Measured on CAME over a 4-layer width-500 list (280 units of 256 rows, 2240 of
+// 32): 162 us with 1024 to 8192, 182 with 512; on Adafactor over a 12-layer width-768 list (2900 units of 256
+// rows): 501 us up to 2048, 521 with 4096 (units of 128 rows).
+constexpr int64_t kFacMinUnits = 2048;
+
+// Block of a factor vector's state (FP32 states have none: 256 elements per wavefront).
+int32_t fac_block(const al_state_spec& s) { return s.codec == AL_CODEC_FP32 ? 256 : s.block; }
+
 
 // Validate the tensor list and lay out the workspace: descriptor table, RMS
 // partials, then per-tensor regions. With ws == NULL only sizes are computed.
@@ -179,31 +189,45 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
             if ((st = check_unused(t.m, t.m_meta, "m", i)) != AL_OK) return st;
         }
     }
-    // 2-D tensors made of whole 256x256 units first (their units take the
-    // streaming kernels' guard-free layout), in list order within each group
-    std::stable_partition(twod.begin(), twod.end(),
-                          [&](int i) { return ts[i].rows % 256 == 0 && ts[i].cols % 256 == 0; });
+    // widths that are a multiple of 256 first (the apply passes take them by rows), in list order within
+    // each group
+    std::stable_partition(twod.begin(), twod.end(), [&](int i) { return ts[i].cols % 256 == 0; });
     P.n2 = (int)twod.size();
     P.n1 = (int)oned.size();
     const int ntot = P.n2 + P.n1;
     P.desc.resize(ntot);
+    // Unit rows: 256, halved down to 32 while the list has fewer than kFacMinUnits units (one wavefront
+    // each): a short list's passes are bound by the longest wavefront, not by memory. More, shorter units
+    // cost column partials (8 bytes per column and unit row), which a short list hardly notices.
+    for (;; P.ur /= 2) {
+        int64_t units = 0;
+        for (int i : twod) units += ((ts[i].rows + P.ur - 1) / P.ur) * ((ts[i].cols + 255) / 256);
+        if (units >= kFacMinUnits || P.ur == 32) break;
+    }
     for (int k = 0; k < P.n2; ++k) {
         const al_tensor& t = ts[twod[k]];
         al::FacDesc& d = P.desc[k];
-        d.nru = (int32_t)((t.rows + 255) / 256);
+        d.nru = (int32_t)((t.rows + P.ur - 1) / P.ur);
         d.ncu = (int32_t)((t.cols + 255) / 256);
         d.unit_begin = P.total_units;
         P.total_units += (int64_t)d.nru * d.ncu;
-        if (t.rows % 256 == 0 && t.cols % 256 == 0) P.whole_units = P.total_units;
-        d.chunk_begin = P.total_chunks;  // chunks only for widths that are not a multiple of 256
-        if (t.cols % 256 != 0) P.total_chunks += (t.rows * t.cols + 1023) / 1024;
-        const int64_t bv = vs.block, bc = came ? cs.block : vs.block;
+        d.ach_begin = P.total_ach;
+        const bool by_rows = t.cols % 256 == 0;
+        P.total_ach += by_rows ? ((t.rows + 255) / 256) * d.ncu * 32 : (t.rows * t.cols + al::kFacFlatChunk - 1) / al::kFacFlatChunk;
+        if (by_rows) P.rows_ach = P.total_ach;
+        if (by_rows && P.ur == 256 && t.rows >= 256) P.any_whole = 1;
+        if (!by_rows || P.ur != 256 || t.rows % 256 != 0) P.any_edge = 1;
+        d.mt_begin = P.total_mt;
+        P.total_mt += (t.rows + 63) / 64 + (t.cols + 63) / 64;
+        const int64_t bv = fac_block(vs), bc = came ? fac_block(cs) : bv;
         d.blk_begin[0] = P.total_blk[0];
         P.total_blk[0] += (t.rows + bv - 1) / bv + (t.cols + bv - 1) / bv;
         d.blk_begin[1] = P.total_blk[1];
         P.total_blk[1] += (t.rows + bc - 1) / bc + (t.cols + bc - 1) / bc;
     }
     size_t off = align256((size_t)ntot * sizeof(al::FacDesc));
+    P.index_off = off;
+    off += align256((size_t)ntot * al::kFacIndex * sizeof(int64_t));
     P.rms_off = off;
     off += align256((size_t)P.total_units * 16);
     auto take = [&](size_t nbytes) -> char* {
@@ -232,7 +256,7 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
         d.cc = t.cc;
         d.ccm = t.cc_meta;
         if (fac) {
-            // (hi, lo) pairs per unit and column / row; whole-unit tensors use the first half
+            // 16 bytes per partial as callers have sized it; the passes use one binary64 of them, packed
             d.colpart = reinterpret_cast<double*>(take((size_t)d.nru * t.cols * 16));
             d.rowpart = reinterpret_cast<double*>(take((size_t)d.ncu * t.rows * 16));
             d.rfac = reinterpret_cast<double*>(take((size_t)t.rows * 8));
@@ -243,8 +267,7 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
             }
             d.rtmp = reinterpret_cast<float*>(take((size_t)t.rows * 4));
             d.ctmp = reinterpret_cast<float*>(take((size_t)t.cols * 4));
-            const int64_t bmin = came && cs.block < vs.block ? cs.block : vs.block;
-            d.rsum = reinterpret_cast<double*>(take((size_t)((t.rows + bmin - 1) / bmin) * 16));
+            d.rsum = reinterpret_cast<double*>(take((size_t)((t.rows + 63) / 64) * 16));
         } else {
             d.nru = d.ncu = 0;
             const size_t n = (size_t)(t.rows * t.cols);
@@ -261,12 +284,23 @@ al::FacArgs fac_args(const FacPlan& P, char* ws) {
     al::FacArgs a;
     std::memset(&a, 0, sizeof(a));
     a.D = reinterpret_cast<const al::FacDesc*>(ws);
+    const int64_t* const x = reinterpret_cast<const int64_t*>(ws + P.index_off);
+    const size_t nt = P.desc.size();
+    a.unit_begins = x;
+    a.ach_begins = x + nt;
+    a.mt_begins = x + 2 * nt;
+    a.blk_begins[0] = x + 3 * nt;
+    a.blk_begins[1] = x + 4 * nt;
     a.rmspart = reinterpret_cast<double*>(ws + P.rms_off);
     a.n2 = P.n2;
     a.n1 = P.n1;
     a.total_units = P.total_units;
-    a.total_chunks = P.total_chunks;
-    a.whole_units = P.whole_units;
+    a.total_ach = P.total_ach;
+    a.total_mt = P.total_mt;
+    a.rows_ach = P.rows_ach;
+    a.any_whole = P.any_whole;
+    a.any_edge = P.any_edge;
+    a.ur = P.ur;
     a.total_blk[0] = P.total_blk[0];
     a.total_blk[1] = P.total_blk[1];
     a.cf = al::exp2_coef();
@@ -796,14 +830,14 @@ al_status al_adafactor_step(const al_tensor* tensors, int32_t nt, const al_adafa
     a.decay = 1.0 - cfg->lr * cfg->weight_decay;
     a.clip_d = cfg->clip_threshold;
     a.v_codec = cfg->v.codec;
-    a.v_block = cfg->v.block;
+    a.v_block = fac_block(cfg->v);
     a.v_floor = cfg->v.log_floor;
     a.exact_all = (cfg->flags & AL_FLAG_EXACT_SUMS) != 0;
     hipStream_t s = as_stream(stream);
     const int G = cfg->grad_dtype;
     hipError_t e;
-    if ((e = al::fac_copy_desc(P.desc.data(), (int)P.desc.size(), const_cast<al::FacDesc*>(a.D), s)) != hipSuccess ||
-        (e = al::launch_fac_marg_g2(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
+    if ((e = al::fac_copy_desc(P.desc.data(), (int)P.desc.size(), const_cast<al::FacDesc*>(a.D), const_cast<int64_t*>(a.unit_begins), s)) != hipSuccess ||
+        (e = al::launch_fac_marg(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
         (e = al::launch_fac_rms(a, G, s)) != hipSuccess || (e = al::launch_fac_clip(a, s)) != hipSuccess ||
         (e = al::launch_ada_apply(a, G, s)) != hipSuccess || (e = al::launch_ada_vec1d(a, G, s)) != hipSuccess)
         return hip_fail(e, "al_adafactor_step launch");
@@ -835,10 +869,10 @@ al_status al_came_step(const al_tensor* tensors, int32_t nt, const al_came_cfg* 
     a.decay = 1.0 - cfg->lr * cfg->weight_decay;
     a.clip_d = cfg->clip_threshold;
     a.v_codec = cfg->v.codec;
-    a.v_block = cfg->v.block;
+    a.v_block = fac_block(cfg->v);
     a.v_floor = cfg->v.log_floor;
     a.c_codec = cfg->conf.codec;
-    a.c_block = cfg->conf.block;
+    a.c_block = fac_block(cfg->conf);
     a.c_floor = cfg->conf.log_floor;
     a.m_codec = cfg->m.codec;
     a.m_block = cfg->m.codec == AL_CODEC_UF8 ? cfg->m.block : 256;
@@ -846,8 +880,8 @@ al_status al_came_step(const al_tensor* tensors, int32_t nt, const al_came_cfg* 
     hipStream_t s = as_stream(stream);
     const int G = cfg->grad_dtype;
     hipError_t e;
-    if ((e = al::fac_copy_desc(P.desc.data(), (int)P.desc.size(), const_cast<al::FacDesc*>(a.D), s)) != hipSuccess ||
-        (e = al::launch_fac_marg_g2(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
+    if ((e = al::fac_copy_desc(P.desc.data(), (int)P.desc.size(), const_cast<al::FacDesc*>(a.D), const_cast<int64_t*>(a.unit_begins), s)) != hipSuccess ||
+        (e = al::launch_fac_marg(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
         (e = al::launch_fac_rms(a, G, s)) != hipSuccess || (e = al::launch_fac_clip(a, s)) != hipSuccess ||
         (e = al::launch_came_res(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 1, G, s)) != hipSuccess ||
         (e = al::launch_came_apply(a, G, s)) != hipSuccess || (e = al::launch_came_vec1d(a, G, s)) != hipSuccess)

@@ -117,8 +117,8 @@ struct FacDesc {
     float* crm;
     void* cc;
     float* ccm;
-    double* colpart;  // [nru][cols] (hi, lo)
-    double* rowpart;  // [ncu][rows] (hi, lo)
+    double* colpart;  // [nru][cols]
+    double* rowpart;  // [ncu][rows]
     double* rfac;     // (R_i / mean R)^-1/2
     double* cfac;     // C_j^-1/2
     double* sr;       // CAME confidence factors
@@ -126,28 +126,33 @@ struct FacDesc {
     float* rtmp;      // staging: R (2-D) or V (1-D)
     float* ctmp;      // staging: C (2-D) or momentum (1-D)
     double* scal;     // [0] = clip divisor max(1, RMS / d)
-    double* rsum;     // (hi, lo) per block of the row factor: partial sums of R (or R')
-    int64_t unit_begin;   // first 256x256 unit of this tensor (2-D)
-    int64_t chunk_begin;  // first 1024-element chunk of this tensor (2-D, cols not a multiple of 256)
+    double* rsum;     // (hi, lo) per 64 elements of the row factor: partial sums of R (or R')
+    int64_t unit_begin;  // first ur x 256 unit of this tensor (2-D)
+    int64_t ach_begin;   // first apply chunk of this tensor (2-D)
+    int64_t mt_begin;    // first 64-element tile of this tensor's R then C (2-D)
     int64_t blk_begin[2];  // first code block of this tensor's R then C (role 0: V, role 1: confidence)
-    int32_t nru, ncu;     // units along rows / columns
-    int32_t pad_;
+    int32_t nru, ncu;    // units along rows / columns
 };
 
-constexpr int kFacCopyBatch = 16;
+constexpr int kFacFlatChunk = 1024;  // elements per apply chunk of matrices whose width is not a multiple of 256
+constexpr int kFacCopyBatch = 15;  // 15 x 256 bytes keep the argument segment under 4 KB
 struct FacDescBatch {
     int32_t count, offset;
     FacDesc d[kFacCopyBatch];
 };
 
+constexpr int kFacIndex = 5;  // packed search arrays behind the descriptor table
+
 struct FacArgs {
     const FacDesc* D;
+    // the descriptors' unit_begin, ach_begin, mt_begin and blk_begin, packed
+    const int64_t *unit_begins, *ach_begins, *mt_begins, *blk_begins[2];
     double* rmspart;      // [total_units] (hi, lo): partial sums of u^2
     int32_t n2, n1;       // 2-D tensors, 1-D tensors (D[n2 .. n2 + n1))
-    int64_t total_units, total_chunks;
-    // units [0, whole_units) belong to the tensors listed first, whose rows and
-    // columns are both multiples of 256 (every unit a full 256x256 tile)
-    int64_t whole_units;
+    int64_t total_units, total_ach, total_mt;
+    int64_t rows_ach;     // apply chunks [0, rows_ach): the tensors of widths that are a multiple of 256, listed first
+    int32_t ur;           // unit rows: 256, or 128 / 64 / 32 for lists of few units
+    int32_t any_whole, any_edge;  // some units are (are not) whole 256 x 256 units of a width that is a multiple of 256
     int64_t total_blk[2];  // code blocks over all 2-D tensors' R and C, per role
     double beta, omb;     // second-moment EMA: Adafactor beta2_t / CAME beta2, and 1 - beta
     double beta1, omb1;   // CAME momentum
@@ -161,8 +166,8 @@ struct FacArgs {
 
 hipError_t launch_diag_levels(int kind, const float* meta, int64_t nblocks, double* out, int grid_cap, hipStream_t s);
 
-hipError_t fac_copy_desc(const FacDesc* host, int count, FacDesc* dev, hipStream_t s);
-hipError_t launch_fac_marg_g2(const FacArgs& a, int grad_dtype, hipStream_t s);
+hipError_t fac_copy_desc(const FacDesc* host, int count, FacDesc* dev, int64_t* index, hipStream_t s);
+hipError_t launch_fac_marg(const FacArgs& a, int grad_dtype, hipStream_t s);
 hipError_t launch_fac_fin(const FacArgs& a, int role, int grad_dtype, hipStream_t s);
 hipError_t launch_fac_rms(const FacArgs& a, int grad_dtype, hipStream_t s);
 hipError_t launch_fac_clip(const FacArgs& a, hipStream_t s);

@@ -14,18 +14,13 @@
 // CAME adds: res (sums of (uhat - m)^2 + eps2 with the in-step momentum),
 // fin over the confidence, and apply (recompute uhat and m, encode m, update p).
 //
-// Marginal sums. A wavefront owns a 256x256 unit, walked as 16 groups of 16
-// rows x 4 tiles of 64 columns. It loads a 16x64 tile in the natural layout
-// (16 lanes x 4 columns x 4 rows, coalesced row segments), adds each term to
-// in-lane column accumulators, and stages its binary64 terms in LDS (8.4 KB
-// per wave, plus 4 KB of row accumulators: 12 waves per CU); 4 lanes then
-// sum each tile row out of LDS.
-// Each lane sums its terms in runs of at most 4 plain binary64 additions
-// (relative error <= 3u) accumulated double-double, so every partial is within
-// 3u of its exact sum. The finalize step keeps the fast sum only where that
-// cannot change the fp32 rounding of the state's EMA and otherwise sums the
-// element's row or column again exactly, so the fp32 states (and their codes)
-// are the ones of the exactly rounded means.
+// Marginal sums. The matrices are cut into units of a.ur rows x 256 columns
+// (ur = 256 for large lists, fewer rows for lists that would leave the chip
+// idle), one wavefront per unit. Every partial is one binary64 sum with a
+// proven relative error bound (below); the finalize step keeps the fast sum
+// only where that cannot change the fp32 rounding of the state's EMA and
+// otherwise sums the element's row or column again exactly, so the fp32 states
+// (and their codes) are the ones of the exactly rounded means.
 #include "al_codec_dev.hpp"
 #include "al_device.hpp"
 #include "al_internal.hpp"
@@ -33,28 +28,25 @@
 namespace al {
 
 // ------------------------------------------------------------------ helpers
-__device__ __forceinline__ int locate_unit(const FacDesc* D, int n, int64_t unit) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (D[mid].unit_begin <= unit)
-            lo = mid;
-        else
-            hi = mid - 1;
+// Largest i of [0, n) with b[i] <= x (b ascending, b[0] <= x), x wave-uniform:
+// scalar halvings down to 64 entries, then one load of those by the wavefront
+// (a list of up to 64 tensors takes one dependent load; the offsets are packed,
+// so it is a few cache lines).
+__device__ __forceinline__ int locate(const int64_t* b, int n, int64_t x) {
+    const __attribute__((address_space(4))) int64_t* const c = (const __attribute__((address_space(4))) int64_t*)b;
+    int lo = 0, len = n;
+    while (len > 64) {
+        const int half = len >> 1;
+        if (c[lo + half] <= x) {
+            lo += half;
+            len -= half;
+        } else {
+            len = half;
+        }
     }
-    return lo;
-}
-
-__device__ __forceinline__ int locate_chunk(const FacDesc* D, int n, int64_t chunk) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (D[mid].chunk_begin <= chunk)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
+    const int lane = threadIdx.x & 63;
+    const uint64_t le = __ballot(lane < len && to_g(b)[lo + (lane < len ? lane : 0)] <= x);
+    return lo + __builtin_popcountll(le) - 1;
 }
 
 // Global-address-space view of the data pointers of a descriptor (the
@@ -68,7 +60,7 @@ struct GD {
     gp<double> colpart, rowpart;
     gp<const double> rfac, cfac, sr, sc;
     gp<const double> scal;
-    int64_t rows, cols, unit_begin;
+    int64_t rows, cols, unit_begin, ach_begin;
     int32_t nru, ncu;
 };
 
@@ -88,6 +80,7 @@ __device__ __forceinline__ GD gview(const FacDesc& d) {
     v.rows = d.rows;
     v.cols = d.cols;
     v.unit_begin = d.unit_begin;
+    v.ach_begin = d.ach_begin;
     v.nru = d.nru;
     v.ncu = d.ncu;
     return v;
@@ -122,22 +115,12 @@ __device__ __forceinline__ float grad1(const void* g, int64_t e) {
         return reinterpret_cast<const float*>(g)[e];
 }
 
-// 4 consecutive gradients at element e (the caller guarantees alignment).
 template <int G>
-__device__ __forceinline__ void grad4(const void* g, int64_t e, float out[4]) {
-    if constexpr (G == G_BF16) {
-        const uint2 w = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(g) + e);
-        out[0] = bf16_to_f32(w.x & 0xFFFFu);
-        out[1] = bf16_to_f32(w.x >> 16);
-        out[2] = bf16_to_f32(w.y & 0xFFFFu);
-        out[3] = bf16_to_f32(w.y >> 16);
-    } else {
-        const float4 w = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(g) + e);
-        out[0] = w.x;
-        out[1] = w.y;
-        out[2] = w.z;
-        out[3] = w.w;
-    }
+__device__ __forceinline__ float grad_at_g(gp<const void> g, int64_t e) {
+    if constexpr (G == G_BF16)
+        return bf16_to_f32(g_as<const uint16_t>(g)[e]);
+    else
+        return g_as<const float>(g)[e];
 }
 
 // Decode element i of a vector state (runtime codec / block).
@@ -219,230 +202,34 @@ __device__ DD block_dd_sum(DD v, DD* sh) {
 }
 
 // --------------------------------------------------------------- descriptors
-__global__ void fac_desc_copy_kernel(const FacDescBatch b, FacDesc* dst) {
+// The packed first units / chunks / tiles / blocks (kFacIndex arrays of nt) go
+// behind the table, for the searches.
+__global__ void fac_desc_copy_kernel(const FacDescBatch b, FacDesc* dst, int64_t* index, int nt) {
     constexpr int W = sizeof(FacDesc) / 8;
     const int total = b.count * W;
     const uint64_t* src = reinterpret_cast<const uint64_t*>(b.d);
     uint64_t* out = reinterpret_cast<uint64_t*>(dst + b.offset);
     for (int i = threadIdx.x; i < total; i += blockDim.x) out[i] = src[i];
+    if (threadIdx.x < b.count) {
+        const FacDesc& d = b.d[threadIdx.x];
+        int64_t* const x = index + b.offset + threadIdx.x;
+        x[0] = d.unit_begin;
+        x[nt] = d.ach_begin;
+        x[2 * nt] = d.mt_begin;
+        x[3 * nt] = d.blk_begin[0];
+        x[4 * nt] = d.blk_begin[1];
+    }
 }
 
-hipError_t fac_copy_desc(const FacDesc* host, int count, FacDesc* dev, hipStream_t s) {
-    static_assert(sizeof(FacDesc) % 8 == 0, "descriptor size");
+hipError_t fac_copy_desc(const FacDesc* host, int count, FacDesc* dev, int64_t* index, hipStream_t s) {
+    static_assert(sizeof(FacDesc) % 8 == 0 && sizeof(FacDescBatch) <= 4096 - 64, "descriptor size");
     for (int off = 0; off < count; off += kFacCopyBatch) {
         FacDescBatch b;
         b.count = count - off < kFacCopyBatch ? count - off : kFacCopyBatch;
         b.offset = off;
         for (int i = 0; i < b.count; ++i) b.d[i] = host[off + i];
-        hipLaunchKernelGGL(fac_desc_copy_kernel, dim3(1), dim3(256), 0, s, b, dev);
+        hipLaunchKernelGGL(fac_desc_copy_kernel, dim3(1), dim3(256), 0, s, b, dev, index, count);
         hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-// ------------------------------------------------------- marginal sums of G2
-// Lane roles in a 16x64 tile of a 256x256 unit. Load layout: lane (lr, lc) =
-// (lane / 16, lane % 16) holds rows lr + 4i (i < 4), columns 4 lc .. 4 lc + 3
-// (16 lanes cover a coalesced 64-column row segment). Row layout: lane
-// (rrow, rq) = (lane / 4, lane % 4) sums row rrow, columns 16 rq .. 16 rq + 15
-// of the tile out of LDS. Column sums stay in the loading lanes across the
-// unit's rows; a row's partial is merged over its 4 lanes after the unit's 4
-// column tiles. Every wave owns one unit, so the kernel has no unit loop.
-constexpr int kTileRows = 16;
-
-// Raw gradient words of one lane's 4 rows x 4 columns of a tile (bf16 pairs or
-// fp32), loaded one tile ahead of the arithmetic; absent elements read as 0.
-template <int G>
-struct GRaw {
-    uint2 w[4];
-};
-template <>
-struct GRaw<G_F32> {
-    float4 w[4];
-};
-
-// Tile width TC = 64: 16 lanes per row, lane rows lr + 4i of a 16-row group;
-// TC = 128: 32 lanes per row, lane rows lr + 2i of an 8-row group.
-// lane_off = lr * cols + 4 lc, the lane's part of every element index (formed
-// once per unit), so each address is a wave-uniform base plus that offset.
-template <int G, bool FULL, int TC = 64>
-__device__ __forceinline__ void load_graw(GRaw<G>& r, const GD& d, int64_t r0, int64_t c0, int nr, int nc,
-                                          int rg, int ct, int lr, int lc, bool vec, int64_t lane_off) {
-    constexpr int LS = 256 / TC, TR = 4 * LS;
-    const int cc = ct * TC + 4 * lc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int rr = rg * TR + lr + LS * i;
-        const int64_t e = (r0 + rg * TR + LS * i) * d.cols + c0 + ct * TC + lane_off;
-        if constexpr (G == G_BF16) {
-            const gp<const uint16_t> g = g_as<const uint16_t>(d.g);
-            if (FULL || (rr < nr && vec && cc + 4 <= nc)) {
-                r.w[i] = ld_u2<false>(g_as<const void>(g + e));
-            } else {
-                uint32_t h[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (rr < nr && cc + j < nc) h[j] = g[e + j];
-                r.w[i] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-            }
-        } else {
-            const gp<const float> g = g_as<const float>(d.g);
-            if (FULL || (rr < nr && vec && cc + 4 <= nc)) {
-                r.w[i] = ld_f4<false>(g + e);
-            } else {
-                float h[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (rr < nr && cc + j < nc) h[j] = g[e + j];
-                r.w[i] = make_float4(h[0], h[1], h[2], h[3]);
-            }
-        }
-    }
-}
-
-template <int G>
-__device__ __forceinline__ void unpack_graw(const GRaw<G>& r, int i, float gv[4]) {
-    if constexpr (G == G_BF16) {
-        gv[0] = bf16_to_f32(r.w[i].x & 0xFFFFu);
-        gv[1] = bf16_to_f32(r.w[i].x >> 16);
-        gv[2] = bf16_to_f32(r.w[i].y & 0xFFFFu);
-        gv[3] = bf16_to_f32(r.w[i].y >> 16);
-    } else {
-        gv[0] = r.w[i].x;
-        gv[1] = r.w[i].y;
-        gv[2] = r.w[i].z;
-        gv[3] = r.w[i].w;
-    }
-}
-
-// Column tiles outermost, 16-row groups inside: the column sums of the current
-// 64-column tile stay in registers, each row's running sum over the column
-// tiles in LDS (owned by one lane), and the next tile's gradients are loaded
-// while the current one is summed.
-template <int G, bool FULL>
-__device__ __forceinline__ void marg_unit(const FacArgs& a, const GD& d, int64_t ru, int64_t cu, int nr_, int nc_,
-                                          bool vec_, double (*tile)[66], DD* racc) {
-    const int lane = threadIdx.x, lc = lane & 15, lr = lane >> 4, rrow = lane >> 2, rq = lane & 3;
-    const int64_t r0 = ru * 256, c0 = cu * 256;
-    const int nr = FULL ? 256 : nr_, nc = FULL ? 256 : nc_;
-    const bool vec = FULL || vec_;
-    const double eps1 = a.eps1;
-    const int nrg = (nr + kTileRows - 1) / kTileRows, nct = (nc + 63) / 64, total = nrg * nct;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) racc[lane + 64 * k] = DD{0.0, 0.0};
-    DD cacc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) cacc[j] = DD{0.0, 0.0};
-    GRaw<G> cur;
-    const int64_t lane_off = (int64_t)lr * d.cols + 4 * lc;
-    load_graw<G, FULL>(cur, d, r0, c0, nr, nc, 0, 0, lr, lc, vec, lane_off);
-    for (int it = 0; it < total; ++it) {
-        const int ct = it / nrg, rg = it - ct * nrg;
-        GRaw<G> nxt = cur;
-        if (it + 1 < total) {
-            const int ct1 = (it + 1) / nrg;
-            load_graw<G, FULL>(nxt, d, r0, c0, nr, nc, it + 1 - ct1 * nrg, ct1, lr, lc, vec, lane_off);
-        }
-        const int cc = ct * 64 + 4 * lc;
-        double gs[4] = {0.0, 0.0, 0.0, 0.0};  // the lane's 4 rows of each column, summed in row order
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float gv[4];
-            unpack_graw<G>(cur, i, gv);
-            double t[4] = {0.0, 0.0, 0.0, 0.0};
-            if (FULL || rg * kTileRows + lr + 4 * i < nr) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (FULL || cc + j < nc) t[j] = marg_term(gv[j], eps1);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) gs[j] += t[j];
-            // the binary64 terms are staged once for the row sums
-            double* tp = &tile[lr + 4 * i][4 * lc];
-            *reinterpret_cast<double2*>(tp) = make_double2(t[0], t[1]);
-            *reinterpret_cast<double2*>(tp + 2) = make_double2(t[2], t[3]);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) dd_add(cacc[j], gs[j]);
-        __syncthreads();
-        DD rsum{0.0, 0.0};
-        const int rr = rg * kTileRows + rrow;
-        const int cq = ct * 64 + 16 * rq;  // first column of this lane's quarter
-        if (FULL || (rr < nr && cq < nc)) {
-            if (FULL || cq + 16 <= nc) {
-#pragma unroll
-                for (int c = 0; c < 16; c += 4) {
-                    const double2 t0 = *reinterpret_cast<const double2*>(&tile[rrow][16 * rq + c]);
-                    const double2 t1 = *reinterpret_cast<const double2*>(&tile[rrow][16 * rq + c + 2]);
-                    dd_add(rsum, ((t0.x + t0.y) + t1.x) + t1.y);
-                }
-            } else {
-                for (int c = 0; c < nc - cq; ++c) dd_add(rsum, tile[rrow][16 * rq + c]);
-            }
-        }
-        rsum = dd_merge(rsum, dd_quad_xor<kDppQuadXor1>(rsum));
-        rsum = dd_merge(rsum, dd_quad_xor<kDppQuadXor2>(rsum));
-        if (rq == 0 && (FULL || rr < nr)) racc[rr] = dd_merge(racc[rr], rsum);
-        __syncthreads();
-        if (rg == nrg - 1) {
-            // column tile done: its column partials over the unit's rows
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                DD v = cacc[j];
-                v = dd_merge(v, dd_shfl_xor(v, 16));
-                v = dd_merge(v, dd_shfl_xor(v, 32));
-                const int col = cc + j;
-                if (lr == 0 && (FULL || col < nc)) {
-                    const gp<double> cp = d.colpart + 2 * (ru * d.cols + c0 + col);
-                    cp[0] = v.hi;
-                    cp[1] = v.lo;
-                }
-                cacc[j] = DD{0.0, 0.0};
-            }
-        }
-        cur = nxt;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int row = lane + 64 * k;
-        if (FULL || row < nr) {
-            const gp<double> rp = d.rowpart + 2 * (cu * d.rows + r0 + row);
-            rp[0] = racc[row].hi;
-            rp[1] = racc[row].lo;
-        }
-    }
-}
-
-// Interior units (256x256, width a multiple of 4) take a guard-free body.
-template <int G>
-__global__ __launch_bounds__(64) void fac_marg_g2_kernel(const FacArgs a, int64_t base) {
-    __shared__ __attribute__((aligned(16))) double tile[kTileRows][66];
-    __shared__ DD racc[256];
-    const int64_t unit = base + xcd_order(blockIdx.x, gridDim.x);
-    if (unit >= a.total_units) return;
-    const FacDesc& d = a.D[locate_unit(a.D, a.n2, unit)];
-    const int64_t u = unit - d.unit_begin;
-    const int64_t ru = u / d.ncu, cu = u % d.ncu;
-    const int nr = (int)(d.rows - ru * 256 < 256 ? d.rows - ru * 256 : 256);
-    const int nc = (int)(d.cols - cu * 256 < 256 ? d.cols - cu * 256 : 256);
-    const bool vec = (d.cols & 3) == 0;
-    if (nr == 256 && nc == 256 && vec)
-        marg_unit<G, true>(a, gview(d), ru, cu, nr, nc, vec, tile, racc);
-    else
-        marg_unit<G, false>(a, gview(d), ru, cu, nr, nc, vec, tile, racc);
-}
-
-// One 64-thread workgroup per unit of [begin, end); lists beyond 2^31 units
-// take several launches. Each kernel checks unit < end itself.
-template <class K>
-static hipError_t launch_per_unit(K kernel, const FacArgs& a, int64_t begin, int64_t end, hipStream_t s) {
-    constexpr int64_t kMaxGrid = int64_t(1) << 31;
-    for (int64_t base = begin; base < end; base += kMaxGrid) {
-        const int64_t left = end - base;
-        const int64_t grid = left < kMaxGrid ? left : kMaxGrid;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64), 0, s, a, base);
-        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -451,10 +238,10 @@ static hipError_t launch_per_unit(K kernel, const FacArgs& a, int64_t begin, int
 // One wavefront per unit (4 per 256-thread workgroup); lists beyond 2^33 units
 // take several launches.
 template <class K>
-static hipError_t launch_wave_per_unit(K kernel, const FacArgs& a, int64_t begin, int64_t end, hipStream_t s) {
+static hipError_t launch_wave_per_unit(K kernel, const FacArgs& a, hipStream_t s) {
     constexpr int64_t kMaxGrid = int64_t(1) << 31;
-    for (int64_t base = begin; base < end; base += 4 * kMaxGrid) {
-        const int64_t left = (end - base + 3) / 4;
+    for (int64_t base = 0; base < a.total_units; base += 4 * kMaxGrid) {
+        const int64_t left = (a.total_units - base + 3) / 4;
         const int64_t grid = left < kMaxGrid ? left : kMaxGrid;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, s, a, base);
         const hipError_t e = hipGetLastError();
@@ -464,26 +251,21 @@ static hipError_t launch_wave_per_unit(K kernel, const FacArgs& a, int64_t begin
 }
 
 // ------------------------------ marginal sums over whole units (streaming)
-// Units of the tensors whose rows and columns are both multiples of 256: no
-// guards, and every unit row starts 16-byte aligned. A batch is 8 unit rows.
-// Lane l = 32 h + q reads columns 8q .. 8q + 7 of rows 2k + h (k < 4) of the
+// Units of 256 x 256 in matrices whose width is a multiple of 256: no guards,
+// and every unit row starts 16-byte aligned. A batch is P::NR unit rows.
+// Lane l = 32 h + q reads columns 8q .. 8q + 7 of rows 2k + h of the
 // batch: 16 bytes of bf16 gradients per lane, one load instruction per pair of
-// unit rows, the next batch's loads issued before the current batch's
-// arithmetic. Rows: each lane adds its 8 terms pairwise (relative error <= 3u
-// for non-negative terms) and stages that partial in LDS; 8 lanes then finish
-// each row from 4 partials apiece (pairwise, then a quad and a half-row DPP
-// merge), so a row's partial over the unit has relative error <= 8u and needs
-// no further merge inside the unit. Columns: with all terms of a batch formed
-// at once (the second moment's terms), the loading lanes add them in plain runs
-// over 16 of their rows (<= 15u) and add the 8 runs of the unit (<= 7u more).
-// CAME's residual terms (uhat - m)^2 + eps2 are formed one row pair at a time
-// (they need the registers) and summed without eps2: each lane accumulates the
-// squares of its 128 rows' differences by fused multiply-adds (<= 128u, one
-// rounding per term) and its row partials likewise (8 terms), and the finalize
-// adds eps2 to the mean; the oracle's terms fl64(fl64(d^2) + eps2) are within
-// 2u of d^2 + eps2. The even- and odd-row halves merge at the end (1u): a
-// column partial has relative error <= 23u or <= 131u against the exact sum
-// of the terms. The finalize step's robustness margin covers these bounds.
+// unit rows, later batches' loads issued before the current batch's
+// arithmetic. Both sums take the terms as squares t^2 by fused multiply-adds
+// (g^2 for the second moment, (uhat - m)^2 for CAME's residual; one rounding
+// per term, u = 2^-53); the additive eps1 / eps2 joins the mean in the
+// finalize. Rows: a lane's 8 terms (<= 8u) are staged in LDS, and 4 or 8 lanes
+// finish each row pairwise and by DPP (<= 5u more): <= 13u. Columns of the
+// second moment: plain runs over 16 of the lane's rows, the 8 runs of the unit
+// added, the even- and odd-row halves merged (<= 25u); CAME's residual: one
+// plain sum over the lane's 128 rows and the merge (<= 129u). The oracle's
+// terms fl64(fl64(t^2) + eps) are within 2u of t^2 + eps. The finalize step's
+// robustness margin covers these bounds.
 constexpr int kWStride = 34;  // LDS stride of a staged row, in doubles (16-byte aligned rows)
 constexpr int kWRunRows = 32; // unit rows per plain column run (16 rows of each lane)
 
@@ -540,13 +322,11 @@ __device__ __forceinline__ void load_wbatch(WBatch<G, NR>& b, gp<const void> g, 
 
 // Shared part of the whole-unit marginal kernels, batches of P::NR unit rows
 // (4, 8 or 16). The policy P supplies the batch type, load(batch, rb) for the
-// rows from rb, and terms(batch, k, t): the 8 binary64 terms of the lane's
-// row 2k + h of that batch (with P::SQUARES, 8 values whose squares are the
-// terms, summed by fused multiply-adds); P::DEPTH batches are in flight (2: the next
-// batch's loads are issued before the current batch's arithmetic; 3: the
-// next two). Row partials go to rowpart, column partials to colpart, one
-// binary64 sum each (the other tensors' partials are (hi, lo) pairs); stage
-// holds NR x kWStride doubles.
+// rows from rb, and terms(batch, k, t): 8 binary64 values of the lane's row
+// 2k + h of that batch whose squares are the terms; P::DEPTH batches are in
+// flight (2: the next batch's loads are issued before the current batch's
+// arithmetic; 3: the next two). Row partials go to rowpart, column partials to
+// colpart, one binary64 sum each; stage holds 2 P::FR x kWStride doubles.
 template <class P>
 __device__ __forceinline__ void whole_unit_sums(const P& pol, const GD& d, int64_t ru, int64_t cu, double* stage) {
     // row partials are finished P::FR rows (FB batches) at a time
@@ -601,13 +381,17 @@ __device__ __forceinline__ void whole_unit_sums(const P& pol, const GD& d, int64
             for (int k = 0; k < NP; ++k) {
                 double t[8];
                 pol.terms(cur, k, t);
+                double rs = t[0] * t[0];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) cs[j] = k == 0 ? t[j] : cs[j] + t[j];
-                sb[(2 * k + h) * kWStride + q] = sum8(t);
+                for (int j = 0; j < 8; ++j) {
+                    cs[j] = k == 0 ? t[j] * t[j] : __builtin_fma(t[j], t[j], cs[j]);
+                    if (j > 0) rs = __builtin_fma(t[j], t[j], rs);
+                }
+                sb[(2 * k + h) * kWStride + q] = rs;
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) crun[j] += cs[j];
-        } else if constexpr (P::SQUARES) {
+        } else {
             // column sums and the lane's row partial take the squares by fused multiply-adds (one
             // rounding per term)
 #pragma unroll
@@ -619,23 +403,11 @@ __device__ __forceinline__ void whole_unit_sums(const P& pol, const GD& d, int64
                 for (int j = 0; j < 8; ++j) {
                     cacc[j] = __builtin_fma(t[j], t[j], cacc[j]);
                     if (j > 0) rs = __builtin_fma(t[j], t[j], rs);
-                    if (k & 1) __asm__ volatile("" : "+v"(cacc[j]));
-                }
-                sb[(2 * k + h) * kWStride + q] = rs;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < NP; ++k) {
-                double t[8];
-                pol.terms(cur, k, t);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    cacc[j] += t[j];
                     // two row pairs' terms live at a time: without the fence the compiler forms all terms
                     // of the batch before the column additions
                     if (k & 1) __asm__ volatile("" : "+v"(cacc[j]));
                 }
-                sb[(2 * k + h) * kWStride + q] = sum8(t);
+                sb[(2 * k + h) * kWStride + q] = rs;
             }
         }
         // the stages belong to this wavefront alone and its LDS accesses
@@ -714,12 +486,12 @@ struct WholeLane {
     int h, q;
 };
 
-__device__ __forceinline__ WholeLane whole_lane(const GD& d, int64_t u) {
+__device__ __forceinline__ WholeLane whole_lane(const GD& d, int64_t ru, int64_t cu) {
     WholeLane w;
     w.h = (int)(threadIdx.x >> 5) & 1;
     w.q = (int)threadIdx.x & 31;
-    w.r0 = (u / d.ncu) * 256;
-    w.c0 = (u % d.ncu) * 256;
+    w.r0 = ru * 256;
+    w.c0 = cu * 256;
     w.cols = d.cols;
     w.lo = (uint32_t)(w.h * d.cols + 8 * w.q);
     return w;
@@ -730,68 +502,256 @@ __device__ __forceinline__ gp<const void> unit_base(const GD& d, const WholeLane
     return g_as<const void>(g_as<const uint8_t>(d.g) + (G == G_BF16 ? 2 : 4) * (w.r0 * w.cols + w.c0));
 }
 
-// Terms of the second moment's marginals: fl64(g^2 + eps1).
+// Terms of the second moment's marginals: g^2 (exact in binary64).
 template <int G>
 struct MargTerms {
     // 8-row batches, all terms of a batch at once: the cheap terms gain more from independent work per
-    // wave than from occupancy (200 registers, 2 waves per SIMD: 2.53 against 2.68 ms on the 7B list)
+    // wave than from occupancy (2 waves per SIMD)
     static constexpr int NR = 8;
     static constexpr int FR = NR;
     static constexpr bool ILP = true;
-    static constexpr bool SQUARES = false;
     static constexpr int DEPTH = 2;
     using Batch = WBatch<G, NR>;
     gp<const void> gu;
     int64_t cols;
     uint32_t lo;
-    double eps1;
     __device__ void load(Batch& b, int rb) const { load_wbatch<G, NR>(b, gu, rb, cols, lo); }
     __device__ void terms(const Batch& b, int k, double t[8]) const {
         float gv[8];
         unpack8<G>(b.r[k], gv);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] = marg_term(gv[j], eps1);
+        for (int j = 0; j < 8; ++j) t[j] = (double)gv[j];
+    }
+};
+
+// ------------------------------------------------------------- edge units
+// Every other unit: ragged rows or columns, widths of any alignment, and the
+// units of fewer rows that short lists are cut into. Lane l = 32 h + q takes the
+// 8 columns from cs = min(c0 + 8q, cols - 8) of rows 2k + h of each 4-row batch,
+// so every access stays inside its row (wide loads at the element's own
+// alignment); the first sh = c0 + 8q - cs columns of a shifted lane belong to the
+// lane before it and are left out, as is everything of a lane past the edge
+// (sh >= 8). Rows past the unit's last repeat it and are left out. Two batches
+// are in flight ahead of the one being formed. Sums, bounds and the staging of
+// the row partials are those of the whole units (columns in runs of 16 rows).
+// Matrices narrower than 8 columns are summed element by element, lane by row.
+// A short list is bound by its longest wavefront, so its units are 32 to 128 rows
+// high (fac_plan). Measured on a 4-layer list of width 500 (fp32 gradients, UF8
+// momentum): marginals 118 -> 14 us, RMS 151 -> 14, residual 338 -> 25 against
+// 256-row units of 16 x 64 tiles with double-double sums and guarded loads.
+typedef uint32_t ua_u4 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float ua_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t ua_u2 __attribute__((ext_vector_type(2), aligned(1)));
+
+template <int G>
+__device__ __forceinline__ void load8_ua(Raw8<G>& r, gp<const void> g, int64_t e) {
+    if constexpr (G == G_BF16) {
+        const ua_u4 x = *g_as<const ua_u4>(g_as<const uint16_t>(g) + e);
+        r.w = make_uint4(x.x, x.y, x.z, x.w);
+    } else {
+        const gp<const float> f = g_as<const float>(g) + e;
+        const ua_f4 x = *g_as<const ua_f4>(f), y = *g_as<const ua_f4>(f + 4);
+        r.a = make_float4(x.x, x.y, x.z, x.w);
+        r.b = make_float4(y.x, y.y, y.z, y.w);
+    }
+}
+
+struct EdgeLane {
+    int64_t r0, cs, cols;
+    int nr, h, q, sh;
+};
+
+__device__ __forceinline__ EdgeLane edge_lane(const GD& d, int ur, int64_t ru, int64_t cu) {
+    EdgeLane w;
+    w.h = (int)(threadIdx.x >> 5) & 1;
+    w.q = (int)threadIdx.x & 31;
+    w.r0 = ru * ur;
+    w.nr = (int)(d.rows - w.r0 < ur ? d.rows - w.r0 : ur);
+    w.cols = d.cols;
+    const int64_t c = cu * 256 + 8 * w.q;
+    w.cs = c < d.cols - 8 ? c : d.cols - 8;
+    w.sh = c - w.cs < 8 ? (int)(c - w.cs) : 8;
+    return w;
+}
+
+constexpr int kEdgeNR = 4;   // rows per batch
+constexpr int kEdgeFR = 16;  // rows per finish group and column run
+
+// Batches 0 .. nb - 1 with two in flight: load(batch, i) for i < nb (the last
+// ones load batch nb - 1 again, so that the loads are not conditional), step(batch, i).
+template <class Batch, class L, class S>
+__device__ __forceinline__ void edge_batches(int nb, L load, S step) {
+    Batch A, B, C;
+    load(A, 0);
+    load(B, 1 < nb ? 1 : nb - 1);
+#pragma unroll 1
+    for (int bi = 0;;) {
+        load(C, bi + 2 < nb ? bi + 2 : nb - 1);
+        step(A, bi);
+        if (++bi >= nb) break;
+        load(A, bi + 2 < nb ? bi + 2 : nb - 1);
+        step(B, bi);
+        if (++bi >= nb) break;
+        load(B, bi + 2 < nb ? bi + 2 : nb - 1);
+        step(C, bi);
+        if (++bi >= nb) break;
+    }
+}
+
+// P: Batch, load(batch, row) for the lane's row of each pair (row already
+// clamped), terms(batch, k, ok, t): 8 values whose squares are the terms, zero
+// where left out (ok: the row is inside the unit).
+template <class P>
+__device__ __forceinline__ void edge_unit_sums(const P& pol, const GD& d, const EdgeLane& w, int64_t ru, int64_t cu,
+                                               double* stage) {
+    constexpr int NR = kEdgeNR, NP = NR / 2, FR = kEdgeFR;
+    const int lane = threadIdx.x & 63, h = w.h, q = w.q, nr = w.nr;
+    double cacc[8], crun[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) cacc[j] = crun[j] = 0.0;
+    const int nb = (nr + NR - 1) / NR;
+    auto load = [&](typename P::Batch& b, int bi) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int row = NR * bi + 2 * k + h;
+            pol.load(b, k, row < nr ? row : nr - 1);
+        }
+    };
+    auto step = [&](const typename P::Batch& b, int bi) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int row = NR * bi + 2 * k + h;
+            double t[8];
+            pol.terms(b, k, row < nr, t);
+            double rs = t[0] * t[0];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                crun[j] = __builtin_fma(t[j], t[j], crun[j]);
+                if (j > 0) rs = __builtin_fma(t[j], t[j], rs);
+                if (k & 1) __asm__ volatile("" : "+v"(crun[j]));  // two row pairs' terms live at a time
+            }
+            stage[(row & (FR - 1)) * kWStride + q] = rs;
+        }
+        if (((bi + 1) * NR) % FR != 0 && bi + 1 < nb) return;
+        // a group of 16 rows is staged: 4 lanes finish each row from 8 partials apiece
+        __builtin_amdgcn_wave_barrier();
+        const int rrow = lane >> 2, rpart = lane & 3, row = (bi * NR & ~(FR - 1)) + rrow;
+        const double2* st = reinterpret_cast<const double2*>(stage + rrow * kWStride + 8 * rpart);
+        const double2 p0 = st[0], p1 = st[1], p2 = st[2], p3 = st[3];
+        double rs = ((p0.x + p0.y) + (p1.x + p1.y)) + ((p2.x + p2.y) + (p3.x + p3.y));
+        rs += dpp_d<kDppQuadXor1>(rs);
+        rs += dpp_d<kDppQuadXor2>(rs);
+        if (rpart == 0 && row < nr) d.rowpart[cu * d.rows + w.r0 + row] = rs;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            cacc[j] += crun[j];
+            crun[j] = 0.0;
+        }
+    };
+    edge_batches<typename P::Batch>(nb, load, step);
+    // the two halves hold the even and the odd rows of the same columns
+    const gp<double> cp = d.colpart + (ru * w.cols + w.cs);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        cacc[j] += __shfl_xor(cacc[j], 32);
+        if ((j < 4) == (h == 0) && j >= w.sh) cp[j] = cacc[j];
+    }
+}
+
+// Matrices narrower than 8 columns: lane l takes rows l, l + 64, .. of the unit
+// (all columns); term(row, column) is the value whose square is summed. Row
+// sums are chains of at most 7, column sums of at most 4 terms and a butterfly.
+template <class T>
+__device__ __forceinline__ void narrow_unit_sums(const GD& d, int ur, int64_t ru, T term) {
+    const int lane = threadIdx.x & 63;
+    const int64_t r0 = ru * ur;
+    const int nr = (int)(d.rows - r0 < ur ? d.rows - r0 : ur), nc = (int)d.cols;
+    double cs[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int r = lane; r < nr; r += 64) {
+        double rs = 0.0;
+#pragma unroll
+        for (int j = 0; j < 7; ++j)
+            if (j < nc) {
+                const double t = term(r0 + r, j);
+                rs = __builtin_fma(t, t, rs);
+                cs[j] = __builtin_fma(t, t, cs[j]);
+            }
+        d.rowpart[r0 + r] = rs;
+    }
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) cs[j] += __shfl_xor(cs[j], m);
+        if (lane == 0 && j < nc) d.colpart[ru * d.cols + j] = cs[j];
+    }
+}
+
+// The whole-unit body takes this unit.
+__device__ __forceinline__ bool whole_unit(const FacArgs& a, const GD& d, int64_t ru) {
+    return a.ur == 256 && (d.cols & 255) == 0 && d.rows - ru * 256 >= 256;
+}
+
+template <int G>
+struct EdgeMarg {
+    struct Batch {
+        Raw8<G> r[kEdgeNR / 2];
+    };
+    gp<const void> g;
+    int64_t e0, cols;  // element of the lane's first column in the unit's first row
+    int sh;
+    __device__ void load(Batch& b, int k, int row) const { load8_ua<G>(b.r[k], g, e0 + row * cols); }
+    __device__ void terms(const Batch& b, int k, bool ok, double t[8]) const {
+        float gv[8];
+        unpack8<G>(b.r[k], gv);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t[j] = (double)(((j >= sh) & ok) ? gv[j] : 0.0f);
     }
 };
 
 // One wavefront per unit, 4 per 256-thread workgroup (each with its own
 // LDS stage), as in the other streaming kernels.
-__device__ __forceinline__ int64_t whole_unit_of_wave(int64_t base) {
+__device__ __forceinline__ int64_t unit_of_wave(int64_t base) {
     return base + xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
 template <int G>
-__global__ __launch_bounds__(256) void fac_marg_whole_kernel(const FacArgs a, int64_t base) {
+__global__ __launch_bounds__(256) void fac_marg_kernel(const FacArgs a, int64_t base) {
     __shared__ __attribute__((aligned(16))) double stages[4][2 * MargTerms<G>::NR * kWStride];
+    static_assert(2 * MargTerms<G>::NR >= kEdgeFR, "the edge units' stage");
     double* stage = stages[threadIdx.x >> 6];
-    const int64_t unit = whole_unit_of_wave(base);
-    if (unit >= a.whole_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    const WholeLane w = whole_lane(d, unit - d.unit_begin);
-    const MargTerms<G> pol{unit_base<G>(d, w), w.cols, w.lo, a.eps1};
-    whole_unit_sums(pol, d, w.r0 / 256, w.c0 / 256, stage);
+    const int64_t unit = unit_of_wave(base);
+    if (unit >= a.total_units) return;
+    const GD d = gview(a.D[locate(a.unit_begins, a.n2, unit)]);
+    const int64_t u = unit - d.unit_begin, ru = u / d.ncu, cu = u % d.ncu;
+    if (whole_unit(a, d, ru)) {
+        const WholeLane w = whole_lane(d, ru, cu);
+        const MargTerms<G> pol{unit_base<G>(d, w), w.cols, w.lo};
+        whole_unit_sums(pol, d, ru, cu, stage);
+    } else if (d.cols >= 8) {
+        const EdgeLane w = edge_lane(d, a.ur, ru, cu);
+        const EdgeMarg<G> pol{d.g, w.r0 * w.cols + w.cs, w.cols, w.sh};
+        edge_unit_sums(pol, d, w, ru, cu, stage);
+    } else {
+        narrow_unit_sums(d, a.ur, ru, [&](int64_t i, int64_t j) { return (double)grad_at_g<G>(d.g, i * d.cols + j); });
+    }
 }
 
-hipError_t launch_fac_marg_g2(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.total_units == 0) return hipSuccess;
-    hipError_t e;
-    if (grad_dtype == G_BF16) {
-        if ((e = launch_wave_per_unit(fac_marg_whole_kernel<G_BF16>, a, 0, a.whole_units, s)) != hipSuccess) return e;
-        return launch_per_unit(fac_marg_g2_kernel<G_BF16>, a, a.whole_units, a.total_units, s);
-    }
-    if ((e = launch_wave_per_unit(fac_marg_whole_kernel<G_F32>, a, 0, a.whole_units, s)) != hipSuccess) return e;
-    return launch_per_unit(fac_marg_g2_kernel<G_F32>, a, a.whole_units, a.total_units, s);
+hipError_t launch_fac_marg(const FacArgs& a, int grad_dtype, hipStream_t s) {
+    if (grad_dtype == G_BF16) return launch_wave_per_unit(fac_marg_kernel<G_BF16>, a, s);
+    return launch_wave_per_unit(fac_marg_kernel<G_F32>, a, s);
 }
 
 // ------------------------------------------------------------- finalize
 // role 0: second moment (EMA beta, codes vr/vc, factors rfac/cfac);
 // role 1: CAME confidence (EMA beta3, codes cr/cc, factors sr/sc).
-// fin_block: one wavefront per code block of a factor vector (R blocks, then C
-// blocks, of every 2-D tensor): merge the unit partials of each element into
-// its mean, EMA with the decoded old value, round to fp32, re-encode the
-// block; R blocks also leave their double-double sum for mean(R), C blocks
-// their factors C_j^-1/2. fin_rows: one workgroup per tensor merges the R
-// block sums in order into mean(R) and writes r_i = (R_i / mean R)^-1/2.
+// fac_mean: one workgroup per 64 elements of a factor vector (R tiles, then C
+// tiles, of every 2-D tensor): its four wavefronts merge every fourth unit
+// partial of each element (a column of a tall matrix has hundreds), then EMA of
+// the mean with the decoded old value, rounded to fp32; R tiles also leave their
+// double-double sum for mean(R). fac_enc: re-encodes each code block and forms
+// the factors C_j^-1/2 and r_i = (R_i / mean R)^-1/2 (each wavefront merges the
+// R tile sums itself).
 struct FinRole {
     int codec, B;
     void *rc, *cc;
@@ -815,18 +775,6 @@ __device__ __forceinline__ FinRole fin_role(const FacArgs& a, const FacDesc& d, 
     r.omb = role ? a.omb3 : a.omb;
     r.lf = role ? a.c_floor : a.v_floor;
     return r;
-}
-
-__device__ __forceinline__ int locate_blk(const FacDesc* D, int n, int64_t blk, int role) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (D[mid].blk_begin[role] <= blk)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
 }
 
 // fl32(y) is the same for every binary64 y' within tol of y >= 0: y lies
@@ -882,268 +830,258 @@ __device__ DD exact_line_sum(const FacArgs& a, const FacDesc& d, int role, bool 
 
 // Relative distance from an fp32 rounding midpoint below which the EMA value
 // from the fast partial sums may round differently from the one from the exact
-// sum. A partial is within 131u (u = 2^-53) of its exact sum: the whole-unit
-// kernels' column partials (the second moment's: plain runs of 16 binary64
-// additions of non-negative terms, 8 runs added, two halves merged, 23u;
-// CAME's residual: fused multiply-add sums of 128 squared differences per
-// lane, two halves merged, eps2 added to the mean, 131u against the sum of
-// the oracle's terms; their row partials: 16u), the other units' runs of at
-// most 4 (3u) accumulated double-double; the partials are merged
-// double-double, and the mean, eps2 and the EMA add at most 5u. 32u bounds
-// the second moment's total (role 0), 160u CAME's confidence (role 1); an EMA
-// value that close to a midpoint is about one in ten million (one in a
-// million) of the elements (the exact sum of its line is then taken).
-constexpr double kRobustTol[2] = {32.0 * 0x1p-53, 160.0 * 0x1p-53};
+// sum. A partial is within 25u (u = 2^-53; second moment) or 129u (CAME's
+// residual) of its exact sum of squares, the oracle's terms are within 2u of
+// ours plus eps, the partials are merged double-double, and the mean, eps and
+// the EMA add at most 6u. 40u bounds the second moment's total (role 0), 160u
+// CAME's confidence (role 1); an EMA value that close to a midpoint is about
+// one in ten million (one in a million) of the elements (the exact sum of its
+// line is then taken).
+constexpr double kRobustTol[2] = {40.0 * 0x1p-53, 160.0 * 0x1p-53};
+constexpr int kMeanTile = 64;  // elements per workgroup of fac_mean
 
 template <int G>
-__global__ __launch_bounds__(256) void fac_fin_block_kernel(const FacArgs a, int role) {
-    const int lane = threadIdx.x & 63;
-    const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (blk >= a.total_blk[role]) return;
-    const FacDesc& d = a.D[locate_blk(a.D, a.n2, blk, role)];
+__global__ __launch_bounds__(256) void fac_mean_kernel(const FacArgs a, int role) {
+    __shared__ DD part[4][64];
+    __shared__ double ysh[64];
+    __shared__ uint64_t pend_sh;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t tile = blockIdx.x;
+    const FacDesc& d = a.D[locate(a.mt_begins, a.n2, tile)];
     const FinRole R = fin_role(a, d, role);
-    const int64_t lb = blk - d.blk_begin[role];
-    const int64_t nbr = (d.rows + R.B - 1) / R.B;
-    const bool isrow = lb < nbr;
+    const int64_t lt = tile - d.mt_begin, nrt = (d.rows + kMeanTile - 1) / kMeanTile;
+    const bool isrow = lt < nrt;
     const int64_t n = isrow ? d.rows : d.cols;
-    const int64_t b = isrow ? lb : lb - nbr;
-    const int64_t s = b * R.B, e = s + R.B < n ? s + R.B : n;
-    void* codes = isrow ? R.rc : R.cc;
-    float* meta = isrow ? R.rm : R.cm;
-    float* x = isrow ? d.rtmp : d.ctmp;
+    const int64_t s = (isrow ? lt : lt - nrt) * kMeanTile, i = s + lane;
+    const bool act = i < n;
+    // 1. the element's partials, every fourth by this wavefront (their loads do not depend on the
+    // running sum: unrolled, they are issued ahead)
+    DD acc{0.0, 0.0};
+    if (act) {
+        const int np = isrow ? d.ncu : d.nru;
+        const gp<const double> pp = to_g((const double*)(isrow ? d.rowpart : d.colpart)) + i;
+#pragma unroll 8
+        for (int k = w; k < np; k += 4) dd_add(acc, pp[(int64_t)k * n]);
+    }
+    part[w][lane] = acc;
+    __syncthreads();
+    // 2. EMA of the mean; where the partials' error could change its fp32 rounding (or with exact_all),
+    // the element's row or column is summed again, exactly, by one of the wavefronts
     const double cnt = (double)(isrow ? d.cols : d.rows);
-    const bool whole = d.unit_begin < a.whole_units;  // the tensor's units are all whole
-    // 1. EMA of the means (each lane handles the elements it encodes). The
-    // marginal kernels' partials are within 3u of the exact sums; where that
-    // could change the fp32 rounding of the EMA (or with exact_all), the
-    // wavefront sums the element's row or column again, exactly.
-    const int64_t nk = (e - s + 63) / 64;
-    for (int64_t k = 0; k < nk; ++k) {
-        const int64_t i = s + lane + 64 * k;
-        const bool act = i < e;
-        float old = 0.0f;
+    float old = 0.0f;
+    if (w == 0) {
         double y = 0.0;
         if (act) {
-            DD acc{0.0, 0.0};
-            // the partials' loads do not depend on the running sum: unrolled, they are issued ahead
-            // (the embedding's column blocks merge 125 row-unit partials per element)
-            // whole-unit tensors' partials are single binary64 sums, the others' (hi, lo) pairs
-            const int st = whole ? 1 : 2;
-            if (isrow) {
-#pragma unroll 8
-                for (int cu = 0; cu < d.ncu; ++cu) {
-                    const double* rp = d.rowpart + st * ((int64_t)cu * d.rows + i);
-                    acc = dd_merge(acc, DD{rp[0], whole ? 0.0 : rp[1]});
-                }
-            } else {
-#pragma unroll 8
-                for (int ru = 0; ru < d.nru; ++ru) {
-                    const double* cp = d.colpart + st * ((int64_t)ru * d.cols + i);
-                    acc = dd_merge(acc, DD{cp[0], whole ? 0.0 : cp[1]});
-                }
-            }
-            old = vec_decode(R.codec, R.B, codes, meta, i, a.cf);
-            // whole-unit residual partials sum (uhat - m)^2 alone: eps2 joins the mean
-            const double mean = role == 1 && whole ? dd_value(acc) / cnt + a.eps2 : dd_value(acc) / cnt;
-            y = R.beta * (double)old + R.omb * mean;
+            acc = dd_merge(dd_merge(part[0][lane], part[1][lane]), dd_merge(part[2][lane], part[3][lane]));
+            old = vec_decode(R.codec, R.B, isrow ? R.rc : R.cc, isrow ? R.rm : R.cm, i, a.cf);
+            y = R.beta * (double)old + R.omb * (dd_value(acc) / cnt + (role ? a.eps2 : a.eps1));
         }
         const bool robust = !act || (!a.exact_all && f32_round_robust(y, kRobustTol[role] * y));
-        uint64_t pend = __ballot(!robust);
-        while (pend) {
+        const uint64_t pend = __ballot(!robust);
+        ysh[lane] = y;
+        if (lane == 0) pend_sh = pend;
+    }
+    __syncthreads();
+    uint64_t pend = pend_sh;
+    if (pend) {
+        for (int k = 0; pend; ++k, pend &= pend - 1) {
+            if ((k & 3) != w) continue;
             const int src = __builtin_ctzll(pend);
-            pend &= pend - 1;
-            const DD S = exact_line_sum<G>(a, d, role, isrow, s + src + 64 * k, lane);
-            if (lane == src) y = R.beta * (double)old + R.omb * (dd_value(S) / cnt);
+            const DD S = exact_line_sum<G>(a, d, role, isrow, s + src, lane);
+            if (lane == 0) ysh[src] = dd_value(S) / cnt;  // the mean; the EMA follows below
         }
-        if (act) x[i] = (float)y;
+        __syncthreads();
     }
-    __threadfence_block();  // the encode below reads x[] back (each lane its own elements)
-    // 2. re-encode the block
-    if (R.codec == FP32) {
-        for (int64_t i = s + lane; i < e; i += 64) reinterpret_cast<float*>(codes)[i] = x[i];
-    } else {
-        uint32_t mn = 0xFFFFFFFFu, mx = 0u;
-        for (int64_t i = s + lane; i < e; i += 64) {
-            mn = OpMin::f(mn, pos_min_key(x[i]));
-            mx = OpMax::f(mx, pos_max_key(x[i]));
-        }
-        mn = group_reduce<OpMin, 64>(mn);
-        mx = group_reduce<OpMax, 64>(mx);
-        const ALFit f = al_fit(mn, mx, R.lf);
-        if (lane == 0) {
-            meta[2 * b] = f.any ? (float)f.lmin : 0.0f;
-            meta[2 * b + 1] = f.any ? (float)f.delta : 0.0f;
-        }
-        const int levels = R.codec == AL16 ? 65534 : 254;
-        const ALEnc enc = al_enc_params(f.lmin, f.any ? (double)levels / f.delta : 1.0);
-        for (int64_t i = s + lane; i < s + R.B; i += 64) {
-            const float v = i < e ? x[i] : 0.0f;
-            if (R.codec == AL16)
-                reinterpret_cast<uint16_t*>(codes)[i] = (uint16_t)al_encode_fast<65534>(v, enc);
-            else
-                reinterpret_cast<uint8_t*>(codes)[i] = (uint8_t)al_encode_fast<254>(v, enc);
-        }
-    }
-    // 3. R: block sum for mean(R); C: factors
+    if (w != 0) return;
+    double y = ysh[lane];
+    if ((pend_sh >> lane) & 1) y = R.beta * (double)old + R.omb * y;
+    const float x = act ? (float)y : 0.0f;
+    if (act) (isrow ? d.rtmp : d.ctmp)[i] = x;
     if (isrow) {
-        DD acc{0.0, 0.0};
-        for (int64_t i = s + lane; i < e; i += 64) dd_add(acc, (double)x[i]);
-        acc = dd_wave_sum(acc);
+        const DD t = dd_wave_sum(DD{(double)x, 0.0});
         if (lane == 0) {
-            d.rsum[2 * b] = acc.hi;
-            d.rsum[2 * b + 1] = acc.lo;
+            d.rsum[2 * lt] = t.hi;
+            d.rsum[2 * lt + 1] = t.lo;
         }
-    } else {
-        for (int64_t i = s + lane; i < e; i += 64) R.fc[i] = 1.0 / sqrt((double)x[i]);
     }
 }
 
-__global__ __launch_bounds__(256) void fac_fin_rows_kernel(const FacArgs a, int role) {
-    __shared__ DD sh[4];
-    const FacDesc& d = a.D[blockIdx.x];
+// One wavefront per code block of up to 256 elements, one workgroup per larger
+// block (up to 8 elements per lane either way).
+__global__ __launch_bounds__(256) void fac_enc_kernel(const FacArgs a, int role) {
+    __shared__ uint32_t smn[4], smx[4];
+    const int codec = role ? a.c_codec : a.v_codec;
+    const int B = role ? a.c_block : a.v_block;
+    const bool wg = B > 256;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t blk = wg ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + w;
+    if (blk >= a.total_blk[role]) return;
+    const FacDesc& d = a.D[locate(a.blk_begins[role], a.n2, blk)];
     const FinRole R = fin_role(a, d, role);
-    const int tid = threadIdx.x;
-    const int64_t nbr = (d.rows + R.B - 1) / R.B;
-    DD acc{0.0, 0.0};
-    for (int64_t k = tid; k < nbr; k += blockDim.x) acc = dd_merge(acc, DD{d.rsum[2 * k], d.rsum[2 * k + 1]});
-    acc = block_dd_sum(acc, sh);
-    const double mr = dd_value(acc) / (double)d.rows;
-    for (int64_t i = tid; i < d.rows; i += blockDim.x) R.fr[i] = 1.0 / sqrt((double)d.rtmp[i] / mr);
+    const int64_t lb = blk - d.blk_begin[role];
+    const int64_t nbr = (d.rows + B - 1) / B;
+    const bool isrow = lb < nbr;
+    const int64_t n = isrow ? d.rows : d.cols;
+    const int64_t b = isrow ? lb : lb - nbr;
+    const int64_t s = b * B, e = s + B < n ? s + B : n;
+    const gp<const float> x = to_g((const float*)(isrow ? d.rtmp : d.ctmp));
+    const int t0 = wg ? (int)threadIdx.x : lane, st = wg ? 256 : 64;
+    const int nk = (B + st - 1) / st;  // 1 .. 8
+    float xv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int64_t i = s + t0 + k * st;
+        xv[k] = k < nk && i < e ? x[i] : 0.0f;
+    }
+    double mr = 1.0;
+    if (isrow) {
+        DD acc{0.0, 0.0};
+        const gp<const double> rs = to_g((const double*)d.rsum);
+        const int64_t nt = (d.rows + kMeanTile - 1) / kMeanTile;
+#pragma unroll 4
+        for (int64_t k = lane; k < nt; k += 64) acc = dd_merge(acc, DD{rs[2 * k], rs[2 * k + 1]});
+        mr = dd_value(dd_wave_sum(acc)) / (double)d.rows;
+    }
+    const gp<double> f = to_g(isrow ? R.fr : R.fc);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int64_t i = s + t0 + k * st;
+        if (k < nk && i < e) f[i] = 1.0 / sqrt(isrow ? (double)xv[k] / mr : (double)xv[k]);
+    }
+    void* codes = isrow ? R.rc : R.cc;
+    float* meta = isrow ? R.rm : R.cm;
+    if (codec == FP32) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t i = s + t0 + k * st;
+            if (k < nk && i < e) reinterpret_cast<float*>(codes)[i] = xv[k];
+        }
+        return;
+    }
+    uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {  // absent elements are +0: in neither reduction
+        mn = OpMin::f(mn, pos_min_key(xv[k]));
+        mx = OpMax::f(mx, pos_max_key(xv[k]));
+    }
+    mn = group_reduce<OpMin, 64>(mn);
+    mx = group_reduce<OpMax, 64>(mx);
+    if (wg) {
+        if (lane == 0) {
+            smn[w] = mn;
+            smx[w] = mx;
+        }
+        __syncthreads();
+        mn = OpMin::f(OpMin::f(smn[0], smn[1]), OpMin::f(smn[2], smn[3]));
+        mx = OpMax::f(OpMax::f(smx[0], smx[1]), OpMax::f(smx[2], smx[3]));
+    }
+    const ALFit fit = al_fit(mn, mx, R.lf);
+    if (t0 == 0) {
+        meta[2 * b] = fit.any ? (float)fit.lmin : 0.0f;
+        meta[2 * b + 1] = fit.any ? (float)fit.delta : 0.0f;
+    }
+    const ALEnc enc = al_enc_params(fit.lmin, fit.any ? (double)(codec == AL16 ? 65534 : 254) / fit.delta : 1.0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int64_t i = s + t0 + k * st;
+        if (k < nk && i < s + B) {
+            if (codec == AL16)
+                reinterpret_cast<uint16_t*>(codes)[i] = (uint16_t)al_encode_fast<65534>(xv[k], enc);
+            else
+                reinterpret_cast<uint8_t*>(codes)[i] = (uint8_t)al_encode_fast<254>(xv[k], enc);
+        }
+    }
 }
 
 hipError_t launch_fac_fin(const FacArgs& a, int role, int grad_dtype, hipStream_t s) {
     if (a.n2 == 0) return hipSuccess;
-    const int64_t grid = (a.total_blk[role] + 3) / 4;
     if (grad_dtype == G_BF16)
-        hipLaunchKernelGGL(fac_fin_block_kernel<G_BF16>, dim3((unsigned)grid), dim3(256), 0, s, a, role);
+        hipLaunchKernelGGL(fac_mean_kernel<G_BF16>, dim3((unsigned)a.total_mt), dim3(256), 0, s, a, role);
     else
-        hipLaunchKernelGGL(fac_fin_block_kernel<G_F32>, dim3((unsigned)grid), dim3(256), 0, s, a, role);
+        hipLaunchKernelGGL(fac_mean_kernel<G_F32>, dim3((unsigned)a.total_mt), dim3(256), 0, s, a, role);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fac_fin_rows_kernel, dim3(a.n2), dim3(256), 0, s, a, role);
+    const bool wg = (role ? a.c_block : a.v_block) > 256;
+    const int64_t grid = wg ? a.total_blk[role] : (a.total_blk[role] + 3) / 4;
+    hipLaunchKernelGGL(fac_enc_kernel, dim3((unsigned)grid), dim3(256), 0, s, a, role);
     return hipGetLastError();
 }
 
 // ------------------------------------------------ RMS partials (per unit)
-// Natural layout: lane = 4 consecutive columns of a 256-column segment; the
-// wave walks the unit's rows, kRowBatch rows at a time with all their loads
-// issued before the arithmetic. u_ij = (r_i c_j) g_ij, exactly the oracle's
-// operation order; u^2 summed double-double. One wave per unit.
-constexpr int kRowBatch = 8;
-
+// u_ij = (r_i c_j) g_ij, exactly the oracle's operation order. One wave per unit.
+//
+// Edge units (see edge_unit_sums): left-out elements have g = 0 (and row
+// factor 0 past the last row). The 8 terms u^2 of a lane's row are added
+// pairwise, those sums double-double, as in the whole units.
 template <int G>
-__device__ __forceinline__ void load_row4(const GD& d, int64_t e, bool vec, int nc, int c, GRaw<G>& r, int k) {
-    if constexpr (G == G_BF16) {
-        const gp<const uint16_t> g = g_as<const uint16_t>(d.g);
-        if (vec) {
-            r.w[k] = ld_u2<true>(g_as<const void>(g + e));
-        } else {
-            uint32_t h[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (c + j < nc) h[j] = g[e + j];
-            r.w[k] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
-        }
-    } else {
-        const gp<const float> g = g_as<const float>(d.g);
-        if (vec) {
-            r.w[k] = ld_f4<true>(g + e);
-        } else {
-            float h[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (c + j < nc) h[j] = g[e + j];
-            r.w[k] = make_float4(h[0], h[1], h[2], h[3]);
-        }
-    }
-}
-
-// Gradient words of R rows (the GRaw layout, R / 4 x 4 rows).
-template <int G, int R = kRowBatch>
-struct GRows {
-    GRaw<G> h[R / 4];
+struct EdgeRmsBatch {
+    Raw8<G> r[kEdgeNR / 2];
+    double ri[kEdgeNR / 2];
 };
 
-// The Adafactor apply pass streams p in and out as well as g: 16-row batches
-// (all loads of a batch issued before its stores, 180 registers, 2 waves per
-// SIMD) run 7% faster than 8-row ones at 4-5 waves per SIMD.
-constexpr int kApplyRows = 16;
-
-// Interior units (256 x 256, width a multiple of 4) take the guard-free body.
-template <int G, bool FULL>
-__device__ __forceinline__ DD rms_unit(const GD& d, int64_t r0, int64_t c0, int nr_, int nc_, int lane) {
-    const int nr = FULL ? 256 : nr_, nc = FULL ? 256 : nc_;
-    const int c = 4 * lane;
-    const bool vec = FULL || ((d.cols & 3) == 0 && c + 4 <= nc);
-    const bool live = FULL || c < nc;
-    double cf[4];
+template <int G>
+__device__ __forceinline__ DD edge_unit_rms(const GD& d, const EdgeLane& w) {
+    constexpr int NR = kEdgeNR, NP = NR / 2;
+    const int nr = w.nr, sh = w.sh;
+    const int64_t e0 = w.r0 * w.cols + w.cs;
+    double cf[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) cf[j] = (FULL || c + j < nc) ? d.cfac[c0 + c + j] : 0.0;
+    for (int j = 0; j < 8; ++j) cf[j] = d.cfac[w.cs + j];
     DD acc{0.0, 0.0};
-    for (int r = 0; r < nr; r += kRowBatch) {
-        GRows<G> g;
-        double ri[kRowBatch];
+    edge_batches<EdgeRmsBatch<G>>(
+        (nr + NR - 1) / NR,
+        [&](EdgeRmsBatch<G>& b, int bi) {
 #pragma unroll
-        for (int k = 0; k < kRowBatch; ++k) {
-            const int rr = (FULL || r + k < nr) ? r + k : nr - 1;  // rows past the end repeat the last one, unused
-            ri[k] = d.rfac[r0 + rr];
-            if (live) load_row4<G>(d, (r0 + rr) * d.cols + c0 + c, vec, nc, c, g.h[k / 4], k % 4);
-        }
-#pragma unroll
-        for (int k = 0; k < kRowBatch; ++k) {
-            if (!FULL && (r + k >= nr || !live)) continue;
-            float gv[4];
-            unpack_graw<G>(g.h[k / 4], k % 4, gv);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (FULL || c + j < nc) {
-                    const double uu = (ri[k] * cf[j]) * (double)gv[j];
-                    dd_add(acc, uu * uu);
-                }
+            for (int k = 0; k < NP; ++k) {
+                const int row = NR * bi + 2 * k + w.h, rr = row < nr ? row : nr - 1;
+                load8_ua<G>(b.r[k], d.g, e0 + rr * w.cols);
+                b.ri[k] = d.rfac[w.r0 + rr];
             }
-        }
-    }
+        },
+        [&](const EdgeRmsBatch<G>& b, int bi) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const bool ok = NR * bi + 2 * k + w.h < nr;
+                const double ri = ok ? b.ri[k] : 0.0;
+                float gv[8];
+                unpack8<G>(b.r[k], gv);
+                double t[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const double uu = (ri * cf[j]) * (double)(((j >= sh) & ok) ? gv[j] : 0.0f);
+                    t[j] = uu * uu;
+                }
+                dd_add(acc, sum8(t));
+            }
+        });
     return acc;
 }
 
+// Matrices narrower than 8 columns, lane by row.
 template <int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void fac_rms_kernel(const FacArgs a, int64_t base) {
-    const int lane = threadIdx.x & 63;
-    const int64_t unit = base + xcd_order(blockIdx.x, gridDim.x) * 4 +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (unit >= a.total_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    const int64_t u = unit - d.unit_begin;
-    const int64_t ru = u / d.ncu, cu = u % d.ncu;
-    const int64_t r0 = ru * 256, c0 = cu * 256;
-    const int nr = (int)(d.rows - r0 < 256 ? d.rows - r0 : 256);
-    const int nc = (int)(d.cols - c0 < 256 ? d.cols - c0 : 256);
-    DD acc = (nr == 256 && nc == 256 && (d.cols & 3) == 0) ? rms_unit<G, true>(d, r0, c0, nr, nc, lane)
-                                                           : rms_unit<G, false>(d, r0, c0, nr, nc, lane);
-    acc = dd_wave_sum(acc);
-    if (lane == 0) {
-        a.rmspart[2 * unit] = acc.hi;
-        a.rmspart[2 * unit + 1] = acc.lo;
-    }
+__device__ __forceinline__ DD narrow_unit_rms(const GD& d, int ur, int64_t ru) {
+    DD acc{0.0, 0.0};
+    for (int64_t i = ru * ur + (threadIdx.x & 63); i < d.rows && i < (ru + 1) * ur; i += 64)
+        for (int64_t j = 0; j < d.cols; ++j) {
+            const double uu = (d.rfac[i] * d.cfac[j]) * (double)grad_at_g<G>(d.g, i * d.cols + j);
+            dd_add(acc, uu * uu);
+        }
+    return acc;
 }
-
 
 // Whole units (the marginal kernels' streaming layout): lane 32 h + q holds
 // columns 8q .. 8q + 7 of rows 2k + h of each 8-row batch, 16-byte gradient
 // loads, the next batch loaded before the current one's arithmetic. The 8
 // terms u^2 of a lane's row are added pairwise (relative error <= 3u) and
 // those sums accumulated double-double, so a unit's partial is within 3u of
-// its exact sum (the other units sum term by term). The clip divisor then
+// its exact sum. The clip divisor then
 // carries a relative error of at most about 2u: it scales Adafactor's update
 // (inside the parameter tolerance), and for CAME it can move fl32(u / clip)
 // by one fp32 ulp only where u / clip lies within that distance of an fp32
 // rounding midpoint, about one element in 10^8.
 template <int G>
-__global__ __launch_bounds__(256) void fac_rms_whole_kernel(const FacArgs a, int64_t base) {
-    const int64_t unit = whole_unit_of_wave(base);
-    if (unit >= a.whole_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    const WholeLane w = whole_lane(d, unit - d.unit_begin);
+__device__ __forceinline__ DD whole_unit_rms(const GD& d, int64_t ru, int64_t cu) {
+    const WholeLane w = whole_lane(d, ru, cu);
     const gp<const void> gu = unit_base<G>(d, w);
     const int64_t cols = w.cols;
     const uint32_t lo = w.lo;
@@ -1189,6 +1127,22 @@ __global__ __launch_bounds__(256) void fac_rms_whole_kernel(const FacArgs a, int
     load(B, rb_, NB - 1);
     step(A, ra);
     step(B, rb_);
+    return acc;
+}
+
+template <int G>
+__global__ __launch_bounds__(256) void fac_rms_kernel(const FacArgs a, int64_t base) {
+    const int64_t unit = unit_of_wave(base);
+    if (unit >= a.total_units) return;
+    const GD d = gview(a.D[locate(a.unit_begins, a.n2, unit)]);
+    const int64_t u = unit - d.unit_begin, ru = u / d.ncu, cu = u % d.ncu;
+    DD acc;
+    if (whole_unit(a, d, ru))
+        acc = whole_unit_rms<G>(d, ru, cu);
+    else if (d.cols >= 8)
+        acc = edge_unit_rms<G>(d, edge_lane(d, a.ur, ru, cu));
+    else
+        acc = narrow_unit_rms<G>(d, a.ur, ru);
     acc = dd_wave_sum(acc);
     if ((threadIdx.x & 63) == 0) {
         a.rmspart[2 * unit] = acc.hi;
@@ -1197,28 +1151,21 @@ __global__ __launch_bounds__(256) void fac_rms_whole_kernel(const FacArgs a, int
 }
 
 hipError_t launch_fac_rms(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.total_units == 0) return hipSuccess;
-    hipError_t e;
-    if (grad_dtype == G_BF16) {
-        if ((e = launch_wave_per_unit(fac_rms_whole_kernel<G_BF16>, a, 0, a.whole_units, s)) != hipSuccess) return e;
-        return launch_wave_per_unit(fac_rms_kernel<G_BF16>, a, a.whole_units, a.total_units, s);
-    }
-    if ((e = launch_wave_per_unit(fac_rms_whole_kernel<G_F32>, a, 0, a.whole_units, s)) != hipSuccess) return e;
-    return launch_wave_per_unit(fac_rms_kernel<G_F32>, a, a.whole_units, a.total_units, s);
+    if (grad_dtype == G_BF16) return launch_wave_per_unit(fac_rms_kernel<G_BF16>, a, s);
+    return launch_wave_per_unit(fac_rms_kernel<G_F32>, a, s);
 }
 
-// ------------------------------------------------ clip divisor (wave / tensor)
-__global__ __launch_bounds__(64) void fac_clip_kernel(const FacArgs a) {
+// ------------------------------------------ clip divisor (workgroup / tensor)
+__global__ __launch_bounds__(256) void fac_clip_kernel(const FacArgs a) {
+    __shared__ DD sh[4];
     const FacDesc& d = a.D[blockIdx.x];
-    const int lane = threadIdx.x;
     const int64_t nu = (int64_t)d.nru * d.ncu;
+    const gp<const double> rp = to_g((const double*)a.rmspart) + 2 * d.unit_begin;
     DD s{0.0, 0.0};
-    for (int64_t k = lane; k < nu; k += 64) {
-        const int64_t unit = d.unit_begin + k;
-        s = dd_merge(s, DD{a.rmspart[2 * unit], a.rmspart[2 * unit + 1]});
-    }
-    s = dd_wave_sum(s);
-    if (lane == 0) {
+#pragma unroll 4
+    for (int64_t k = threadIdx.x; k < nu; k += 256) s = dd_merge(s, DD{rp[2 * k], rp[2 * k + 1]});
+    s = block_dd_sum(s, sh);
+    if (threadIdx.x == 0) {
         const double rms = sqrt(dd_value(s) / (double)(d.rows * d.cols));
         d.scal[0] = rms / a.clip_d > 1.0 ? rms / a.clip_d : 1.0;
     }
@@ -1226,82 +1173,22 @@ __global__ __launch_bounds__(64) void fac_clip_kernel(const FacArgs a) {
 
 hipError_t launch_fac_clip(const FacArgs& a, hipStream_t s) {
     if (a.n2 == 0) return hipSuccess;
-    hipLaunchKernelGGL(fac_clip_kernel, dim3(a.n2), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(fac_clip_kernel, dim3(a.n2), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
 // --------------------------------------------------- Adafactor apply (2-D)
-// The RMS pass's layout in kApplyRows-row batches; p <- p (1 - lr wd) - lr u / clip.
-template <int G>
-__global__ __launch_bounds__(256) void ada_apply_kernel(const FacArgs a, int64_t base) {
-    const int lane = threadIdx.x & 63;
-    const int64_t unit = base + xcd_order(blockIdx.x, gridDim.x) * 4 +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (unit >= a.total_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    const int64_t u = unit - d.unit_begin;
-    const int64_t ru = u / d.ncu, cu = u % d.ncu;
-    const int64_t r0 = ru * 256, c0 = cu * 256;
-    const int nr = (int)(d.rows - r0 < 256 ? d.rows - r0 : 256);
-    const int nc = (int)(d.cols - c0 < 256 ? d.cols - c0 : 256);
-    const int c = 4 * lane;
-    const bool vec = (d.cols & 3) == 0 && c + 4 <= nc;
-    if (c >= nc) return;
-    const double rclip = 1.0 / d.scal[0];
-    double cf[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) cf[j] = c + j < nc ? d.cfac[c0 + c + j] : 0.0;
-    for (int r = 0; r < nr; r += kApplyRows) {
-        GRows<G, kApplyRows> g;
-        double ri[kApplyRows];
-        float4 pv[kApplyRows];
-#pragma unroll
-        for (int k = 0; k < kApplyRows; ++k) {
-            const int rr = r + k < nr ? r + k : nr - 1;
-            const int64_t e = (r0 + rr) * d.cols + c0 + c;
-            ri[k] = d.rfac[r0 + rr];
-            load_row4<G>(d, e, vec, nc, c, g.h[k / 4], k % 4);
-            if (vec) {
-                pv[k] = ld_f4<true>(d.p + e);
-            } else {
-                float h[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (c + j < nc) h[j] = d.p[e + j];
-                pv[k] = make_float4(h[0], h[1], h[2], h[3]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kApplyRows; ++k) {
-            if (r + k >= nr) continue;
-            const int64_t e = (r0 + r + k) * d.cols + c0 + c;
-            float gv[4];
-            unpack_graw<G>(g.h[k / 4], k % 4, gv);
-            const float pin[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
-            float out[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double uu = (ri[k] * cf[j]) * (double)gv[j];
-                const double pd = (double)pin[j] * a.decay;
-                out[j] = (float)(pd - a.lr * (uu * rclip));  // p carries a tolerance: multiply by 1 / clip
-            }
-            if (vec) {
-                st_f4<true>(d.p + e, make_float4(out[0], out[1], out[2], out[3]));
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (c + j < nc) d.p[e + j] = out[j];
-            }
-        }
-    }
-}
-
-// Whole units, one wavefront per chunk of 2048 elements (32 per unit, 4 per
-// 256-thread workgroup) with no loop: the grid itself streams, as in the
+// p <- p (1 - lr wd) - lr u / clip. Widths that are a multiple of 256: one
+// wavefront per chunk of 2048 elements (32 per 256 x 256, 4 per 256-thread
+// workgroup) with no loop: the grid itself streams, as in the
 // AdamW step. Lanes take 4 consecutive columns of each 256-column row
 // segment, so every load and store instruction covers a contiguous 1 KB of
 // parameters (512 bytes of bf16 gradients); 16-byte non-temporal parameter
-// accesses.
+// accesses. Other widths: one wavefront per kFlatChunk consecutive elements of
+// the row-major flattening, so that the accesses are as wide and aligned as
+// there; each lane's row and column follow from one division per chunk, and the
+// factors are gathered (they stay in cache). Measured on the width-500 list:
+// CAME's apply 151 -> 60 us (3.7 TB/s) against element-by-element accesses.
 constexpr int kChunksPerUnit = 32;
 
 template <int G>
@@ -1315,18 +1202,17 @@ __device__ __forceinline__ void load_g4(gp<const void> g, int64_t e, float gv[4]
     }
 }
 
-// A whole-unit chunk as rows and columns: 8 / W rows from row0, 256 W
-// columns from col0 (W units side by side; the unit columns left over in a
-// unit row, ncu mod W, take W = 1: 8 rows x 256). A unit row holds 32 ncu
-// chunks.
+// A chunk of a matrix whose width is a multiple of 256 as rows and columns: 8 / W
+// rows from row0, 256 W columns from col0 (W units side by side; the unit columns
+// left over in a unit row, ncu mod W, take W = 1: 8 rows x 256). A unit row (256
+// rows) holds 32 ncu chunks; rows past the matrix's last are left out.
 struct RowChunk {
     int64_t row0, col0;
     bool full;  // W units (else one)
 };
 
 template <int W>
-__device__ __forceinline__ RowChunk row_chunk(const GD& d, int64_t chunk) {
-    const int64_t t_ch = chunk - d.unit_begin * kChunksPerUnit;
+__device__ __forceinline__ RowChunk row_chunk(const GD& d, int64_t t_ch) {
     const int64_t cpr = (int64_t)d.ncu * kChunksPerUnit;  // chunks per unit row
     const int64_t ur = t_ch / cpr, r = t_ch - ur * cpr;
     const int64_t ng = d.ncu / W;             // groups of W units in a unit row
@@ -1344,11 +1230,69 @@ __device__ __forceinline__ RowChunk row_chunk(const GD& d, int64_t chunk) {
     return c;
 }
 
+// Rows and columns of a lane's 4 consecutive elements of the flattening, one
+// 256-element sub-tile after another. step256: the way from a lane's element to
+// the one 256 further on.
+constexpr int kFlatChunk = kFacFlatChunk;
+struct FlatPos {
+    int64_t rows, cols;
+    int i, j;        // of the lane's first element (wide = false)
+    int di, dj;      // 256 / cols, 256 % cols
+    bool wide;       // outside the 32-bit, at-most-one-wrap range: divide per element
+    __device__ FlatPos(int64_t rows_, int64_t cols_, int64_t e) : rows(rows_), cols(cols_) {
+        wide = cols < 4 || cols >= (int64_t(1) << 30) || rows >= (int64_t(1) << 30);
+        i = j = di = dj = 0;
+        if (wide) return;
+        // binary64 estimate of the quotient, then exact correction
+        int64_t q = (int64_t)((double)e / (double)cols), r = e - q * cols;
+        if (r < 0) {
+            --q;
+            r += cols;
+        } else if (r >= cols) {
+            ++q;
+            r -= cols;
+        }
+        i = (int)q;
+        j = (int)r;
+        di = 256 / (int)cols;
+        dj = 256 % (int)cols;
+    }
+    // factors of the lane's 4 elements (e: the first; elements past the matrix take those of the last row)
+    template <class F>
+    __device__ __forceinline__ void each(int64_t e, F f) const {
+        if (!wide) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                int jj = j + t, ii = i;
+                if (jj >= (int)cols) {
+                    jj -= (int)cols;
+                    ++ii;
+                }
+                f(t, (int64_t)(ii < (int)rows ? ii : (int)rows - 1), (int64_t)jj);
+            }
+        } else {
+#pragma unroll 1
+            for (int t = 0; t < 4; ++t) {
+                const int64_t ii = (e + t) / cols;
+                f(t, ii < rows ? ii : rows - 1, (e + t) % cols);
+            }
+        }
+    }
+    __device__ void next() {
+        i += di;
+        j += dj;
+        if (j >= (int)cols) {
+            j -= (int)cols;
+            ++i;
+        }
+    }
+};
+
 // Adafactor apply over a row chunk (lane l: columns 4l .. 4l + 3 of each
 // 256-column segment): every load of the chunk is issued before the
-// arithmetic.
-template <int G, int W>
-__device__ __forceinline__ void ada_apply_rows(const FacArgs& a, const GD& d, int64_t row0, int64_t col0) {
+// arithmetic. RAG: only nrow of the chunk's rows exist.
+template <int G, int W, bool RAG>
+__device__ __forceinline__ void ada_apply_rows(const FacArgs& a, const GD& d, int64_t row0, int64_t col0, int nrow) {
     constexpr int R = 8 / W;
     const int64_t cb = col0 + 4 * (threadIdx.x & 63);
     const double rclip = 1.0 / d.scal[0], lr = a.lr, decay = a.decay;
@@ -1357,10 +1301,11 @@ __device__ __forceinline__ void ada_apply_rows(const FacArgs& a, const GD& d, in
     double ri[R], cf[W][4];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-        ri[k] = d.rfac[row0 + k];
+        const int64_t row = row0 + (!RAG || k < nrow ? k : nrow - 1);
+        ri[k] = d.rfac[row];
 #pragma unroll
         for (int sg = 0; sg < W; ++sg) {
-            const int64_t e = (row0 + k) * d.cols + cb + 256 * sg;
+            const int64_t e = row * d.cols + cb + 256 * sg;
             load_g4<G>(d.g, e, gv[k][sg]);
             pv[k][sg] = ld_f4<true>(d.p + e);
         }
@@ -1371,6 +1316,7 @@ __device__ __forceinline__ void ada_apply_rows(const FacArgs& a, const GD& d, in
         for (int j = 0; j < 4; ++j) cf[sg][j] = d.cfac[cb + 256 * sg + j];
 #pragma unroll
     for (int k = 0; k < R; ++k) {
+        if (RAG && k >= nrow) break;
 #pragma unroll
         for (int sg = 0; sg < W; ++sg) {
             const float pin[4] = {pv[k][sg].x, pv[k][sg].y, pv[k][sg].z, pv[k][sg].w};
@@ -1386,28 +1332,102 @@ __device__ __forceinline__ void ada_apply_rows(const FacArgs& a, const GD& d, in
     }
 }
 
-constexpr int kAdaApplyW = 2;
-
-template <int G>
-__global__ __launch_bounds__(256) void ada_apply_whole_kernel(const FacArgs a, int64_t base) {
-    const int64_t chunk = base + xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t unit = chunk / kChunksPerUnit;
-    if (unit >= a.whole_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    const RowChunk c = row_chunk<kAdaApplyW>(d, chunk);
-    if (c.full)
-        ada_apply_rows<G, kAdaApplyW>(a, d, c.row0, c.col0);
-    else
-        ada_apply_rows<G, 1>(a, d, c.row0, c.col0);
+// kFlatChunk elements from e0, the first `valid` of them inside the matrix
+// (FULL: all).
+template <int G, bool FULL>
+__device__ __forceinline__ void ada_apply_flat(const FacArgs& a, const GD& d, int64_t e0, int valid) {
+    constexpr int K = kFlatChunk / 256;
+    const int l4 = 4 * (threadIdx.x & 63);
+    float gv[K][4];
+    float4 pv[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t e = e0 + 256 * k + l4;
+        if constexpr (FULL) {
+            load_g4<G>(d.g, e, gv[k]);
+            pv[k] = ld_f4<true>(d.p + e);
+        } else {
+            float h[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bool ok = 256 * k + l4 + t < valid;
+                gv[k][t] = ok ? grad_at_g<G>(d.g, e + t) : 0.0f;
+                h[t] = ok ? d.p[e + t] : 0.0f;
+            }
+            pv[k] = make_float4(h[0], h[1], h[2], h[3]);
+        }
+    }
+    const double rclip = 1.0 / d.scal[0], lr = a.lr, decay = a.decay;
+    FlatPos pos(d.rows, d.cols, e0 + l4);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t e = e0 + 256 * k + l4;
+        const float pin[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
+        float out[4];
+        pos.each(e, [&](int t, int64_t i, int64_t j) {
+            const double uu = (d.rfac[i] * d.cfac[j]) * (double)gv[k][t];
+            const double pd = (double)pin[t] * decay;
+            out[t] = (float)(pd - lr * (uu * rclip));
+        });
+        pos.next();
+        if constexpr (FULL) {
+            st_f4<true>(d.p + e, make_float4(out[0], out[1], out[2], out[3]));
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (256 * k + l4 + t < valid) d.p[e + t] = out[t];
+        }
+    }
 }
 
-// One wavefront per whole-unit chunk, 4 per 256-thread workgroup; grids
-// beyond 2^31 workgroups take several launches.
+constexpr int kAdaApplyW = 2;
+
+// Wavefront -> apply chunk.
+__device__ __forceinline__ int64_t chunk_of_wave(int64_t base) {
+    return base + xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+// Four waves per SIMD: more of them in flight mix the pass's streams and slow it (the 1.1B list's step 2739
+// us at the six its registers allow, 2673-2676 at 4 and 5, 2687 at 3).
+template <int G>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void ada_apply_kernel(const FacArgs a, int64_t base) {
+    const int64_t chunk = chunk_of_wave(base);
+    if (chunk >= a.rows_ach) return;
+    const GD d = gview(a.D[locate(a.ach_begins, a.n2, chunk)]);
+    const RowChunk c = row_chunk<kAdaApplyW>(d, chunk - d.ach_begin);
+    constexpr int R = 8 / kAdaApplyW;
+    const int64_t left = d.rows - c.row0;
+    if (left <= 0) return;
+    if (c.full) {
+        if (left >= R)
+            ada_apply_rows<G, kAdaApplyW, false>(a, d, c.row0, c.col0, R);
+        else
+            ada_apply_rows<G, kAdaApplyW, true>(a, d, c.row0, c.col0, (int)left);
+    } else if (left >= 8) {
+        ada_apply_rows<G, 1, false>(a, d, c.row0, c.col0, 8);
+    } else {
+        ada_apply_rows<G, 1, true>(a, d, c.row0, c.col0, (int)left);
+    }
+}
+
+template <int G>
+__global__ __launch_bounds__(256) void ada_apply_flat_kernel(const FacArgs a, int64_t base) {
+    const int64_t chunk = chunk_of_wave(base);
+    if (chunk >= a.total_ach) return;
+    const GD d = gview(a.D[locate(a.ach_begins, a.n2, chunk)]);
+    const int64_t e0 = (chunk - d.ach_begin) * kFlatChunk, left = d.rows * d.cols - e0;
+    if (left >= kFlatChunk)
+        ada_apply_flat<G, true>(a, d, e0, kFlatChunk);
+    else
+        ada_apply_flat<G, false>(a, d, e0, (int)left);
+}
+
+// One wavefront per apply chunk of [begin, end), 4 per 256-thread workgroup;
+// grids beyond 2^31 workgroups take several launches.
 template <class K>
-static hipError_t launch_per_chunk(K kernel, const FacArgs& a, hipStream_t s) {
+static hipError_t launch_per_chunk(K kernel, const FacArgs& a, int64_t begin, int64_t end, hipStream_t s) {
     constexpr int64_t kMaxGrid = int64_t(1) << 31;
-    const int64_t end = a.whole_units * kChunksPerUnit;
-    for (int64_t base = 0; base < end; base += 4 * kMaxGrid) {
+    for (int64_t base = begin; base < end; base += 4 * kMaxGrid) {
         const int64_t left = (end - base + 3) / 4;
         const int64_t grid = left < kMaxGrid ? left : kMaxGrid;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, s, a, base);
@@ -1418,14 +1438,12 @@ static hipError_t launch_per_chunk(K kernel, const FacArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_ada_apply(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.total_units == 0) return hipSuccess;
-    hipError_t e;
-    if (grad_dtype == G_BF16) {
-        if ((e = launch_per_chunk(ada_apply_whole_kernel<G_BF16>, a, s)) != hipSuccess) return e;
-        return launch_wave_per_unit(ada_apply_kernel<G_BF16>, a, a.whole_units, a.total_units, s);
-    }
-    if ((e = launch_per_chunk(ada_apply_whole_kernel<G_F32>, a, s)) != hipSuccess) return e;
-    return launch_wave_per_unit(ada_apply_kernel<G_F32>, a, a.whole_units, a.total_units, s);
+    const bool bf = grad_dtype == G_BF16;
+    const hipError_t e = bf ? launch_per_chunk(ada_apply_kernel<G_BF16>, a, 0, a.rows_ach, s)
+                            : launch_per_chunk(ada_apply_kernel<G_F32>, a, 0, a.rows_ach, s);
+    if (e != hipSuccess) return e;
+    return bf ? launch_per_chunk(ada_apply_flat_kernel<G_BF16>, a, a.rows_ach, a.total_ach, s)
+              : launch_per_chunk(ada_apply_flat_kernel<G_F32>, a, a.rows_ach, a.total_ach, s);
 }
 
 // ------------------------------------------- Adafactor 1-D tensors (WG each)
@@ -1485,199 +1503,10 @@ __device__ __forceinline__ float came_momentum(const FacArgs& a, const FacDesc& 
     return (float)(a.beta1 * (double)mh + a.omb1 * (double)uh);
 }
 
-// --------------------------- CAME residual marginal sums (tile layout, fp64)
-// Term (uhat - m)^2 + eps2 with uhat = fl32(u / clip), m the in-step
-// momentum; the loop order and one-tile-ahead loads of the marginals of G2,
-// on 8x128 tiles: lane (lr, lc) = (lane / 32, lane % 32) holds rows lr + 2i
-// (i < 4), columns 4 lc .. 4 lc + 3, so each row's 128 momentum codes are one
-// full 128-byte line; the binary64 terms are staged in LDS and 8 lanes sum
-// each tile row (16 columns each, merged with DPP).
-constexpr int kResRows = 8, kResCols = 128;
-
-template <int G>
-struct ResRaw {
-    GRaw<G> g;
-    uint32_t mw[4];  // UF8 codes of the 4 columns (fp32 momentum: read directly)
-    double ri[4];
-    float ms[4];
-};
-
-template <int G, bool FULL, bool UF>
-__device__ __forceinline__ void load_resraw(ResRaw<G>& r, const FacArgs& a, const GD& d, int64_t r0,
-                                            int64_t c0, int nr, int nc, int rg, int ct, int lr, int lc, bool vec,
-                                            int64_t lane_off) {
-    load_graw<G, FULL, kResCols>(r.g, d, r0, c0, nr, nc, rg, ct, lr, lc, vec, lane_off);
-    const int cc = ct * kResCols + 4 * lc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int rr = rg * kResRows + lr + 2 * i;
-        const int64_t e = (r0 + rg * kResRows + 2 * i) * d.cols + c0 + ct * kResCols + lane_off;
-        r.ri[i] = (FULL || rr < nr) ? d.rfac[r0 + rr] : 0.0;
-        r.mw[i] = 0u;
-        r.ms[i] = 0.0f;
-        if (UF && (FULL || rr < nr)) {
-            if (FULL || (vec && cc + 4 <= nc)) {
-                // e % 4 == 0: the 4 codes are one word of one momentum block
-                r.mw[i] = *g_as<const uint32_t>(g_as<const uint8_t>(d.m) + e);
-                r.ms[i] = d.mm[(uint64_t)e >> 8];
-            }
-        }
-    }
-}
-
-template <int G, bool FULL, bool UF>
-__device__ __forceinline__ void res_unit(const FacArgs& a, const GD& d, double clip, int64_t ru, int64_t cu, int nr_,
-                                         int nc_, bool vec_, double (*tile)[kResCols + 2], DD* racc) {
-    const int lane = threadIdx.x, lc = lane & 31, lr = lane >> 5, rrow = lane >> 3, re = lane & 7;
-    const int64_t r0 = ru * 256, c0 = cu * 256;
-    const int nr = FULL ? 256 : nr_, nc = FULL ? 256 : nc_;
-    const bool vec = FULL || vec_;
-    const double rclip = 1.0 / clip;
-    constexpr bool uf8 = UF;
-    const int nrg = (nr + kResRows - 1) / kResRows, nct = (nc + kResCols - 1) / kResCols, total = nrg * nct;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) racc[lane + 64 * k] = DD{0.0, 0.0};
-    DD cacc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) cacc[j] = DD{0.0, 0.0};
-    double cf[4] = {0.0, 0.0, 0.0, 0.0};
-    ResRaw<G> cur;
-    const int64_t lane_off = (int64_t)lr * d.cols + 4 * lc;
-    load_resraw<G, FULL, UF>(cur, a, d, r0, c0, nr, nc, 0, 0, lr, lc, vec, lane_off);
-    for (int it = 0; it < total; ++it) {
-        const int ct = it / nrg, rg = it - ct * nrg;
-        const int cc = ct * kResCols + 4 * lc;
-        if (rg == 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cf[j] = (FULL || cc + j < nc) ? d.cfac[c0 + cc + j] : 0.0;
-        }
-        ResRaw<G> nxt = cur;
-        if (it + 1 < total) {
-            const int ct1 = (it + 1) / nrg;
-            load_resraw<G, FULL, UF>(nxt, a, d, r0, c0, nr, nc, it + 1 - ct1 * nrg, ct1, lr, lc, vec, lane_off);
-        }
-        double gs[4] = {0.0, 0.0, 0.0, 0.0};  // the lane's 4 rows of each column, summed in row order
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int rr = rg * kResRows + lr + 2 * i;
-            double term[4] = {0.0, 0.0, 0.0, 0.0};
-            if (FULL || rr < nr) {
-                const int64_t e = (r0 + rg * kResRows + 2 * i) * d.cols + c0 + ct * kResCols + lane_off;
-                float gv[4], mh[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                unpack_graw<G>(cur.g, i, gv);
-                if (FULL || (vec && cc + 4 <= nc)) {
-                    if constexpr (uf8) {
-                        const double st = div127((double)cur.ms[i]);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            mh[j] = uf8_decode((int32_t)(int8_t)(uint8_t)(cur.mw[i] >> (8 * j)), st);
-                    } else {
-                        const float4 t = ld_f4<false>(g_as<const float>(d.m) + e);
-                        mh[0] = t.x;
-                        mh[1] = t.y;
-                        mh[2] = t.z;
-                        mh[3] = t.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        if (cc + j < nc) {
-                            if constexpr (uf8)
-                                mh[j] = uf8_decode(g_as<const int8_t>(d.m)[e + j],
-                                                   div127((double)d.mm[(e + j) / 256]));
-                            else
-                                mh[j] = g_as<const float>(d.m)[e + j];
-                        }
-                    }
-                }
-                double uu[4];
-                float uh[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) uu[j] = (cur.ri[i] * cf[j]) * (double)gv[j];
-                div4_to_f32(uu, clip, rclip, uh);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (FULL || cc + j < nc) term[j] = res_term(a, mh[j], uh[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) gs[j] += term[j];
-            double* tp = &tile[lr + 2 * i][4 * lc];
-            *reinterpret_cast<double2*>(tp) = make_double2(term[0], term[1]);
-            *reinterpret_cast<double2*>(tp + 2) = make_double2(term[2], term[3]);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) dd_add(cacc[j], gs[j]);
-        __syncthreads();
-        DD rsum{0.0, 0.0};
-        const int rr = rg * kResRows + rrow;
-        const int cq = ct * kResCols + 16 * re;  // first column of this lane's sixteenth
-        if (FULL || (rr < nr && cq < nc)) {
-            const int cnt = nc - cq < 16 ? nc - cq : 16;
-            if (FULL || cnt == 16) {
-#pragma unroll
-                for (int c = 0; c < 16; c += 4) {
-                    const double2 t0 = *reinterpret_cast<const double2*>(&tile[rrow][16 * re + c]);
-                    const double2 t1 = *reinterpret_cast<const double2*>(&tile[rrow][16 * re + c + 2]);
-                    dd_add(rsum, ((t0.x + t0.y) + t1.x) + t1.y);
-                }
-            } else {
-                for (int c = 0; c < cnt; ++c) dd_add(rsum, tile[rrow][16 * re + c]);
-            }
-        }
-        rsum = dd_merge(rsum, dd_quad_xor<kDppQuadXor1>(rsum));
-        rsum = dd_merge(rsum, dd_quad_xor<kDppQuadXor2>(rsum));
-        rsum = dd_merge(rsum, dd_quad_xor<kDppRowHalfMirror>(rsum));  // the other quad of the 8 lanes
-        if (re == 0 && (FULL || rr < nr)) racc[rr] = dd_merge(racc[rr], rsum);
-        __syncthreads();
-        if (rg == nrg - 1) {
-            // column tile done: merge the two lanes of each column
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                DD v = cacc[j];
-                v = dd_merge(v, dd_shfl_xor(v, 32));
-                const int col = cc + j;
-                if (lr == 0 && (FULL || col < nc)) {
-                    const gp<double> cp = d.colpart + 2 * (ru * d.cols + c0 + col);
-                    cp[0] = v.hi;
-                    cp[1] = v.lo;
-                }
-                cacc[j] = DD{0.0, 0.0};
-            }
-        }
-        cur = nxt;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int row = lane + 64 * k;
-        if (FULL || row < nr) {
-            const gp<double> rp = d.rowpart + 2 * (cu * d.rows + r0 + row);
-            rp[0] = racc[row].hi;
-            rp[1] = racc[row].lo;
-        }
-    }
-}
-
-// UF: UF8 momentum codes (else fp32 momentum).
-template <int G, bool UF>
-__global__ __launch_bounds__(64) void came_res_kernel(const FacArgs a, int64_t base) {
-    __shared__ __attribute__((aligned(16))) double tile[kResRows][kResCols + 2];
-    __shared__ DD racc[256];
-    const int64_t unit = base + xcd_order(blockIdx.x, gridDim.x);
-    if (unit >= a.total_units) return;
-    const FacDesc& d = a.D[locate_unit(a.D, a.n2, unit)];
-    const int64_t u = unit - d.unit_begin;
-    const int64_t ru = u / d.ncu, cu = u % d.ncu;
-    const int nr = (int)(d.rows - ru * 256 < 256 ? d.rows - ru * 256 : 256);
-    const int nc = (int)(d.cols - cu * 256 < 256 ? d.cols - cu * 256 : 256);
-    const bool vec = (d.cols & 3) == 0;
-    if (nr == 256 && nc == 256 && vec)
-        res_unit<G, true, UF>(a, gview(d), d.scal[0], ru, cu, nr, nc, vec, tile, racc);
-    else
-        res_unit<G, false, UF>(a, gview(d), d.scal[0], ru, cu, nr, nc, vec, tile, racc);
-}
-
-// Whole units: the marginal kernels' streaming layout (whole_unit_sums) with
-// CAME's residual terms. Each unit row is one 256-element momentum block
+// ------------------------------------------- CAME residual marginal sums
+// Terms (uhat - m)^2 with uhat = fl32(u / clip) and m the in-step momentum.
+// Whole units: the marginal kernels' streaming layout (whole_unit_sums).
+// Each unit row is one 256-element momentum block
 // (the width is a multiple of 256), so a row's codes share one scale; the
 // lane's 8 momentum values of a row are one 8-byte word of codes (or two
 // 16-byte fp32 loads), loaded with the gradients one batch ahead.
@@ -1703,8 +1532,6 @@ struct ResTerms {
     static constexpr int NR = kResNR;
     static constexpr int FR = 16;  // row partials finished 16 rows at a time (4 batches)
     static constexpr bool ILP = false;  // the residual terms need the registers for occupancy
-    // terms() gives uhat - m; the sums take its square (eps2 is added to the means in the finalize)
-    static constexpr bool SQUARES = true;
     // the registers the single column sum frees (against runs) hold a third batch: 3 waves per SIMD either way
     static constexpr int DEPTH = 3;
     using Batch = ResBatch<G, UF>;
@@ -1770,13 +1597,8 @@ struct ResTerms {
 };
 
 template <int G, bool UF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void came_res_whole_kernel(const FacArgs a, int64_t base) {
-    __shared__ __attribute__((aligned(16))) double stages[4][2 * ResTerms<G, UF>::FR * kWStride];
-    double* stage = stages[threadIdx.x >> 6];
-    const int64_t unit = whole_unit_of_wave(base);
-    if (unit >= a.whole_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    const WholeLane w = whole_lane(d, unit - d.unit_begin);
+__device__ __forceinline__ void whole_unit_res(const FacArgs& a, const GD& d, int64_t ru, int64_t cu, double* stage) {
+    const WholeLane w = whole_lane(d, ru, cu);
     ResTerms<G, UF> pol;
     pol.a = &a;
     pol.gu = unit_base<G>(d, w);
@@ -1794,212 +1616,307 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void c
     for (int j = 1; j < 8; ++j) pol.cfmin = pol.cf[j] < pol.cfmin ? pol.cf[j] : pol.cfmin;
     pol.clip = d.scal[0];
     pol.rclip = 1.0 / pol.clip;
-    whole_unit_sums(pol, d, w.r0 / 256, w.c0 / 256, stage);
+    whole_unit_sums(pol, d, ru, cu, stage);
+}
+
+// Edge units (see edge_unit_sums). A lane's 8 momentum codes may straddle two
+// 256-element blocks of the flattening: both scales are loaded.
+template <int G, bool UF>
+struct EdgeRes {
+    struct Batch {
+        Raw8<G> r[kEdgeNR / 2];
+        double ri[kEdgeNR / 2];
+        uint2 mc[UF ? kEdgeNR / 2 : 1];        // codes,
+        float ms0[UF ? kEdgeNR / 2 : 1], ms1[UF ? kEdgeNR / 2 : 1];  // absmax of the first code's block and of the next,
+        int cut[UF ? kEdgeNR / 2 : 1];         // codes of the first block
+        float4 ma[UF ? 1 : kEdgeNR / 2], mb[UF ? 1 : kEdgeNR / 2];  // or fp32 momentum
+    };
+    const FacArgs* a;
+    gp<const void> g, m;
+    gp<const float> mm;
+    gp<const double> rf;  // row factor of the unit's first row
+    int64_t e0, cols, lastblk;
+    int sh;
+    double cf[8], cfmin, clip, rclip;
+    __device__ void load(Batch& b, int k, int row) const {
+        const int64_t e = e0 + row * cols;
+        load8_ua<G>(b.r[k], g, e);
+        b.ri[k] = rf[row];
+        if constexpr (UF) {
+            const ua_u2 c = *g_as<const ua_u2>(g_as<const uint8_t>(m) + e);
+            const int64_t blk = e >> 8;
+            b.mc[k] = make_uint2(c.x, c.y);
+            b.ms0[k] = mm[blk];
+            b.ms1[k] = mm[blk < lastblk ? blk + 1 : blk];
+            b.cut[k] = 256 - (int)(e & 255);
+        } else {
+            const gp<const float> f = g_as<const float>(m) + e;
+            const ua_f4 x = *g_as<const ua_f4>(f), y = *g_as<const ua_f4>(f + 4);
+            b.ma[k] = make_float4(x.x, x.y, x.z, x.w);
+            b.mb[k] = make_float4(y.x, y.y, y.z, y.w);
+        }
+    }
+    __device__ void terms(const Batch& b, int k, bool ok, double t[8]) const {
+        float gv[8], mh[8], uh[8];
+        unpack8<G>(b.r[k], gv);
+        if constexpr (UF) {
+            const double st0 = div127((double)b.ms0[k]), st1 = div127((double)b.ms1[k]);
+            const uint32_t w[2] = {b.mc[k].x, b.mc[k].y};
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                mh[j] = uf8_decode((int32_t)(int8_t)(uint8_t)(w[j >> 2] >> (8 * (j & 3))), j < b.cut[k] ? st0 : st1);
+        } else {
+            mh[0] = b.ma[k].x, mh[1] = b.ma[k].y, mh[2] = b.ma[k].z, mh[3] = b.ma[k].w;
+            mh[4] = b.mb[k].x, mh[5] = b.mb[k].y, mh[6] = b.mb[k].z, mh[7] = b.mb[k].w;
+        }
+        // left out: g = m = 0, so uhat - m = 0
+        const double ri = ok ? b.ri[k] : 0.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool in = (j >= sh) & ok;
+            gv[j] = in ? gv[j] : 0.0f;
+            mh[j] = in ? mh[j] : 0.0f;
+        }
+        const double rk = ri * rclip;
+        double qv[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) qv[j] = (rk * cf[j]) * (double)gv[j];
+        // (the range test can be dropped as in the whole units; a row left out has rk = 0 and keeps it)
+        bool dec;
+        if (G == G_BF16 && __builtin_expect(__all(rk * cfmin >= 0x1.00004p7), 1))
+            dec = f32_midpoints_decided<8>(qv, uh);
+        else
+            dec = f32_roundings_decided<8>(qv, uh);
+        if (__builtin_expect(!dec, 0)) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) uh[j] = (float)(((ri * cf[j]) * (double)gv[j]) / clip);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t[j] = res_diff(*a, mh[j], uh[j]);
+    }
+};
+
+template <int G, bool UF>
+__device__ __forceinline__ void edge_unit_res(const FacArgs& a, const GD& d, int64_t ru, int64_t cu, double* stage) {
+    const EdgeLane w = edge_lane(d, a.ur, ru, cu);
+    EdgeRes<G, UF> pol;
+    pol.a = &a;
+    pol.g = d.g;
+    pol.m = d.m;
+    pol.mm = d.mm;
+    pol.rf = d.rfac + w.r0;
+    pol.e0 = w.r0 * w.cols + w.cs;
+    pol.cols = w.cols;
+    pol.lastblk = (d.rows * d.cols - 1) >> 8;
+    pol.sh = w.sh;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pol.cf[j] = d.cfac[w.cs + j];
+    pol.cfmin = pol.cf[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) pol.cfmin = pol.cf[j] < pol.cfmin ? pol.cf[j] : pol.cfmin;
+    pol.clip = d.scal[0];
+    pol.rclip = 1.0 / pol.clip;
+    edge_unit_sums(pol, d, w, ru, cu, stage);
+}
+
+// Whole units and edge units in a kernel each (the edge body needs the registers of one wavefront per
+// SIMD less); each leaves the other's units alone.
+template <int G, bool UF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void came_res_whole_kernel(const FacArgs a, int64_t base) {
+    __shared__ __attribute__((aligned(16))) double stages[4][2 * ResTerms<G, UF>::FR * kWStride];
+    const int64_t unit = unit_of_wave(base);
+    if (unit >= a.total_units) return;
+    const GD d = gview(a.D[locate(a.unit_begins, a.n2, unit)]);
+    const int64_t u = unit - d.unit_begin, ru = u / d.ncu, cu = u % d.ncu;
+    if (whole_unit(a, d, ru)) whole_unit_res<G, UF>(a, d, ru, cu, stages[threadIdx.x >> 6]);
+}
+
+template <int G, bool UF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void came_res_edge_kernel(const FacArgs a, int64_t base) {
+    __shared__ __attribute__((aligned(16))) double stages[4][kEdgeFR * kWStride];
+    double* stage = stages[threadIdx.x >> 6];
+    const int64_t unit = unit_of_wave(base);
+    if (unit >= a.total_units) return;
+    const GD d = gview(a.D[locate(a.unit_begins, a.n2, unit)]);
+    const int64_t u = unit - d.unit_begin, ru = u / d.ncu, cu = u % d.ncu;
+    if (whole_unit(a, d, ru)) return;
+    if (d.cols >= 8) {
+        edge_unit_res<G, UF>(a, d, ru, cu, stage);
+    } else {
+        const double clip = d.scal[0], rclip = 1.0 / clip;
+        narrow_unit_sums(d, a.ur, ru, [&](int64_t i, int64_t j) {
+            const int64_t e = i * d.cols + j;
+            const double uu = (d.rfac[i] * d.cfac[j]) * (double)grad_at_g<G>(d.g, e);
+            return res_diff(a, came_mhat(a, d, e), div_to_f32(uu, clip, rclip));
+        });
+    }
 }
 
 hipError_t launch_came_res(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.total_units == 0) return hipSuccess;
     const bool uf = a.m_codec == UF8;
-    hipError_t e;
-    if (grad_dtype == G_BF16) {
-        if ((e = uf ? launch_wave_per_unit(came_res_whole_kernel<G_BF16, true>, a, 0, a.whole_units, s)
-                    : launch_wave_per_unit(came_res_whole_kernel<G_BF16, false>, a, 0, a.whole_units, s)) != hipSuccess)
-            return e;
-        return uf ? launch_per_unit(came_res_kernel<G_BF16, true>, a, a.whole_units, a.total_units, s)
-                  : launch_per_unit(came_res_kernel<G_BF16, false>, a, a.whole_units, a.total_units, s);
-    }
-    if ((e = uf ? launch_wave_per_unit(came_res_whole_kernel<G_F32, true>, a, 0, a.whole_units, s)
-                : launch_wave_per_unit(came_res_whole_kernel<G_F32, false>, a, 0, a.whole_units, s)) != hipSuccess)
-        return e;
-    return uf ? launch_per_unit(came_res_kernel<G_F32, true>, a, a.whole_units, a.total_units, s)
-              : launch_per_unit(came_res_kernel<G_F32, false>, a, a.whole_units, a.total_units, s);
+    hipError_t e = hipSuccess;
+    if (a.any_whole)
+        e = grad_dtype == G_BF16 ? (uf ? launch_wave_per_unit(came_res_whole_kernel<G_BF16, true>, a, s)
+                                       : launch_wave_per_unit(came_res_whole_kernel<G_BF16, false>, a, s))
+                                 : (uf ? launch_wave_per_unit(came_res_whole_kernel<G_F32, true>, a, s)
+                                       : launch_wave_per_unit(came_res_whole_kernel<G_F32, false>, a, s));
+    if (e != hipSuccess || !a.any_edge) return e;
+    return grad_dtype == G_BF16 ? (uf ? launch_wave_per_unit(came_res_edge_kernel<G_BF16, true>, a, s)
+                                      : launch_wave_per_unit(came_res_edge_kernel<G_BF16, false>, a, s))
+                                : (uf ? launch_wave_per_unit(came_res_edge_kernel<G_F32, true>, a, s)
+                                      : launch_wave_per_unit(came_res_edge_kernel<G_F32, false>, a, s));
 }
 
 // ------------------------------------------------------ CAME apply (2-D)
-// Recompute uhat and m, encode m, and p <- p (1 - lr wd) - lr (s_i s_j) m.
-// Widths that are a multiple of 256: one wave per unit in the RMS pass's
-// layout, so each unit row is exactly one 256-element momentum block (one
-// wave-wide absmax per row); rows in batches with their loads issued first.
-template <int G, bool UF>
-__global__ __launch_bounds__(256) void came_apply_unit_kernel(const FacArgs a, int64_t base) {
-    const int lane = threadIdx.x & 63;
-    const int64_t unit = base + xcd_order(blockIdx.x, gridDim.x) * 4 +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (unit >= a.total_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    if (d.cols & 255) return;  // other widths: the chunk kernel
-    const int64_t u = unit - d.unit_begin;
-    const int64_t ru = u / d.ncu, cu = u % d.ncu;
-    const int64_t r0 = ru * 256, c0 = cu * 256;
-    const int nr = (int)(d.rows - r0 < 256 ? d.rows - r0 : 256);
-    const int c = 4 * lane;
-    const double clip = d.scal[0], rclip = 1.0 / clip;
-    constexpr bool uf8 = UF;
-    double cf[4], sf[4];
+// Recompute uhat and m, encode m, and p <- p (1 - lr wd) - lr (s_i s_j) m, in
+// the Adafactor apply's chunks. The parameter update runs in fp32 (the states
+// never depend on p, which is held to a relative tolerance):
+// p' = fma(-lr, (s_i s_j) m, p (1 - lr wd)) on the fp32 roundings of the factors.
+//
+// One 256-element momentum block (4 consecutive elements per lane): new momentum
+// and parameters from the inputs and factors; mw: the lane's codes, ms the
+// block's absmax (UF8), else mv the fp32 momentum. Returns the new codes and
+// their absmax in mw / am, or the new momentum in mv.
+template <bool UF>
+__device__ __forceinline__ void came_apply_block(const FacArgs& a, const double ri[4], const double cf[4],
+                                                 const float si[4], const float sf[4], double clip, double rclip,
+                                                 const float gv[4], float4& pv, uint32_t& mw, float ms, float4& mv,
+                                                 const bool in[4], uint32_t& am) {
+    const float lrf = (float)a.lr, decayf = (float)a.decay;
+    float mh[4], uh[4], mnew[4], pout[4];
+    if constexpr (UF) {
+        const double st = div127((double)ms);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mh[j] = uf8_decode((int32_t)(int8_t)(uint8_t)(mw >> (8 * j)), st);
+    } else {
+        mh[0] = mv.x, mh[1] = mv.y, mh[2] = mv.z, mh[3] = mv.w;
+    }
+    double qv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qv[j] = ((ri[j] * rclip) * cf[j]) * (double)gv[j];
+    if (__builtin_expect(!f32_roundings_decided<4>(qv, uh), 0)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) uh[j] = (float)(((ri[j] * cf[j]) * (double)gv[j]) / clip);
+    }
+    const float pin[4] = {pv.x, pv.y, pv.z, pv.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        cf[j] = d.cfac[c0 + c + j];
-        sf[j] = d.sc[c0 + c + j];
+        mnew[j] = (float)(a.beta1 * (double)mh[j] + a.omb1 * (double)uh[j]);
+        if (!in[j]) mnew[j] = 0.0f;
+        const float upd = (si[j] * sf[j]) * mnew[j];
+        pout[j] = __builtin_fmaf(-lrf, upd, pin[j] * decayf);
     }
-    constexpr int RB = 8;  // rows per batch: 165 registers, 3 waves per SIMD (4% faster than 4 rows; 16 slower)
-    for (int r = 0; r < nr; r += RB) {
-        GRows<G, RB> g;
-        float4 pv[RB];
-        uint32_t mw[UF ? RB : 1];
-        float4 mf[UF ? 1 : RB];
-        double ri[RB], si[RB];
-        float ms[RB];
+    pv = make_float4(pout[0], pout[1], pout[2], pout[3]);
+    if constexpr (UF) {
+        am = 0u;
 #pragma unroll
-        for (int k = 0; k < RB; ++k) {
-            const int rr = r + k < nr ? r + k : nr - 1;  // rows past the end repeat the last one, unused
-            const int64_t e = (r0 + rr) * d.cols + c0 + c;
-            ri[k] = d.rfac[r0 + rr];
-            si[k] = d.sr[r0 + rr];
-            load_row4<G>(d, e, true, 256, c, g.h[k / 4], k % 4);
+        for (int j = 0; j < 4; ++j) am = OpMax::f(am, abs_bits(mnew[j]));
+        am = group_reduce<OpMax, 64>(am);
+        const double rs = am != 0u ? rdiv127((double)u2f(am)) : 0.0;
+        uint32_t q[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[j] = rint_low_bits((double)mnew[j] * rs) & 0xFFu;
+        mw = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
+    } else {
+        mv = make_float4(mnew[0], mnew[1], mnew[2], mnew[3]);
+    }
+}
+
+// kFlatChunk elements of the flattening from e0 (widths that are not a multiple
+// of 256), the first `valid` of them inside the matrix (FULL: all): a momentum
+// block is one 256-element sub-tile.
+template <int G, bool UF, bool FULL>
+__device__ __forceinline__ void came_apply_flat(const FacArgs& a, const GD& d, int64_t e0, int valid) {
+    constexpr int K = kFlatChunk / 256;
+    const int lane = threadIdx.x & 63, l4 = 4 * lane;
+    const gp<uint8_t> mc = g_as<uint8_t>(d.m);
+    const gp<float> mf = g_as<float>(d.m);
+    float gv[K][4], ms[K];
+    float4 pv[K], mv[K];
+    uint32_t mw[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t e = e0 + 256 * k + l4;
+        ms[k] = 0.0f;
+        mw[k] = 0u;
+        mv[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const bool live = FULL || 256 * k < valid;  // codes and scales are padded to whole blocks
+        if (UF && live) {
+            mw[k] = ld_u1<true>(g_as<const void>(mc + e));
+            ms[k] = d.mm[(e0 >> 8) + k];
+        }
+        if constexpr (FULL) {
+            load_g4<G>(d.g, e, gv[k]);
             pv[k] = ld_f4<true>(d.p + e);
-            if constexpr (uf8) {
-                mw[k] = ld_u1<true>(g_as<const void>(g_as<const uint8_t>(d.m) + e));
-                ms[k] = d.mm[(e - c) / 256];
-            } else {
-                mf[k] = ld_f4<true>(g_as<const float>(d.m) + e);
+            if constexpr (!UF) mv[k] = ld_f4<true>(gp<const float>(mf + e));
+        } else {
+            float h[4], f[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bool ok = 256 * k + l4 + t < valid;
+                gv[k][t] = ok ? grad_at_g<G>(d.g, e + t) : 0.0f;
+                h[t] = ok ? d.p[e + t] : 0.0f;
+                f[t] = !UF && ok ? mf[e + t] : 0.0f;
             }
+            pv[k] = make_float4(h[0], h[1], h[2], h[3]);
+            mv[k] = make_float4(f[0], f[1], f[2], f[3]);
         }
+    }
+    const double clip = d.scal[0], rclip = 1.0 / clip;
+    FlatPos pos(d.rows, d.cols, e0 + l4);
 #pragma unroll
-        for (int k = 0; k < RB; ++k) {
-            if (r + k >= nr) break;
-            const int64_t e = (r0 + r + k) * d.cols + c0 + c;
-            float gv[4], mh[4];
-            unpack_graw<G>(g.h[k / 4], k % 4, gv);
-            if constexpr (uf8) {
-                const double st = div127((double)ms[k]);
+    for (int k = 0; k < K; ++k) {
+        if (!FULL && 256 * k >= valid) break;
+        const int64_t e = e0 + 256 * k + l4;
+        double ri[4], cf[4];
+        float si[4], sf[4];
+        pos.each(e, [&](int t, int64_t i, int64_t j) {
+            ri[t] = d.rfac[i];
+            cf[t] = d.cfac[j];
+            si[t] = (float)d.sr[i];
+            sf[t] = (float)d.sc[j];
+        });
+        pos.next();
+        bool in[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) mh[j] = uf8_decode((int32_t)(int8_t)(uint8_t)(mw[k] >> (8 * j)), st);
-            } else {
-                mh[0] = mf[k].x;
-                mh[1] = mf[k].y;
-                mh[2] = mf[k].z;
-                mh[3] = mf[k].w;
-            }
-            const float pin[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
-            float mnew[4], pout[4], uh[4];
-            double uu[4];
+        for (int t = 0; t < 4; ++t) in[t] = FULL || 256 * k + l4 + t < valid;
+        uint32_t am = 0u;
+        came_apply_block<UF>(a, ri, cf, si, sf, clip, rclip, gv[k], pv[k], mw[k], ms[k], mv[k], in, am);
+        if constexpr (FULL) {
+            st_f4<true>(d.p + e, pv[k]);
+            if constexpr (!UF) st_f4<true>(mf + e, mv[k]);
+        } else {
+            const float po[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w}, mo[4] = {mv[k].x, mv[k].y, mv[k].z, mv[k].w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) uu[j] = (ri[k] * cf[j]) * (double)gv[j];
-            div4_to_f32(uu, clip, rclip, uh);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                mnew[j] = (float)(a.beta1 * (double)mh[j] + a.omb1 * (double)uh[j]);
-                const double upd = (si[k] * sf[j]) * (double)mnew[j];
-                pout[j] = (float)((double)pin[j] * a.decay - a.lr * upd);
-            }
-            st_f4<true>(d.p + e, make_float4(pout[0], pout[1], pout[2], pout[3]));
-            if constexpr (uf8) {
-                uint32_t am = 0u;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) am = OpMax::f(am, abs_bits(mnew[j]));
-                am = group_reduce<OpMax, 64>(am);
-                const double rs = am != 0u ? rdiv127((double)u2f(am)) : 0.0;
-                uint32_t q[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) q[j] = rint_low_bits((double)mnew[j] * rs) & 0xFFu;
-                const uint32_t w = (q[0] & 0xFFu) | ((q[1] & 0xFFu) << 8) | ((q[2] & 0xFFu) << 16) | (q[3] << 24);
-                st_u1<true>(g_as<void>(g_as<uint8_t>(d.m) + e), w);
-                if (lane == 0) d.mm[(e - c) / 256] = u2f(am);
-            } else {
-                st_f4<true>(g_as<float>(d.m) + e, make_float4(mnew[0], mnew[1], mnew[2], mnew[3]));
-            }
+            for (int t = 0; t < 4; ++t)
+                if (in[t]) {
+                    d.p[e + t] = po[t];
+                    if constexpr (!UF) mf[e + t] = mo[t];
+                }
+        }
+        if constexpr (UF) {
+            st_u1<true>(g_as<void>(mc + e), mw[k]);
+            if (lane == 0) d.mm[(e0 >> 8) + k] = u2f(am);
         }
     }
 }
 
-// Other widths: flattened 1024-element chunks, 4 sub-tiles of 256 per wave,
-// so each momentum block (256) is one sub-tile; element by element.
-template <int G>
-__global__ __launch_bounds__(256) void came_apply_chunk_kernel(const FacArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = xcd_order(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * 4;
-    for (int64_t chunk = wave; chunk < a.total_chunks; chunk += nw) {
-        const FacDesc& d = a.D[locate_chunk(a.D, a.n2, chunk)];
-        const int64_t n = d.rows * d.cols;
-        const int64_t e0 = (chunk - d.chunk_begin) * 1024;
-        const double clip = d.scal[0], rclip = 1.0 / clip;
-        for (int k = 0; k < 4; ++k) {
-            const int64_t sb = e0 + 256 * k;
-            if (sb >= n) break;
-            const int64_t eb = sb + 4 * lane;
-            // row / column of the lane's first element (binary64 estimate, then exact correction)
-            int64_t i = (int64_t)((double)eb / (double)d.cols);
-            int64_t jc = eb - i * d.cols;
-            while (jc < 0) {
-                --i;
-                jc += d.cols;
-            }
-            while (jc >= d.cols) {
-                ++i;
-                jc -= d.cols;
-            }
-            float mnew[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t e = eb + j;
-                if (e < n) {
-                    const double uu = (d.rfac[i] * d.cfac[jc]) * (double)grad1<G>(d.g, e);
-                    const float uh = div_to_f32(uu, clip, rclip);
-                    const float m = came_momentum(a, d, e, uh);
-                    mnew[j] = m;
-                    const double upd = (d.sr[i] * d.sc[jc]) * (double)m;
-                    const double pd = (double)d.p[e] * a.decay;
-                    d.p[e] = (float)(pd - a.lr * upd);
-                }
-                if (++jc == d.cols) {
-                    jc = 0;
-                    ++i;
-                }
-            }
-            if (a.m_codec == UF8) {
-                uint32_t am = 0u;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) am = OpMax::f(am, abs_bits(mnew[j]));
-                am = group_reduce<OpMax, 64>(am);
-                const double r = am != 0u ? rdiv127((double)u2f(am)) : 0.0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int32_t q = (int32_t)__builtin_rint((double)mnew[j] * r);
-                    reinterpret_cast<int8_t*>(d.m)[eb + j] = (int8_t)q;  // padded to whole blocks
-                }
-                if (lane == 0) d.mm[sb / 256] = u2f(am);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (eb + j < n) reinterpret_cast<float*>(d.m)[eb + j] = mnew[j];
-            }
-        }
-    }
-}
-
-// Whole units: a wavefront takes a chunk of 8 / W rows x 256 W columns, W
-// units side by side (lane l: columns 4l .. 4l + 3 of each 256-column
-// segment), one row at a time: each row is one contiguous segment of 256 W
-// elements. A unit row holds 32 chunks' worth of the unit columns; the unit
-// columns left over in a row (ncu mod W) take W = 1 (8 rows x 256). Each
+// Widths that are a multiple of 256: a wavefront takes a chunk of 8 / W rows x
+// 256 W columns (lane l: columns 4l .. 4l + 3 of each 256-column segment), one
+// row at a time: each row is one contiguous segment of 256 W elements, and each
 // 256-column segment of a row is one momentum block over all 64 lanes.
 // W = 2 (2 KB parameter segments, 88 registers) measured 1.8% faster than
 // 8 rows x 256 columns in two 32-lane halves; W = 1 and 4 no faster, W = 8
 // (232 registers) 21% slower.
 constexpr int kCameApplyW = 2;
 template <int G, bool UF, int W>
-__device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, int64_t row0, int64_t col0) {
-    constexpr int R = 8 / W;
+__device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, int64_t row0, int64_t col0, int nrow) {
     const int lane = threadIdx.x & 63;
     const int64_t cb = col0 + 4 * lane;
     const int64_t cols = d.cols;
     const double clip = d.scal[0], rclip = 1.0 / clip;
     const gp<uint8_t> mc = g_as<uint8_t>(d.m);
     const gp<float> mf = g_as<float>(d.m);
-    // The parameter update runs in fp32 (the states never depend on p, which is held to a relative
-    // tolerance): p' = fma(-lr, (s_i s_j) m, p (1 - lr wd)) on the fp32 roundings of the factors.
-    const float lrf = (float)a.lr, decayf = (float)a.decay;
     double cf[W][4];
     float sf[W][4];
 #pragma unroll
@@ -2010,106 +1927,82 @@ __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, i
             sf[sg][j] = (float)d.sc[cb + 256 * sg + j];
         }
 #pragma unroll 1
-    for (int k = 0; k < R; ++k) {
+    for (int k = 0; k < nrow; ++k) {
         const int64_t row = row0 + k;
-        const double ri = d.rfac[row], rk = ri * rclip;
+        const double ri = d.rfac[row];
         const float si = (float)d.sr[row];
         float gv[W][4], ms[W];
-        float4 pv[W], mv[UF ? 1 : W];
+        float4 pv[W], mv[W];
         uint32_t mw[W];
 #pragma unroll
         for (int sg = 0; sg < W; ++sg) {
             const int64_t e = row * cols + cb + 256 * sg;
             load_g4<G>(d.g, e, gv[sg]);
             pv[sg] = ld_f4<true>(d.p + e);
+            ms[sg] = 0.0f;
+            mw[sg] = 0u;
             if constexpr (UF) {
                 mw[sg] = ld_u1<true>(g_as<const void>(mc + e));
                 ms[sg] = d.mm[e >> 8];
             } else {
-                mv[sg] = ld_f4<true>(mf + e);
+                mv[sg] = ld_f4<true>(gp<const float>(mf + e));
             }
         }
 #pragma unroll
         for (int sg = 0; sg < W; ++sg) {
             const int64_t e = row * cols + cb + 256 * sg;
-            float mh[4], uh[4], mnew[4];
+            const double r4[4] = {ri, ri, ri, ri};
+            const float s4[4] = {si, si, si, si};
+            const bool in[4] = {true, true, true, true};
+            uint32_t am = 0u;
+            came_apply_block<UF>(a, r4, cf[sg], s4, sf[sg], clip, rclip, gv[sg], pv[sg], mw[sg], ms[sg], mv[sg], in, am);
+            st_f4<true>(d.p + e, pv[sg]);
             if constexpr (UF) {
-                const double st = div127((double)ms[sg]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) mh[j] = uf8_decode((int32_t)(int8_t)(uint8_t)(mw[sg] >> (8 * j)), st);
-            } else {
-                mh[0] = mv[sg].x, mh[1] = mv[sg].y, mh[2] = mv[sg].z, mh[3] = mv[sg].w;
-            }
-            double qv[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) qv[j] = (rk * cf[sg][j]) * (double)gv[sg][j];
-            if (__builtin_expect(!f32_roundings_decided<4>(qv, uh), 0)) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) uh[j] = (float)(((ri * cf[sg][j]) * (double)gv[sg][j]) / clip);
-            }
-            const float pin[4] = {pv[sg].x, pv[sg].y, pv[sg].z, pv[sg].w};
-            float pout[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                mnew[j] = (float)(a.beta1 * (double)mh[j] + a.omb1 * (double)uh[j]);
-                const float upd = (si * sf[sg][j]) * mnew[j];
-                pout[j] = __builtin_fmaf(-lrf, upd, pin[j] * decayf);
-            }
-            st_f4<true>(d.p + e, make_float4(pout[0], pout[1], pout[2], pout[3]));
-            if constexpr (UF) {
-                uint32_t am = 0u;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) am = OpMax::f(am, abs_bits(mnew[j]));
-                am = group_reduce<OpMax, 64>(am);
-                const double rs = am != 0u ? rdiv127((double)u2f(am)) : 0.0;
-                uint32_t qv[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) qv[j] = rint_low_bits((double)mnew[j] * rs) & 0xFFu;
-                st_u1<true>(g_as<void>(mc + e), qv[0] | (qv[1] << 8) | (qv[2] << 16) | (qv[3] << 24));
+                st_u1<true>(g_as<void>(mc + e), mw[sg]);
                 if (lane == 0) d.mm[e >> 8] = u2f(am);
             } else {
-                st_f4<true>(mf + e, make_float4(mnew[0], mnew[1], mnew[2], mnew[3]));
+                st_f4<true>(mf + e, mv[sg]);
             }
         }
     }
 }
 
 template <int G, bool UF>
-__global__ __launch_bounds__(256) void came_apply_whole_kernel(const FacArgs a, int64_t base) {
-    const int64_t chunk = base + xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t unit = chunk / kChunksPerUnit;
-    if (unit >= a.whole_units) return;
-    const GD d = gview(a.D[locate_unit(a.D, a.n2, unit)]);
-    const RowChunk c = row_chunk<kCameApplyW>(d, chunk);
+__global__ __launch_bounds__(256) void came_apply_kernel(const FacArgs a, int64_t base) {
+    const int64_t chunk = chunk_of_wave(base);
+    if (chunk >= a.rows_ach) return;
+    const GD d = gview(a.D[locate(a.ach_begins, a.n2, chunk)]);
+    const RowChunk c = row_chunk<kCameApplyW>(d, chunk - d.ach_begin);
+    const int64_t left = d.rows - c.row0;
+    if (left <= 0) return;
     if (c.full)
-        came_apply_rows<G, UF, kCameApplyW>(a, d, c.row0, c.col0);
+        came_apply_rows<G, UF, kCameApplyW>(a, d, c.row0, c.col0, left < 8 / kCameApplyW ? (int)left : 8 / kCameApplyW);
     else
-        came_apply_rows<G, UF, 1>(a, d, c.row0, c.col0);
+        came_apply_rows<G, UF, 1>(a, d, c.row0, c.col0, left < 8 ? (int)left : 8);
+}
+
+template <int G, bool UF>
+__global__ __launch_bounds__(256) void came_apply_flat_kernel(const FacArgs a, int64_t base) {
+    const int64_t chunk = chunk_of_wave(base);
+    if (chunk >= a.total_ach) return;
+    const GD d = gview(a.D[locate(a.ach_begins, a.n2, chunk)]);
+    const int64_t e0 = (chunk - d.ach_begin) * kFlatChunk, left = d.rows * d.cols - e0;
+    if (left >= kFlatChunk)
+        came_apply_flat<G, UF, true>(a, d, e0, kFlatChunk);
+    else
+        came_apply_flat<G, UF, false>(a, d, e0, (int)left);
+}
+
+template <int G, bool UF>
+static hipError_t came_apply_launch(const FacArgs& a, hipStream_t s) {
+    const hipError_t e = launch_per_chunk(came_apply_kernel<G, UF>, a, 0, a.rows_ach, s);
+    return e != hipSuccess ? e : launch_per_chunk(came_apply_flat_kernel<G, UF>, a, a.rows_ach, a.total_ach, s);
 }
 
 hipError_t launch_came_apply(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.total_units == 0) return hipSuccess;
     const bool uf = a.m_codec == UF8;
-    const bool bf = grad_dtype == G_BF16;
-    hipError_t e = bf ? (uf ? launch_per_chunk(came_apply_whole_kernel<G_BF16, true>, a, s)
-                            : launch_per_chunk(came_apply_whole_kernel<G_BF16, false>, a, s))
-                      : (uf ? launch_per_chunk(came_apply_whole_kernel<G_F32, true>, a, s)
-                            : launch_per_chunk(came_apply_whole_kernel<G_F32, false>, a, s));
-    if (e != hipSuccess) return e;
-    const int64_t b0 = a.whole_units, b1 = a.total_units;
-    e = bf ? (uf ? launch_wave_per_unit(came_apply_unit_kernel<G_BF16, true>, a, b0, b1, s)
-                 : launch_wave_per_unit(came_apply_unit_kernel<G_BF16, false>, a, b0, b1, s))
-           : (uf ? launch_wave_per_unit(came_apply_unit_kernel<G_F32, true>, a, b0, b1, s)
-                 : launch_wave_per_unit(came_apply_unit_kernel<G_F32, false>, a, b0, b1, s));
-    if (e != hipSuccess || a.total_chunks == 0) return e;
-    const int64_t cap = int64_t(1) << 30;
-    const int64_t want = (a.total_chunks + 3) / 4;
-    const int grid = (int)(want < cap ? want : cap);
-    if (grad_dtype == G_BF16)
-        hipLaunchKernelGGL(came_apply_chunk_kernel<G_BF16>, dim3(grid), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(came_apply_chunk_kernel<G_F32>, dim3(grid), dim3(256), 0, s, a);
-    return hipGetLastError();
+    if (grad_dtype == G_BF16) return uf ? came_apply_launch<G_BF16, true>(a, s) : came_apply_launch<G_BF16, false>(a, s);
+    return uf ? came_apply_launch<G_F32, true>(a, s) : came_apply_launch<G_F32, false>(a, s);
 }
 
 // ------------------------------------------------ CAME 1-D tensors (WG each)
