@@ -475,8 +475,7 @@ al_status al_quantize(int32_t codec, const float* x, int64_t n, int32_t block, f
     if (n == 0) return AL_OK;
     if (!x || !codes || !meta) return fail(AL_EINVAL, "al_quantize: NULL buffer");
     if (!aligned16(x) || !aligned16(codes) || !aligned16(meta)) return fail(AL_EALIGN, "al_quantize: alignment");
-    hipError_t e = al::launch_quantize(codec, x, n, block, log_floor, codes, meta, al::device_cu_count() * 8,
-                                       as_stream(stream));
+    hipError_t e = al::launch_quantize(codec, x, n, block, log_floor, codes, meta, as_stream(stream));
     return e == hipSuccess ? AL_OK : hip_fail(e, "al_quantize launch");
 }
 
@@ -490,8 +489,7 @@ al_status al_dequantize(int32_t codec, const void* codes, const float* meta, int
     if (n == 0) return AL_OK;
     if (!codes || !meta || !out) return fail(AL_EINVAL, "al_dequantize: NULL buffer");
     if (!aligned16(out) || !aligned16(codes) || !aligned16(meta)) return fail(AL_EALIGN, "al_dequantize: alignment");
-    hipError_t e = al::launch_dequantize(codec, codes, meta, n, block, out, al::device_cu_count() * 8,
-                                         as_stream(stream));
+    hipError_t e = al::launch_dequantize(codec, codes, meta, n, block, out, as_stream(stream));
     return e == hipSuccess ? AL_OK : hip_fail(e, "al_dequantize launch");
 }
 

@@ -72,54 +72,6 @@ __device__ __forceinline__ uint32_t group_reduce(uint32_t x) {
     return x;
 }
 
-// ------------------------------------------------------------------ AL code
-// Fitted interval of one block from its exact positive min / max bit
-// patterns (0 max means "no positive value").
-struct ALFit {
-    double lmin;   // unrounded binary64 l_min
-    double delta;  // unrounded binary64 width
-    bool any;
-};
-
-__device__ __forceinline__ ALFit al_fit(uint32_t min_bits, uint32_t max_bits, float log_floor) {
-    ALFit f;
-    f.any = max_bits != 0u;
-    if (!f.any) {
-        f.lmin = 0.0;
-        f.delta = 0.0;
-        return f;
-    }
-    double lo = log2((double)u2f(min_bits));
-    double hi = log2((double)u2f(max_bits));
-    double l0 = lo > (double)log_floor ? lo : (double)log_floor;
-    double l1 = hi < 126.0 ? hi : 126.0;
-    if (min_bits == max_bits) l1 = l0 + 1.0;
-    double d = l1 - l0;
-    if (d < 1e-12) d = 1e-12;
-    f.lmin = l0;
-    f.delta = d;
-    return f;
-}
-
-// Code of one element under a fitted interval; LEVELS = L - 2.
-template <int LEVELS>
-__device__ __forceinline__ uint32_t al_encode(float x, const ALFit& f) {
-    if (!(x > 0.0f)) return 0u;
-    double z = (log2((double)x) - f.lmin) / f.delta;
-    z = z < 0.0 ? 0.0 : z;
-    z = z > 1.0 ? 1.0 : z;
-    double y = (double)LEVELS * z;
-    return 1u + (uint32_t)__builtin_rint(y);
-}
-
-// Decode of one code from the stored fp32 metadata: step = delta32 / (L-2),
-// value = fl32(2^(lmin32 + (q-1) * step)).
-__device__ __forceinline__ float al_decode(uint32_t q, double lmin32, double step) {
-    if (q == 0u) return 0.0f;
-    double e = lmin32 + (double)(q - 1u) * step;
-    return (float)exp2(e);
-}
-
 // ------------------------------------------------- fast binary64 exp2 / encode
 // 2^E in binary64 for |E| < 1000: E = n + f with n = rint(E), |f| <= 1/2, and
 // 2^f = e^(f ln 2) by its Taylor series to degree 13 (coefficients
@@ -217,15 +169,44 @@ __device__ __forceinline__ double fit_log2(float xf) {
     return sum + (err + tail);
 }
 
+// ------------------------------------------------------------------ AL code
+// Fitted interval of one block from its exact positive min / max bit
+// patterns (0 max means "no positive value").
+struct ALFit {
+    double lmin;   // unrounded binary64 l_min
+    double delta;  // unrounded binary64 width
+    bool any;
+};
+
+__device__ __forceinline__ ALFit al_fit(uint32_t min_bits, uint32_t max_bits, float log_floor) {
+    ALFit f;
+    f.any = max_bits != 0u;
+    if (!f.any) {
+        f.lmin = 0.0;
+        f.delta = 0.0;
+        return f;
+    }
+    double lo = fit_log2(u2f(min_bits));
+    double hi = fit_log2(u2f(max_bits));
+    double l0 = lo > (double)log_floor ? lo : (double)log_floor;
+    double l1 = hi < 126.0 ? hi : 126.0;
+    if (min_bits == max_bits) l1 = l0 + 1.0;
+    double d = l1 - l0;
+    if (d < 1e-12) d = 1e-12;
+    f.lmin = l0;
+    f.delta = d;
+    return f;
+}
+
 // Per-block encode parameters: the binary64 interval start, LEVELS/delta,
 // and a guard band on the code position (binary64 and fp32 arithmetic).
 struct ALEnc {
     double lmin;
     double inv;    // (L - 2) / delta
-    double fr;     // lmin - floor(lmin), exact
+    double c;      // -(lmin - floor(lmin)) inv
     double guard;  // bound on |fast position - binary64 position|
     int I;         // floor(lmin)
-    float inv32, fr32, guard32;  // the fp32 path (AL8): fl32(inv), fl32(fr), its guard
+    float inv32, fr32, guard32;  // the fp32 path (AL8): fl32(inv), fl32(lmin - floor(lmin)), its guard
 };
 
 __device__ __forceinline__ ALEnc al_enc_params(double lmin, double inv) {
@@ -234,37 +215,43 @@ __device__ __forceinline__ ALEnc al_enc_params(double lmin, double inv) {
     p.inv = inv;
     const double I = __builtin_floor(lmin);
     p.I = (int)I;
-    p.fr = lmin - I;
+    const double fr = lmin - I;  // exact
+    p.c = -fr * inv;
     p.guard = inv * kLog2MantErr + 1e-9;
     // fp32 path: |y32 - y| <= inv (kLog2MantErr + 2^-24 + 2^-25) + 3 * 2^-24 |y| (the mantissa log,
     // the fp32 rounding of fr and of l - fr, and three relative roundings of at most 2^-24: d, inv, the
     // product); only |y| <= 255 decides a code (beyond it both sides clamp), so 1.25 * 2^-21 inv +
     // 2^-14 bounds it
     p.inv32 = (float)inv;
-    p.fr32 = (float)p.fr;
+    p.fr32 = (float)fr;
     p.guard32 = (float)(inv * 0x1.4p-21 + 0x1p-14);
     return p;
 }
 
 // Code of x > 0 (0 for x <= 0). The position y = LEVELS * (log2 x - lmin) /
-// delta comes from x = mant * 2^ex: y = ((ex - I) + (log2f_hw(mant) - fr)) *
-// inv, whose only sizeable error is the fp32 mantissa log (kLog2MantErr); a
-// position within that guard of a rounding boundary is recomputed with the
-// binary64 log2, so the rounding decision is the binary64 one.
+// delta comes from x = mant * 2^ex: y = (ex - I) inv + (log2f_hw(mant) - fr)
+// inv, whose only sizeable error is the fp32 mantissa log (kLog2MantErr; the
+// fused multiply-adds round at 2^-53 of at most 65534); a position within that
+// guard of a rounding boundary is recomputed with the binary64 log2 of the fp32
+// value, so the rounding decision is the binary64 one. The position is rounded by
+// adding 1.5 2^52 (the low word of the sum is the code's offset). An AL16 block
+// rechecks about one element in 500 at a width of 15 bits, so most wavefronts
+// take that branch for some of their elements: fit_log2 costs half the general
+// logarithm there.
 template <int LEVELS>
 __device__ __forceinline__ uint32_t al_encode_fast(float x, const ALEnc& p) {
+    constexpr double kMagic = 0x1.8p52;
     const float mant = __builtin_amdgcn_frexp_mantf(x);
     const int ex = __builtin_amdgcn_frexp_expf(x);
     const float l = __builtin_amdgcn_logf(mant);
-    const double d = (double)(ex - p.I) + ((double)l - p.fr);
-    double yc = __builtin_fmin(__builtin_fmax(d * p.inv, 0.0), (double)LEVELS);
-    double r = __builtin_rint(yc);
-    if (__builtin_fabs(yc - r) > 0.5 - p.guard) {
-        const double ys = (log2((double)x) - p.lmin) * p.inv;
-        yc = __builtin_fmin(__builtin_fmax(ys, 0.0), (double)LEVELS);
-        r = __builtin_rint(yc);
+    const double y = __builtin_fma((double)(ex - p.I), p.inv, __builtin_fma((double)l, p.inv, p.c));
+    const double yc = __builtin_fmin(__builtin_fmax(y, 0.0), (double)LEVELS);
+    double t = yc + kMagic;
+    if (__builtin_fabs(yc - (t - kMagic)) > 0.5 - p.guard) {
+        const double ys = (fit_log2(x) - p.lmin) * p.inv;
+        t = __builtin_fmin(__builtin_fmax(ys, 0.0), (double)LEVELS) + kMagic;
     }
-    return x > 0.0f ? 1u + (uint32_t)r : 0u;
+    return x > 0.0f ? 1u + (uint32_t)__builtin_bit_cast(uint64_t, t) : 0u;
 }
 
 // AL8 code of x with the fast position in fp32 arithmetic (AL8 positions are
@@ -284,7 +271,7 @@ __device__ __forceinline__ uint32_t al_encode_f32(float x, int I, float fr32, fl
     float r = __builtin_rintf(yc);
     if (__builtin_fabsf(yc - r) > 0.5f - guard32) {
         const double2 li = slow();
-        const double ys = (log2((double)x) - li.x) * li.y;
+        const double ys = (fit_log2(x) - li.x) * li.y;
         r = (float)__builtin_rint(__builtin_fmin(__builtin_fmax(ys, 0.0), 254.0));
     }
     return x > 0.0f ? 1u + (uint32_t)r : 0u;

@@ -79,9 +79,9 @@ hipError_t launch_adamw(const AdamWLaunch& a, int grad_dtype, int m_codec, int v
 
 // ------------------------------------------------------------------ codec
 hipError_t launch_quantize(int codec, const float* x, int64_t n, int block, float log_floor, void* codes,
-                           float* meta, int grid_cap, hipStream_t s);
+                           float* meta, hipStream_t s);
 hipError_t launch_dequantize(int codec, const void* codes, const float* meta, int64_t n, int block,
-                             float* out, int grid_cap, hipStream_t s);
+                             float* out, hipStream_t s);
 
 hipError_t launch_diag_stream(int mode, float* p, const uint16_t* g, uint8_t* m, uint8_t* v, int64_t n,
                               hipStream_t s);

@@ -2,15 +2,19 @@
 // (section 4.1, Eq. al_bounds, al_quant, al_dequant; section 4.2) and the
 // uniform signed 8-bit code UF8 (section 4.3).
 //
-// Quantize: a wavefront owns a tile of max(B, 256) consecutive elements,
-// 4 per lane; the block reduction (positive min/max, or absmax) runs in
-// registers and across lanes; each element is read once and its code
-// written once. Dequantize is elementwise, 4 elements per lane.
-#include "al_codec_dev.hpp"
+// A wavefront owns a chunk of max(B, 256 K) consecutive elements, 4 per lane in
+// each 256-element sub-tile, all of its loads issued before the arithmetic and
+// each byte touched once. K = 8 where that fills the chip: the per-block scalar
+// work of a chunk (binary64 divisions and endpoint logarithms) then runs once, one
+// block per lane pair, for up to 32 blocks at a time; short arrays take K = 1 for
+// more wavefronts.
 #include "al_device.hpp"
 #include "al_internal.hpp"
 
 namespace al {
+
+// The decode polynomial's coefficients, read with scalar loads.
+__constant__ Exp2Coef kExp2Codec = AL_EXP2_TAYLOR;
 
 const Exp2Coef& exp2_coef() {
     static const Exp2Coef c = AL_EXP2_TAYLOR;
@@ -18,61 +22,240 @@ const Exp2Coef& exp2_coef() {
 }
 
 
-template <int C, int B>
-__global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__ x, int64_t n, float log_floor,
-                                                        void* codes, float* meta) {
-    constexpr int T = B > kSub ? B : kSub;
-    const int lane = threadIdx.x & 63;
-    const int64_t wpb = blockDim.x >> 6;
-    const int64_t wave = (int64_t)blockIdx.x * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * wpb;
-    const int64_t tiles = (n + T - 1) / T;
-    for (int64_t tile = wave; tile < tiles; tile += nwaves) {
-        const int64_t e0 = tile * T;
-        const int64_t valid = n - e0;
-        if (valid >= T)
-            quantize_tile<C, B, true>(x, e0, T, lane, log_floor, codes, meta);
-        else
-            quantize_tile<C, B, false>(x, e0, valid, lane, log_floor, codes, meta);
+// Encode parameters of blocks smaller than a sub-tile, in LDS.
+struct BlockEnc {
+    ALEnc e;
+};
+
+// One chunk of K sub-tiles from element e0, the first `valid` elements inside the
+// array (FULL: all).
+template <int C, int B, int K, bool FULL>
+__device__ __forceinline__ void quantize_chunk(gp<const float> x, int64_t e0, int valid, int lane, float log_floor,
+                                               gp<uint8_t> codes, gp<float> meta, uint2* skey, BlockEnc* senc) {
+    constexpr int NB = 256 * K / B;               // blocks
+    constexpr int GL = B < kSub ? B / 4 : 64;     // lanes per block within a sub-tile
+    constexpr int PER = B < kSub ? kSub / B : 1;  // blocks per sub-tile
+    constexpr int SUBS = B < kSub ? 1 : B / kSub; // sub-tiles per block
+    float xv[K][4];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int rel = k * kSub + 4 * lane;
+        if constexpr (FULL) {
+            const float4 t = ld_f4<true>(x + e0 + rel);
+            xv[k][0] = t.x, xv[k][1] = t.y, xv[k][2] = t.z, xv[k][3] = t.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xv[k][j] = rel + j < valid ? x[e0 + rel + j] : 0.0f;
+        }
+    }
+    const int64_t b0 = e0 / B;
+    const auto store = [&](int k, const uint32_t q[4]) {
+        // a block is written whole (padding codes are 0) if any of its elements is inside the array
+        const int first = (k * kSub + 4 * lane) / B * B;
+        if (FULL || first < valid) store_codes4<C, true>(codes, e0 + k * kSub + 4 * lane, q);
+    };
+    if constexpr (C == UF8) {
+        uint32_t am = 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) am = OpMax::f(am, abs_bits(xv[k][j]));
+            if ((k + 1) % SUBS != 0) continue;
+            am = group_reduce<OpMax, GL>(am);
+            const int b = (k * kSub + (B < kSub ? 4 * lane : 0)) / B;
+            const double r = am != 0u ? rdiv127((double)u2f(am)) : 0.0;
+            if (lane % GL == 0 && (FULL || b * B < valid)) meta[b0 + b] = u2f(am);
+#pragma unroll
+            for (int s = k + 1 - SUBS; s <= k; ++s) {
+                uint32_t q[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) q[j] = rint_low_bits((double)xv[s][j] * r) & 0xFFu;
+                store(s, q);
+            }
+            am = 0u;
+        }
+    } else {
+        constexpr int LEVELS = levels_of<C>();
+        // 1. exact positive minimum and maximum of each block; lanes 2b, 2b + 1 take block b's
+        const int pb = lane >> 1;
+        uint32_t kmin = 0xFFFFFFFFu, kmax = 0u, mn = 0xFFFFFFFFu, mx = 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                mn = OpMin::f(mn, pos_min_key(xv[k][j]));
+                mx = OpMax::f(mx, pos_max_key(xv[k][j]));
+            }
+            if ((k + 1) % SUBS != 0) continue;
+            mn = group_reduce<OpMin, GL>(mn);
+            mx = group_reduce<OpMax, GL>(mx);
+            if constexpr (B < kSub) {
+                if (lane % GL == 0) skey[k * PER + lane / GL] = make_uint2(mn, mx);
+            } else {
+                kmin = pb == k / SUBS ? mn : kmin;
+                kmax = pb == k / SUBS ? mx : kmax;
+            }
+            mn = 0xFFFFFFFFu;
+            mx = 0u;
+        }
+        if constexpr (B < kSub) {
+            __builtin_amdgcn_wave_barrier();  // this wavefront's LDS accesses run in order
+            if (pb < NB) {
+                kmin = skey[pb].x;
+                kmax = skey[pb].y;
+            }
+        }
+        // 2. the intervals, one block per lane pair (each lane one endpoint's logarithm)
+        const bool any = kmax != 0u;
+        const double lg = fit_log2(any ? u2f((lane & 1) ? kmax : kmin) : 1.0f);
+        const double lg_other = dpp_d<kDppQuadXor1>(lg);
+        const double lo = (lane & 1) ? lg_other : lg, hi = (lane & 1) ? lg : lg_other;
+        const double l0 = lo > (double)log_floor ? lo : (double)log_floor;
+        double l1 = hi < 126.0 ? hi : 126.0;
+        if (kmin == kmax) l1 = l0 + 1.0;
+        double dl = l1 - l0;
+        dl = dl < 1e-12 ? 1e-12 : dl;
+        if ((lane & 1) == 0 && pb < NB && (FULL || pb * B < valid)) {
+            meta[2 * (b0 + pb)] = any ? (float)l0 : 0.0f;
+            meta[2 * (b0 + pb) + 1] = any ? (float)dl : 0.0f;
+        }
+        const double inv = any ? (double)LEVELS / dl : 1.0;
+        if constexpr (B < kSub) {
+            if ((lane & 1) == 0 && pb < NB) senc[pb].e = al_enc_params(any ? l0 : 0.0, inv);
+            __builtin_amdgcn_wave_barrier();
+        }
+        // 3. codes
+        ALEnc enc;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if constexpr (B < kSub)
+                enc = senc[(k * kSub + 4 * lane) / B].e;
+            else if (k % SUBS == 0)
+                enc = al_enc_params(readlane_d(any ? l0 : 0.0, 2 * (k / SUBS)), readlane_d(inv, 2 * (k / SUBS)));
+            uint32_t q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                q[j] = C == AL8 ? al_encode_f32(xv[k][j], enc) : al_encode_fast<LEVELS>(xv[k][j], enc);
+            store(k, q);
+        }
     }
 }
 
-template <int C, int B>
-__global__ __launch_bounds__(256) void dequantize_kernel(const void* __restrict__ codes,
-                                                          const float* __restrict__ meta, int64_t n,
-                                                          float* __restrict__ out, const Exp2Coef cf) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; 4 * i < n; i += stride) {
-        const int64_t e = 4 * i;
-        const int64_t blk = e / B;
-        uint32_t q[4];
-        const bool full = e + 4 <= n;
-        if (full) {
-            load_codes4<C>(codes, e, q);
-        } else {
+__device__ __forceinline__ int64_t codec_chunk() {
+    return xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+template <int C, int B, int K>
+__global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__ x, int64_t n, int64_t base,
+                                                        float log_floor, void* codes, float* meta) {
+    constexpr int E = 256 * K;
+    constexpr int NS = C != UF8 && B < kSub ? E / B : 1;
+    __shared__ uint2 skey[4][NS];
+    __shared__ BlockEnc senc[4][NS];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t e0 = (base + codec_chunk()) * E, left = n - e0;
+    const gp<const float> xg = to_g(x);
+    const gp<uint8_t> cg = (gp<uint8_t>)to_g(codes);
+    if (left >= E)
+        quantize_chunk<C, B, K, true>(xg, e0, E, lane, log_floor, cg, to_g(meta), skey[w], senc[w]);
+    else if (left > 0)
+        quantize_chunk<C, B, K, false>(xg, e0, (int)left, lane, log_floor, cg, to_g(meta), skey[w], senc[w]);
+}
+
+// AL8 blocks of 512 and more decode through a table of the block's levels in LDS
+// (255 evaluations, 4 per lane, in place of one per element; entry 0 is exact zero,
+// so the values are those of al_decode_fast); other codes evaluate each element.
+template <int C, int B, int K, bool FULL>
+__device__ __forceinline__ void dequantize_chunk(gp<const uint8_t> codes, gp<const float> meta, int64_t e0, int valid,
+                                                 int lane, gp<float> out, float* lut) {
+    constexpr int NB = 256 * K / B;
+    constexpr int SUBS = B < kSub ? 1 : B / kSub;
+    constexpr bool LUT = C == AL8 && B >= 512;
+    using W = typename std::conditional<C == AL16, uint2, uint32_t>::type;
+    W w[K];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) q[j] = (e + j < n) ? load_code1<C>(codes, e + j) : 0u;
-        }
-        F4 o;
+    for (int k = 0; k < K; ++k) {
+        const int rel = k * kSub + 4 * lane;
+        // code arrays hold whole blocks: a sub-tile's words are there if its block has an element
+        const bool live = FULL || rel / B * B < valid;
+        if constexpr (C == AL16)
+            w[k] = live ? ld_u2<true>(g_as<const void>(codes + 2 * (e0 + rel))) : make_uint2(0u, 0u);
+        else
+            w[k] = live ? ld_u1<true>(g_as<const void>(codes + e0 + rel)) : 0u;
+    }
+    // decode step and l_min of block `lane`
+    const int64_t b0 = e0 / B;
+    float l32 = 0.0f;
+    double step = 0.0;
+    if (lane < NB && (FULL || lane * B < valid)) {
         if constexpr (C == UF8) {
-            const double step = div127((double)meta[blk]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o.v[j] = uf8_decode((int32_t)(int8_t)(uint8_t)q[j], step);
+            step = div127((double)meta[b0 + lane]);
         } else {
-            const float2 mm = *reinterpret_cast<const float2*>(meta + 2 * blk);
-            const double l32 = (double)mm.x;
-            const double step = (double)mm.y / (double)levels_of<C>();
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o.v[j] = al_decode_fast(q[j], l32, step, cf);
+            l32 = meta[2 * (b0 + lane)];
+            step = (double)meta[2 * (b0 + lane) + 1] / (double)levels_of<C>();
         }
-        if (full) {
-            store_f4(out + e, o);
+    }
+    if constexpr (LUT) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const double st = readlane_d(step, b), l = (double)u2f(readlane_u(f2u(l32), b));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lut[b * 256 + lane + 64 * i] = al_decode_fast((uint32_t)(lane + 64 * i), l, st, kExp2Codec);
+        }
+        __builtin_amdgcn_wave_barrier();  // this wavefront's LDS accesses run in order
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        uint32_t q[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (C == AL16)
+                q[j] = ((j < 2 ? w[k].x : w[k].y) >> (16 * (j & 1))) & 0xFFFFu;
+            else
+                q[j] = (w[k] >> (8 * j)) & 0xFFu;
+        }
+        float o[4];
+        if constexpr (LUT) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] = lut[(k / SUBS) * 256 + q[j]];
+        } else {
+            double st, l = 0.0;
+            if constexpr (B >= kSub) {
+                st = readlane_d(step, k / SUBS);
+                if constexpr (C != UF8) l = (double)u2f(readlane_u(f2u(l32), k / SUBS));
+            } else {
+                const int src = (k * kSub + 4 * lane) / B;
+                st = shfl_d(step, src);
+                if constexpr (C != UF8) l = (double)__shfl(l32, src);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                o[j] = C == UF8 ? uf8_decode((int32_t)(int8_t)(uint8_t)q[j], st) : al_decode_fast(q[j], l, st, kExp2Codec);
+        }
+        const int rel = k * kSub + 4 * lane;
+        if constexpr (FULL) {
+            st_f4<false>(out + e0 + rel, make_float4(o[0], o[1], o[2], o[3]));
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (e + j < n) out[e + j] = o.v[j];
+                if (rel + j < valid) out[e0 + rel + j] = o[j];
         }
     }
+}
+
+template <int C, int B, int K>
+__global__ __launch_bounds__(256) void dequantize_kernel(const void* __restrict__ codes,
+                                                          const float* __restrict__ meta, int64_t n, int64_t base,
+                                                          float* __restrict__ out) {
+    constexpr int E = 256 * K;
+    __shared__ float lut[4][C == AL8 && B >= 512 ? E / B * 256 : 1];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t e0 = (base + codec_chunk()) * E, left = n - e0;
+    const gp<const uint8_t> cg = (gp<const uint8_t>)to_g(codes);
+    if (left >= E)
+        dequantize_chunk<C, B, K, true>(cg, to_g(meta), e0, E, lane, to_g(out), lut[w]);
+    else if (left > 0)
+        dequantize_chunk<C, B, K, false>(cg, to_g(meta), e0, (int)left, lane, to_g(out), lut[w]);
 }
 
 // Device math primitives the codes rely on, evaluated elementwise so a test
@@ -309,68 +492,86 @@ hipError_t launch_diag_stream(int mode, float* p, const uint16_t* g, uint8_t* m,
     return hipSuccess;
 }
 
-template <int C>
-static hipError_t quant_b(const float* x, int64_t n, int block, float lf, void* codes, float* meta, int grid,
-                          hipStream_t s) {
-    switch (block) {
-#define AL_Q(BB)                                                                                         \
-    case BB:                                                                                             \
-        hipLaunchKernelGGL((quantize_kernel<C, BB>), dim3(grid), dim3(256), 0, s, x, n, lf, codes, meta); \
-        return hipGetLastError();
-        AL_Q(64)
-        AL_Q(128)
-        AL_Q(256)
-        AL_Q(512)
-        AL_Q(1024)
-        AL_Q(2048)
-#undef AL_Q
+// Chunks of 2048 elements (K = 8), or of max(B, 256) where the array has too few
+// of those to give every SIMD a wavefront.
+constexpr int64_t kCodecLong = 2048 * 1024;
+
+// One wavefront per chunk, 4 per workgroup; launches beyond 2^32 chunks are split.
+template <class F>
+static hipError_t codec_launch(int64_t n, int64_t elems, F launch) {
+    constexpr int64_t kMaxGrid = int64_t(1) << 30;
+    const int64_t chunks = (n + elems - 1) / elems;
+    for (int64_t base = 0; base < chunks; base += 4 * kMaxGrid) {
+        const int64_t left = (chunks - base + 3) / 4;
+        launch(dim3((unsigned)(left < kMaxGrid ? left : kMaxGrid)), base);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
+    return hipSuccess;
+}
+
+template <int C, int B>
+static hipError_t quant_t(const float* x, int64_t n, float lf, void* codes, float* meta, hipStream_t s) {
+    constexpr int KS = B > kSub ? B / kSub : 1;
+    if (n >= kCodecLong)
+        return codec_launch(n, 2048, [&](dim3 g, int64_t base) {
+            hipLaunchKernelGGL((quantize_kernel<C, B, 8>), g, dim3(256), 0, s, x, n, base, lf, codes, meta);
+        });
+    return codec_launch(n, KS * kSub, [&](dim3 g, int64_t base) {
+        hipLaunchKernelGGL((quantize_kernel<C, B, KS>), g, dim3(256), 0, s, x, n, base, lf, codes, meta);
+    });
+}
+
+template <int C, int B>
+static hipError_t dequant_t(const void* codes, const float* meta, int64_t n, float* out, hipStream_t s) {
+    constexpr int KS = B > kSub ? B / kSub : 1;
+    if (n >= kCodecLong)
+        return codec_launch(n, 2048, [&](dim3 g, int64_t base) {
+            hipLaunchKernelGGL((dequantize_kernel<C, B, 8>), g, dim3(256), 0, s, codes, meta, n, base, out);
+        });
+    return codec_launch(n, KS * kSub, [&](dim3 g, int64_t base) {
+        hipLaunchKernelGGL((dequantize_kernel<C, B, KS>), g, dim3(256), 0, s, codes, meta, n, base, out);
+    });
+}
+
+#define AL_BLOCKS(F, ...)                       \
+    switch (block) {                            \
+        case 64: return F<C, 64>(__VA_ARGS__);     \
+        case 128: return F<C, 128>(__VA_ARGS__);   \
+        case 256: return F<C, 256>(__VA_ARGS__);   \
+        case 512: return F<C, 512>(__VA_ARGS__);   \
+        case 1024: return F<C, 1024>(__VA_ARGS__); \
+        case 2048: return F<C, 2048>(__VA_ARGS__); \
+    }                                           \
     return hipErrorInvalidValue;
+
+template <int C>
+static hipError_t quant_b(const float* x, int64_t n, int block, float lf, void* codes, float* meta, hipStream_t s) {
+    AL_BLOCKS(quant_t, x, n, lf, codes, meta, s)
 }
 
 template <int C>
-static hipError_t dequant_b(const void* codes, const float* meta, int64_t n, int block, float* out, int grid,
-                            hipStream_t s) {
-    switch (block) {
-#define AL_D(BB)                                                                                           \
-    case BB:                                                                                               \
-        hipLaunchKernelGGL((dequantize_kernel<C, BB>), dim3(grid), dim3(256), 0, s, codes, meta, n, out, exp2_coef()); \
-        return hipGetLastError();
-        AL_D(64)
-        AL_D(128)
-        AL_D(256)
-        AL_D(512)
-        AL_D(1024)
-        AL_D(2048)
-#undef AL_D
-    }
-    return hipErrorInvalidValue;
+static hipError_t dequant_b(const void* codes, const float* meta, int64_t n, int block, float* out, hipStream_t s) {
+    AL_BLOCKS(dequant_t, codes, meta, n, out, s)
 }
+#undef AL_BLOCKS
 
 hipError_t launch_quantize(int codec, const float* x, int64_t n, int block, float log_floor, void* codes,
-                           float* meta, int grid_cap, hipStream_t s) {
-    const int64_t T = block > kSub ? block : kSub;
-    const int64_t tiles = (n + T - 1) / T;
-    const int64_t want = (tiles + 3) / 4;
-    const int grid = (int)(want < grid_cap ? want : grid_cap);
-    if (grid <= 0) return hipSuccess;
+                           float* meta, hipStream_t s) {
     switch (codec) {
-        case AL8: return quant_b<AL8>(x, n, block, log_floor, codes, meta, grid, s);
-        case AL16: return quant_b<AL16>(x, n, block, log_floor, codes, meta, grid, s);
-        case UF8: return quant_b<UF8>(x, n, block, log_floor, codes, meta, grid, s);
+        case AL8: return quant_b<AL8>(x, n, block, log_floor, codes, meta, s);
+        case AL16: return quant_b<AL16>(x, n, block, log_floor, codes, meta, s);
+        case UF8: return quant_b<UF8>(x, n, block, log_floor, codes, meta, s);
     }
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_dequantize(int codec, const void* codes, const float* meta, int64_t n, int block, float* out,
-                             int grid_cap, hipStream_t s) {
-    const int64_t want = ((n + 3) / 4 + 255) / 256;
-    const int grid = (int)(want < grid_cap ? want : grid_cap);
-    if (grid <= 0) return hipSuccess;
+                             hipStream_t s) {
     switch (codec) {
-        case AL8: return dequant_b<AL8>(codes, meta, n, block, out, grid, s);
-        case AL16: return dequant_b<AL16>(codes, meta, n, block, out, grid, s);
-        case UF8: return dequant_b<UF8>(codes, meta, n, block, out, grid, s);
+        case AL8: return dequant_b<AL8>(codes, meta, n, block, out, s);
+        case AL16: return dequant_b<AL16>(codes, meta, n, block, out, s);
+        case UF8: return dequant_b<UF8>(codes, meta, n, block, out, s);
     }
     return hipErrorInvalidValue;
 }

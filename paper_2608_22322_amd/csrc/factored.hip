@@ -21,7 +21,6 @@
 // only where that cannot change the fp32 rounding of the state's EMA and
 // otherwise sums the element's row or column again exactly, so the fp32 states
 // (and their codes) are the ones of the exactly rounded means.
-#include "al_codec_dev.hpp"
 #include "al_device.hpp"
 #include "al_internal.hpp"
 
