@@ -7,8 +7,8 @@
 // corrections; codes per section 4 (Eq. al_bounds, al_quant, al_dequant,
 // exact_zero) and the uniform signed momentum code of section 4.3.
 //
-// Work decomposition. A chunk is max(2048, B_V) consecutive elements of one
-// tensor for AL8 blocks of 128+, else max(1024, B_V), owned by one wavefront:
+// Work decomposition. A chunk is max(1024, B_V) consecutive elements of one
+// tensor (512 where a state is fp32, and for short lists), owned by one wavefront:
 // 4 consecutive elements per lane in each of K = chunk/256 sub-tiles, so every
 // load and store is a coalesced 16/8/4-byte access and every block reduction
 // stays inside the wavefront (DPP, swizzle, readlane). The momentum block
@@ -81,18 +81,27 @@ __device__ __forceinline__ double split3_level(const double* t, uint32_t q) {
 constexpr bool kNtLoad = AL_ADAMW_NT_LOAD != 0;
 constexpr bool kNtStore = AL_ADAMW_NT_STORE != 0;
 
-__host__ __device__ constexpr int chunk_elems(int vc, int bv) {
-    return vc == FP32 ? 1024 : (vc == AL8 && bv >= 128) ? (bv > 2048 ? bv : 2048) : (bv > 1024 ? bv : 1024);
+// Elements per chunk (one wavefront). Coded momentum and second moment: 1024, so
+// that the per-chunk work (block fits, tables) is shared by several blocks but the
+// loads of the chunk stay one phase; 2048 held more registers and streamed no
+// better (256M parameters, us per step at 2048 / 1024 / 512: bf16 gradients B_V 256
+// 714 / 713 / 756, fp32 gradients 781 / 756 / 783 and at B_V 1024 778 / 714 / -; 32M
+// bf16 B_V 512 98.6 / 90.3 / 93.6). An fp32 state streams 4 bytes a value and leaves
+// little per-chunk work: 512 (fp32 momentum, bf16, AL8 B_V 256: 944 / 931 / 874; both
+// fp32: - / 1220 / 1194). A block is never cut.
+__host__ __device__ constexpr int chunk_elems(int mc, int vc, int bv) {
+    const int c = mc == FP32 || vc == FP32 ? 512 : 1024;
+    return vc == FP32 || bv < c ? c : bv;
 }
 
-template <int MC, int VC, int BV>
+// Chunks of a short list (kAdamWSmall): a wavefront's chain of sub-tiles is what
+// its step takes, so it is cut into more and shorter ones.
+__host__ __device__ constexpr int small_chunk_elems(int vc, int bv) { return vc == FP32 || bv < 512 ? 512 : bv; }
+
+template <int MC, int VC, int BV, int CE>
 struct Geo {
     static constexpr bool VQ = (VC == AL8 || VC == AL16);
-    // elements per chunk: AL8 blocks of 128+ take 2048 (the per-chunk work amortised over twice
-    // the elements; blocks of 128 then need 138 registers and run 3 waves per SIMD, 1% faster
-    // than 1024-element chunks at 4); blocks of 64 (no gain at 2048), AL16 (wider codes) and an
-    // fp32 second moment take max(1024, B_V)
-    static constexpr int C = chunk_elems(VC, BV);
+    static constexpr int C = CE;
     static constexpr int K = C / kSub;                       // sub-tiles per chunk
     static constexpr int NB = VQ ? C / BV : 1;               // v blocks per chunk
     static constexpr int GL = BV < kSub ? BV / 4 : 64;       // lanes per v block within a sub-tile
@@ -121,9 +130,9 @@ __device__ __forceinline__ float f4_at(const float4& v, int j) {
 
 // Raw inputs of up to 4 sub-tiles as loaded from HBM (packed: a bf16 pair or
 // four 8-bit codes per register).
-template <int G, int MC, int VC, int BV>
+template <int G, int MC, int VC, int BV, int CE>
 struct Raw {
-    using Q = Geo<MC, VC, BV>;
+    using Q = Geo<MC, VC, BV, CE>;
     using GT = typename Pick<G == G_BF16, uint2, float4>::T;
     using MT = typename Pick<MC == UF8, uint32_t, float4>::T;
     using VT = typename Pick<VC == AL16, uint2, typename Pick<VC == AL8, uint32_t, float4>::T>::T;
@@ -170,10 +179,10 @@ __device__ __forceinline__ DescG gview(cp<const AdamWDesc> D, int i) {
 
 typedef float f2v __attribute__((ext_vector_type(2)));
 
-template <int G, int MC, int VC, int BV, bool FULL, bool APO>
-__device__ __forceinline__ void load_raw(Raw<G, MC, VC, BV>& r, const DescG& d, int64_t e0, int64_t valid,
+template <int G, int MC, int VC, int BV, int CE, bool FULL, bool APO>
+__device__ __forceinline__ void load_raw(Raw<G, MC, VC, BV, CE>& r, const DescG& d, int64_t e0, int64_t valid,
                                          int lane, int ph) {
-    using R = Raw<G, MC, VC, BV>;
+    using R = Raw<G, MC, VC, BV, CE>;
 #pragma unroll
     for (int k = 0; k < R::P; ++k) {
         const int rel = (ph * R::P + k) * kSub + 4 * lane;
@@ -223,9 +232,9 @@ __device__ __forceinline__ void load_raw(Raw<G, MC, VC, BV>& r, const DescG& d, 
     }
 }
 
-template <int MC, int VC, int BV, bool FULL>
+template <int MC, int VC, int BV, int CE, bool FULL>
 __device__ __forceinline__ OldMeta load_meta(const DescG& d, int64_t e0, int64_t valid, int lane) {
-    using Q = Geo<MC, VC, BV>;
+    using Q = Geo<MC, VC, BV, CE>;
     OldMeta r;
     r.a = 0.0f;
     r.l = 0.0f;
@@ -295,21 +304,21 @@ __device__ __forceinline__ double row16_sum(double x) {
 // and sum R^2 over its rows of 16 lanes into LDS (csum); after the last
 // sub-tile, lane k adds its channel's four row sums and forms the channel
 // scale.
-template <int G, int MC, int VC, int BV, bool FULL, bool APO>
+template <int G, int MC, int VC, int BV, int CE, bool FULL, bool APO>
 __device__ __forceinline__ void adamw_compute(const AdamWLaunch& a, const DescG& d, int64_t e0, int64_t valid,
                                               int lane, double* lut, double* stab, uint2* skey, uint4* encp,
                                               double2* encd, double2* csum) {
-    using Q = Geo<MC, VC, BV>;
+    using Q = Geo<MC, VC, BV, CE>;
     constexpr int K = Q::K;
     constexpr int NB = Q::NB;
     constexpr bool VQ = Q::VQ;
     constexpr int LEVELS = Q::LEVELS;
 
-    using R = Raw<G, MC, VC, BV>;
+    using R = Raw<G, MC, VC, BV, CE>;
     // first load phase and the old metadata are issued before any arithmetic
     R r;
-    load_raw<G, MC, VC, BV, FULL, APO>(r, d, e0, valid, lane, 0);
-    const OldMeta om = load_meta<MC, VC, BV, FULL>(d, e0, valid, lane);
+    load_raw<G, MC, VC, BV, CE, FULL, APO>(r, d, e0, valid, lane, 0);
+    const OldMeta om = load_meta<MC, VC, BV, CE, FULL>(d, e0, valid, lane);
 
     // ------------------------------------------------ 1. decode steps of the old metadata, one block per lane
     double num = 1.0, den = 1.0;
@@ -389,14 +398,13 @@ __device__ __forceinline__ void adamw_compute(const AdamWLaunch& a, const DescG&
     // binary64 products per element (relative error below (ln 2 (|l_min| + 3 (q - 1)
     // st) + 7) 2^-53, then rounded to fp32).
     if constexpr (Q::SPLIT3) {
-        static_assert(NB * 20 % kWave == 0, "three-factor tables fill whole wavefront passes");
 #pragma unroll
-        for (int i = 0; i < NB * 20 / kWave; ++i) {
+        for (int i = 0; i < (NB * 20 + kWave - 1) / kWave; ++i) {
             const int e = lane + kWave * i;
             const int b = e / 20, j = e - 20 * b;
             const double st = shfl_d(q1, 32 + b);
             const double l32 = (double)__shfl(om.l, 32 + b);
-            stab[e] = split3_entry(l32, st, j);
+            if (NB * 20 % kWave == 0 || e < NB * 20) stab[e] = split3_entry(l32, st, j);
         }
     }
 
@@ -420,7 +428,7 @@ __device__ __forceinline__ void adamw_compute(const AdamWLaunch& a, const DescG&
         const int kk = k % R::P;  // slot of this sub-tile in the current load phase
         if (k > 0 && kk == 0) {
             __builtin_amdgcn_sched_barrier(0);  // keep the next phase's loads after this phase's arithmetic
-            load_raw<G, MC, VC, BV, FULL, APO>(r, d, e0, valid, lane, k / R::P);
+            load_raw<G, MC, VC, BV, CE, FULL, APO>(r, d, e0, valid, lane, k / R::P);
         }
         float mh[4], vh[4], mn[4], vn[4], pn[4];
         double vhd[4];  // the decoded second moment, widened for the EMA
@@ -680,42 +688,38 @@ __device__ __forceinline__ void adamw_compute(const AdamWLaunch& a, const DescG&
     }
 }
 
-// At least 4 waves per SIMD (at most 128 VGPRs) with a UF8 momentum: with one
-// chunk per wave the step needs about 95-127 registers, and the extra resident
-// waves hide HBM latency behind the per-element decode/encode arithmetic. An
-// fp32 momentum carries 12 more registers per sub-tile and gets 3 (168), or 2
-// with 2048-element AL16 chunks; AL8 blocks of 128 in 2048-element chunks get 3.
-template <int MC, int VC, int BV>
-constexpr int adamw_waves_per_eu() {
-    return (MC == UF8 && !(VC == AL8 && BV == 128)) ? 4 : (VC == AL16 && Geo<MC, VC, BV>::C >= 2048 ? 2 : 3);
+// Waves per SIMD. At least 4 (at most 128 VGPRs) with a UF8 momentum: the extra
+// resident waves hide HBM latency behind the per-element decode / encode arithmetic.
+// Where the stream and not the arithmetic is the bound, fewer waves are faster: each
+// has more bytes in flight and fewer streams mix in the memory system. So two fp32
+// states get exactly 2 (8 layers of 2048 / 5632, bf16, us per step with all that the
+// registers allow, 4, 3 and 2: 1652, 1631, 1580, 1540), an fp32 second moment alone 3
+// (1248, 1207, 1218; fp32 gradients 1349, 1314, 1294), fp32 momentum with AL8 4 (1212
+// free, 1164 at 4, 1206 at 3). AL16 with fp32 momentum is best left free (1403; 1414
+// at 4, 1502 at 3).
+template <int MC, int VC, int BV, int CE>
+constexpr int adamw_min_waves() {
+    if (VC == FP32) return MC == FP32 ? 2 : 3;
+    if (MC == UF8 || VC == AL8) return 4;
+    return CE >= 2048 ? 2 : 3;
 }
-
-// largest ti with tb[ti] <= chunk (tb ascending, tb[0] = 0); wave-uniform, so
-// every probe is a scalar load of the packed offsets (a few cache lines)
-__device__ __forceinline__ int locate(cp<const int64_t> tb, int nt, int64_t chunk) {
-    int lo = 0, hi = nt - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tb[mid] <= chunk)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
+template <int MC, int VC, int BV, int CE>
+constexpr int adamw_max_waves() {
+    return VC == FP32 || (MC == FP32 && VC == AL8) ? adamw_min_waves<MC, VC, BV, CE>() : 8;
 }
 
 // One chunk per wave; each wave issues the loads of up to 4 sub-tiles
 // (packed, 8 registers per sub-tile for bf16/UF8/AL8) before it computes on
 // them. A chunk that ends a tensor takes the guarded path.
-template <int G, int MC, int VC, int BV, bool APO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adamw_waves_per_eu<MC, VC, BV>())))
-void adamw_kernel(const AdamWLaunch a) {
-    constexpr int C = Geo<MC, VC, BV>::C;
+template <int G, int MC, int VC, int BV, int CE, bool APO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adamw_min_waves<MC, VC, BV, CE>(), adamw_max_waves<MC, VC, BV, CE>())))
+void adamw_kernel(const AdamWLaunch a, const AdamWInline in) {
+    constexpr int C = Geo<MC, VC, BV, CE>::C;
     const int lane = threadIdx.x & 63;
     const int64_t chunk = a.chunk_base + xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    constexpr int NT = Geo<MC, VC, BV>::LUT ? Geo<MC, VC, BV>::NB * 256 : 1;
-    constexpr int NS = (Geo<MC, VC, BV>::SPLIT || Geo<MC, VC, BV>::LUT) ? Geo<MC, VC, BV>::NB * 32 : Geo<MC, VC, BV>::SPLIT3 ? Geo<MC, VC, BV>::NB * 20 : 1;
-    constexpr int NK = (Geo<MC, VC, BV>::VQ && BV < kSub) ? Geo<MC, VC, BV>::NB : 1;
+    constexpr int NT = Geo<MC, VC, BV, CE>::LUT ? Geo<MC, VC, BV, CE>::NB * 256 : 1;
+    constexpr int NS = (Geo<MC, VC, BV, CE>::SPLIT || Geo<MC, VC, BV, CE>::LUT) ? Geo<MC, VC, BV, CE>::NB * 32 : Geo<MC, VC, BV, CE>::SPLIT3 ? Geo<MC, VC, BV, CE>::NB * 20 : 1;
+    constexpr int NK = (Geo<MC, VC, BV, CE>::VQ && BV < kSub) ? Geo<MC, VC, BV, CE>::NB : 1;
     __shared__ double lut_all[4][NT];
     __shared__ double stab_all[4][NS];
     __shared__ uint2 skey_all[4][NK];
@@ -731,8 +735,15 @@ void adamw_kernel(const AdamWLaunch a) {
     if (chunk >= a.total_tiles) return;
     // the descriptor's pointers come from memory: mark them global so the
     // streams use global (not flat) loads and stores
-    const cp<const AdamWDesc> D = (cp<const AdamWDesc>)a.D;
-    const int ti = locate((cp<const int64_t>)a.tb, a.nt, chunk);
+    // (a list of up to kAdamWInline tensors carries its descriptors in the arguments)
+    cp<const AdamWDesc> D = (cp<const AdamWDesc>)a.D;
+    int ti = 0;
+    if (a.nt <= kAdamWInline) {
+        D = (cp<const AdamWDesc>)in.d;
+        while (ti + 1 < a.nt && D[ti + 1].tile_begin <= chunk) ++ti;
+    } else {
+        ti = locate(a.tb, a.nt, chunk);
+    }
     DescG d = gview(D, ti);
     if constexpr (APO) {
         d.cs = to_g(a.apollo[ti].s);
@@ -742,12 +753,15 @@ void adamw_kernel(const AdamWLaunch a) {
     const int64_t e0 = (chunk - D[ti].tile_begin) * C;
     const int64_t valid = d.n - e0;
     if (valid >= C)
-        adamw_compute<G, MC, VC, BV, true, APO>(a, d, e0, C, lane, lut, stab, skey, encp, encd, csum);
+        adamw_compute<G, MC, VC, BV, CE, true, APO>(a, d, e0, C, lane, lut, stab, skey, encp, encd, csum);
     else
-        adamw_compute<G, MC, VC, BV, false, APO>(a, d, e0, valid, lane, lut, stab, skey, encp, encd, csum);
+        adamw_compute<G, MC, VC, BV, CE, false, APO>(a, d, e0, valid, lane, lut, stab, skey, encp, encd, csum);
 }
 
-int adamw_tile_elems(int v_codec, int v_block) { return chunk_elems(v_codec, v_block); }
+int adamw_tile_elems(int m_codec, int v_codec, int v_block, bool small) {
+    return small ? small_chunk_elems(v_codec, v_block) : chunk_elems(m_codec, v_codec, v_block);
+}
+
 
 // al_diag_levels: every positive AL8 level of each block through the step
 // kernel's split-table functions, as the binary64 product before the fp32
@@ -813,13 +827,15 @@ hipError_t adamw_write_batch(const AdamWDesc* host, int count, int offset, void*
 }
 
 void adamw_bind_table(void* table, int64_t nt, AdamWLaunch& a) {
-    a.D = table_desc(table);
-    a.tb = table_tb(table, nt);
+    a.D = nt > kAdamWInline ? table_desc(table) : nullptr;
+    a.tb = nt > kAdamWInline ? table_tb(table, nt) : nullptr;
     a.nt = (int32_t)nt;
 }
 
-hipError_t adamw_write_table(const AdamWDesc* host, int nt, void* table, AdamWLaunch& a, hipStream_t s) {
-    for (int off = 0; off < nt; off += kAdamWCopyBatch) {
+hipError_t adamw_write_table(const AdamWDesc* host, int nt, void* table, AdamWLaunch& a, AdamWInline& in,
+                             hipStream_t s) {
+    for (int i = 0; nt <= kAdamWInline && i < nt; ++i) in.d[i] = host[i];
+    for (int off = 0; off < nt && nt > kAdamWInline; off += kAdamWCopyBatch) {
         const hipError_t e = adamw_write_batch(host + off, nt - off < kAdamWCopyBatch ? nt - off : kAdamWCopyBatch,
                                                off, table, nt, s);
         if (e != hipSuccess) return e;
@@ -861,66 +877,74 @@ hipError_t adamw_static_table(void** table) {
 // sized by occupancy moves the same byte mix about 6% slower on gfx950, and a
 // chunk loop lets the compiler hoist per-chunk constants into spilled
 // registers.) Lists beyond 2^32 chunks take several launches.
-template <int G, int MC, int VC, int BV, bool APO>
-static hipError_t launch_t(const AdamWLaunch& a, hipStream_t s) {
+template <int G, int MC, int VC, int BV, int CE, bool APO>
+static hipError_t launch_c(const AdamWLaunch& a, const AdamWInline& in, hipStream_t s) {
     constexpr int64_t kMaxGrid = int64_t(1) << 30;  // workgroups (4 waves each) per launch
     AdamWLaunch b = a;
     for (b.chunk_base = 0; b.chunk_base < a.total_tiles; b.chunk_base += 4 * kMaxGrid) {
         const int64_t left = (a.total_tiles - b.chunk_base + 3) / 4;
         const int64_t grid = left < kMaxGrid ? left : kMaxGrid;
-        hipLaunchKernelGGL((adamw_kernel<G, MC, VC, BV, APO>), dim3((unsigned)grid), dim3(256), 0, s, b);
+        hipLaunchKernelGGL((adamw_kernel<G, MC, VC, BV, CE, APO>), dim3((unsigned)grid), dim3(256), 0, s, b, in);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
+template <int G, int MC, int VC, int BV, bool APO>
+static hipError_t launch_t(const AdamWLaunch& a, const AdamWInline& in, hipStream_t s) {
+    constexpr int C = chunk_elems(MC, VC, BV), CS = small_chunk_elems(VC, BV);
+    if constexpr (CS != C && !APO)
+        if (a.tile == CS) return launch_c<G, MC, VC, BV, CS, false>(a, in, s);
+    return a.tile == C ? launch_c<G, MC, VC, BV, C, APO>(a, in, s) : hipErrorInvalidValue;
+}
+
 template <int G, int MC, int VC, bool APO>
-static hipError_t launch_bv(const AdamWLaunch& a, int bv, hipStream_t s) {
+static hipError_t launch_bv(const AdamWLaunch& a, const AdamWInline& in, int bv, hipStream_t s) {
     if constexpr (VC == FP32) {
-        return launch_t<G, MC, VC, 256, APO>(a, s);
+        return launch_t<G, MC, VC, 256, APO>(a, in, s);
     } else {
         switch (bv) {
-            case 64: return launch_t<G, MC, VC, 64, APO>(a, s);
-            case 128: return launch_t<G, MC, VC, 128, APO>(a, s);
-            case 256: return launch_t<G, MC, VC, 256, APO>(a, s);
-            case 512: return launch_t<G, MC, VC, 512, APO>(a, s);
-            case 1024: return launch_t<G, MC, VC, 1024, APO>(a, s);
-            case 2048: return launch_t<G, MC, VC, 2048, APO>(a, s);
+            case 64: return launch_t<G, MC, VC, 64, APO>(a, in, s);
+            case 128: return launch_t<G, MC, VC, 128, APO>(a, in, s);
+            case 256: return launch_t<G, MC, VC, 256, APO>(a, in, s);
+            case 512: return launch_t<G, MC, VC, 512, APO>(a, in, s);
+            case 1024: return launch_t<G, MC, VC, 1024, APO>(a, in, s);
+            case 2048: return launch_t<G, MC, VC, 2048, APO>(a, in, s);
         }
         return hipErrorInvalidValue;
     }
 }
 
 template <int G, int MC, bool APO>
-static hipError_t launch_vc(const AdamWLaunch& a, int vc, int bv, hipStream_t s) {
+static hipError_t launch_vc(const AdamWLaunch& a, const AdamWInline& in, int vc, int bv, hipStream_t s) {
     switch (vc) {
-        case AL8: return launch_bv<G, MC, AL8, APO>(a, bv, s);
-        case AL16: return launch_bv<G, MC, AL16, APO>(a, bv, s);
-        case FP32: return launch_bv<G, MC, FP32, APO>(a, bv, s);
+        case AL8: return launch_bv<G, MC, AL8, APO>(a, in, bv, s);
+        case AL16: return launch_bv<G, MC, AL16, APO>(a, in, bv, s);
+        case FP32: return launch_bv<G, MC, FP32, APO>(a, in, bv, s);
     }
     return hipErrorInvalidValue;
 }
 
 template <int G, bool APO>
-static hipError_t launch_mc(const AdamWLaunch& a, int mc, int vc, int bv, hipStream_t s) {
+static hipError_t launch_mc(const AdamWLaunch& a, const AdamWInline& in, int mc, int vc, int bv, hipStream_t s) {
     switch (mc) {
-        case UF8: return launch_vc<G, UF8, APO>(a, vc, bv, s);
-        case FP32: return launch_vc<G, FP32, APO>(a, vc, bv, s);
+        case UF8: return launch_vc<G, UF8, APO>(a, in, vc, bv, s);
+        case FP32: return launch_vc<G, FP32, APO>(a, in, vc, bv, s);
     }
     return hipErrorInvalidValue;
 }
 
 // apollo: APOLLO's projected moments at rank 256 (fp32 gradient R, no parameter
 // stream, channel scales out; see AdamWLaunch::apollo).
-hipError_t launch_adamw(const AdamWLaunch& a, int grad_dtype, int m_codec, int v_codec, int v_block, hipStream_t s,
+hipError_t launch_adamw(const AdamWLaunch& a, const AdamWInline& in, int grad_dtype, int m_codec, int v_codec, int v_block, hipStream_t s,
                         bool apollo) {
     if (apollo) {
         if (grad_dtype != G_F32 || !a.apollo) return hipErrorInvalidValue;
-        return launch_mc<G_F32, true>(a, m_codec, v_codec, v_block, s);
+        return launch_mc<G_F32, true>(a, in, m_codec, v_codec, v_block, s);
     }
-    if (grad_dtype == G_BF16) return launch_mc<G_BF16, false>(a, m_codec, v_codec, v_block, s);
-    return launch_mc<G_F32, false>(a, m_codec, v_codec, v_block, s);
+    if (grad_dtype == G_BF16) return launch_mc<G_BF16, false>(a, in, m_codec, v_codec, v_block, s);
+    return launch_mc<G_F32, false>(a, in, m_codec, v_codec, v_block, s);
 }
 
 }  // namespace al

@@ -520,7 +520,7 @@ al_status adamw_check(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* 
 
     std::memset(&a, 0, sizeof(a));
     *ndesc = 0;
-    const int T = al::adamw_tile_elems(cfg->v.codec, cfg->v.block);
+    int64_t total = 0;
     for (int i = 0; i < nt; ++i) {
         const al_tensor& t = tensors[i];
         int64_t n = 0;
@@ -533,8 +533,10 @@ al_status adamw_check(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* 
         if ((st = check_unused(t.cc, t.cc_meta, "cc", i)) != AL_OK) return st;
         if (n == 0) continue;
         ++*ndesc;
-        a.total_tiles += (n + T - 1) / T;
+        if (total < al::kAdamWSmall) total += n;
     }
+    a.tile = al::adamw_tile_elems(cfg->m.codec, cfg->v.codec, cfg->v.block, total < al::kAdamWSmall);
+    for (int i = 0; i < nt; ++i) a.total_tiles += (tensors[i].rows * tensors[i].cols + a.tile - 1) / a.tile;
     const double bc1 = 1.0 - std::pow(cfg->beta1, (double)step);
     const double bc2 = 1.0 - std::pow(cfg->beta2, (double)step);
     a.beta1 = cfg->beta1;
@@ -554,7 +556,10 @@ al_status adamw_check(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* 
 // the table and launch the step.
 al_status adamw_run(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* cfg, int64_t ndesc, void* table,
                     al::AdamWLaunch& a, hipStream_t s, const char* who) {
-    const int T = al::adamw_tile_elems(cfg->v.codec, cfg->v.block);
+    const int T = a.tile;
+    const bool inl = ndesc <= al::kAdamWInline;
+    al::AdamWInline in;
+    std::memset(&in, 0, sizeof(in));
     al::AdamWDesc batch[al::kAdamWCopyBatch];
     int nb = 0, off = 0;
     int64_t tile = 0;
@@ -563,7 +568,7 @@ al_status adamw_run(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* cf
         const al_tensor& t = tensors[i];
         const int64_t n = t.rows * t.cols;
         if (n == 0) continue;
-        al::AdamWDesc& d = batch[nb++];
+        al::AdamWDesc& d = inl ? in.d[nb++] : batch[nb++];
         d.p = t.param;
         d.g = t.grad;
         d.m = t.m;
@@ -573,15 +578,15 @@ al_status adamw_run(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* cf
         d.n = n;
         d.tile_begin = tile;
         tile += (n + T - 1) / T;
-        if (nb == al::kAdamWCopyBatch) {
+        if (!inl && nb == al::kAdamWCopyBatch) {
             if ((e = al::adamw_write_batch(batch, nb, off, table, ndesc, s)) != hipSuccess) return hip_fail(e, who);
             off += nb;
             nb = 0;
         }
     }
-    if (nb > 0 && (e = al::adamw_write_batch(batch, nb, off, table, ndesc, s)) != hipSuccess) return hip_fail(e, who);
+    if (!inl && nb > 0 && (e = al::adamw_write_batch(batch, nb, off, table, ndesc, s)) != hipSuccess) return hip_fail(e, who);
     al::adamw_bind_table(table, ndesc, a);
-    if ((e = al::launch_adamw(a, cfg->grad_dtype, cfg->m.codec, cfg->v.codec, cfg->v.block, s)) != hipSuccess)
+    if ((e = al::launch_adamw(a, in, cfg->grad_dtype, cfg->m.codec, cfg->v.codec, cfg->v.block, s)) != hipSuccess)
         return hip_fail(e, who);
     return AL_OK;
 }
@@ -690,7 +695,10 @@ al_status al_apollo_step(const al_apollo_tensor* tensors, int32_t nt, const al_a
     w.decay = 1.0f;
     w.v_floor = cfg->v.log_floor;
     w.apollo = fused ? a.D : nullptr;  // descriptor i of the AdamW table is projected tensor i
-    const int T = al::adamw_tile_elems(cfg->v.codec, cfg->v.block);
+    w.tile = al::adamw_tile_elems(cfg->m.codec, cfg->v.codec, cfg->v.block, !fused && P.total_chans * cfg->rank < al::kAdamWSmall);
+    const int T = w.tile;
+    al::AdamWInline win;
+    std::memset(&win, 0, sizeof(win));
     std::vector<al::AdamWDesc> wd(P.desc.size());
     for (size_t k = 0; k < P.desc.size(); ++k) {
         const al::ApolloDesc& d = P.desc[k];
@@ -711,9 +719,9 @@ al_status al_apollo_step(const al_apollo_tensor* tensors, int32_t nt, const al_a
     hipError_t e;
     if ((e = al::apollo_copy_desc(P.desc.data(), a.nt, const_cast<al::ApolloDesc*>(a.D), s)) != hipSuccess ||
         (e = al::launch_apollo_proj(a, cfg->grad_dtype, s)) != hipSuccess ||
-        (e = al::adamw_write_table(wd.data(), (int)wd.size(), static_cast<char*>(ws) + P.adamw_off, w, s)) !=
+        (e = al::adamw_write_table(wd.data(), (int)wd.size(), static_cast<char*>(ws) + P.adamw_off, w, win, s)) !=
             hipSuccess ||
-        (e = al::launch_adamw(w, AL_DTYPE_F32, cfg->m.codec, cfg->v.codec, cfg->v.block, s, fused)) != hipSuccess)
+        (e = al::launch_adamw(w, win, AL_DTYPE_F32, cfg->m.codec, cfg->v.codec, cfg->v.block, s, fused)) != hipSuccess)
         return hip_fail(e, "al_apollo_step launch");
     if ((!fused && (e = al::launch_apollo_scale(a, s)) != hipSuccess) ||
         (e = al::launch_apollo_norm(a, s)) != hipSuccess || (e = al::launch_apollo_update(a, cfg->grad_dtype, s)) != hipSuccess)

@@ -634,6 +634,21 @@ __device__ __forceinline__ gp<U> g_as(gp<T> p) {
     return (gp<U>)p;
 }
 
+// Largest i of [0, n) with b[i] <= x (b ascending, b[0] <= x), x wave-uniform: a
+// binary search by scalar loads of the packed offsets.
+__device__ __forceinline__ int locate(const int64_t* b, int n, int64_t x) {
+    const __attribute__((address_space(4))) int64_t* const c = (const __attribute__((address_space(4))) int64_t*)b;
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (c[mid] <= x)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
 template <bool NT>
 __device__ __forceinline__ float4 ld_f4(gp<const float> p) {
     if constexpr (NT) {

@@ -36,6 +36,7 @@ struct AdamWLaunch {
     const AdamWDesc* D;               // nt descriptors, ascending tile_begin (device memory)
     const int64_t* tb;                // D[i].tile_begin again, packed (the chunk -> tensor search)
     int32_t nt;
+    int32_t tile;         // elements per chunk (adamw_tile_elems)
     int64_t total_tiles;
     int64_t chunk_base;  // first chunk of this launch (one wave per chunk)
     // APOLLO's moments on the projected gradient at rank 256 (launch_adamw with
@@ -45,6 +46,14 @@ struct AdamWLaunch {
     // s_c^2 gn2_c into apollo[i].sg, Rt being the step's direction (the
     // parameter output from zero with lr 1)
     const ApolloDesc* apollo;
+};
+
+// The descriptors of a list of up to kAdamWInline tensors travel in the step
+// kernel's own arguments: no table, no copy launch. (Every CU fetches them from the
+// argument segment, so only short lists do.)
+constexpr int kAdamWInline = 8;
+struct AdamWInline {
+    AdamWDesc d[kAdamWInline];
 };
 
 // Descriptors per copy launch: 60 x 64 bytes keep the argument segment under
@@ -61,7 +70,8 @@ hipError_t adamw_write_batch(const AdamWDesc* host, int count, int offset, void*
 void adamw_bind_table(void* table, int64_t nt, AdamWLaunch& a);
 // Write nt descriptors (host array) into a table at `table` on the stream and
 // bind it.
-hipError_t adamw_write_table(const AdamWDesc* host, int nt, void* table, AdamWLaunch& a, hipStream_t s);
+hipError_t adamw_write_table(const AdamWDesc* host, int nt, void* table, AdamWLaunch& a, AdamWInline& in,
+                             hipStream_t s);
 
 // The allocation-free AdamW entry point keeps its table in a fixed device
 // array of kAdamWScratchBytes (room for kAdamWStaticTensors descriptors) per
@@ -72,9 +82,10 @@ constexpr size_t kAdamWScratchBytes = 4096 * 64 + 4096 * 8;  // 288 KiB
 constexpr int kMaxDevices = 64;
 hipError_t adamw_static_table(void** table);
 
-// Elements per tile: max(block of v, 256).
-int adamw_tile_elems(int v_codec, int v_block);
-hipError_t launch_adamw(const AdamWLaunch& a, int grad_dtype, int m_codec, int v_codec, int v_block,
+// Elements per chunk; small: of a list shorter than kAdamWSmall elements.
+constexpr int64_t kAdamWSmall = 3 << 20;
+int adamw_tile_elems(int m_codec, int v_codec, int v_block, bool small);
+hipError_t launch_adamw(const AdamWLaunch& a, const AdamWInline& in, int grad_dtype, int m_codec, int v_codec, int v_block,
                         hipStream_t s, bool apollo = false);
 
 // ------------------------------------------------------------------ codec

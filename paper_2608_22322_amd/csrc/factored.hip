@@ -27,27 +27,6 @@
 namespace al {
 
 // ------------------------------------------------------------------ helpers
-// Largest i of [0, n) with b[i] <= x (b ascending, b[0] <= x), x wave-uniform:
-// scalar halvings down to 64 entries, then one load of those by the wavefront
-// (a list of up to 64 tensors takes one dependent load; the offsets are packed,
-// so it is a few cache lines).
-__device__ __forceinline__ int locate(const int64_t* b, int n, int64_t x) {
-    const __attribute__((address_space(4))) int64_t* const c = (const __attribute__((address_space(4))) int64_t*)b;
-    int lo = 0, len = n;
-    while (len > 64) {
-        const int half = len >> 1;
-        if (c[lo + half] <= x) {
-            lo += half;
-            len -= half;
-        } else {
-            len = half;
-        }
-    }
-    const int lane = threadIdx.x & 63;
-    const uint64_t le = __ballot(lane < len && to_g(b)[lo + (lane < len ? lane : 0)] <= x);
-    return lo + __builtin_popcountll(le) - 1;
-}
-
 // Global-address-space view of the data pointers of a descriptor (the
 // descriptors are read from the workspace, so their pointers are generic to
 // the compiler; see gp in al_device.hpp).
