@@ -127,7 +127,7 @@ al_status check_ws(void* ws, size_t ws_bytes, size_t need, const char* who) {
 }
 
 struct FacPlan {
-    std::vector<al::FacDesc> desc;  // 2-D tensors first, then 1-D
+    std::vector<al::FacRec> rec;  // 2-D tensors first, then 1-D
     int n2 = 0, n1 = 0;
     int64_t total_units = 0, total_ach = 0, total_mt = 0, rows_ach = 0;
     int32_t ur = 256, any_whole = 0, any_edge = 0;
@@ -148,9 +148,9 @@ int32_t fac_block(const al_state_spec& s) { return s.codec == AL_CODEC_FP32 ? 25
 
 
 // Validate the tensor list and lay out the workspace: descriptor table, RMS
-// partials, then per-tensor regions. With ws == NULL only sizes are computed.
+// partials, then per-tensor regions (offsets from its start).
 al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& ms, const al_state_spec& vs,
-                   const al_state_spec& cs, char* ws, FacPlan& P) {
+                   const al_state_spec& cs, FacPlan& P) {
     const char* who = came ? "al_came_step" : "al_adafactor_step";
     if (nt < 0) return fail(AL_EINVAL, "%s: nt < 0", who);
     if (nt > 0 && !ts) return fail(AL_EINVAL, "%s: tensors is NULL", who);
@@ -195,7 +195,7 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
     P.n2 = (int)twod.size();
     P.n1 = (int)oned.size();
     const int ntot = P.n2 + P.n1;
-    P.desc.resize(ntot);
+    P.rec.resize(ntot);
     // Unit rows: 256, halved down to 32 while the list has fewer than kFacMinUnits units (one wavefront
     // each): a short list's passes are bound by the longest wavefront, not by memory. More, shorter units
     // cost column partials (8 bytes per column and unit row), which a short list hardly notices.
@@ -204,77 +204,56 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
         for (int i : twod) units += ((ts[i].rows + P.ur - 1) / P.ur) * ((ts[i].cols + 255) / 256);
         if (units >= kFacMinUnits || P.ur == 32) break;
     }
-    for (int k = 0; k < P.n2; ++k) {
-        const al_tensor& t = ts[twod[k]];
-        al::FacDesc& d = P.desc[k];
-        d.nru = (int32_t)((t.rows + P.ur - 1) / P.ur);
-        d.ncu = (int32_t)((t.cols + 255) / 256);
-        d.unit_begin = P.total_units;
-        P.total_units += (int64_t)d.nru * d.ncu;
-        d.ach_begin = P.total_ach;
-        const bool by_rows = t.cols % 256 == 0;
-        P.total_ach += by_rows ? ((t.rows + 255) / 256) * d.ncu * 32 : (t.rows * t.cols + al::kFacFlatChunk - 1) / al::kFacFlatChunk;
-        if (by_rows) P.rows_ach = P.total_ach;
-        if (by_rows && P.ur == 256 && t.rows >= 256) P.any_whole = 1;
-        if (!by_rows || P.ur != 256 || t.rows % 256 != 0) P.any_edge = 1;
-        d.mt_begin = P.total_mt;
-        P.total_mt += (t.rows + 63) / 64 + (t.cols + 63) / 64;
-        const int64_t bv = fac_block(vs), bc = came ? fac_block(cs) : bv;
-        d.blk_begin[0] = P.total_blk[0];
-        P.total_blk[0] += (t.rows + bv - 1) / bv + (t.cols + bv - 1) / bv;
-        d.blk_begin[1] = P.total_blk[1];
-        P.total_blk[1] += (t.rows + bc - 1) / bc + (t.cols + bc - 1) / bc;
-    }
     size_t off = align256((size_t)ntot * sizeof(al::FacDesc));
     P.index_off = off;
     off += align256((size_t)ntot * al::kFacIndex * sizeof(int64_t));
+    for (int k = 0; k < P.n2; ++k) {
+        const al_tensor& t = ts[twod[k]];
+        uint64_t* const r = P.rec[k].w;
+        const int64_t nru = (t.rows + P.ur - 1) / P.ur, ncu = (t.cols + 255) / 256;
+        r[al::kRecUnit] = (uint64_t)P.total_units;
+        P.total_units += nru * ncu;
+        r[al::kRecAch] = (uint64_t)P.total_ach;
+        const bool by_rows = t.cols % 256 == 0;
+        P.total_ach += by_rows ? ((t.rows + 255) / 256) * ncu * 32 : (t.rows * t.cols + al::kFacFlatChunk - 1) / al::kFacFlatChunk;
+        if (by_rows) P.rows_ach = P.total_ach;
+        if (by_rows && P.ur == 256 && t.rows >= 256) P.any_whole = 1;
+        if (!by_rows || P.ur != 256 || t.rows % 256 != 0) P.any_edge = 1;
+        r[al::kRecMt] = (uint64_t)P.total_mt;
+        P.total_mt += (t.rows + 63) / 64 + (t.cols + 63) / 64;
+        const int64_t bv = fac_block(vs), bc = came ? fac_block(cs) : bv;
+        r[al::kRecBlk0] = (uint64_t)P.total_blk[0];
+        P.total_blk[0] += (t.rows + bv - 1) / bv + (t.cols + bv - 1) / bv;
+        r[al::kRecBlk1] = (uint64_t)P.total_blk[1];
+        P.total_blk[1] += (t.rows + bc - 1) / bc + (t.cols + bc - 1) / bc;
+    }
     P.rms_off = off;
     off += align256((size_t)P.total_units * 16);
-    auto take = [&](size_t nbytes) -> char* {
-        char* ptr = ws ? ws + off : nullptr;
-        off += align256(nbytes);
-        return ptr;
-    };
+    const auto word = [](const void* p) { return (uint64_t)reinterpret_cast<uintptr_t>(p); };
     for (int k = 0; k < ntot; ++k) {
         const bool fac = k < P.n2;
         const al_tensor& t = ts[fac ? twod[k] : oned[k - P.n2]];
-        al::FacDesc& d = P.desc[k];
-        d.p = t.param;
-        d.g = t.grad;
+        uint64_t* const r = P.rec[k].w;
+        if (!fac) r[al::kRecUnit] = r[al::kRecAch] = r[al::kRecMt] = r[al::kRecBlk0] = r[al::kRecBlk1] = 0;
+        r[al::kRecP] = word(t.param);
+        r[al::kRecG] = word(t.grad);
+        r[al::kRecRows] = (uint64_t)t.rows;
+        r[al::kRecCols] = (uint64_t)t.cols;
+        r[al::kRecS0] = word(fac ? t.vr : t.v);
+        r[al::kRecS1] = word(fac ? t.vr_meta : t.v_meta);
+        r[al::kRecS2] = word(fac ? t.vc : nullptr);
+        r[al::kRecS3] = word(fac ? t.vc_meta : nullptr);
+        r[al::kRecM] = word(t.m);
+        r[al::kRecMm] = word(t.m_meta);
+        r[al::kRecCr] = word(t.cr);
+        r[al::kRecCrm] = word(t.cr_meta);
+        r[al::kRecCc] = word(t.cc);
+        r[al::kRecCcm] = word(t.cc_meta);
+        r[al::kRecOff] = (uint64_t)off;
+        al::FacDesc d;
         d.rows = t.rows;
         d.cols = t.cols;
-        d.v = t.v;
-        d.vm = t.v_meta;
-        d.vr = t.vr;
-        d.vrm = t.vr_meta;
-        d.vc = t.vc;
-        d.vcm = t.vc_meta;
-        d.m = t.m;
-        d.mm = t.m_meta;
-        d.cr = t.cr;
-        d.crm = t.cr_meta;
-        d.cc = t.cc;
-        d.ccm = t.cc_meta;
-        if (fac) {
-            // 16 bytes per partial as callers have sized it; the passes use one binary64 of them, packed
-            d.colpart = reinterpret_cast<double*>(take((size_t)d.nru * t.cols * 16));
-            d.rowpart = reinterpret_cast<double*>(take((size_t)d.ncu * t.rows * 16));
-            d.rfac = reinterpret_cast<double*>(take((size_t)t.rows * 8));
-            d.cfac = reinterpret_cast<double*>(take((size_t)t.cols * 8));
-            if (came) {
-                d.sr = reinterpret_cast<double*>(take((size_t)t.rows * 8));
-                d.sc = reinterpret_cast<double*>(take((size_t)t.cols * 8));
-            }
-            d.rtmp = reinterpret_cast<float*>(take((size_t)t.rows * 4));
-            d.ctmp = reinterpret_cast<float*>(take((size_t)t.cols * 4));
-            d.rsum = reinterpret_cast<double*>(take((size_t)((t.rows + 63) / 64) * 16));
-        } else {
-            d.nru = d.ncu = 0;
-            const size_t n = (size_t)(t.rows * t.cols);
-            d.rtmp = reinterpret_cast<float*>(take(n * 4));
-            if (came) d.ctmp = reinterpret_cast<float*>(take(n * 4));
-        }
-        d.scal = reinterpret_cast<double*>(take(16));
+        off = al::fac_regions(d, nullptr, off, came, P.ur);
     }
     P.bytes = off;
     return AL_OK;
@@ -285,7 +264,7 @@ al::FacArgs fac_args(const FacPlan& P, char* ws) {
     std::memset(&a, 0, sizeof(a));
     a.D = reinterpret_cast<const al::FacDesc*>(ws);
     const int64_t* const x = reinterpret_cast<const int64_t*>(ws + P.index_off);
-    const size_t nt = P.desc.size();
+    const size_t nt = P.rec.size();
     a.unit_begins = x;
     a.ach_begins = x + nt;
     a.mt_begins = x + 2 * nt;
@@ -799,7 +778,7 @@ al_status al_adafactor_workspace_bytes(const al_tensor* tensors, int32_t nt, con
     al_status st = check_adafactor_cfg(cfg);
     if (st != AL_OK) return st;
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, false, kNoSpec, cfg->v, kNoSpec, nullptr, P)) != AL_OK) return st;
+    if ((st = fac_plan(tensors, nt, false, kNoSpec, cfg->v, kNoSpec, P)) != AL_OK) return st;
     *bytes = P.bytes;
     return AL_OK;
 }
@@ -811,7 +790,7 @@ al_status al_came_workspace_bytes(const al_tensor* tensors, int32_t nt, const al
     al_status st = check_came_cfg(cfg);
     if (st != AL_OK) return st;
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, true, cfg->m, cfg->v, cfg->conf, nullptr, P)) != AL_OK) return st;
+    if ((st = fac_plan(tensors, nt, true, cfg->m, cfg->v, cfg->conf, P)) != AL_OK) return st;
     *bytes = P.bytes;
     return AL_OK;
 }
@@ -823,10 +802,9 @@ al_status al_adafactor_step(const al_tensor* tensors, int32_t nt, const al_adafa
     if (st != AL_OK) return st;
     if (step < 1) return fail(AL_EINVAL, "al_adafactor_step: step must be >= 1");
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, false, kNoSpec, cfg->v, kNoSpec, nullptr, P)) != AL_OK) return st;
-    if (P.desc.empty()) return AL_OK;
+    if ((st = fac_plan(tensors, nt, false, kNoSpec, cfg->v, kNoSpec, P)) != AL_OK) return st;
+    if (P.rec.empty()) return AL_OK;
     if ((st = check_ws(ws, ws_bytes, P.bytes, "al_adafactor_step")) != AL_OK) return st;
-    if ((st = fac_plan(tensors, nt, false, kNoSpec, cfg->v, kNoSpec, static_cast<char*>(ws), P)) != AL_OK) return st;
 
     al::FacArgs a = fac_args(P, static_cast<char*>(ws));
     a.beta = 1.0 - std::pow((double)step, cfg->decay_rate);
@@ -842,10 +820,10 @@ al_status al_adafactor_step(const al_tensor* tensors, int32_t nt, const al_adafa
     hipStream_t s = as_stream(stream);
     const int G = cfg->grad_dtype;
     hipError_t e;
-    if ((e = al::fac_copy_desc(P.desc.data(), (int)P.desc.size(), const_cast<al::FacDesc*>(a.D), const_cast<int64_t*>(a.unit_begins), s)) != hipSuccess ||
-        (e = al::launch_fac_marg(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
+    if ((e = al::fac_copy_desc(P.rec.data(), (int)P.rec.size(), static_cast<char*>(ws), P.index_off, false, P.ur, s)) != hipSuccess ||
+        (e = al::launch_fac_marg(a, G, false, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
         (e = al::launch_fac_rms(a, G, s)) != hipSuccess || (e = al::launch_fac_clip(a, s)) != hipSuccess ||
-        (e = al::launch_ada_apply(a, G, s)) != hipSuccess || (e = al::launch_ada_vec1d(a, G, s)) != hipSuccess)
+        (e = al::launch_ada_apply(a, G, s)) != hipSuccess)
         return hip_fail(e, "al_adafactor_step launch");
     return AL_OK;
 }
@@ -857,10 +835,9 @@ al_status al_came_step(const al_tensor* tensors, int32_t nt, const al_came_cfg* 
     if (st != AL_OK) return st;
     if (step < 1) return fail(AL_EINVAL, "al_came_step: step must be >= 1");
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, true, cfg->m, cfg->v, cfg->conf, nullptr, P)) != AL_OK) return st;
-    if (P.desc.empty()) return AL_OK;
+    if ((st = fac_plan(tensors, nt, true, cfg->m, cfg->v, cfg->conf, P)) != AL_OK) return st;
+    if (P.rec.empty()) return AL_OK;
     if ((st = check_ws(ws, ws_bytes, P.bytes, "al_came_step")) != AL_OK) return st;
-    if ((st = fac_plan(tensors, nt, true, cfg->m, cfg->v, cfg->conf, static_cast<char*>(ws), P)) != AL_OK) return st;
 
     al::FacArgs a = fac_args(P, static_cast<char*>(ws));
     a.beta = cfg->beta2;
@@ -886,11 +863,11 @@ al_status al_came_step(const al_tensor* tensors, int32_t nt, const al_came_cfg* 
     hipStream_t s = as_stream(stream);
     const int G = cfg->grad_dtype;
     hipError_t e;
-    if ((e = al::fac_copy_desc(P.desc.data(), (int)P.desc.size(), const_cast<al::FacDesc*>(a.D), const_cast<int64_t*>(a.unit_begins), s)) != hipSuccess ||
-        (e = al::launch_fac_marg(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
+    if ((e = al::fac_copy_desc(P.rec.data(), (int)P.rec.size(), static_cast<char*>(ws), P.index_off, true, P.ur, s)) != hipSuccess ||
+        (e = al::launch_fac_marg(a, G, true, s)) != hipSuccess || (e = al::launch_fac_fin(a, 0, G, s)) != hipSuccess ||
         (e = al::launch_fac_rms(a, G, s)) != hipSuccess || (e = al::launch_fac_clip(a, s)) != hipSuccess ||
         (e = al::launch_came_res(a, G, s)) != hipSuccess || (e = al::launch_fac_fin(a, 1, G, s)) != hipSuccess ||
-        (e = al::launch_came_apply(a, G, s)) != hipSuccess || (e = al::launch_came_vec1d(a, G, s)) != hipSuccess)
+        (e = al::launch_came_apply(a, G, s)) != hipSuccess)
         return hip_fail(e, "al_came_step launch");
     return AL_OK;
 }

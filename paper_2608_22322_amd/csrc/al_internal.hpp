@@ -146,11 +146,63 @@ struct FacDesc {
 };
 
 constexpr int kFacFlatChunk = 1024;  // elements per apply chunk of matrices whose width is not a multiple of 256
-constexpr int kFacCopyBatch = 15;  // 15 x 256 bytes keep the argument segment under 4 KB
-struct FacDescBatch {
-    int32_t count, offset;
-    FacDesc d[kFacCopyBatch];
+// What the host sends of a tensor: kFacRecWords words, the first kFacRecAda of them
+// for Adafactor. The device expands it into its FacDesc (fac_regions gives the
+// workspace regions from the record's offset), so a copy launch carries 35 (25)
+// tensors in its arguments in place of 15.
+enum FacRecWord : int {
+    kRecP, kRecG, kRecRows, kRecCols,
+    kRecS0, kRecS1, kRecS2, kRecS3,  // vr, vr_meta, vc, vc_meta (2-D) or v, v_meta (1-D)
+    kRecOff,                         // workspace offset of the tensor's regions
+    kRecUnit, kRecAch, kRecMt, kRecBlk0, kRecBlk1,
+    kFacRecAda,
+    kRecM = kFacRecAda, kRecMm, kRecCr, kRecCrm, kRecCc, kRecCcm,  // CAME
+    kFacRecWords
 };
+struct FacRec {
+    uint64_t w[kFacRecWords];
+};
+constexpr int kFacBatchWords = 500;  // 4000 bytes: the argument segment stays under 4 KB
+struct FacRecBatch {
+    uint64_t w[kFacBatchWords];
+};
+
+__host__ __device__ inline size_t fac_align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// The workspace regions of a tensor (d.rows, d.cols set) from byte `off` of the
+// workspace at ws; returns the offset behind them. ur: unit rows.
+__host__ __device__ inline size_t fac_regions(FacDesc& d, char* ws, size_t off, bool came, int ur) {
+    const auto take = [&](size_t nbytes) {
+        char* const ptr = ws + off;
+        off += fac_align256(nbytes);
+        return ptr;
+    };
+    d.colpart = d.rowpart = d.rfac = d.cfac = d.sr = d.sc = d.rsum = nullptr;
+    d.ctmp = nullptr;
+    if (d.rows > 1) {
+        d.nru = (int32_t)((d.rows + ur - 1) / ur);
+        d.ncu = (int32_t)((d.cols + 255) / 256);
+        // 16 bytes per partial as callers have sized it; the passes use one binary64 of them, packed
+        d.colpart = reinterpret_cast<double*>(take((size_t)d.nru * d.cols * 16));
+        d.rowpart = reinterpret_cast<double*>(take((size_t)d.ncu * d.rows * 16));
+        d.rfac = reinterpret_cast<double*>(take((size_t)d.rows * 8));
+        d.cfac = reinterpret_cast<double*>(take((size_t)d.cols * 8));
+        if (came) {
+            d.sr = reinterpret_cast<double*>(take((size_t)d.rows * 8));
+            d.sc = reinterpret_cast<double*>(take((size_t)d.cols * 8));
+        }
+        d.rtmp = reinterpret_cast<float*>(take((size_t)d.rows * 4));
+        d.ctmp = reinterpret_cast<float*>(take((size_t)d.cols * 4));
+        d.rsum = reinterpret_cast<double*>(take((size_t)((d.rows + 63) / 64) * 16));
+    } else {
+        d.nru = d.ncu = 0;
+        const size_t n = (size_t)(d.rows * d.cols);
+        d.rtmp = reinterpret_cast<float*>(take(n * 4));
+        if (came) d.ctmp = reinterpret_cast<float*>(take(n * 4));
+    }
+    d.scal = reinterpret_cast<double*>(take(16));
+    return off;
+}
 
 constexpr int kFacIndex = 5;  // packed search arrays behind the descriptor table
 
@@ -177,16 +229,16 @@ struct FacArgs {
 
 hipError_t launch_diag_levels(int kind, const float* meta, int64_t nblocks, double* out, int grid_cap, hipStream_t s);
 
-hipError_t fac_copy_desc(const FacDesc* host, int count, FacDesc* dev, int64_t* index, hipStream_t s);
-hipError_t launch_fac_marg(const FacArgs& a, int grad_dtype, hipStream_t s);
+// Expand count records into the descriptor table (and its packed index) of the workspace at ws, on the stream.
+hipError_t fac_copy_desc(const FacRec* host, int count, char* ws, size_t index_off, bool came, int ur, hipStream_t s);
+// The 1-D tensors' whole step runs beside the marginal sums (came: CAME's).
+hipError_t launch_fac_marg(const FacArgs& a, int grad_dtype, bool came, hipStream_t s);
 hipError_t launch_fac_fin(const FacArgs& a, int role, int grad_dtype, hipStream_t s);
 hipError_t launch_fac_rms(const FacArgs& a, int grad_dtype, hipStream_t s);
 hipError_t launch_fac_clip(const FacArgs& a, hipStream_t s);
 hipError_t launch_ada_apply(const FacArgs& a, int grad_dtype, hipStream_t s);
-hipError_t launch_ada_vec1d(const FacArgs& a, int grad_dtype, hipStream_t s);
 hipError_t launch_came_res(const FacArgs& a, int grad_dtype, hipStream_t s);
 hipError_t launch_came_apply(const FacArgs& a, int grad_dtype, hipStream_t s);
-hipError_t launch_came_vec1d(const FacArgs& a, int grad_dtype, hipStream_t s);
 
 // ------------------------------------------------------------------ APOLLO
 // One descriptor per projected tensor, held in the caller's workspace. A

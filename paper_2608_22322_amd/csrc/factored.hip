@@ -182,31 +182,58 @@ __device__ DD block_dd_sum(DD v, DD* sh) {
 // --------------------------------------------------------------- descriptors
 // The packed first units / chunks / tiles / blocks (kFacIndex arrays of nt) go
 // behind the table, for the searches.
-__global__ void fac_desc_copy_kernel(const FacDescBatch b, FacDesc* dst, int64_t* index, int nt) {
-    constexpr int W = sizeof(FacDesc) / 8;
-    const int total = b.count * W;
-    const uint64_t* src = reinterpret_cast<const uint64_t*>(b.d);
-    uint64_t* out = reinterpret_cast<uint64_t*>(dst + b.offset);
-    for (int i = threadIdx.x; i < total; i += blockDim.x) out[i] = src[i];
-    if (threadIdx.x < b.count) {
-        const FacDesc& d = b.d[threadIdx.x];
-        int64_t* const x = index + b.offset + threadIdx.x;
-        x[0] = d.unit_begin;
-        x[nt] = d.ach_begin;
-        x[2 * nt] = d.mt_begin;
-        x[3 * nt] = d.blk_begin[0];
-        x[4 * nt] = d.blk_begin[1];
-    }
+__global__ __launch_bounds__(64) void fac_desc_copy_kernel(const FacRecBatch b, int count, int first, int words, char* ws,
+                                                           size_t index_off, int nt, int ur) {
+    const int k = threadIdx.x;
+    if (k >= count) return;
+    const uint64_t* const r = b.w + k * words;
+    const bool came = words > kFacRecAda;
+    FacDesc d;
+    d.p = reinterpret_cast<float*>(r[kRecP]);
+    d.g = reinterpret_cast<const void*>(r[kRecG]);
+    d.rows = (int64_t)r[kRecRows];
+    d.cols = (int64_t)r[kRecCols];
+    const bool fac = d.rows > 1;
+    void* const s0 = reinterpret_cast<void*>(r[kRecS0]);
+    float* const s1 = reinterpret_cast<float*>(r[kRecS1]);
+    d.v = fac ? nullptr : s0;
+    d.vm = fac ? nullptr : s1;
+    d.vr = fac ? s0 : nullptr;
+    d.vrm = fac ? s1 : nullptr;
+    d.vc = reinterpret_cast<void*>(r[kRecS2]);
+    d.vcm = reinterpret_cast<float*>(r[kRecS3]);
+    d.m = came ? reinterpret_cast<void*>(r[kRecM]) : nullptr;
+    d.mm = came ? reinterpret_cast<float*>(r[kRecMm]) : nullptr;
+    d.cr = came ? reinterpret_cast<void*>(r[kRecCr]) : nullptr;
+    d.crm = came ? reinterpret_cast<float*>(r[kRecCrm]) : nullptr;
+    d.cc = came ? reinterpret_cast<void*>(r[kRecCc]) : nullptr;
+    d.ccm = came ? reinterpret_cast<float*>(r[kRecCcm]) : nullptr;
+    d.unit_begin = (int64_t)r[kRecUnit];
+    d.ach_begin = (int64_t)r[kRecAch];
+    d.mt_begin = (int64_t)r[kRecMt];
+    d.blk_begin[0] = (int64_t)r[kRecBlk0];
+    d.blk_begin[1] = (int64_t)r[kRecBlk1];
+    fac_regions(d, ws, r[kRecOff], came, ur);
+    reinterpret_cast<FacDesc*>(ws)[first + k] = d;
+    int64_t* const x = reinterpret_cast<int64_t*>(ws + index_off) + first + k;
+    x[0] = d.unit_begin;
+    x[nt] = d.ach_begin;
+    x[2 * nt] = d.mt_begin;
+    x[3 * nt] = d.blk_begin[0];
+    x[4 * nt] = d.blk_begin[1];
 }
 
-hipError_t fac_copy_desc(const FacDesc* host, int count, FacDesc* dev, int64_t* index, hipStream_t s) {
-    static_assert(sizeof(FacDesc) % 8 == 0 && sizeof(FacDescBatch) <= 4096 - 64, "descriptor size");
-    for (int off = 0; off < count; off += kFacCopyBatch) {
-        FacDescBatch b;
-        b.count = count - off < kFacCopyBatch ? count - off : kFacCopyBatch;
-        b.offset = off;
-        for (int i = 0; i < b.count; ++i) b.d[i] = host[off + i];
-        hipLaunchKernelGGL(fac_desc_copy_kernel, dim3(1), dim3(256), 0, s, b, dev, index, count);
+hipError_t fac_copy_desc(const FacRec* host, int count, char* ws, size_t index_off, bool came, int ur, hipStream_t s) {
+    const int words = came ? (int)kFacRecWords : (int)kFacRecAda;
+    const int per = kFacBatchWords / words;
+    static_assert(kFacBatchWords / kFacRecAda <= 64, "one thread per record");
+    static_assert(sizeof(FacRecBatch) + 64 <= 4096, "copy arguments");
+    for (int off = 0; off < count; off += per) {
+        FacRecBatch b;
+        const int nb = count - off < per ? count - off : per;
+        for (int i = 0; i < nb; ++i)
+            for (int w = 0; w < words; ++w) b.w[i * words + w] = host[off + i].w[w];
+        hipLaunchKernelGGL(fac_desc_copy_kernel, dim3(1), dim3(64), 0, s, b, nb, off, words, ws, index_off, count, ur);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -693,12 +720,106 @@ __device__ __forceinline__ int64_t unit_of_wave(int64_t base) {
     return base + xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
+// ------------------------------------------- Adafactor 1-D tensors (WG each)
 template <int G>
-__global__ __launch_bounds__(256) void fac_marg_kernel(const FacArgs a, int64_t base) {
+__device__ __forceinline__ void ada_vec1d(const FacArgs& a, const FacDesc& d, DD* sh, double& clip_s) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t n = d.rows * d.cols;
+    for (int64_t i = tid; i < n; i += blockDim.x) {
+        const double gi = (double)grad1<G>(d.g, i);
+        const float old = vec_decode(a.v_codec, a.v_block, d.v, d.vm, i, a.cf);
+        d.rtmp[i] = (float)(a.beta * (double)old + a.omb * (gi * gi + a.eps1));
+    }
+    __syncthreads();
+    vec_encode(a.v_codec, a.v_block, d.rtmp, n, a.v_floor, d.v, d.vm, wave, 4, lane);
+    DD s{0.0, 0.0};
+    for (int64_t i = tid; i < n; i += blockDim.x) {
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        dd_add(s, uu * uu);
+    }
+    s = block_dd_sum(s, sh);
+    if (tid == 0) {
+        const double rms = sqrt(dd_value(s) / (double)n);
+        clip_s = rms / a.clip_d > 1.0 ? rms / a.clip_d : 1.0;
+    }
+    __syncthreads();
+    const double clip = clip_s;
+    for (int64_t i = tid; i < n; i += blockDim.x) {
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        const double pd = (double)d.p[i] * a.decay;
+        d.p[i] = (float)(pd - a.lr * (uu / clip));
+    }
+}
+
+// ---------------------------------------------------------- CAME momentum
+// In-step momentum of element e of tensor d from its uhat (binary64 EMA,
+// rounded to fp32): m = fl32(beta1 * mhat + (1 - beta1) * uhat).
+__device__ __forceinline__ float came_momentum(const FacArgs& a, const FacDesc& d, int64_t e, float uh) {
+    float mh;
+    if (a.m_codec == UF8) {
+        const int32_t q = reinterpret_cast<const int8_t*>(d.m)[e];
+        mh = uf8_decode(q, div127((double)d.mm[e / a.m_block]));
+    } else {
+        mh = reinterpret_cast<const float*>(d.m)[e];
+    }
+    return (float)(a.beta1 * (double)mh + a.omb1 * (double)uh);
+}
+
+// ------------------------------------------------ CAME 1-D tensors (WG each)
+template <int G>
+__device__ __forceinline__ void came_vec1d(const FacArgs& a, const FacDesc& d, DD* sh, double& clip_s) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t n = d.rows * d.cols;
+    for (int64_t i = tid; i < n; i += blockDim.x) {
+        const double gi = (double)grad1<G>(d.g, i);
+        const float old = vec_decode(a.v_codec, a.v_block, d.v, d.vm, i, a.cf);
+        d.rtmp[i] = (float)(a.beta * (double)old + a.omb * (gi * gi + a.eps1));
+    }
+    __syncthreads();
+    vec_encode(a.v_codec, a.v_block, d.rtmp, n, a.v_floor, d.v, d.vm, wave, 4, lane);
+    DD s{0.0, 0.0};
+    for (int64_t i = tid; i < n; i += blockDim.x) {
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        dd_add(s, uu * uu);
+    }
+    s = block_dd_sum(s, sh);
+    if (tid == 0) {
+        const double rms = sqrt(dd_value(s) / (double)n);
+        clip_s = rms / a.clip_d > 1.0 ? rms / a.clip_d : 1.0;
+    }
+    __syncthreads();
+    const double clip = clip_s;
+    for (int64_t i = tid; i < n; i += blockDim.x) {
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        const float uh = (float)(uu / clip);
+        const float m = came_momentum(a, d, i, uh);
+        d.ctmp[i] = m;
+        const double pd = (double)d.p[i] * a.decay;
+        d.p[i] = (float)(pd - a.lr * (double)m);
+    }
+    __syncthreads();
+    vec_encode(a.m_codec, a.m_block, d.ctmp, n, 0.0f, d.m, d.mm, wave, 4, lane);
+}
+
+// The first a.n1 workgroups of the first launch (lead = a.n1) step a 1-D tensor each: one workgroup is
+// latency-bound (4096 elements take 85 us, as a pass of its own at the end of the step), and beside the
+// streaming units it is hidden.
+template <int G, bool CAME>
+__global__ __launch_bounds__(256) void fac_marg_kernel(const FacArgs a, int64_t base, int lead) {
     __shared__ __attribute__((aligned(16))) double stages[4][2 * MargTerms<G>::NR * kWStride];
     static_assert(2 * MargTerms<G>::NR >= kEdgeFR, "the edge units' stage");
+    if ((int)blockIdx.x < lead) {
+        const FacDesc& d = a.D[a.n2 + blockIdx.x];
+        DD* const sh = reinterpret_cast<DD*>(&stages[0][0]);
+        if constexpr (CAME)
+            came_vec1d<G>(a, d, sh, stages[1][0]);
+        else
+            ada_vec1d<G>(a, d, sh, stages[1][0]);
+        return;
+    }
     double* stage = stages[threadIdx.x >> 6];
-    const int64_t unit = unit_of_wave(base);
+    const int64_t unit = base + xcd_order(blockIdx.x - lead, gridDim.x - lead) * 4 +
+                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (unit >= a.total_units) return;
     const GD d = gview(a.D[locate(a.unit_begins, a.n2, unit)]);
     const int64_t u = unit - d.unit_begin, ru = u / d.ncu, cu = u % d.ncu;
@@ -715,9 +836,24 @@ __global__ __launch_bounds__(256) void fac_marg_kernel(const FacArgs a, int64_t 
     }
 }
 
-hipError_t launch_fac_marg(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (grad_dtype == G_BF16) return launch_wave_per_unit(fac_marg_kernel<G_BF16>, a, s);
-    return launch_wave_per_unit(fac_marg_kernel<G_F32>, a, s);
+template <int G, bool CAME>
+static hipError_t marg_launch(const FacArgs& a, hipStream_t s) {
+    constexpr int64_t kMaxGrid = int64_t(1) << 30;
+    int lead = a.n1;
+    for (int64_t base = 0; base < a.total_units || lead > 0; base += 4 * kMaxGrid) {
+        const int64_t left = (a.total_units - base + 3) / 4;
+        const int64_t grid = (left < kMaxGrid ? left : kMaxGrid) + lead;
+        hipLaunchKernelGGL((fac_marg_kernel<G, CAME>), dim3((unsigned)grid), dim3(256), 0, s, a, base, lead);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        lead = 0;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_fac_marg(const FacArgs& a, int grad_dtype, bool came, hipStream_t s) {
+    if (grad_dtype == G_BF16) return came ? marg_launch<G_BF16, true>(a, s) : marg_launch<G_BF16, false>(a, s);
+    return came ? marg_launch<G_F32, true>(a, s) : marg_launch<G_F32, false>(a, s);
 }
 
 // ------------------------------------------------------------- finalize
@@ -1424,63 +1560,6 @@ hipError_t launch_ada_apply(const FacArgs& a, int grad_dtype, hipStream_t s) {
               : launch_per_chunk(ada_apply_flat_kernel<G_F32>, a, a.rows_ach, a.total_ach, s);
 }
 
-// ------------------------------------------- Adafactor 1-D tensors (WG each)
-template <int G>
-__global__ __launch_bounds__(256) void ada_vec1d_kernel(const FacArgs a) {
-    __shared__ DD sh[4];
-    __shared__ double clip_s;
-    const FacDesc& d = a.D[a.n2 + blockIdx.x];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t n = d.rows * d.cols;
-    for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double gi = (double)grad1<G>(d.g, i);
-        const float old = vec_decode(a.v_codec, a.v_block, d.v, d.vm, i, a.cf);
-        d.rtmp[i] = (float)(a.beta * (double)old + a.omb * (gi * gi + a.eps1));
-    }
-    __syncthreads();
-    vec_encode(a.v_codec, a.v_block, d.rtmp, n, a.v_floor, d.v, d.vm, wave, 4, lane);
-    DD s{0.0, 0.0};
-    for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
-        dd_add(s, uu * uu);
-    }
-    s = block_dd_sum(s, sh);
-    if (tid == 0) {
-        const double rms = sqrt(dd_value(s) / (double)n);
-        clip_s = rms / a.clip_d > 1.0 ? rms / a.clip_d : 1.0;
-    }
-    __syncthreads();
-    const double clip = clip_s;
-    for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
-        const double pd = (double)d.p[i] * a.decay;
-        d.p[i] = (float)(pd - a.lr * (uu / clip));
-    }
-}
-
-hipError_t launch_ada_vec1d(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.n1 == 0) return hipSuccess;
-    if (grad_dtype == G_BF16)
-        hipLaunchKernelGGL(ada_vec1d_kernel<G_BF16>, dim3(a.n1), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(ada_vec1d_kernel<G_F32>, dim3(a.n1), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------- CAME momentum
-// In-step momentum of element e of tensor d from its uhat (binary64 EMA,
-// rounded to fp32): m = fl32(beta1 * mhat + (1 - beta1) * uhat).
-__device__ __forceinline__ float came_momentum(const FacArgs& a, const FacDesc& d, int64_t e, float uh) {
-    float mh;
-    if (a.m_codec == UF8) {
-        const int32_t q = reinterpret_cast<const int8_t*>(d.m)[e];
-        mh = uf8_decode(q, div127((double)d.mm[e / a.m_block]));
-    } else {
-        mh = reinterpret_cast<const float*>(d.m)[e];
-    }
-    return (float)(a.beta1 * (double)mh + a.omb1 * (double)uh);
-}
-
 // ------------------------------------------- CAME residual marginal sums
 // Terms (uhat - m)^2 with uhat = fl32(u / clip) and m the in-step momentum.
 // Whole units: the marginal kernels' streaming layout (whole_unit_sums).
@@ -1981,54 +2060,6 @@ hipError_t launch_came_apply(const FacArgs& a, int grad_dtype, hipStream_t s) {
     const bool uf = a.m_codec == UF8;
     if (grad_dtype == G_BF16) return uf ? came_apply_launch<G_BF16, true>(a, s) : came_apply_launch<G_BF16, false>(a, s);
     return uf ? came_apply_launch<G_F32, true>(a, s) : came_apply_launch<G_F32, false>(a, s);
-}
-
-// ------------------------------------------------ CAME 1-D tensors (WG each)
-template <int G>
-__global__ __launch_bounds__(256) void came_vec1d_kernel(const FacArgs a) {
-    __shared__ DD sh[4];
-    __shared__ double clip_s;
-    const FacDesc& d = a.D[a.n2 + blockIdx.x];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t n = d.rows * d.cols;
-    for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double gi = (double)grad1<G>(d.g, i);
-        const float old = vec_decode(a.v_codec, a.v_block, d.v, d.vm, i, a.cf);
-        d.rtmp[i] = (float)(a.beta * (double)old + a.omb * (gi * gi + a.eps1));
-    }
-    __syncthreads();
-    vec_encode(a.v_codec, a.v_block, d.rtmp, n, a.v_floor, d.v, d.vm, wave, 4, lane);
-    DD s{0.0, 0.0};
-    for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
-        dd_add(s, uu * uu);
-    }
-    s = block_dd_sum(s, sh);
-    if (tid == 0) {
-        const double rms = sqrt(dd_value(s) / (double)n);
-        clip_s = rms / a.clip_d > 1.0 ? rms / a.clip_d : 1.0;
-    }
-    __syncthreads();
-    const double clip = clip_s;
-    for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
-        const float uh = (float)(uu / clip);
-        const float m = came_momentum(a, d, i, uh);
-        d.ctmp[i] = m;
-        const double pd = (double)d.p[i] * a.decay;
-        d.p[i] = (float)(pd - a.lr * (double)m);
-    }
-    __syncthreads();
-    vec_encode(a.m_codec, a.m_block, d.ctmp, n, 0.0f, d.m, d.mm, wave, 4, lane);
-}
-
-hipError_t launch_came_vec1d(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.n1 == 0) return hipSuccess;
-    if (grad_dtype == G_BF16)
-        hipLaunchKernelGGL(came_vec1d_kernel<G_BF16>, dim3(a.n1), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(came_vec1d_kernel<G_F32>, dim3(a.n1), dim3(256), 0, s, a);
-    return hipGetLastError();
 }
 
 }  // namespace al
