@@ -313,8 +313,8 @@ al_status check_apollo_cfg(const al_apollo_cfg* cfg) {
 struct ApolloPlan {
     std::vector<al::ApolloDesc> desc;
     std::vector<int> idx;  // tensor index of each descriptor (empty tensors are skipped)
-    int64_t total_tiles = 0, total_chans = 0, total_units = 0;
-    int32_t any_whole = 0, any_ragged = 0;
+    int64_t total_tiles = 0, total_chans = 0, total_units = 0, total_fch = 0;
+    size_t index_off = 0;
     size_t adamw_off = 0;  // descriptor table of the AdamW launch over the projected moments
     size_t bytes = 0;
 };
@@ -359,23 +359,26 @@ al_status apollo_plan(const al_apollo_tensor* ts, int nt, const al_apollo_cfg* c
         d.right = t.rows >= t.cols;
         d.C = C;
         d.L = d.right ? t.cols : t.rows;
-        d.nru = (int32_t)((t.rows + 255) / 256);
+        const bool whole = t.rows % 256 == 0 && t.cols % 256 == 0;
+        const int64_t tch = al::apollo_tile_ch(cfg->rank);
         d.ncu = (int32_t)((t.cols + 255) / 256);
         d.tile_begin = P.total_tiles;
-        P.total_tiles += (C + al::kApolloTileCh - 1) / al::kApolloTileCh;
+        P.total_tiles += (C + tch - 1) / tch;
         d.chan_begin = P.total_chans;
         P.total_chans += C;
         d.unit_begin = P.total_units;
-        P.total_units += (int64_t)d.nru * d.ncu;
-        d.whole = t.rows % 256 == 0 && t.cols % 256 == 0;
-        (d.whole ? P.any_whole : P.any_ragged) = 1;
+        if (whole) P.total_units += (t.rows / 256) * (t.cols / 256);
+        d.fch_begin = P.total_fch;
+        if (!whole) P.total_fch += (t.rows * t.cols + al::kApolloFlatChunk - 1) / al::kApolloFlatChunk;
         P.desc.push_back(d);
         P.idx.push_back(i);
     }
     if (P.total_tiles >= (int64_t(1) << 31) || P.total_chans / 4 >= (int64_t(1) << 31) ||
-        P.total_units / 4 >= (int64_t(1) << 31))
+        P.total_units / 4 >= (int64_t(1) << 31) || P.total_fch / 4 >= (int64_t(1) << 31))
         return fail(AL_EUNSUPPORTED, "apollo: tensor list too large for one launch");
     size_t off = align256(P.desc.size() * sizeof(al::ApolloDesc));
+    P.index_off = off;
+    off += align256(P.desc.size() * al::kApolloIndex * sizeof(int64_t));
     auto take = [&](size_t nbytes) -> char* {
         char* ptr = ws ? ws + off : nullptr;
         off += align256(nbytes);
@@ -649,8 +652,12 @@ al_status al_apollo_step(const al_apollo_tensor* tensors, int32_t nt, const al_a
     a.total_tiles = P.total_tiles;
     a.total_chans = P.total_chans;
     a.total_units = P.total_units;
-    a.any_whole = P.any_whole;
-    a.any_ragged = P.any_ragged;
+    a.total_fch = P.total_fch;
+    int64_t* const index = reinterpret_cast<int64_t*>(static_cast<char*>(ws) + P.index_off);
+    a.tile_begins = index;
+    a.chan_begins = index + a.nt;
+    a.unit_begins = index + 2 * a.nt;
+    a.fch_begins = index + 3 * a.nt;
     a.lr = cfg->lr;
     a.decay = 1.0 - cfg->lr * cfg->weight_decay;
     a.gamma = cfg->gamma;
@@ -696,7 +703,7 @@ al_status al_apollo_step(const al_apollo_tensor* tensors, int32_t nt, const al_a
 
     hipStream_t s = as_stream(stream);
     hipError_t e;
-    if ((e = al::apollo_copy_desc(P.desc.data(), a.nt, const_cast<al::ApolloDesc*>(a.D), s)) != hipSuccess ||
+    if ((e = al::apollo_copy_desc(P.desc.data(), a.nt, const_cast<al::ApolloDesc*>(a.D), index, s)) != hipSuccess ||
         (e = al::launch_apollo_proj(a, cfg->grad_dtype, s)) != hipSuccess ||
         (e = al::adamw_write_table(wd.data(), (int)wd.size(), static_cast<char*>(ws) + P.adamw_off, w, win, s)) !=
             hipSuccess ||

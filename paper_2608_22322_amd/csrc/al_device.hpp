@@ -749,4 +749,81 @@ constexpr int levels_of() {
     return C == AL16 ? 65534 : 254;
 }
 
+// Gradients in global memory: one as fp32, or 4 consecutive ones (aligned, streaming).
+template <int G>
+__device__ __forceinline__ float grad_at_g(gp<const void> g, int64_t e) {
+    if constexpr (G == G_BF16)
+        return bf16_to_f32(g_as<const uint16_t>(g)[e]);
+    else
+        return g_as<const float>(g)[e];
+}
+
+template <int G>
+__device__ __forceinline__ void load_g4(gp<const void> g, int64_t e, float gv[4]) {
+    if constexpr (G == G_BF16) {
+        const uint2 w = ld_u2<true>(g_as<const void>(g_as<const uint16_t>(g) + e));
+        gv[0] = u2f(w.x << 16), gv[1] = u2f(w.x & 0xFFFF0000u), gv[2] = u2f(w.y << 16), gv[3] = u2f(w.y & 0xFFFF0000u);
+    } else {
+        const float4 w = ld_f4<true>(g_as<const float>(g) + e);
+        gv[0] = w.x, gv[1] = w.y, gv[2] = w.z, gv[3] = w.w;
+    }
+}
+
+// Rows and columns of a lane's 4 consecutive elements of the flattening, one
+// 256-element sub-tile after another. step256: the way from a lane's element to
+// the one 256 further on.
+struct FlatPos {
+    int64_t rows, cols;
+    int i, j;        // of the lane's first element (wide = false)
+    int di, dj;      // 256 / cols, 256 % cols
+    bool wide;       // outside the 32-bit, at-most-one-wrap range: divide per element
+    __device__ FlatPos(int64_t rows_, int64_t cols_, int64_t e) : rows(rows_), cols(cols_) {
+        wide = cols < 4 || cols >= (int64_t(1) << 30) || rows >= (int64_t(1) << 30);
+        i = j = di = dj = 0;
+        if (wide) return;
+        // binary64 estimate of the quotient, then exact correction
+        int64_t q = (int64_t)((double)e / (double)cols), r = e - q * cols;
+        if (r < 0) {
+            --q;
+            r += cols;
+        } else if (r >= cols) {
+            ++q;
+            r -= cols;
+        }
+        i = (int)q;
+        j = (int)r;
+        di = 256 / (int)cols;
+        dj = 256 % (int)cols;
+    }
+    // factors of the lane's 4 elements (e: the first; elements past the matrix take those of the last row)
+    template <class F>
+    __device__ __forceinline__ void each(int64_t e, F f) const {
+        if (!wide) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                int jj = j + t, ii = i;
+                if (jj >= (int)cols) {
+                    jj -= (int)cols;
+                    ++ii;
+                }
+                f(t, (int64_t)(ii < (int)rows ? ii : (int)rows - 1), (int64_t)jj);
+            }
+        } else {
+#pragma unroll 1
+            for (int t = 0; t < 4; ++t) {
+                const int64_t ii = (e + t) / cols;
+                f(t, ii < rows ? ii : rows - 1, (e + t) % cols);
+            }
+        }
+    }
+    __device__ void next() {
+        i += di;
+        j += dj;
+        if (j >= (int)cols) {
+            j -= (int)cols;
+            ++i;
+        }
+    }
+};
+
 }  // namespace al

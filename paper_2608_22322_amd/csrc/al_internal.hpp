@@ -245,7 +245,9 @@ hipError_t launch_came_apply(const FacArgs& a, int grad_dtype, hipStream_t s);
 // tensor has C channels of L inputs (A = G or G^T as C x L) and rank r; its
 // workspace regions hold R and Rt (C x r fp32, channel-major) and per-channel
 // binary64 sums.
-constexpr int kApolloTileCh = 32;  // channels per projection workgroup
+// channels per projection workgroup: four wavefronts of 32 channels x 64 columns
+constexpr int apollo_tile_ch(int rank) { return 32 * 256 / rank; }
+constexpr int kApolloFlatChunk = 1024;  // elements per update chunk of tensors that are not whole units
 struct ApolloDesc {
     float* p;
     const void* g;
@@ -258,14 +260,15 @@ struct ApolloDesc {
     double* sg;          // C: s_c^2 gn2_c
     double* lam;         // [0]: limiter divisor
     int64_t rows, cols, C, L;
-    int64_t tile_begin;  // first projection tile (kApolloTileCh channels)
+    int64_t tile_begin;  // first projection tile (apollo_tile_ch channels)
     int64_t chan_begin;  // first channel over the list
-    int64_t unit_begin;  // first 256x256 update unit
+    int64_t unit_begin;  // first 256x256 update unit (tensors of whole units only)
+    int64_t fch_begin;   // first flattened update chunk (the other tensors)
     int32_t right;       // channels are rows (rows >= cols)
-    int32_t nru, ncu;
-    int32_t whole;       // rows and columns multiples of 256 (the update takes the streaming chunk layout)
+    int32_t ncu;         // units along the columns
 };
 
+constexpr int kApolloIndex = 4;  // packed search arrays behind the descriptor table
 constexpr int kApolloCopyBatch = 16;
 struct ApolloDescBatch {
     int32_t count, offset;
@@ -274,14 +277,15 @@ struct ApolloDescBatch {
 
 struct ApolloArgs {
     const ApolloDesc* D;
+    // the descriptors' tile_begin, chan_begin, unit_begin and fch_begin, packed
+    const int64_t *tile_begins, *chan_begins, *unit_begins, *fch_begins;
     int32_t nt, rank;
-    int32_t any_whole, any_ragged;  // some tensors are (are not) made of whole 256x256 units
-    int64_t total_tiles, total_chans, total_units;
+    int64_t total_tiles, total_chans, total_units, total_fch;
     double lr, decay, gamma;
     int64_t step;
 };
 
-hipError_t apollo_copy_desc(const ApolloDesc* host, int count, ApolloDesc* dev, hipStream_t s);
+hipError_t apollo_copy_desc(const ApolloDesc* host, int count, ApolloDesc* dev, int64_t* index, hipStream_t s);
 hipError_t launch_apollo_proj(const ApolloArgs& a, int grad_dtype, hipStream_t s);
 hipError_t launch_apollo_scale(const ApolloArgs& a, hipStream_t s);
 hipError_t launch_apollo_norm(const ApolloArgs& a, hipStream_t s);

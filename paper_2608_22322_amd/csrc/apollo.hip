@@ -30,19 +30,6 @@ namespace al {
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-template <int64_t ApolloDesc::*F>
-__device__ __forceinline__ int apollo_locate(const ApolloDesc* D, int n, int64_t x) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (D[mid].*F <= x)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
 // Fixed-order butterfly sum of a double over the wavefront (every lane gets the total).
 __device__ __forceinline__ double wave_sum_d(double x) {
 #pragma unroll
@@ -50,31 +37,31 @@ __device__ __forceinline__ double wave_sum_d(double x) {
     return x;
 }
 
-template <int G>
-__device__ __forceinline__ double grad_d(const void* g, int64_t e) {
-    if constexpr (G == G_BF16)
-        return (double)bf16_to_f32(reinterpret_cast<const uint16_t*>(g)[e]);
-    else
-        return (double)reinterpret_cast<const float*>(g)[e];
-}
-
 // --------------------------------------------------------------- descriptors
-__global__ void apollo_desc_copy_kernel(const ApolloDescBatch b, ApolloDesc* dst) {
+__global__ void apollo_desc_copy_kernel(const ApolloDescBatch b, ApolloDesc* dst, int64_t* index, int nt) {
     constexpr int W = sizeof(ApolloDesc) / 8;
     const int total = b.count * W;
     const uint64_t* src = reinterpret_cast<const uint64_t*>(b.d);
     uint64_t* out = reinterpret_cast<uint64_t*>(dst + b.offset);
     for (int i = threadIdx.x; i < total; i += blockDim.x) out[i] = src[i];
+    if (threadIdx.x < b.count) {
+        const ApolloDesc& d = b.d[threadIdx.x];
+        int64_t* const x = index + b.offset + threadIdx.x;
+        x[0] = d.tile_begin;
+        x[nt] = d.chan_begin;
+        x[2 * nt] = d.unit_begin;
+        x[3 * nt] = d.fch_begin;
+    }
 }
 
-hipError_t apollo_copy_desc(const ApolloDesc* host, int count, ApolloDesc* dev, hipStream_t s) {
-    static_assert(sizeof(ApolloDesc) % 8 == 0, "descriptor size");
+hipError_t apollo_copy_desc(const ApolloDesc* host, int count, ApolloDesc* dev, int64_t* index, hipStream_t s) {
+    static_assert(sizeof(ApolloDesc) % 8 == 0 && sizeof(ApolloDescBatch) <= 4096 - 64, "descriptor size");
     for (int off = 0; off < count; off += kApolloCopyBatch) {
         ApolloDescBatch b;
         b.count = count - off < kApolloCopyBatch ? count - off : kApolloCopyBatch;
         b.offset = off;
         for (int i = 0; i < b.count; ++i) b.d[i] = host[off + i];
-        hipLaunchKernelGGL(apollo_desc_copy_kernel, dim3(1), dim3(256), 0, s, b, dev);
+        hipLaunchKernelGGL(apollo_desc_copy_kernel, dim3(1), dim3(256), 0, s, b, dev, index, count);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -84,9 +71,12 @@ hipError_t apollo_copy_desc(const ApolloDesc* host, int count, ApolloDesc* dev, 
 // ---------------------------------------------------------------- projection
 constexpr int kLK = 16;  // inputs per LDS slice
 
-// One workgroup of 4 wavefronts per tile of 32 channels; wave w computes output
-// columns [64 w, 64 w + 64) of the tile (2 x 4 MFMA tiles of 16 x 16, eight
-// binary64 accumulators) when 64 w < r. Four such workgroups share a CU (one
+// One workgroup of 4 wavefronts per tile of 32 * 256 / r channels: each wavefront
+// computes 32 channels x 64 output columns (2 x 4 MFMA tiles of 16 x 16, eight
+// binary64 accumulators), the four of them side by side along the columns at rank
+// 256, 2 x 2 at rank 128 and along the channels at rank 64 (with 32-channel tiles at
+// every rank, rank 64 left three of the four without matrix work: a 6-layer list of
+// width 640 took 135 us in this kernel, now 119: too few tiles are left to hide the loads). Four such workgroups share a CU (one
 // wavefront of each per SIMD), so one workgroup's barrier leaves three to feed
 // the matrix cores. (Eight wavefronts on 64 channels: 2 workgroups per CU,
 // projection 2% slower; four wavefronts of 64 x 64 outputs -- 16 accumulators,
@@ -106,15 +96,23 @@ constexpr int kLK = 16;  // inputs per LDS slice
 // register v of lane l is D[l / 16 + 4 v][l % 16].
 constexpr int kProjWaves = 4;                                     // wavefronts per workgroup
 constexpr int kProjThreads = 64 * kProjWaves;
-constexpr int kProjIT = kApolloTileCh / 16;                       // 16-channel MFMA tiles per wavefront
-constexpr int kProjCW = 256 / kProjWaves;                         // output columns per wavefront
+constexpr int kProjCh = 32;                                       // channels per wavefront
+constexpr int kProjIT = kProjCh / 16;                             // 16-channel MFMA tiles per wavefront
+constexpr int kProjCW = 64;                                       // output columns per wavefront
 constexpr int kProjJT = kProjCW / 16;                             // 16-column MFMA tiles per wavefront
 constexpr int kProjRows = kLK / kProjWaves;                       // rows of Pi each wavefront copies per slice
-constexpr int kAPer = kApolloTileCh * kLK / kProjThreads;         // A values per thread and slice
 constexpr int kAsPitch = 18;                                      // A row pitch in LDS (floats)
-constexpr int kBsPitch = 256 + 16;                                // Pi row pitch in LDS (floats)
-static_assert(kProjIT * kProjJT == 8 && kLK % kProjWaves == 0 && kAPer * kProjThreads == kApolloTileCh * kLK,
-              "projection tiling");
+static_assert(kProjIT * kProjJT == 8 && kLK % kProjWaves == 0, "projection tiling");
+// Of rank R: channels per tile, A values per thread and slice, Pi row pitch in LDS (floats; the four
+// rows of an operand read start 16 banks apart).
+template <int R>
+struct ProjGeo {
+    static constexpr int CG = R / kProjCW;  // wavefronts along the columns
+    static constexpr int TCH = apollo_tile_ch(R);
+    static constexpr int APer = TCH * kLK / kProjThreads;
+    static constexpr int BsPitch = R + 16;
+    static_assert(TCH == kProjCh * (kProjWaves / CG) && APer * kProjThreads == TCH * kLK, "projection tiling");
+};
 
 // A pointer known to be the same on every lane, made scalar, so that a load
 // from it plus a 32-bit lane offset needs no vector address arithmetic.
@@ -131,8 +129,9 @@ __device__ __forceinline__ P uniform_ptr(P p) {
 // Every slice loads from a uniform slice base plus a fixed 32-bit byte offset
 // per value (no vector address work): one offset for slices wholly inside the
 // tensor, one for a ragged last slice, which clamps l to L - 1 (and zeroes it).
-template <int G>
+template <int G, int R>
 struct ProjA {
+    static constexpr int kAPer = ProjGeo<R>::APer;
     using T = typename std::conditional<G == G_BF16, uint16_t, uint32_t>::type;
     gp<const T> tile;       // element (c0, 0): the tile's first channel, first input
     int64_t stride;         // distance between consecutive inputs of a channel
@@ -144,10 +143,11 @@ struct ProjA {
     bool cfull;             // every channel of the tile inside the tensor (uniform)
 };
 
-template <int G>
-__device__ __forceinline__ void proj_a_setup(ProjA<G>& A, const void* g, int64_t cols, int64_t C, int64_t c0,
+template <int G, int R>
+__device__ __forceinline__ void proj_a_setup(ProjA<G, R>& A, const void* g, int64_t cols, int64_t C, int64_t c0,
                                              int L, bool right, int tid) {
-    using T = typename ProjA<G>::T;
+    using T = typename ProjA<G, R>::T;
+    constexpr int kAPer = ProjGeo<R>::APer, kApolloTileCh = ProjGeo<R>::TCH;
     A.stride = right ? 1 : cols;
     A.tile = to_g(reinterpret_cast<const T*>(g)) + (right ? c0 * cols : c0);
     A.cfull = c0 + kApolloTileCh <= C;
@@ -170,9 +170,10 @@ __device__ __forceinline__ void proj_a_setup(ProjA<G>& A, const void* g, int64_t
 
 // Slice l0 of A as raw bits into registers (the wait for them falls after the
 // matrix work, where proj_store_a consumes them).
-template <int G>
-__device__ __forceinline__ void proj_fetch_a(const ProjA<G>& A, int l0, int L, uint32_t (&ra)[kAPer]) {
-    using T = typename ProjA<G>::T;
+template <int G, int R>
+__device__ __forceinline__ void proj_fetch_a(const ProjA<G, R>& A, int l0, int L, uint32_t (&ra)[ProjGeo<R>::APer]) {
+    using T = typename ProjA<G, R>::T;
+    constexpr int kAPer = ProjGeo<R>::APer;
     const bool inside = l0 + kLK <= L;  // otherwise the last slice
     const gp<const char> sb = uniform_ptr(g_as<const char>(A.tile + (int64_t)l0 * A.stride));
 #pragma unroll
@@ -181,9 +182,10 @@ __device__ __forceinline__ void proj_fetch_a(const ProjA<G>& A, int l0, int L, u
 
 // The slice into LDS as fp32, inputs outside the tensor as zero; each thread
 // also accumulates the squares of the values it stores (binary64, exact products).
-template <int G>
-__device__ __forceinline__ void proj_store_a(const ProjA<G>& A, int l0, int L, float* As,
-                                             const uint32_t (&ra)[kAPer], double (&gq)[kAPer]) {
+template <int G, int R>
+__device__ __forceinline__ void proj_store_a(const ProjA<G, R>& A, int l0, int L, float* As,
+                                             const uint32_t (&ra)[ProjGeo<R>::APer], double (&gq)[ProjGeo<R>::APer]) {
+    constexpr int kAPer = ProjGeo<R>::APer;
     const bool full = A.cfull && l0 + kLK <= L;
 #pragma unroll
     for (int q = 0; q < kAPer; ++q) {
@@ -198,21 +200,23 @@ __device__ __forceinline__ void proj_store_a(const ProjA<G>& A, int l0, int L, f
 // the same rows of the LDS buffer; rows past L repeat row L - 1. w is uniform,
 // so the row addresses are scalar (32-bit row arithmetic: a 64-bit compare has no
 // scalar form). Completion is counted by vmcnt.
-__device__ __forceinline__ void proj_copy_pi(const float* proj, int L, int l0, int r, int w, int lane,
-                                             float (*Bs)[kBsPitch]) {
+__device__ __forceinline__ void proj_copy_pi(const float* proj, int L, int l0, int r, int pitch, int w, int lane,
+                                             float* Bs) {
     if (4 * lane >= r) return;
 #pragma unroll
     for (int t = 0; t < kProjRows; ++t) {
         int row = l0 + kProjRows * w + t;
         row = row < L ? row : L - 1;
         const float* rp = uniform_ptr(proj + (int64_t)row * r);
-        __builtin_amdgcn_global_load_lds(rp + 4 * lane, &Bs[kProjRows * w + t][0], 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(rp + 4 * lane, Bs + (kProjRows * w + t) * pitch, 16, 0, 0);
     }
 }
 
-template <int G>
-__global__ __launch_bounds__(kProjThreads) __attribute__((amdgpu_waves_per_eu(4)))
+template <int G, int R>
+__global__ __launch_bounds__(kProjThreads) __attribute__((amdgpu_waves_per_eu(R == 64 ? 2 : 4)))
 void apollo_proj_kernel(const ApolloArgs a) {
+    using P = ProjGeo<R>;
+    constexpr int kAPer = P::APer, kApolloTileCh = P::TCH, kBsPitch = P::BsPitch, r = R;
     // Two buffers of each operand as four separate LDS objects, named statically
     // in each half of the unrolled slice loop: the compiler then knows that the
     // copy into one buffer does not alias the reads of the other and does not
@@ -222,11 +226,12 @@ void apollo_proj_kernel(const ApolloArgs a) {
     __shared__ __attribute__((aligned(16))) float Bs0[kLK][kBsPitch];
     __shared__ __attribute__((aligned(16))) float Bs1[kLK][kBsPitch];
     const int64_t tile = blockIdx.x;
-    const ApolloDesc& d = a.D[apollo_locate<&ApolloDesc::tile_begin>(a.D, a.nt, tile)];
+    const ApolloDesc& d = a.D[locate(a.tile_begins, a.nt, tile)];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, l4 = lane >> 4;
-    const int r = a.rank;
+    // the wavefront's 64 columns and 32 channels of the tile
+    const int cw = kProjCW * (w % P::CG), ch = kProjCh * (w / P::CG);
     // the descriptor's fields, read once (read through the descriptor they are
     // fetched again every slice, and those fetches wait for the copies in flight)
     const int64_t C = d.C;
@@ -239,9 +244,8 @@ void apollo_proj_kernel(const ApolloArgs a) {
     float* const Rtp = d.Rt;
     double* const gn2 = d.gn2;
     const bool right = d.right != 0;
-    ProjA<G> A;
-    proj_a_setup<G>(A, d.g, d.cols, C, c0, L, right, tid);
-    const bool active = kProjCW * w < r;
+    ProjA<G, R> A;
+    proj_a_setup<G, R>(A, d.g, d.cols, C, c0, L, right, tid);
     d4v acc[kProjIT][kProjJT];
 #pragma unroll
     for (int i = 0; i < kProjIT; ++i)
@@ -257,17 +261,17 @@ void apollo_proj_kernel(const ApolloArgs a) {
                      float (*Bn)[kBsPitch]) {
         const bool more = n + 1 < ns;
         if (more) {
-            proj_copy_pi(proj, L, (n + 1) * kLK, r, w, lane, Bn);
-            proj_fetch_a<G>(A, (n + 1) * kLK, L, ra);
+            proj_copy_pi(proj, L, (n + 1) * kLK, r, kBsPitch, w, lane, &Bn[0][0]);
+            proj_fetch_a<G, R>(A, (n + 1) * kLK, L, ra);
         }
-        if (active) {
+        {
             // the operands of step kk + 4 are read before the matrix work of step kk
             float xa[2][kProjIT], xb[2][kProjJT];
             auto rd = [&](int st, int kk) {
 #pragma unroll
-                for (int i = 0; i < kProjIT; ++i) xa[st][i] = Ac[16 * i + l16][kk + l4];
+                for (int i = 0; i < kProjIT; ++i) xa[st][i] = Ac[ch + 16 * i + l16][kk + l4];
 #pragma unroll
-                for (int j = 0; j < kProjJT; ++j) xb[st][j] = Bc[kk + l4][kProjCW * w + 16 * j + l16];
+                for (int j = 0; j < kProjJT; ++j) xb[st][j] = Bc[kk + l4][cw + 16 * j + l16];
             };
             rd(0, 0);
 #pragma unroll
@@ -293,15 +297,15 @@ void apollo_proj_kernel(const ApolloArgs a) {
                 __builtin_amdgcn_sched_group_barrier(0x008, kProjIT * kProjJT - kProjIT - kProjJT, 0);
             }
         }
-        if (more) proj_store_a<G>(A, (n + 1) * kLK, L, &An[0][0], ra, gq);
+        if (more) proj_store_a<G, R>(A, (n + 1) * kLK, L, &An[0][0], ra, gq);
         // the copies into the other buffers have landed and every read of these is done
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     };
     if (ns > 0) {
-        proj_copy_pi(proj, L, 0, r, w, lane, Bs0);
-        proj_fetch_a<G>(A, 0, L, ra);
-        proj_store_a<G>(A, 0, L, &As0[0][0], ra, gq);
+        proj_copy_pi(proj, L, 0, r, kBsPitch, w, lane, &Bs0[0][0]);
+        proj_fetch_a<G, R>(A, 0, L, ra);
+        proj_store_a<G, R>(A, 0, L, &As0[0][0], ra, gq);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     }
@@ -309,28 +313,23 @@ void apollo_proj_kernel(const ApolloArgs a) {
         slice(n, As0, Bs0, As1, Bs1);
         if (n + 1 < ns) slice(n + 1, As1, Bs1, As0, Bs0);
     }
-    // Channel sums of g^2 in a fixed order: the per-thread sums go to LDS (the
-    // first Pi buffer, free after the last barrier), then thread c adds the 16
-    // of channel c -- value q of threads c + kApolloTileCh m (channels along the
-    // rows of g) or value c / G16 of threads 16 (c % G16) + m, G16 = threads / 16
-    // (channels along the columns).
-    constexpr int kG16 = kProjThreads / 16;
-    static_assert(kAPer * kProjThreads / kApolloTileCh == 16 && kProjThreads % kApolloTileCh == 0 &&
-                      kAPer * kProjThreads * 8 <= (int)sizeof(Bs0),
-                  "the reduction below takes 16 values per channel");
-    double* red = reinterpret_cast<double*>(&Bs0[0][0]);
+    // Channel sums of g^2 in a fixed order: the per-thread sums go to LDS (the A buffers, free after the
+    // last barrier, half of them each) in the order of the slice values e = tid + threads q, then thread c
+    // adds the 16 of channel c: e = 16 c + m (channels along the rows of g) or c + tile channels m (along the
+    // columns).
+    constexpr int kHalf = kAPer / 2 * kProjThreads;
+    static_assert(kAPer % 2 == 0 && kHalf * 8 <= (int)sizeof(As0), "the reduction's halves");
+    double* const red0 = reinterpret_cast<double*>(&As0[0][0]);
+    double* const red1 = reinterpret_cast<double*>(&As1[0][0]);
 #pragma unroll
-    for (int q = 0; q < kAPer; ++q) red[q * kProjThreads + tid] = gq[q];
+    for (int q = 0; q < kAPer; ++q)
+        (q < kAPer / 2 ? red0 + q * kProjThreads : red1 + (q - kAPer / 2) * kProjThreads)[tid] = gq[q];
     __syncthreads();
     if (tid < kApolloTileCh && c0 + tid < C) {
         double x = 0.0;
-        if (right) {
-            const int q = tid / kG16, t0 = 16 * (tid % kG16);
-            for (int m = 0; m < 16; ++m) x += red[q * kProjThreads + t0 + m];
-        } else {
-            for (int q = 0; q < kAPer; ++q)
-                for (int m = 0; m < kProjThreads / kApolloTileCh; ++m)
-                    x += red[q * kProjThreads + tid + kApolloTileCh * m];
+        for (int m = 0; m < 16; ++m) {
+            const int e = right ? 16 * tid + m : tid + kApolloTileCh * m;
+            x += e < kHalf ? red0[e] : red1[e - kHalf];
         }
         to_g(gn2)[c0 + tid] = x;
     }
@@ -338,15 +337,15 @@ void apollo_proj_kernel(const ApolloArgs a) {
     const bool clear_rt = Rtp != nullptr;
     const gp<float> Rg = to_g(Rp);
     const gp<float> Rtg = to_g(Rtp);
-    if (active) {
+    {
 #pragma unroll
         for (int i = 0; i < kProjIT; ++i)
 #pragma unroll
             for (int j = 0; j < kProjJT; ++j)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int64_t c = c0 + 16 * i + l4 + 4 * v;
-                    const int k = kProjCW * w + 16 * j + l16;
+                    const int64_t c = c0 + ch + 16 * i + l4 + 4 * v;
+                    const int k = cw + 16 * j + l16;
                     if (c < C) {
                         Rg[c * r + k] = (float)acc[i][j][v];
                         if (clear_rt) Rtg[c * r + k] = 0.0f;
@@ -355,15 +354,21 @@ void apollo_proj_kernel(const ApolloArgs a) {
     }
 }
 
+template <int G>
+static hipError_t proj_launch(const ApolloArgs& a, hipStream_t s) {
+    const dim3 grid((unsigned)a.total_tiles), block(kProjThreads);
+    switch (a.rank) {
+        case 64: hipLaunchKernelGGL((apollo_proj_kernel<G, 64>), grid, block, 0, s, a); break;
+        case 128: hipLaunchKernelGGL((apollo_proj_kernel<G, 128>), grid, block, 0, s, a); break;
+        case 256: hipLaunchKernelGGL((apollo_proj_kernel<G, 256>), grid, block, 0, s, a); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_apollo_proj(const ApolloArgs& a, int grad_dtype, hipStream_t s) {
     if (a.total_tiles == 0) return hipSuccess;
-    // an active wavefront stores all kProjCW of its columns, and Pi rows are copied 16 B per lane
-    if (a.rank <= 0 || a.rank > 256 || a.rank % kProjCW != 0) return hipErrorInvalidValue;
-    if (grad_dtype == G_BF16)
-        hipLaunchKernelGGL(apollo_proj_kernel<G_BF16>, dim3((unsigned)a.total_tiles), dim3(kProjThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(apollo_proj_kernel<G_F32>, dim3((unsigned)a.total_tiles), dim3(kProjThreads), 0, s, a);
-    return hipGetLastError();
+    return grad_dtype == G_BF16 ? proj_launch<G_BF16>(a, s) : proj_launch<G_F32>(a, s);
 }
 
 // ------------------------------------------------------------ channel scales
@@ -383,6 +388,19 @@ __device__ __forceinline__ double row16_sum_d(double x) {
     return x;
 }
 
+// locate with a channel of its own per lane.
+__device__ __forceinline__ int lane_locate(const int64_t* b, int n, int64_t x) {
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (to_g(b)[mid] <= x)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
 __global__ __launch_bounds__(256) void apollo_scale_kernel(const ApolloArgs a) {
     const int lane = threadIdx.x & 63, sub = lane >> 4, l16 = lane & 15;
     const int64_t ch0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kScaleCh;
@@ -395,7 +413,7 @@ __global__ __launch_bounds__(256) void apollo_scale_kernel(const ApolloArgs a) {
         int64_t c = 0;
         const ApolloDesc* dp = nullptr;
         if (live) {
-            dp = &a.D[apollo_locate<&ApolloDesc::chan_begin>(a.D, a.nt, ch)];
+            dp = &a.D[lane_locate(a.chan_begins, a.nt, ch)];
             c = ch - dp->chan_begin;
             const gp<const float> rt = to_g((const float*)dp->Rt) + c * r;
             const gp<const float> rr = to_g((const float*)dp->R) + c * r;
@@ -453,105 +471,77 @@ hipError_t launch_apollo_norm(const ApolloArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------ parameter update
-// One wave per 256 x 256 unit, lane = 4 consecutive columns, rows in batches of
-// kUpdRows with all their loads issued before the stores (non-temporal: p and g
-// are touched once). The row scales s_r / lambda of the unit's 256 rows are
-// divided once per unit (4 per lane) and read back from LDS as broadcasts, so a
-// row costs no binary64 division.
-constexpr int kUpdRows = 16;
+// Tensors that are not whole 256 x 256 units: one wavefront per kApolloFlatChunk
+// consecutive elements of the row-major flattening, so that the parameter and
+// gradient accesses are as wide and aligned as in the whole units; the channel
+// scales are gathered by row or column (they stay in cache). A 6-layer list of width
+// 640 (fp32 gradients): 184 us with a wavefront per unit and guarded rows, now 50.
+template <int G, bool FULL>
+__device__ __forceinline__ void apollo_update_flat(const ApolloArgs& a, const ApolloDesc& d, int64_t e0, int valid) {
+    constexpr int K = kApolloFlatChunk / 256;
+    const int l4 = 4 * (threadIdx.x & 63);
+    const gp<float> pp = to_g(d.p);
+    const gp<const void> gg = to_g(d.g);
+    float gv[K][4];
+    float4 pv[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t e = e0 + 256 * k + l4;
+        if constexpr (FULL) {
+            load_g4<G>(gg, e, gv[k]);
+            pv[k] = ld_f4<true>(gp<const float>(pp + e));
+        } else {
+            float h[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bool ok = 256 * k + l4 + t < valid;
+                gv[k][t] = ok ? grad_at_g<G>(gg, e + t) : 0.0f;
+                h[t] = ok ? pp[e + t] : 0.0f;
+            }
+            pv[k] = make_float4(h[0], h[1], h[2], h[3]);
+        }
+    }
+    const double rlam = 1.0 / d.lam[0];
+    const gp<const double> sv = to_g((const double*)d.s);
+    const bool right = d.right != 0;
+    FlatPos pos(d.rows, d.cols, e0 + l4);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t e = e0 + 256 * k + l4;
+        const float pin[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
+        float out[4];
+        pos.each(e, [&](int t, int64_t i, int64_t j) {
+            const double upd = (double)gv[k][t] * (sv[right ? i : j] * rlam);
+            out[t] = (float)((double)pin[t] * a.decay - a.lr * upd);
+        });
+        pos.next();
+        if constexpr (FULL) {
+            st_f4<true>(pp + e, make_float4(out[0], out[1], out[2], out[3]));
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (256 * k + l4 + t < valid) pp[e + t] = out[t];
+        }
+    }
+}
 
 template <int G>
-__global__ __launch_bounds__(256) void apollo_update_kernel(const ApolloArgs a) {
-    __shared__ double srow_all[4][256];
-    const int lane = threadIdx.x & 63;
-    double* srow = srow_all[threadIdx.x >> 6];
-    const int64_t unit = xcd_order(blockIdx.x, gridDim.x) * 4 +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (unit >= a.total_units) return;
-    const ApolloDesc& d = a.D[apollo_locate<&ApolloDesc::unit_begin>(a.D, a.nt, unit)];
-    if (d.whole) return;  // the chunk kernel's
-    const int64_t u = unit - d.unit_begin;
-    const int64_t ru = u / d.ncu, cu = u % d.ncu;
-    const int64_t r0 = ru * 256, c0 = cu * 256, cols = d.cols;
-    const int nr = (int)(d.rows - r0 < 256 ? d.rows - r0 : 256);
-    const int nc = (int)(cols - c0 < 256 ? cols - c0 : 256);
-    const int c = 4 * lane;
-    const bool right = d.right != 0;
-    const double lam = d.lam[0];
-    const gp<const double> sv = to_g((const double*)d.s);
-    if (right) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int r = lane + 64 * k;
-            srow[r] = r < nr ? sv[r0 + r] / lam : 0.0;
-        }
-    }
-    if (c >= nc) return;
-    const bool vec = (cols & 3) == 0 && c + 4 <= nc;
-    const gp<float> pp = to_g(d.p);
-    double sc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) sc[j] = (!right && c + j < nc) ? sv[c0 + c + j] / lam : 0.0;
-    for (int rb = 0; rb < nr; rb += kUpdRows) {
-        float4 pv[kUpdRows];
-        float gv[kUpdRows][4];
-#pragma unroll
-        for (int k = 0; k < kUpdRows; ++k) {
-            const int rr = rb + k < nr ? rb + k : nr - 1;  // rows past the end repeat the last one, unused
-            const int64_t e = (r0 + rr) * cols + c0 + c;
-            if (vec) {
-                pv[k] = ld_f4<true>(gp<const float>(pp + e));
-                if constexpr (G == G_BF16) {
-                    const uint2 w = ld_u2<true>(g_as<const void>(to_g((const uint16_t*)d.g) + e));
-                    gv[k][0] = bf16_to_f32(w.x & 0xFFFFu);
-                    gv[k][1] = bf16_to_f32(w.x >> 16);
-                    gv[k][2] = bf16_to_f32(w.y & 0xFFFFu);
-                    gv[k][3] = bf16_to_f32(w.y >> 16);
-                } else {
-                    const float4 y = ld_f4<true>(to_g((const float*)d.g) + e);
-                    gv[k][0] = y.x;
-                    gv[k][1] = y.y;
-                    gv[k][2] = y.z;
-                    gv[k][3] = y.w;
-                }
-            } else {
-                float h[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    h[j] = c + j < nc ? pp[e + j] : 0.0f;
-                    gv[k][j] = c + j < nc ? (float)grad_d<G>(d.g, e + j) : 0.0f;
-                }
-                pv[k] = make_float4(h[0], h[1], h[2], h[3]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kUpdRows; ++k) {
-            if (rb + k >= nr) continue;
-            const int64_t e = (r0 + rb + k) * cols + c0 + c;
-            const double sr = right ? srow[rb + k] : 0.0;
-            const float pin[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
-            float out[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double upd = (double)gv[k][j] * (right ? sr : sc[j]);
-                out[j] = (float)((double)pin[j] * a.decay - a.lr * upd);
-            }
-            if (vec) {
-                st_f4<true>(pp + e, make_float4(out[0], out[1], out[2], out[3]));
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (c + j < nc) pp[e + j] = out[j];
-            }
-        }
-    }
+__global__ __launch_bounds__(256) void apollo_update_flat_kernel(const ApolloArgs a) {
+    const int64_t chunk = xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (chunk >= a.total_fch) return;
+    const ApolloDesc& d = a.D[locate(a.fch_begins, a.nt, chunk)];
+    const int64_t e0 = (chunk - d.fch_begin) * kApolloFlatChunk, left = d.rows * d.cols - e0;
+    if (left >= kApolloFlatChunk)
+        apollo_update_flat<G, true>(a, d, e0, kApolloFlatChunk);
+    else
+        apollo_update_flat<G, false>(a, d, e0, (int)left);
 }
 
 // Tensors of whole 256x256 units: one wavefront per chunk of 8 unit rows
 // (2048 elements, 4 per 256-thread workgroup) with no loop, lane 32 h + q on
 // rows 2k + h and columns 4q .. 4q + 3 and 128 + 4q .. 128 + 4q + 3, so every
 // access covers contiguous row segments; all loads of the chunk before its
-// stores. A chunk of another tensor returns (the unit kernel takes those).
+// stores.
 constexpr int kUpdChunkRows = 8;
 
 template <int G, bool RIGHT>
@@ -618,8 +608,7 @@ __global__ __launch_bounds__(256) void apollo_update_chunk_kernel(const ApolloAr
     const int64_t chunk = xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t unit = chunk / (256 / kUpdChunkRows);
     if (unit >= a.total_units) return;
-    const ApolloDesc& d = a.D[apollo_locate<&ApolloDesc::unit_begin>(a.D, a.nt, unit)];
-    if (!d.whole) return;
+    const ApolloDesc& d = a.D[locate(a.unit_begins, a.nt, unit)];
     const int64_t u = unit - d.unit_begin;
     const int64_t r0 = (u / d.ncu) * 256, c0 = (u % d.ncu) * 256;
     const int64_t row0 = r0 + (chunk % (256 / kUpdChunkRows)) * kUpdChunkRows + h;
@@ -630,8 +619,7 @@ __global__ __launch_bounds__(256) void apollo_update_chunk_kernel(const ApolloAr
 }
 
 hipError_t launch_apollo_update(const ApolloArgs& a, int grad_dtype, hipStream_t s) {
-    if (a.total_units == 0) return hipSuccess;
-    if (a.any_whole) {
+    if (a.total_units > 0) {
         const unsigned grid = (unsigned)((a.total_units * (256 / kUpdChunkRows) + 3) / 4);
         if (grad_dtype == G_BF16)
             hipLaunchKernelGGL(apollo_update_chunk_kernel<G_BF16>, dim3(grid), dim3(256), 0, s, a);
@@ -640,12 +628,12 @@ hipError_t launch_apollo_update(const ApolloArgs& a, int grad_dtype, hipStream_t
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (!a.any_ragged) return hipSuccess;
-    const unsigned grid = (unsigned)((a.total_units + 3) / 4);
+    if (a.total_fch == 0) return hipSuccess;
+    const unsigned grid = (unsigned)((a.total_fch + 3) / 4);
     if (grad_dtype == G_BF16)
-        hipLaunchKernelGGL(apollo_update_kernel<G_BF16>, dim3(grid), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(apollo_update_flat_kernel<G_BF16>, dim3(grid), dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL(apollo_update_kernel<G_F32>, dim3(grid), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(apollo_update_flat_kernel<G_F32>, dim3(grid), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -93,14 +93,6 @@ __device__ __forceinline__ float grad1(const void* g, int64_t e) {
         return reinterpret_cast<const float*>(g)[e];
 }
 
-template <int G>
-__device__ __forceinline__ float grad_at_g(gp<const void> g, int64_t e) {
-    if constexpr (G == G_BF16)
-        return bf16_to_f32(g_as<const uint16_t>(g)[e]);
-    else
-        return g_as<const float>(g)[e];
-}
-
 // Decode element i of a vector state (runtime codec / block).
 __device__ __forceinline__ float vec_decode(int codec, int B, const void* codes, const float* meta, int64_t i,
                                             const Exp2Coef& cf) {
@@ -1304,17 +1296,7 @@ hipError_t launch_fac_clip(const FacArgs& a, hipStream_t s) {
 // factors are gathered (they stay in cache). Measured on the width-500 list:
 // CAME's apply 151 -> 60 us (3.7 TB/s) against element-by-element accesses.
 constexpr int kChunksPerUnit = 32;
-
-template <int G>
-__device__ __forceinline__ void load_g4(gp<const void> g, int64_t e, float gv[4]) {
-    if constexpr (G == G_BF16) {
-        const uint2 w = ld_u2<true>(g_as<const void>(g_as<const uint16_t>(g) + e));
-        gv[0] = u2f(w.x << 16), gv[1] = u2f(w.x & 0xFFFF0000u), gv[2] = u2f(w.y << 16), gv[3] = u2f(w.y & 0xFFFF0000u);
-    } else {
-        const float4 w = ld_f4<true>(g_as<const float>(g) + e);
-        gv[0] = w.x, gv[1] = w.y, gv[2] = w.z, gv[3] = w.w;
-    }
-}
+constexpr int kFlatChunk = kFacFlatChunk;
 
 // A chunk of a matrix whose width is a multiple of 256 as rows and columns: 8 / W
 // rows from row0, 256 W columns from col0 (W units side by side; the unit columns
@@ -1343,64 +1325,6 @@ __device__ __forceinline__ RowChunk row_chunk(const GD& d, int64_t t_ch) {
     }
     return c;
 }
-
-// Rows and columns of a lane's 4 consecutive elements of the flattening, one
-// 256-element sub-tile after another. step256: the way from a lane's element to
-// the one 256 further on.
-constexpr int kFlatChunk = kFacFlatChunk;
-struct FlatPos {
-    int64_t rows, cols;
-    int i, j;        // of the lane's first element (wide = false)
-    int di, dj;      // 256 / cols, 256 % cols
-    bool wide;       // outside the 32-bit, at-most-one-wrap range: divide per element
-    __device__ FlatPos(int64_t rows_, int64_t cols_, int64_t e) : rows(rows_), cols(cols_) {
-        wide = cols < 4 || cols >= (int64_t(1) << 30) || rows >= (int64_t(1) << 30);
-        i = j = di = dj = 0;
-        if (wide) return;
-        // binary64 estimate of the quotient, then exact correction
-        int64_t q = (int64_t)((double)e / (double)cols), r = e - q * cols;
-        if (r < 0) {
-            --q;
-            r += cols;
-        } else if (r >= cols) {
-            ++q;
-            r -= cols;
-        }
-        i = (int)q;
-        j = (int)r;
-        di = 256 / (int)cols;
-        dj = 256 % (int)cols;
-    }
-    // factors of the lane's 4 elements (e: the first; elements past the matrix take those of the last row)
-    template <class F>
-    __device__ __forceinline__ void each(int64_t e, F f) const {
-        if (!wide) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                int jj = j + t, ii = i;
-                if (jj >= (int)cols) {
-                    jj -= (int)cols;
-                    ++ii;
-                }
-                f(t, (int64_t)(ii < (int)rows ? ii : (int)rows - 1), (int64_t)jj);
-            }
-        } else {
-#pragma unroll 1
-            for (int t = 0; t < 4; ++t) {
-                const int64_t ii = (e + t) / cols;
-                f(t, ii < rows ? ii : rows - 1, (e + t) % cols);
-            }
-        }
-    }
-    __device__ void next() {
-        i += di;
-        j += dj;
-        if (j >= (int)cols) {
-            j -= (int)cols;
-            ++i;
-        }
-    }
-};
 
 // Adafactor apply over a row chunk (lane l: columns 4l .. 4l + 3 of each
 // 256-column segment): every load of the chunk is issued before the
