@@ -795,6 +795,9 @@ struct FlatPos {
         di = 256 / (int)cols;
         dj = 256 % (int)cols;
     }
+    // The lane's 4 elements lie in one row (i, columns j .. j + 3), for every lane of the wavefront: most
+    // sub-tiles of a wide matrix. Its factors are then one value of the row and two 16-byte loads of the columns.
+    __device__ __forceinline__ bool straight() const { return __all(!wide & (j + 3 < (int)cols) & (i < (int)rows)); }
     // factors of the lane's 4 elements (e: the first; elements past the matrix take those of the last row)
     template <class F>
     __device__ __forceinline__ void each(int64_t e, F f) const {
@@ -815,6 +818,11 @@ struct FlatPos {
                 f(t, ii < rows ? ii : rows - 1, (e + t) % cols);
             }
         }
+    }
+    __device__ __forceinline__ void cols4(gp<const double> f, double out[4]) const {
+        typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+        const d2 x = *g_as<const d2>(f + j), y = *g_as<const d2>(f + j + 2);
+        out[0] = x.x, out[1] = x.y, out[2] = y.x, out[3] = y.y;
     }
     __device__ void next() {
         i += di;

@@ -510,11 +510,21 @@ __device__ __forceinline__ void apollo_update_flat(const ApolloArgs& a, const Ap
         const int64_t e = e0 + 256 * k + l4;
         const float pin[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
         float out[4];
-        pos.each(e, [&](int t, int64_t i, int64_t j) {
-            const double upd = (double)gv[k][t] * (sv[right ? i : j] * rlam);
-            out[t] = (float)((double)pin[t] * a.decay - a.lr * upd);
-        });
+        double sc[4];
+        if (pos.straight()) {
+            if (right)
+                sc[0] = sc[1] = sc[2] = sc[3] = sv[pos.i];
+            else
+                pos.cols4(sv, sc);
+        } else {
+            pos.each(e, [&](int t, int64_t i, int64_t j) { sc[t] = sv[right ? i : j]; });
+        }
         pos.next();
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const double upd = (double)gv[k][t] * (sc[t] * rlam);
+            out[t] = (float)((double)pin[t] * a.decay - a.lr * upd);
+        }
         if constexpr (FULL) {
             st_f4<true>(pp + e, make_float4(out[0], out[1], out[2], out[3]));
         } else {
