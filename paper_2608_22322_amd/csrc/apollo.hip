@@ -16,7 +16,7 @@
 //   scale   16 lanes per channel: s_c = ||Rt_c|| / (||R_c|| + 1e-8) (below rank
 //           256; at rank 256 a channel is one sub-tile of the AdamW step, which
 //           forms s_c itself and never writes Rt).
-//   norm    one wavefront per tensor: ||G~||^2 = sum_c s_c^2 ||G_c||^2 and the
+//   norm    one workgroup per tensor: ||G~||^2 = sum_c s_c^2 ||G_c||^2 and the
 //           norm-growth limiter.
 //   update  p = fl32(p (1 - lr wd) - lr g (s_c / lam)): one wavefront per
 //           8-row chunk of a 256x256 unit (per unit for tensors of other
@@ -388,32 +388,24 @@ __device__ __forceinline__ double row16_sum_d(double x) {
     return x;
 }
 
-// locate with a channel of its own per lane.
-__device__ __forceinline__ int lane_locate(const int64_t* b, int n, int64_t x) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (to_g(b)[mid] <= x)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
 __global__ __launch_bounds__(256) void apollo_scale_kernel(const ApolloArgs a) {
     const int lane = threadIdx.x & 63, sub = lane >> 4, l16 = lane & 15;
-    const int64_t ch0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kScaleCh;
+    const int64_t ch0 = ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kScaleCh;
     const int r = a.rank;
+    if (ch0 >= a.total_chans) return;
+    // the first channel's tensor by one scalar search, the lane's from there
+    int ti = locate(a.chan_begins, a.nt, ch0);
+    const gp<const int64_t> begins = to_g(a.chan_begins);
     for (int q = 0; q < kScaleCh; q += 4) {
         const int64_t ch = ch0 + q + sub;  // this lane's channel
         const bool live = ch < a.total_chans;
-        if (__builtin_amdgcn_readfirstlane(ch0 + q) >= a.total_chans) return;
+        if (ch0 + q >= a.total_chans) return;
         double st = 0.0, sr = 0.0;
         int64_t c = 0;
         const ApolloDesc* dp = nullptr;
         if (live) {
-            dp = &a.D[lane_locate(a.chan_begins, a.nt, ch)];
+            while (ti + 1 < a.nt && begins[ti + 1] <= ch) ++ti;
+            dp = &a.D[ti];
             c = ch - dp->chan_begin;
             const gp<const float> rt = to_g((const float*)dp->Rt) + c * r;
             const gp<const float> rr = to_g((const float*)dp->R) + c * r;
@@ -442,12 +434,19 @@ hipError_t launch_apollo_scale(const ApolloArgs& a, hipStream_t s) {
 }
 
 // --------------------------------------------------------- limiter per tensor
-__global__ __launch_bounds__(64) void apollo_norm_kernel(const ApolloArgs a) {
+__global__ __launch_bounds__(256) void apollo_norm_kernel(const ApolloArgs a) {
+    __shared__ double part[4];
     const ApolloDesc& d = a.D[blockIdx.x];
     const int lane = threadIdx.x;
+    const gp<const double> sg = to_g((const double*)d.sg);
+    const int64_t C = d.C;
     double acc = 0.0;
-    for (int64_t c = lane; c < d.C; c += 64) acc += d.sg[c];
+#pragma unroll 4
+    for (int64_t c = lane; c < C; c += 256) acc += sg[c];
     acc = wave_sum_d(acc);
+    if ((lane & 63) == 0) part[lane >> 6] = acc;
+    __syncthreads();
+    acc = (part[0] + part[1]) + (part[2] + part[3]);
     if (lane == 0) {
         const double n = sqrt(acc);
         double lam = 1.0;
@@ -466,7 +465,7 @@ __global__ __launch_bounds__(64) void apollo_norm_kernel(const ApolloArgs a) {
 
 hipError_t launch_apollo_norm(const ApolloArgs& a, hipStream_t s) {
     if (a.nt == 0) return hipSuccess;
-    hipLaunchKernelGGL(apollo_norm_kernel, dim3(a.nt), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(apollo_norm_kernel, dim3(a.nt), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -612,8 +611,10 @@ __device__ __forceinline__ void apollo_update_chunk(const ApolloArgs& a, const A
     }
 }
 
+// Two waves per SIMD, each with all of its chunk's loads in flight (the 1.1B list's step 9776 us at the four its
+// registers allow, 9751 at 2, no better at 3).
 template <int G>
-__global__ __launch_bounds__(256) void apollo_update_chunk_kernel(const ApolloArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void apollo_update_chunk_kernel(const ApolloArgs a) {
     const int lane = threadIdx.x & 63, h = lane >> 5, q = lane & 31;
     const int64_t chunk = xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t unit = chunk / (256 / kUpdChunkRows);
