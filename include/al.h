@@ -251,9 +251,10 @@ al_status al_adamw_workspace_bytes(const al_tensor* tensors, int32_t nt, const a
  * (+meta). Uses per tensor: param, grad, m, m_meta, v, v_meta; the other
  * slots must be NULL. ws: device workspace of at least
  * al_adamw_workspace_bytes, 256-byte aligned (AL_EWORKSPACE otherwise); the
- * call writes the descriptor table there on the stream (small copy kernels)
- * and runs the whole list in one launch of the step kernel (several for
- * lists beyond 2^32 chunks of 1024-2048 elements). ws is scratch: its
+ * call writes the descriptor table there on the stream (small copy kernels;
+ * the descriptors of up to 8 tensors travel in the step kernel's arguments
+ * instead) and runs the whole list in one launch of the step kernel (several
+ * for lists beyond 2^32 chunks of 512-2048 elements). ws is scratch: its
  * contents need not survive between calls, and calls that share it must be
  * ordered on one stream. */
 al_status al_adamw_step(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* cfg, int64_t step, void* ws,

@@ -83,15 +83,22 @@ constexpr bool kNtStore = AL_ADAMW_NT_STORE != 0;
 
 // Elements per chunk (one wavefront). Coded momentum and second moment: 1024, so
 // that the per-chunk work (block fits, tables) is shared by several blocks but the
-// loads of the chunk stay one phase; 2048 held more registers and streamed no
-// better (256M parameters, us per step at 2048 / 1024 / 512: bf16 gradients B_V 256
-// 714 / 713 / 756, fp32 gradients 781 / 756 / 783 and at B_V 1024 778 / 714 / -; 32M
-// bf16 B_V 512 98.6 / 90.3 / 93.6). An fp32 state streams 4 bytes a value and leaves
-// little per-chunk work: 512 (fp32 momentum, bf16, AL8 B_V 256: 944 / 931 / 874; both
-// fp32: - / 1220 / 1194). A block is never cut.
+// loads of the chunk stay one phase (256M parameters in one tensor, us per step at
+// 2048 / 1024 / 512: fp32 gradients B_V 256 781 / 756 / 783, B_V 1024 778 / 714 / -;
+// bf16 B_V 256 714 / 713 / 756, at 32M 102 / 97 / 103). An fp32 state streams 4 bytes
+// a value and leaves little per-chunk work: 512 (fp32 momentum, bf16, AL8 B_V 256:
+// 944 / 931 / 874; both fp32: - / 1220 / 1194). A block is never cut.
 __host__ __device__ constexpr int chunk_elems(int mc, int vc, int bv) {
     const int c = mc == FP32 || vc == FP32 ? 512 : 1024;
     return vc == FP32 || bv < c ? c : bv;
+}
+
+// Chunks of a long list (kAdamWLong): with bf16 gradients, UF8 momentum and AL8
+// blocks of 128-1024 the arithmetic nearly bounds the stream and sharing the
+// per-chunk work over 2048 elements wins in the end (7B list, ms per step at 2048 and
+// 1024: B_V 128 18.4 and 18.6, 256 17.5 and 17.9, 512 16.7 and 17.0, 1024 16.5 and 16.7).
+__host__ __device__ constexpr int long_chunk_elems(int g, int mc, int vc, int bv) {
+    return g == G_BF16 && mc == UF8 && vc == AL8 && bv >= 128 ? 2048 : chunk_elems(mc, vc, bv);
 }
 
 // Chunks of a short list (kAdamWSmall): a wavefront's chain of sub-tiles is what
@@ -758,8 +765,10 @@ void adamw_kernel(const AdamWLaunch a, const AdamWInline in) {
         adamw_compute<G, MC, VC, BV, CE, false, APO>(a, d, e0, valid, lane, lut, stab, skey, encp, encd, csum);
 }
 
-int adamw_tile_elems(int m_codec, int v_codec, int v_block, bool small) {
-    return small ? small_chunk_elems(v_codec, v_block) : chunk_elems(m_codec, v_codec, v_block);
+int adamw_tile_elems(int grad_dtype, int m_codec, int v_codec, int v_block, int64_t total) {
+    if (total < kAdamWSmall) return small_chunk_elems(v_codec, v_block);
+    if (total >= kAdamWLong) return long_chunk_elems(grad_dtype, m_codec, v_codec, v_block);
+    return chunk_elems(m_codec, v_codec, v_block);
 }
 
 
@@ -893,9 +902,11 @@ static hipError_t launch_c(const AdamWLaunch& a, const AdamWInline& in, hipStrea
 
 template <int G, int MC, int VC, int BV, bool APO>
 static hipError_t launch_t(const AdamWLaunch& a, const AdamWInline& in, hipStream_t s) {
-    constexpr int C = chunk_elems(MC, VC, BV), CS = small_chunk_elems(VC, BV);
+    constexpr int C = chunk_elems(MC, VC, BV), CS = small_chunk_elems(VC, BV), CL = long_chunk_elems(G, MC, VC, BV);
     if constexpr (CS != C && !APO)
         if (a.tile == CS) return launch_c<G, MC, VC, BV, CS, false>(a, in, s);
+    if constexpr (CL != C && !APO)
+        if (a.tile == CL) return launch_c<G, MC, VC, BV, CL, false>(a, in, s);
     return a.tile == C ? launch_c<G, MC, VC, BV, C, APO>(a, in, s) : hipErrorInvalidValue;
 }
 

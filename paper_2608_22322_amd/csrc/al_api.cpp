@@ -515,9 +515,9 @@ al_status adamw_check(const al_tensor* tensors, int32_t nt, const al_adamw_cfg* 
         if ((st = check_unused(t.cc, t.cc_meta, "cc", i)) != AL_OK) return st;
         if (n == 0) continue;
         ++*ndesc;
-        if (total < al::kAdamWSmall) total += n;
+        if (total < al::kAdamWLong) total += n;
     }
-    a.tile = al::adamw_tile_elems(cfg->m.codec, cfg->v.codec, cfg->v.block, total < al::kAdamWSmall);
+    a.tile = al::adamw_tile_elems(cfg->grad_dtype, cfg->m.codec, cfg->v.codec, cfg->v.block, total);
     for (int i = 0; i < nt; ++i) a.total_tiles += (tensors[i].rows * tensors[i].cols + a.tile - 1) / a.tile;
     const double bc1 = 1.0 - std::pow(cfg->beta1, (double)step);
     const double bc2 = 1.0 - std::pow(cfg->beta2, (double)step);
@@ -681,7 +681,8 @@ al_status al_apollo_step(const al_apollo_tensor* tensors, int32_t nt, const al_a
     w.decay = 1.0f;
     w.v_floor = cfg->v.log_floor;
     w.apollo = fused ? a.D : nullptr;  // descriptor i of the AdamW table is projected tensor i
-    w.tile = al::adamw_tile_elems(cfg->m.codec, cfg->v.codec, cfg->v.block, !fused && P.total_chans * cfg->rank < al::kAdamWSmall);
+    w.tile = al::adamw_tile_elems(AL_DTYPE_F32, cfg->m.codec, cfg->v.codec, cfg->v.block,
+                                  fused ? al::kAdamWLong : P.total_chans * cfg->rank);
     const int T = w.tile;
     al::AdamWInline win;
     std::memset(&win, 0, sizeof(win));

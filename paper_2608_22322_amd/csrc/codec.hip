@@ -178,12 +178,23 @@ __device__ __forceinline__ void dequantize_chunk(gp<const uint8_t> codes, gp<con
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int rel = k * kSub + 4 * lane;
-        // code arrays hold whole blocks: a sub-tile's words are there if its block has an element
-        const bool live = FULL || rel / B * B < valid;
-        if constexpr (C == AL16)
-            w[k] = live ? ld_u2<true>(g_as<const void>(codes + 2 * (e0 + rel))) : make_uint2(0u, 0u);
-        else
-            w[k] = live ? ld_u1<true>(g_as<const void>(codes + e0 + rel)) : 0u;
+        if constexpr (FULL) {
+            if constexpr (C == AL16)
+                w[k] = ld_u2<true>(g_as<const void>(codes + 2 * (e0 + rel)));
+            else
+                w[k] = ld_u1<true>(g_as<const void>(codes + e0 + rel));
+        } else {  // only the codes of the n elements are read
+            uint32_t q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                q[j] = 0u;
+                if (rel + j < valid) q[j] = C == AL16 ? g_as<const uint16_t>(codes)[e0 + rel + j] : codes[e0 + rel + j];
+            }
+            if constexpr (C == AL16)
+                w[k] = make_uint2(q[0] | (q[1] << 16), q[2] | (q[3] << 16));
+            else
+                w[k] = q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24);
+        }
     }
     // decode step and l_min of block `lane`
     const int64_t b0 = e0 / B;

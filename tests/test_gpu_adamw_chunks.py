@@ -1,5 +1,5 @@
-"""AdamW's chunk lengths and descriptor routes: a list under 3 * 2^20 elements is cut into short chunks, up to 8
-tensors travel in the kernel arguments. The same tensors stepped in a short list, in a long one (with a large tensor
+"""AdamW's chunk lengths and descriptor routes: a list under 3 * 2^20 elements is cut into short chunks, one of 2^28
+and more into long ones (bf16 gradients, AL8 blocks of 128-1024), up to 8 tensors travel in the kernel arguments. The same tensors stepped in a short list, in a long one (with a large tensor
 beside them) and in a list of more than 8 must give the same parameters, codes and metadata bit for bit (the short
 route is held to the oracle in test_gpu_adamw.py)."""
 import pytest
@@ -47,6 +47,8 @@ def test_chunk_lengths_and_descriptor_routes_agree(dev, grad_bf16, mc, vc, block
         return out
 
     lists = [states(SIZES), states(SIZES + [1 << 22]), states(SIZES + [300] * 5)]
+    if grad_bf16 and (mc, vc) == ("UF8", "AL8"):
+        lists.append(states(SIZES + [1 << 28]))
     for sts in lists:
         arr = al.tensor_array(sts)
         ws = al.workspace(al.adamw_workspace_bytes(sts, cfg, arr=arr))
