@@ -8,7 +8,8 @@
 // exact_zero) and the uniform signed momentum code of section 4.3.
 //
 // Work decomposition. A chunk is max(1024, B_V) consecutive elements of one
-// tensor (512 where a state is fp32, and for short lists), owned by one wavefront:
+// tensor (at least 512 where a state is fp32 and for short lists, 2048 for some long
+// ones: *chunk_elems below), owned by one wavefront:
 // 4 consecutive elements per lane in each of K = chunk/256 sub-tiles, so every
 // load and store is a coalesced 16/8/4-byte access and every block reduction
 // stays inside the wavefront (DPP, swizzle, readlane). The momentum block
@@ -22,7 +23,8 @@
 // broadcast back (readlane for blocks that span whole sub-tiles, ds_bpermute
 // for smaller ones). The grid holds one wave per chunk over the whole tensor
 // list, and the chunk -> tensor map is a binary search over the descriptor
-// table in device memory (one launch per step). Full chunks use non-temporal
+// table in device memory, or over the kernel's arguments for lists of up to 8
+// tensors (one launch per step). Full chunks use non-temporal
 // loads and stores: every byte of the step is touched exactly once.
 #include <mutex>
 

@@ -4,7 +4,7 @@
 //
 // Kernel sequence of one step (the fused AdamW step over the projected
 // moments runs between proj and scale, launched by the C ABI):
-//   proj    R = fl32(A Pi) for a tile of 32 channels and all r columns, in
+//   proj    R = fl32(A Pi) for a tile of 32 * 256 / r channels and all r columns, in
 //           binary64 on the matrix cores (v_mfma_f64_16x16x4f64): A (bf16 or
 //           fp32 gradient, as C x L) and Pi (fp32) are staged through LDS in
 //           slices of 16 inputs (Pi by LDS DMA) and widened to binary64 as the
@@ -19,8 +19,8 @@
 //   norm    one workgroup per tensor: ||G~||^2 = sum_c s_c^2 ||G_c||^2 and the
 //           norm-growth limiter.
 //   update  p = fl32(p (1 - lr wd) - lr g (s_c / lam)): one wavefront per
-//           8-row chunk of a 256x256 unit (per unit for tensors of other
-//           shapes).
+//           8-row chunk of a 256x256 unit (per flattened chunk of 1024
+//           elements for tensors of other shapes).
 // The projection is the one dense contraction of the path (2 r flops per
 // parameter); everything else streams.
 #include "al_device.hpp"

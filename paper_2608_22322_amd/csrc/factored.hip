@@ -3,16 +3,17 @@
 // momentum), section 3.1, with AL/UF8/FP32 codes per state role (section 4).
 //
 // Kernel sequence of one Adafactor step (2-D tensors):
-//   marg   row and column sums of G2 = g^2 + eps1, exact (double-double)
-//   fin    one wavefront per code block of R and C: EMA of the exact means,
-//          rounded to fp32, re-encoded; then per tensor mean(R) and the
-//          factors r_i = (R_i / mean R)^-1/2, c_j = C_j^-1/2
-//   rms    partial sums of u^2, u_ij = (r_i c_j) g_ij, per 256x256 unit
+//   marg   row and column partial sums of g^2 per unit, with a bounded error;
+//          its leading workgroups run the whole step of the 1-D tensors
+//   mean   per 64 elements of R or C: the unit partials merged, eps1 added to
+//          the mean, EMA rounded to fp32, sums for mean(R)
+//   enc    per code block of R and C: re-encoded, and the factors
+//          r_i = (R_i / mean R)^-1/2, c_j = C_j^-1/2
+//   rms    partial sums of u^2, u_ij = (r_i c_j) g_ij, per unit
 //   clip   per tensor: max(1, RMS(u) / d)
 //   apply  p <- p (1 - lr wd) - lr u / clip
-// 1-D tensors run their whole step in one workgroup (vec1d).
 // CAME adds: res (sums of (uhat - m)^2 + eps2 with the in-step momentum),
-// fin over the confidence, and apply (recompute uhat and m, encode m, update p).
+// mean and enc over the confidence, and apply (recompute uhat and m, encode m, update p).
 //
 // Marginal sums. The matrices are cut into units of a.ur rows x 256 columns
 // (ur = 256 for large lists, fewer rows for lists that would leave the chip
