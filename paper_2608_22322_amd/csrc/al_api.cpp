@@ -129,7 +129,7 @@ al_status check_ws(void* ws, size_t ws_bytes, size_t need, const char* who) {
 struct FacPlan {
     std::vector<al::FacRec> rec;  // 2-D tensors first, then 1-D
     int n2 = 0, n1 = 0;
-    int64_t total_units = 0, total_ach = 0, total_mt = 0, rows_ach = 0;
+    int64_t total_units = 0, total_ach = 0, total_mt = 0, whole_ach = 0, rows_ach = 0;
     int32_t ur = 256, any_whole = 0, any_edge = 0;
     int64_t total_blk[2] = {0, 0};
     size_t bytes = 0;
@@ -189,9 +189,12 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
             if ((st = check_unused(t.m, t.m_meta, "m", i)) != AL_OK) return st;
         }
     }
-    // widths that are a multiple of 256 first (the apply passes take them by rows), in list order within
-    // each group
-    std::stable_partition(twod.begin(), twod.end(), [&](int i) { return ts[i].cols % 256 == 0; });
+    // whole units first, then the other widths that are a multiple of 256 (the apply passes take both by rows;
+    // CAME's update of p is fp32 in the former, binary64 in the latter), in list order within each group
+    const auto by_rows = [](const al_tensor& t) { return t.cols % 256 == 0; };
+    const auto whole = [](const al_tensor& t) { return t.rows % 256 == 0 && t.cols % 256 == 0; };
+    const auto others = std::stable_partition(twod.begin(), twod.end(), [&](int i) { return whole(ts[i]); });
+    std::stable_partition(others, twod.end(), [&](int i) { return by_rows(ts[i]); });
     P.n2 = (int)twod.size();
     P.n1 = (int)oned.size();
     const int ntot = P.n2 + P.n1;
@@ -214,11 +217,11 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
         r[al::kRecUnit] = (uint64_t)P.total_units;
         P.total_units += nru * ncu;
         r[al::kRecAch] = (uint64_t)P.total_ach;
-        const bool by_rows = t.cols % 256 == 0;
-        P.total_ach += by_rows ? ((t.rows + 255) / 256) * ncu * 32 : (t.rows * t.cols + al::kFacFlatChunk - 1) / al::kFacFlatChunk;
-        if (by_rows) P.rows_ach = P.total_ach;
-        if (by_rows && P.ur == 256 && t.rows >= 256) P.any_whole = 1;
-        if (!by_rows || P.ur != 256 || t.rows % 256 != 0) P.any_edge = 1;
+        P.total_ach += by_rows(t) ? ((t.rows + 255) / 256) * ncu * 32 : (t.rows * t.cols + al::kFacFlatChunk - 1) / al::kFacFlatChunk;
+        if (by_rows(t)) P.rows_ach = P.total_ach;
+        if (whole(t)) P.whole_ach = P.total_ach;
+        if (by_rows(t) && P.ur == 256 && t.rows >= 256) P.any_whole = 1;
+        if (!whole(t) || P.ur != 256) P.any_edge = 1;
         r[al::kRecMt] = (uint64_t)P.total_mt;
         P.total_mt += (t.rows + 63) / 64 + (t.cols + 63) / 64;
         const int64_t bv = fac_block(vs), bc = came ? fac_block(cs) : bv;
@@ -276,6 +279,7 @@ al::FacArgs fac_args(const FacPlan& P, char* ws) {
     a.total_units = P.total_units;
     a.total_ach = P.total_ach;
     a.total_mt = P.total_mt;
+    a.whole_ach = P.whole_ach;
     a.rows_ach = P.rows_ach;
     a.any_whole = P.any_whole;
     a.any_edge = P.any_edge;

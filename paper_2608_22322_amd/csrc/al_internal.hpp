@@ -213,7 +213,9 @@ struct FacArgs {
     double* rmspart;      // [total_units] (hi, lo): partial sums of u^2
     int32_t n2, n1;       // 2-D tensors, 1-D tensors (D[n2 .. n2 + n1))
     int64_t total_units, total_ach, total_mt;
-    int64_t rows_ach;     // apply chunks [0, rows_ach): the tensors of widths that are a multiple of 256, listed first
+    // apply chunks [0, whole_ach): tensors of whole units, listed first; [whole_ach, rows_ach): the other widths that
+    // are a multiple of 256; the rest: flattened chunks
+    int64_t whole_ach, rows_ach;
     int32_t ur;           // unit rows: 256, or 128 / 64 / 32 for lists of few units
     int32_t any_whole, any_edge;  // some units are (are not) whole 256 x 256 units of a width that is a multiple of 256
     int64_t total_blk[2];  // code blocks over all 2-D tensors' R and C, per role

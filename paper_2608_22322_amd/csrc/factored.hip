@@ -1763,22 +1763,17 @@ hipError_t launch_came_res(const FacArgs& a, int grad_dtype, hipStream_t s) {
 }
 
 // ------------------------------------------------------ CAME apply (2-D)
-// Recompute uhat and m, encode m, and p <- p (1 - lr wd) - lr (s_i s_j) m, in
-// the Adafactor apply's chunks. The parameter update runs in fp32 (the states
-// never depend on p, which is held to a relative tolerance):
-// p' = fma(-lr, (s_i s_j) m, p (1 - lr wd)) on the fp32 roundings of the factors.
+// Recompute uhat and m, encode m, and p <- p (1 - lr wd) - lr (s_i s_j) m, in the Adafactor apply's chunks.
 //
 // One 256-element momentum block (4 consecutive elements per lane): new momentum
-// and parameters from the inputs and factors (rk = r_i / clip); mw: the lane's codes, ms the
-// block's absmax (UF8), else mv the fp32 momentum. Returns the new codes and
-// their absmax in mw / am, or the new momentum in mv.
-template <bool UF>
-__device__ __forceinline__ void came_apply_block(const FacArgs& a, const double ri[4], const double rk[4], const double cf[4],
-                                                 const float si[4], const float sf[4], double clip,
-                                                 const float gv[4], float4& pv, uint32_t& mw, float ms, float4& mv,
-                                                 const bool in[4], uint32_t& am) {
-    const float lrf = (float)a.lr, decayf = (float)a.decay;
-    float mh[4], uh[4], mnew[4], pout[4];
+// from the updates u(j) = (r_i c_j) g and their quotients qv = ((r_i / clip) c_j) g; mw: the lane's codes, ms the
+// block's absmax (UF8), else mv the fp32 momentum. Leaves the momentum in mnew, its codes and
+// their absmax in mw / am (UF8) or itself in mv.
+template <bool UF, class U>
+__device__ __forceinline__ void came_apply_block(const FacArgs& a, const double qv[4], U u, double clip,
+                                                 uint32_t& mw, float ms, float4& mv, const bool in[4], uint32_t& am,
+                                                 float mnew[4]) {
+    float mh[4], uh[4];
     if constexpr (UF) {
         const double st = div127((double)ms);
 #pragma unroll
@@ -1786,22 +1781,15 @@ __device__ __forceinline__ void came_apply_block(const FacArgs& a, const double 
     } else {
         mh[0] = mv.x, mh[1] = mv.y, mh[2] = mv.z, mh[3] = mv.w;
     }
-    double qv[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) qv[j] = (rk[j] * cf[j]) * (double)gv[j];
     if (__builtin_expect(!f32_roundings_decided<4>(qv, uh), 0)) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) uh[j] = (float)(((ri[j] * cf[j]) * (double)gv[j]) / clip);
+        for (int j = 0; j < 4; ++j) uh[j] = (float)(u(j) / clip);
     }
-    const float pin[4] = {pv.x, pv.y, pv.z, pv.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         mnew[j] = (float)(a.beta1 * (double)mh[j] + a.omb1 * (double)uh[j]);
         if (!in[j]) mnew[j] = 0.0f;
-        const float upd = (si[j] * sf[j]) * mnew[j];
-        pout[j] = __builtin_fmaf(-lrf, upd, pin[j] * decayf);
     }
-    pv = make_float4(pout[0], pout[1], pout[2], pout[3]);
     if constexpr (UF) {
         am = 0u;
 #pragma unroll
@@ -1818,11 +1806,14 @@ __device__ __forceinline__ void came_apply_block(const FacArgs& a, const double 
 }
 
 // kFlatChunk elements of the flattening from e0 (widths that are not a multiple
-// of 256), the first `valid` of them inside the matrix (FULL: all): a momentum
-// block is one 256-element sub-tile.
+// of 256), or kCameTail of the last chunk, the first `valid` of them inside the matrix (FULL: all): a momentum
+// block is one 256-element sub-tile. The parameter is formed in binary64 and rounded once (three matrices of
+// 20000 x 6000, bf16: 1596 us per step, 1580 with an fp32 update). The guarded tail sets the registers: in
+// pieces of 512 elements it needs 104 (4 waves per SIMD) in place of 131 to 134.
+constexpr int kCameTail = 512;
 template <int G, bool UF, bool FULL>
 __device__ __forceinline__ void came_apply_flat(const FacArgs& a, const GD& d, int64_t e0, int valid) {
-    constexpr int K = kFlatChunk / 256;
+    constexpr int K = (FULL ? kFlatChunk : kCameTail) / 256;
     const int lane = threadIdx.x & 63, l4 = 4 * lane;
     const gp<uint8_t> mc = g_as<uint8_t>(d.m);
     const gp<float> mf = g_as<float>(d.m);
@@ -1863,23 +1854,20 @@ __device__ __forceinline__ void came_apply_flat(const FacArgs& a, const GD& d, i
     for (int k = 0; k < K; ++k) {
         if (!FULL && 256 * k >= valid) break;
         const int64_t e = e0 + 256 * k + l4;
-        double ri[4], rk[4], cf[4];
-        float si[4], sf[4];
+        double rc[4], qv[4], ss[4];  // r_i c_j, ((r_i / clip) c_j) g, s_i s_j
         if (pos.straight()) {
-            const double r = d.rfac[pos.i], rc = r * rclip;
-            const float sri = (float)d.sr[pos.i];
-            double sc[4];
+            const double r = d.rfac[pos.i], rk = r * rclip, sri = d.sr[pos.i];
+            double cf[4], sf[4];
             pos.cols4(d.cfac, cf);
-            pos.cols4(d.sc, sc);
+            pos.cols4(d.sc, sf);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) ri[t] = r, rk[t] = rc, si[t] = sri, sf[t] = (float)sc[t];
+            for (int t = 0; t < 4; ++t) rc[t] = r * cf[t], qv[t] = rk * cf[t], ss[t] = sri * sf[t];
         } else {
             pos.each(e, [&](int t, int64_t i, int64_t j) {
-                ri[t] = d.rfac[i];
-                rk[t] = ri[t] * rclip;
-                cf[t] = d.cfac[j];
-                si[t] = (float)d.sr[i];
-                sf[t] = (float)d.sc[j];
+                const double r = d.rfac[i], c = d.cfac[j];
+                rc[t] = r * c;
+                qv[t] = (r * rclip) * c;
+                ss[t] = d.sr[i] * d.sc[j];
             });
         }
         pos.next();
@@ -1887,17 +1875,26 @@ __device__ __forceinline__ void came_apply_flat(const FacArgs& a, const GD& d, i
 #pragma unroll
         for (int t = 0; t < 4; ++t) in[t] = FULL || 256 * k + l4 + t < valid;
         uint32_t am = 0u;
-        came_apply_block<UF>(a, ri, rk, cf, si, sf, clip, gv[k], pv[k], mw[k], ms[k], mv[k], in, am);
+        float mnew[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) qv[t] *= (double)gv[k][t];
+        came_apply_block<UF>(a, qv, [&](int t) { return rc[t] * (double)gv[k][t]; }, clip, mw[k], ms[k], mv[k], in, am, mnew);
+        const float pin[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w};
+        float po[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const double upd = ss[t] * (double)mnew[t];
+            po[t] = (float)((double)pin[t] * a.decay - a.lr * upd);
+        }
         if constexpr (FULL) {
-            st_f4<true>(d.p + e, pv[k]);
+            st_f4<true>(d.p + e, make_float4(po[0], po[1], po[2], po[3]));
             if constexpr (!UF) st_f4<true>(mf + e, mv[k]);
         } else {
-            const float po[4] = {pv[k].x, pv[k].y, pv[k].z, pv[k].w}, mo[4] = {mv[k].x, mv[k].y, mv[k].z, mv[k].w};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
                 if (in[t]) {
                     d.p[e + t] = po[t];
-                    if constexpr (!UF) mf[e + t] = mo[t];
+                    if constexpr (!UF) mf[e + t] = mnew[t];
                 }
         }
         if constexpr (UF) {
@@ -1911,32 +1908,37 @@ __device__ __forceinline__ void came_apply_flat(const FacArgs& a, const GD& d, i
 // 256 W columns (lane l: columns 4l .. 4l + 3 of each 256-column segment), one
 // row at a time: each row is one contiguous segment of 256 W elements, and each
 // 256-column segment of a row is one momentum block over all 64 lanes.
+// WHOLE (rows a multiple of 256 too): the parameter update runs in fp32 (the states never depend on p, which is
+// held to a relative tolerance), p' = fma(-lr, (s_i s_j) m, p (1 - lr wd)) on the fp32 roundings of the factors.
+// Otherwise in binary64, rounded once, for the chunk's first nrow rows.
 // W = 2 (2 KB parameter segments, 88 registers) measured 1.8% faster than
 // 8 rows x 256 columns in two 32-lane halves; W = 1 and 4 no faster, W = 8
 // (232 registers) 21% slower.
 constexpr int kCameApplyW = 2;
-template <int G, bool UF, int W>
+template <int G, bool UF, int W, bool WHOLE>
 __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, int64_t row0, int64_t col0, int nrow) {
+    using F = typename std::conditional<WHOLE, float, double>::type;
     const int lane = threadIdx.x & 63;
     const int64_t cb = col0 + 4 * lane;
     const int64_t cols = d.cols;
     const double clip = d.scal[0], rclip = 1.0 / clip;
+    const float lrf = (float)a.lr, decayf = (float)a.decay;
     const gp<uint8_t> mc = g_as<uint8_t>(d.m);
     const gp<float> mf = g_as<float>(d.m);
     double cf[W][4];
-    float sf[W][4];
+    F sf[W][4];
 #pragma unroll
     for (int sg = 0; sg < W; ++sg)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             cf[sg][j] = d.cfac[cb + 256 * sg + j];
-            sf[sg][j] = (float)d.sc[cb + 256 * sg + j];
+            sf[sg][j] = (F)d.sc[cb + 256 * sg + j];
         }
 #pragma unroll 1
     for (int k = 0; k < nrow; ++k) {
         const int64_t row = row0 + k;
         const double ri = d.rfac[row], rk = ri * rclip;
-        const float si = (float)d.sr[row];
+        const F si = (F)d.sr[row];
         float gv[W][4], ms[W];
         float4 pv[W], mv[W];
         uint32_t mw[W];
@@ -1957,12 +1959,24 @@ __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, i
 #pragma unroll
         for (int sg = 0; sg < W; ++sg) {
             const int64_t e = row * cols + cb + 256 * sg;
-            const double r4[4] = {ri, ri, ri, ri}, k4[4] = {rk, rk, rk, rk};
-            const float s4[4] = {si, si, si, si};
+            double qv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) qv[j] = (rk * cf[sg][j]) * (double)gv[sg][j];
             const bool in[4] = {true, true, true, true};
             uint32_t am = 0u;
-            came_apply_block<UF>(a, r4, k4, cf[sg], s4, sf[sg], clip, gv[sg], pv[sg], mw[sg], ms[sg], mv[sg], in, am);
-            st_f4<true>(d.p + e, pv[sg]);
+            float mnew[4], pout[4];
+            came_apply_block<UF>(a, qv, [&](int j) { return (ri * cf[sg][j]) * (double)gv[sg][j]; }, clip, mw[sg], ms[sg], mv[sg],
+                                 in, am, mnew);
+            const float pin[4] = {pv[sg].x, pv[sg].y, pv[sg].z, pv[sg].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const F upd = (si * sf[sg][j]) * (F)mnew[j];
+                if constexpr (WHOLE)
+                    pout[j] = __builtin_fmaf(-lrf, upd, pin[j] * decayf);
+                else
+                    pout[j] = (float)((double)pin[j] * a.decay - a.lr * upd);
+            }
+            st_f4<true>(d.p + e, make_float4(pout[0], pout[1], pout[2], pout[3]));
             if constexpr (UF) {
                 st_u1<true>(g_as<void>(mc + e), mw[sg]);
                 if (lane == 0) d.mm[e >> 8] = u2f(am);
@@ -1973,18 +1987,18 @@ __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, i
     }
 }
 
-template <int G, bool UF>
+template <int G, bool UF, bool WHOLE>
 __global__ __launch_bounds__(256) void came_apply_kernel(const FacArgs a, int64_t base) {
     const int64_t chunk = chunk_of_wave(base);
-    if (chunk >= a.rows_ach) return;
+    if (chunk >= (WHOLE ? a.whole_ach : a.rows_ach)) return;
     const GD d = gview(a.D[locate(a.ach_begins, a.n2, chunk)]);
     const RowChunk c = row_chunk<kCameApplyW>(d, chunk - d.ach_begin);
     const int64_t left = d.rows - c.row0;
     if (left <= 0) return;
     if (c.full)
-        came_apply_rows<G, UF, kCameApplyW>(a, d, c.row0, c.col0, left < 8 / kCameApplyW ? (int)left : 8 / kCameApplyW);
+        came_apply_rows<G, UF, kCameApplyW, WHOLE>(a, d, c.row0, c.col0, left < 8 / kCameApplyW ? (int)left : 8 / kCameApplyW);
     else
-        came_apply_rows<G, UF, 1>(a, d, c.row0, c.col0, left < 8 ? (int)left : 8);
+        came_apply_rows<G, UF, 1, WHOLE>(a, d, c.row0, c.col0, left < 8 ? (int)left : 8);
 }
 
 template <int G, bool UF>
@@ -1996,12 +2010,13 @@ __global__ __launch_bounds__(256) void came_apply_flat_kernel(const FacArgs a, i
     if (left >= kFlatChunk)
         came_apply_flat<G, UF, true>(a, d, e0, kFlatChunk);
     else
-        came_apply_flat<G, UF, false>(a, d, e0, (int)left);
+        for (int o = 0; o < left; o += kCameTail) came_apply_flat<G, UF, false>(a, d, e0 + o, (int)left - o);
 }
 
 template <int G, bool UF>
 static hipError_t came_apply_launch(const FacArgs& a, hipStream_t s) {
-    const hipError_t e = launch_per_chunk(came_apply_kernel<G, UF>, a, 0, a.rows_ach, s);
+    hipError_t e = launch_per_chunk(came_apply_kernel<G, UF, true>, a, 0, a.whole_ach, s);
+    if (e == hipSuccess) e = launch_per_chunk(came_apply_kernel<G, UF, false>, a, a.whole_ach, a.rows_ach, s);
     return e != hipSuccess ? e : launch_per_chunk(came_apply_flat_kernel<G, UF>, a, a.rows_ach, a.total_ach, s);
 }
 
