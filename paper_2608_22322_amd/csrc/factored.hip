@@ -1909,7 +1909,8 @@ __device__ __forceinline__ void came_apply_flat(const FacArgs& a, const GD& d, i
 // row at a time: each row is one contiguous segment of 256 W elements, and each
 // 256-column segment of a row is one momentum block over all 64 lanes.
 // WHOLE (rows a multiple of 256 too): the parameter update runs in fp32 (the states never depend on p, which is
-// held to a relative tolerance), p' = fma(-lr, (s_i s_j) m, p (1 - lr wd)) on the fp32 roundings of the factors.
+// held to a relative tolerance), p' = p - fma(lr wd, p, ((lr s_i) s_j) m) on the fp32 roundings of the factors: the
+// change carries a few fp32 roundings, p' one (1 - lr wd itself has no fp32 form near 1: steps of 2^-24).
 // Otherwise in binary64, rounded once, for the chunk's first nrow rows.
 // W = 2 (2 KB parameter segments, 88 registers) measured 1.8% faster than
 // 8 rows x 256 columns in two 32-lane halves; W = 1 and 4 no faster, W = 8
@@ -1922,7 +1923,7 @@ __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, i
     const int64_t cb = col0 + 4 * lane;
     const int64_t cols = d.cols;
     const double clip = d.scal[0], rclip = 1.0 / clip;
-    const float lrf = (float)a.lr, decayf = (float)a.decay;
+    const float lrwd = (float)(1.0 - a.decay);
     const gp<uint8_t> mc = g_as<uint8_t>(d.m);
     const gp<float> mf = g_as<float>(d.m);
     double cf[W][4];
@@ -1938,7 +1939,7 @@ __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, i
     for (int k = 0; k < nrow; ++k) {
         const int64_t row = row0 + k;
         const double ri = d.rfac[row], rk = ri * rclip;
-        const F si = (F)d.sr[row];
+        const F si = WHOLE ? (F)(a.lr * d.sr[row]) : (F)d.sr[row];
         float gv[W][4], ms[W];
         float4 pv[W], mv[W];
         uint32_t mw[W];
@@ -1972,7 +1973,7 @@ __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, i
             for (int j = 0; j < 4; ++j) {
                 const F upd = (si * sf[sg][j]) * (F)mnew[j];
                 if constexpr (WHOLE)
-                    pout[j] = __builtin_fmaf(-lrf, upd, pin[j] * decayf);
+                    pout[j] = pin[j] - __builtin_fmaf(lrwd, pin[j], upd);
                 else
                     pout[j] = (float)((double)pin[j] * a.decay - a.lr * upd);
             }
