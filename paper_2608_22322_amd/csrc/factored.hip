@@ -1118,8 +1118,8 @@ hipError_t launch_fac_fin(const FacArgs& a, int role, int grad_dtype, hipStream_
 // u_ij = (r_i c_j) g_ij, exactly the oracle's operation order. One wave per unit.
 //
 // Edge units (see edge_unit_sums): left-out elements have g = 0 (and row
-// factor 0 past the last row). The 8 terms u^2 of a lane's row are added
-// pairwise, those sums double-double, as in the whole units.
+// factor 0 past the last row). Every term u^2 is added double-double, so a unit's
+// partial is its exact sum to about 2^-100.
 template <int G>
 struct EdgeRmsBatch {
     Raw8<G> r[kEdgeNR / 2];
@@ -1152,13 +1152,11 @@ __device__ __forceinline__ DD edge_unit_rms(const GD& d, const EdgeLane& w) {
                 const double ri = ok ? b.ri[k] : 0.0;
                 float gv[8];
                 unpack8<G>(b.r[k], gv);
-                double t[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const double uu = (ri * cf[j]) * (double)(((j >= sh) & ok) ? gv[j] : 0.0f);
-                    t[j] = uu * uu;
+                    dd_add(acc, uu * uu);
                 }
-                dd_add(acc, sum8(t));
             }
         });
     return acc;
@@ -1178,7 +1176,8 @@ __device__ __forceinline__ DD narrow_unit_rms(const GD& d, int ur, int64_t ru) {
 
 // Whole units (the marginal kernels' streaming layout): lane 32 h + q holds
 // columns 8q .. 8q + 7 of rows 2k + h of each 8-row batch, 16-byte gradient
-// loads, the next batch loaded before the current one's arithmetic. The 8
+// loads, the next batch loaded before the current one's arithmetic. TERMS (units
+// of a matrix with ragged rows): summed term by term like the edge units. Otherwise the 8
 // terms u^2 of a lane's row are added pairwise (relative error <= 3u) and
 // those sums accumulated double-double, so a unit's partial is within 3u of
 // its exact sum. The clip divisor then
@@ -1186,7 +1185,7 @@ __device__ __forceinline__ DD narrow_unit_rms(const GD& d, int ur, int64_t ru) {
 // (inside the parameter tolerance), and for CAME it can move fl32(u / clip)
 // by one fp32 ulp only where u / clip lies within that distance of an fp32
 // rounding midpoint, about one element in 10^8.
-template <int G>
+template <int G, bool TERMS>
 __device__ __forceinline__ DD whole_unit_rms(const GD& d, int64_t ru, int64_t cu) {
     const WholeLane w = whole_lane(d, ru, cu);
     const gp<const void> gu = unit_base<G>(d, w);
@@ -1196,16 +1195,17 @@ __device__ __forceinline__ DD whole_unit_rms(const GD& d, int64_t ru, int64_t cu
 #pragma unroll
     for (int j = 0; j < 8; ++j) cf[j] = d.cfac[w.c0 + 8 * w.q + j];
     const gp<const double> rf = d.rfac + w.r0 + w.h;  // row factor of row 2k + h of a batch: rf[rb + 2k]
-    constexpr int NR = 8;
+    constexpr int NR = TERMS ? 4 : 8;  // the term-by-term sum needs more registers
+    constexpr int NP = NR / 2;
     DD acc{0.0, 0.0};
     WBatch<G, NR> A, B;
-    double ra[4], rb_[4];
+    double ra[NP], rb_[NP];
     load_wbatch<G, NR>(A, gu, 0, cols, lo);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) ra[k] = rf[2 * k];
-    auto step = [&](const WBatch<G, NR>& cur, const double ri[4]) {
+    for (int k = 0; k < NP; ++k) ra[k] = rf[2 * k];
+    auto step = [&](const WBatch<G, NR>& cur, const double ri[NP]) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NP; ++k) {
             float gv[8];
             unpack8<G>(cur.r[k], gv);
             double t[8];
@@ -1213,15 +1213,16 @@ __device__ __forceinline__ DD whole_unit_rms(const GD& d, int64_t ru, int64_t cu
             for (int j = 0; j < 8; ++j) {
                 const double uu = (ri[k] * cf[j]) * (double)gv[j];
                 t[j] = uu * uu;
+                if constexpr (TERMS) dd_add(acc, t[j]);
             }
-            dd_add(acc, sum8(t));
+            if constexpr (!TERMS) dd_add(acc, sum8(t));
         }
     };
     constexpr int NB = 256 / NR;
-    auto load = [&](WBatch<G, NR>& b, double ri[4], int bi) {
+    auto load = [&](WBatch<G, NR>& b, double ri[NP], int bi) {
         load_wbatch<G, NR>(b, gu, bi * NR, cols, lo);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) ri[k] = rf[bi * NR + 2 * k];
+        for (int k = 0; k < NP; ++k) ri[k] = rf[bi * NR + 2 * k];
     };
     // last pair of batches peeled (see whole_unit_sums)
 #pragma unroll 1
@@ -1237,19 +1238,25 @@ __device__ __forceinline__ DD whole_unit_rms(const GD& d, int64_t ru, int64_t cu
     return acc;
 }
 
-template <int G>
+// WHOLE: a list of whole units alone, without the term-by-term bodies, whose registers cost a wavefront per SIMD
+// (the 1.1B list's step 2617 us with the kernel below, 2627 with the other).
+template <int G, bool WHOLE>
 __global__ __launch_bounds__(256) void fac_rms_kernel(const FacArgs a, int64_t base) {
     const int64_t unit = unit_of_wave(base);
     if (unit >= a.total_units) return;
     const GD d = gview(a.D[locate(a.unit_begins, a.n2, unit)]);
     const int64_t u = unit - d.unit_begin, ru = u / d.ncu, cu = u % d.ncu;
     DD acc;
-    if (whole_unit(a, d, ru))
-        acc = whole_unit_rms<G>(d, ru, cu);
-    else if (d.cols >= 8)
-        acc = edge_unit_rms<G>(d, edge_lane(d, a.ur, ru, cu));
-    else
-        acc = narrow_unit_rms<G>(d, a.ur, ru);
+    if constexpr (WHOLE) {
+        acc = whole_unit_rms<G, false>(d, ru, cu);
+    } else {
+        if (whole_unit(a, d, ru))
+            acc = (d.rows & 255) == 0 ? whole_unit_rms<G, false>(d, ru, cu) : whole_unit_rms<G, true>(d, ru, cu);
+        else if (d.cols >= 8)
+            acc = edge_unit_rms<G>(d, edge_lane(d, a.ur, ru, cu));
+        else
+            acc = narrow_unit_rms<G>(d, a.ur, ru);
+    }
     acc = dd_wave_sum(acc);
     if ((threadIdx.x & 63) == 0) {
         a.rmspart[2 * unit] = acc.hi;
@@ -1258,8 +1265,12 @@ __global__ __launch_bounds__(256) void fac_rms_kernel(const FacArgs a, int64_t b
 }
 
 hipError_t launch_fac_rms(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    if (grad_dtype == G_BF16) return launch_wave_per_unit(fac_rms_kernel<G_BF16>, a, s);
-    return launch_wave_per_unit(fac_rms_kernel<G_F32>, a, s);
+    const bool bf = grad_dtype == G_BF16;
+    if (!a.any_edge)
+        return bf ? launch_wave_per_unit(fac_rms_kernel<G_BF16, true>, a, s)
+                  : launch_wave_per_unit(fac_rms_kernel<G_F32, true>, a, s);
+    return bf ? launch_wave_per_unit(fac_rms_kernel<G_BF16, false>, a, s)
+              : launch_wave_per_unit(fac_rms_kernel<G_F32, false>, a, s);
 }
 
 // ------------------------------------------ clip divisor (workgroup / tensor)
