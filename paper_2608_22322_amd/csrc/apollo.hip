@@ -500,7 +500,7 @@ __device__ __forceinline__ void apollo_update_flat(const ApolloArgs& a, const Ap
             pv[k] = make_float4(h[0], h[1], h[2], h[3]);
         }
     }
-    const double rlam = 1.0 / d.lam[0];
+    const double lam = d.lam[0];
     const gp<const double> sv = to_g((const double*)d.s);
     const bool right = d.right != 0;
     FlatPos pos(d.rows, d.cols, e0 + l4);
@@ -511,17 +511,20 @@ __device__ __forceinline__ void apollo_update_flat(const ApolloArgs& a, const Ap
         float out[4];
         double sc[4];
         if (pos.straight()) {
-            if (right)
-                sc[0] = sc[1] = sc[2] = sc[3] = sv[pos.i];
-            else
+            if (right) {
+                sc[0] = sc[1] = sc[2] = sc[3] = sv[pos.i] / lam;
+            } else {
                 pos.cols4(sv, sc);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) sc[t] /= lam;
+            }
         } else {
-            pos.each(e, [&](int t, int64_t i, int64_t j) { sc[t] = sv[right ? i : j]; });
+            pos.each(e, [&](int t, int64_t i, int64_t j) { sc[t] = sv[right ? i : j] / lam; });
         }
         pos.next();
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const double upd = (double)gv[k][t] * (sc[t] * rlam);
+            const double upd = (double)gv[k][t] * sc[t];
             out[t] = (float)((double)pin[t] * a.decay - a.lr * upd);
         }
         if constexpr (FULL) {
