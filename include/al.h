@@ -276,7 +276,9 @@ al_status al_adamw_step_noalloc(const al_tensor* tensors, int32_t nt, const al_a
                                 void* stream);
 
 /* Workspace size (bytes) that al_adafactor_step / al_came_step need for this
- * tensor list and config. */
+ * tensor list and config. A part of a list (frozen tensors left out, one
+ * parameter group) never needs more than the list, so one workspace sized for
+ * the whole list serves every part of it. */
 al_status al_adafactor_workspace_bytes(const al_tensor* tensors, int32_t nt,
                                        const al_adafactor_cfg* cfg, size_t* bytes);
 al_status al_came_workspace_bytes(const al_tensor* tensors, int32_t nt, const al_came_cfg* cfg,

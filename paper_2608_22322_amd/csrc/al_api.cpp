@@ -142,10 +142,33 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // 32): 162 us with 1024 to 8192, 182 with 512; on Adafactor over a 12-layer width-768 list (2900 units of 256
 // rows): 501 us up to 2048, 521 with 4096 (units of 128 rows).
 constexpr int64_t kFacMinUnits = 2048;
+// A list cut into units of fewer than 256 rows has fewer than kFacMinUnits of twice the height, so at most this many
+// units, and fewer than kFacMinUnits tensors: its column partials (2048 bytes a unit, each tensor's region aligned)
+// are bounded.
+constexpr int64_t kFacMaxShortUnits = 2 * kFacMinUnits;
+constexpr size_t kFacMaxShortCols = (size_t)kFacMaxShortUnits * 2048 + (size_t)kFacMinUnits * 256;
 
 // Block of a factor vector's state (FP32 states have none: 256 elements per wavefront).
 int32_t fac_block(const al_state_spec& s) { return s.codec == AL_CODEC_FP32 ? 256 : s.block; }
 
+// What the query asks for beyond the regions that the passes use at this list's unit height, so that a list's need
+// is never below that of a part of it (a shorter list may be cut into more units): each term grows with the
+// list, and bounds what the passes use at any height. units: RMS partials; partials: column and row partials,
+// 16 bytes each at 256 rows, or what the list's or any part's shorter units can take.
+struct FacReserve {
+    int64_t u256 = 0, u32 = 0;
+    size_t at256 = 0, rows8 = 0, cols32 = 0;
+    void add(int64_t rows, int64_t cols) {
+        const int64_t ncu = (cols + 255) / 256, n256 = (rows + 255) / 256, n32 = (rows + 31) / 32;
+        u256 += n256 * ncu;
+        u32 += n32 * ncu;
+        at256 += align256((size_t)(n256 * cols) * 16) + align256((size_t)(ncu * rows) * 16);
+        rows8 += align256((size_t)(ncu * rows) * 8);
+        cols32 += align256((size_t)(n32 * cols) * 8);
+    }
+    size_t units() const { return align256((size_t)std::max(u256, std::min(u32, kFacMaxShortUnits)) * 16); }
+    size_t partials() const { return std::max(at256, rows8 + std::min(cols32, kFacMaxShortCols)); }
+};
 
 // Validate the tensor list and lay out the workspace: descriptor table, RMS
 // partials, then per-tensor regions (offsets from its start).
@@ -232,6 +255,13 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
     }
     P.rms_off = off;
     off += align256((size_t)P.total_units * 16);
+    FacReserve reserve;
+    size_t used = off - P.rms_off;  // RMS, column and row partials at this unit height
+    for (int i : twod) {
+        const al_tensor& t = ts[i];
+        reserve.add(t.rows, t.cols);
+        used += align256((size_t)((t.rows + P.ur - 1) / P.ur * t.cols) * 8) + align256((size_t)((t.cols + 255) / 256 * t.rows) * 8);
+    }
     const auto word = [](const void* p) { return (uint64_t)reinterpret_cast<uintptr_t>(p); };
     for (int k = 0; k < ntot; ++k) {
         const bool fac = k < P.n2;
@@ -258,7 +288,7 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
         d.cols = t.cols;
         off = al::fac_regions(d, nullptr, off, came, P.ur);
     }
-    P.bytes = off;
+    P.bytes = off - used + reserve.units() + reserve.partials();
     return AL_OK;
 }
 

@@ -182,9 +182,8 @@ __host__ __device__ inline size_t fac_regions(FacDesc& d, char* ws, size_t off, 
     if (d.rows > 1) {
         d.nru = (int32_t)((d.rows + ur - 1) / ur);
         d.ncu = (int32_t)((d.cols + 255) / 256);
-        // 16 bytes per partial as callers have sized it; the passes use one binary64 of them, packed
-        d.colpart = reinterpret_cast<double*>(take((size_t)d.nru * d.cols * 16));
-        d.rowpart = reinterpret_cast<double*>(take((size_t)d.ncu * d.rows * 16));
+        d.colpart = reinterpret_cast<double*>(take((size_t)d.nru * d.cols * 8));
+        d.rowpart = reinterpret_cast<double*>(take((size_t)d.ncu * d.rows * 8));
         d.rfac = reinterpret_cast<double*>(take((size_t)d.rows * 8));
         d.cfac = reinterpret_cast<double*>(take((size_t)d.cols * 8));
         if (came) {

@@ -295,6 +295,33 @@ def test_factored_validation_workspace(came):
     assert _status(lambda: al.check(fn(arr, 0, ctypes.byref(cfg), None))) == 1
 
 
+@pytest.mark.parametrize("came", [False, True])
+def test_factored_workspace_of_a_part_of_a_list(came):
+    """A workspace sized for a list is accepted for every part of it, whatever unit height the part is cut to."""
+    import random
+
+    rng = random.Random(5)
+    mlp = [(2048, 2048), (256, 2048), (256, 2048), (2048, 2048), (5632, 2048), (5632, 2048), (2048, 5632), (1, 2048)]
+    lists = [mlp * 4, [(16384, 8192)] * 2, [(16384, 4096)] * 5, [(4096, 4096)] * 8, [(1, 4096)] * 3]
+    for _ in range(60):
+        k = rng.choice([1, 3, 10, 60])
+        dim = lambda: rng.choice([rng.randint(1, 40), rng.randint(1, 3000), 256 * rng.randint(1, 64)])
+        lists.append([(dim(), dim()) for _ in range(k)])
+    for shapes in lists:
+        ts = [_ft(rows=r, cols=c, came=came) for r, c in shapes]
+        need = _fac_ws(ts, came)
+        for _ in range(8):
+            part = rng.sample(ts, rng.randint(1, len(ts)))
+            assert _fac_ws(part, came) <= need, (shapes, [(t.rows, t.cols) for t in part])
+    # a matrix just short of the height's limit; n / 8 of partials, at most 24 bytes per row and column of factors
+    # and staging, 16 per unit and the tables
+    full, less = [_ft(rows=16384, cols=8192, came=came)], [_ft(rows=16128, cols=8192, came=came)]
+    assert _fac_ws(less, came) <= _fac_ws(full, came) <= 16384 * 8192 / 8 + 24 * (16384 + 8192) + 16 * 2048 + 4096
+    # the reserve for shorter units is bounded: 8.9 MB of column partials
+    small = _fac_ws([_ft(rows=4096, cols=4096, came=came)], came)
+    assert small <= 4096 * 4096 / 32 + 8.92e6 + 24 * 8192 + 16 * 4096 + 4096
+
+
 def test_adafactor_cfg_validation():
     t = [_ft()]
     bad = [dict(lr=-1.0), dict(eps1=math.nan), dict(clip_threshold=0.0), dict(decay_rate=0.5),
