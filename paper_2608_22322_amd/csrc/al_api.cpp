@@ -348,10 +348,13 @@ struct ApolloPlan {
     std::vector<al::ApolloDesc> desc;
     std::vector<int> idx;  // tensor index of each descriptor (empty tensors are skipped)
     int64_t total_tiles = 0, total_chans = 0, total_units = 0, total_fch = 0;
+    int32_t tile_ch = 32;  // channels per projection tile
     size_t index_off = 0;
     size_t adamw_off = 0;  // descriptor table of the AdamW launch over the projected moments
     size_t bytes = 0;
 };
+
+constexpr int64_t kApolloNarrowTiles = 256 * 128;
 
 // Validate the list and lay out the workspace: descriptor table, then per
 // tensor R, Rt (C x rank fp32; no Rt at rank 256, where the AdamW step on R
@@ -394,10 +397,7 @@ al_status apollo_plan(const al_apollo_tensor* ts, int nt, const al_apollo_cfg* c
         d.C = C;
         d.L = d.right ? t.cols : t.rows;
         const bool whole = t.rows % 256 == 0 && t.cols % 256 == 0;
-        const int64_t tch = al::apollo_tile_ch(cfg->rank);
         d.ncu = (int32_t)((t.cols + 255) / 256);
-        d.tile_begin = P.total_tiles;
-        P.total_tiles += (C + tch - 1) / tch;
         d.chan_begin = P.total_chans;
         P.total_chans += C;
         d.unit_begin = P.total_units;
@@ -406,6 +406,17 @@ al_status apollo_plan(const al_apollo_tensor* ts, int nt, const al_apollo_cfg* c
         if (!whole) P.total_fch += (t.rows * t.cols + al::kApolloFlatChunk - 1) / al::kApolloFlatChunk;
         P.desc.push_back(d);
         P.idx.push_back(i);
+    }
+    const auto tiles = [&](int ch) {
+        int64_t n = 0;
+        for (const al::ApolloDesc& d : P.desc) n += (d.C + ch - 1) / ch;
+        return n;
+    };
+    // 32 channels up to two of those tiles per CU at rank 64, one at rank 128 (measured, see apollo_proj_kernel)
+    if (tiles(32) > kApolloNarrowTiles / cfg->rank) P.tile_ch = 32 * 256 / cfg->rank;
+    for (al::ApolloDesc& d : P.desc) {
+        d.tile_begin = P.total_tiles;
+        P.total_tiles += (d.C + P.tile_ch - 1) / P.tile_ch;
     }
     if (P.total_tiles >= (int64_t(1) << 31) || P.total_chans / 4 >= (int64_t(1) << 31) ||
         P.total_units / 4 >= (int64_t(1) << 31) || P.total_fch / 4 >= (int64_t(1) << 31))
@@ -683,6 +694,7 @@ al_status al_apollo_step(const al_apollo_tensor* tensors, int32_t nt, const al_a
     a.D = reinterpret_cast<const al::ApolloDesc*>(ws);
     a.nt = (int32_t)P.desc.size();
     a.rank = cfg->rank;
+    a.tile_ch = P.tile_ch;
     a.total_tiles = P.total_tiles;
     a.total_chans = P.total_chans;
     a.total_units = P.total_units;

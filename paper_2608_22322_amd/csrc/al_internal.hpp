@@ -246,8 +246,6 @@ hipError_t launch_came_apply(const FacArgs& a, int grad_dtype, hipStream_t s);
 // tensor has C channels of L inputs (A = G or G^T as C x L) and rank r; its
 // workspace regions hold R and Rt (C x r fp32, channel-major) and per-channel
 // binary64 sums.
-// channels per projection workgroup: four wavefronts of 32 channels x 64 columns
-constexpr int apollo_tile_ch(int rank) { return 32 * 256 / rank; }
 constexpr int kApolloFlatChunk = 1024;  // elements per update chunk of tensors that are not whole units
 struct ApolloDesc {
     float* p;
@@ -261,7 +259,7 @@ struct ApolloDesc {
     double* sg;          // C: s_c^2 gn2_c
     double* lam;         // [0]: limiter divisor
     int64_t rows, cols, C, L;
-    int64_t tile_begin;  // first projection tile (apollo_tile_ch channels)
+    int64_t tile_begin;  // first projection tile (ApolloArgs::tile_ch channels)
     int64_t chan_begin;  // first channel over the list
     int64_t unit_begin;  // first 256x256 update unit (tensors of whole units only)
     int64_t fch_begin;   // first flattened update chunk (the other tensors)
@@ -281,6 +279,7 @@ struct ApolloArgs {
     // the descriptors' tile_begin, chan_begin, unit_begin and fch_begin, packed
     const int64_t *tile_begins, *chan_begins, *unit_begins, *fch_begins;
     int32_t nt, rank;
+    int32_t tile_ch;  // channels per projection workgroup: 32, or up to 32 * 256 / rank
     int64_t total_tiles, total_chans, total_units, total_fch;
     double lr, decay, gamma;
     int64_t step;

@@ -4,7 +4,7 @@
 //
 // Kernel sequence of one step (the fused AdamW step over the projected
 // moments runs between proj and scale, launched by the C ABI):
-//   proj    R = fl32(A Pi) for a tile of 32 * 256 / r channels and all r columns, in
+//   proj    R = fl32(A Pi) for a tile of 32 or 32 * 256 / r channels and all r columns, in
 //           binary64 on the matrix cores (v_mfma_f64_16x16x4f64): A (bf16 or
 //           fp32 gradient, as C x L) and Pi (fp32) are staged through LDS in
 //           slices of 16 inputs (Pi by LDS DMA) and widened to binary64 as the
@@ -74,9 +74,12 @@ constexpr int kLK = 16;  // inputs per LDS slice
 // One workgroup of 4 wavefronts per tile of 32 * 256 / r channels: each wavefront
 // computes 32 channels x 64 output columns (2 x 4 MFMA tiles of 16 x 16, eight
 // binary64 accumulators), the four of them side by side along the columns at rank
-// 256, 2 x 2 at rank 128 and along the channels at rank 64 (with 32-channel tiles at
-// every rank, rank 64 left three of the four without matrix work: a 6-layer list of
-// width 640 took 135 us in this kernel, now 119: too few tiles are left to hide the loads). Four such workgroups share a CU (one
+// 256, 2 x 2 at rank 128 and along the channels at rank 64. Short lists below rank 256 take tiles of 32
+// channels, where one (rank 64) or two wavefronts have matrix work: more workgroups to spread over
+// the CUs. The line (apollo_plan): at most two 32-channel tiles per CU at rank 64 (us per step with 32 and
+// 128 channels: 4096 x 4096, 128 tiles, 373 and 441; four of them, 512 tiles, 467 and 518; three 2048 x 5632, 528 tiles,
+// 290 and 286; 50 of 640 x 640, 1000 tiles, 180 and 149), one at rank 128 (32 and 64 channels: two 4096 x 4096, 256
+// tiles, 408 and 427; 11008 x 4096, 344 tiles, 669 and 449). Four such workgroups share a CU (one
 // wavefront of each per SIMD), so one workgroup's barrier leaves three to feed
 // the matrix cores. (Eight wavefronts on 64 channels: 2 workgroups per CU,
 // projection 2% slower; four wavefronts of 64 x 64 outputs -- 16 accumulators,
@@ -103,15 +106,16 @@ constexpr int kProjJT = kProjCW / 16;                             // 16-column M
 constexpr int kProjRows = kLK / kProjWaves;                       // rows of Pi each wavefront copies per slice
 constexpr int kAsPitch = 18;                                      // A row pitch in LDS (floats)
 static_assert(kProjIT * kProjJT == 8 && kLK % kProjWaves == 0, "projection tiling");
-// Of rank R: channels per tile, A values per thread and slice, Pi row pitch in LDS (floats; the four
+// Of rank R with T channels per tile: A values per thread and slice, Pi row pitch in LDS (floats; the four
 // rows of an operand read start 16 banks apart).
-template <int R>
+template <int R, int T>
 struct ProjGeo {
-    static constexpr int CG = R / kProjCW;  // wavefronts along the columns
-    static constexpr int TCH = apollo_tile_ch(R);
+    static constexpr int CG = R / kProjCW;             // wavefronts along the columns
+    static constexpr bool ALL = T / kProjCh * CG == kProjWaves;  // every wavefront has matrix work
+    static constexpr int TCH = T;
     static constexpr int APer = TCH * kLK / kProjThreads;
     static constexpr int BsPitch = R + 16;
-    static_assert(TCH == kProjCh * (kProjWaves / CG) && APer * kProjThreads == TCH * kLK, "projection tiling");
+    static_assert(T % kProjCh == 0 && T / kProjCh * CG <= kProjWaves && APer * kProjThreads == TCH * kLK, "projection tiling");
 };
 
 // A pointer known to be the same on every lane, made scalar, so that a load
@@ -129,9 +133,9 @@ __device__ __forceinline__ P uniform_ptr(P p) {
 // Every slice loads from a uniform slice base plus a fixed 32-bit byte offset
 // per value (no vector address work): one offset for slices wholly inside the
 // tensor, one for a ragged last slice, which clamps l to L - 1 (and zeroes it).
-template <int G, int R>
+template <int G, int R, int T_>
 struct ProjA {
-    static constexpr int kAPer = ProjGeo<R>::APer;
+    static constexpr int kAPer = ProjGeo<R, T_>::APer;
     using T = typename std::conditional<G == G_BF16, uint16_t, uint32_t>::type;
     gp<const T> tile;       // element (c0, 0): the tile's first channel, first input
     int64_t stride;         // distance between consecutive inputs of a channel
@@ -143,11 +147,11 @@ struct ProjA {
     bool cfull;             // every channel of the tile inside the tensor (uniform)
 };
 
-template <int G, int R>
-__device__ __forceinline__ void proj_a_setup(ProjA<G, R>& A, const void* g, int64_t cols, int64_t C, int64_t c0,
+template <int G, int R, int TCH>
+__device__ __forceinline__ void proj_a_setup(ProjA<G, R, TCH>& A, const void* g, int64_t cols, int64_t C, int64_t c0,
                                              int L, bool right, int tid) {
-    using T = typename ProjA<G, R>::T;
-    constexpr int kAPer = ProjGeo<R>::APer, kApolloTileCh = ProjGeo<R>::TCH;
+    using T = typename ProjA<G, R, TCH>::T;
+    constexpr int kAPer = ProjGeo<R, TCH>::APer, kApolloTileCh = TCH;
     A.stride = right ? 1 : cols;
     A.tile = to_g(reinterpret_cast<const T*>(g)) + (right ? c0 * cols : c0);
     A.cfull = c0 + kApolloTileCh <= C;
@@ -170,10 +174,10 @@ __device__ __forceinline__ void proj_a_setup(ProjA<G, R>& A, const void* g, int6
 
 // Slice l0 of A as raw bits into registers (the wait for them falls after the
 // matrix work, where proj_store_a consumes them).
-template <int G, int R>
-__device__ __forceinline__ void proj_fetch_a(const ProjA<G, R>& A, int l0, int L, uint32_t (&ra)[ProjGeo<R>::APer]) {
-    using T = typename ProjA<G, R>::T;
-    constexpr int kAPer = ProjGeo<R>::APer;
+template <int G, int R, int TCH>
+__device__ __forceinline__ void proj_fetch_a(const ProjA<G, R, TCH>& A, int l0, int L, uint32_t (&ra)[ProjGeo<R, TCH>::APer]) {
+    using T = typename ProjA<G, R, TCH>::T;
+    constexpr int kAPer = ProjGeo<R, TCH>::APer;
     const bool inside = l0 + kLK <= L;  // otherwise the last slice
     const gp<const char> sb = uniform_ptr(g_as<const char>(A.tile + (int64_t)l0 * A.stride));
 #pragma unroll
@@ -182,10 +186,11 @@ __device__ __forceinline__ void proj_fetch_a(const ProjA<G, R>& A, int l0, int L
 
 // The slice into LDS as fp32, inputs outside the tensor as zero; each thread
 // also accumulates the squares of the values it stores (binary64, exact products).
-template <int G, int R>
-__device__ __forceinline__ void proj_store_a(const ProjA<G, R>& A, int l0, int L, float* As,
-                                             const uint32_t (&ra)[ProjGeo<R>::APer], double (&gq)[ProjGeo<R>::APer]) {
-    constexpr int kAPer = ProjGeo<R>::APer;
+template <int G, int R, int TCH>
+__device__ __forceinline__ void proj_store_a(const ProjA<G, R, TCH>& A, int l0, int L, float* As,
+                                             const uint32_t (&ra)[ProjGeo<R, TCH>::APer],
+                                             double (&gq)[ProjGeo<R, TCH>::APer]) {
+    constexpr int kAPer = ProjGeo<R, TCH>::APer;
     const bool full = A.cfull && l0 + kLK <= L;
 #pragma unroll
     for (int q = 0; q < kAPer; ++q) {
@@ -212,10 +217,10 @@ __device__ __forceinline__ void proj_copy_pi(const float* proj, int L, int l0, i
     }
 }
 
-template <int G, int R>
-__global__ __launch_bounds__(kProjThreads) __attribute__((amdgpu_waves_per_eu(R == 64 ? 2 : 4)))
+template <int G, int R, int TCH>
+__global__ __launch_bounds__(kProjThreads) __attribute__((amdgpu_waves_per_eu(TCH == 128 ? 2 : 4)))
 void apollo_proj_kernel(const ApolloArgs a) {
-    using P = ProjGeo<R>;
+    using P = ProjGeo<R, TCH>;
     constexpr int kAPer = P::APer, kApolloTileCh = P::TCH, kBsPitch = P::BsPitch, r = R;
     // Two buffers of each operand as four separate LDS objects, named statically
     // in each half of the unrolled slice loop: the compiler then knows that the
@@ -232,6 +237,7 @@ void apollo_proj_kernel(const ApolloArgs a) {
     const int l16 = lane & 15, l4 = lane >> 4;
     // the wavefront's 64 columns and 32 channels of the tile
     const int cw = kProjCW * (w % P::CG), ch = kProjCh * (w / P::CG);
+    const bool active = P::ALL || ch < TCH;
     // the descriptor's fields, read once (read through the descriptor they are
     // fetched again every slice, and those fetches wait for the copies in flight)
     const int64_t C = d.C;
@@ -244,8 +250,8 @@ void apollo_proj_kernel(const ApolloArgs a) {
     float* const Rtp = d.Rt;
     double* const gn2 = d.gn2;
     const bool right = d.right != 0;
-    ProjA<G, R> A;
-    proj_a_setup<G, R>(A, d.g, d.cols, C, c0, L, right, tid);
+    ProjA<G, R, TCH> A;
+    proj_a_setup<G, R, TCH>(A, d.g, d.cols, C, c0, L, right, tid);
     d4v acc[kProjIT][kProjJT];
 #pragma unroll
     for (int i = 0; i < kProjIT; ++i)
@@ -262,9 +268,9 @@ void apollo_proj_kernel(const ApolloArgs a) {
         const bool more = n + 1 < ns;
         if (more) {
             proj_copy_pi(proj, L, (n + 1) * kLK, r, kBsPitch, w, lane, &Bn[0][0]);
-            proj_fetch_a<G, R>(A, (n + 1) * kLK, L, ra);
+            proj_fetch_a<G, R, TCH>(A, (n + 1) * kLK, L, ra);
         }
-        {
+        if (active) {
             // the operands of step kk + 4 are read before the matrix work of step kk
             float xa[2][kProjIT], xb[2][kProjJT];
             auto rd = [&](int st, int kk) {
@@ -297,15 +303,15 @@ void apollo_proj_kernel(const ApolloArgs a) {
                 __builtin_amdgcn_sched_group_barrier(0x008, kProjIT * kProjJT - kProjIT - kProjJT, 0);
             }
         }
-        if (more) proj_store_a<G, R>(A, (n + 1) * kLK, L, &An[0][0], ra, gq);
+        if (more) proj_store_a<G, R, TCH>(A, (n + 1) * kLK, L, &An[0][0], ra, gq);
         // the copies into the other buffers have landed and every read of these is done
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     };
     if (ns > 0) {
         proj_copy_pi(proj, L, 0, r, kBsPitch, w, lane, &Bs0[0][0]);
-        proj_fetch_a<G, R>(A, 0, L, ra);
-        proj_store_a<G, R>(A, 0, L, &As0[0][0], ra, gq);
+        proj_fetch_a<G, R, TCH>(A, 0, L, ra);
+        proj_store_a<G, R, TCH>(A, 0, L, &As0[0][0], ra, gq);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     }
@@ -337,7 +343,7 @@ void apollo_proj_kernel(const ApolloArgs a) {
     const bool clear_rt = Rtp != nullptr;
     const gp<float> Rg = to_g(Rp);
     const gp<float> Rtg = to_g(Rtp);
-    {
+    if (active) {
 #pragma unroll
         for (int i = 0; i < kProjIT; ++i)
 #pragma unroll
@@ -354,21 +360,27 @@ void apollo_proj_kernel(const ApolloArgs a) {
     }
 }
 
-template <int G>
+template <int G, int R, int TCH>
 static hipError_t proj_launch(const ApolloArgs& a, hipStream_t s) {
-    const dim3 grid((unsigned)a.total_tiles), block(kProjThreads);
-    switch (a.rank) {
-        case 64: hipLaunchKernelGGL((apollo_proj_kernel<G, 64>), grid, block, 0, s, a); break;
-        case 128: hipLaunchKernelGGL((apollo_proj_kernel<G, 128>), grid, block, 0, s, a); break;
-        case 256: hipLaunchKernelGGL((apollo_proj_kernel<G, 256>), grid, block, 0, s, a); break;
-        default: return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL((apollo_proj_kernel<G, R, TCH>), dim3((unsigned)a.total_tiles), dim3(kProjThreads), 0, s, a);
     return hipGetLastError();
+}
+
+template <int G>
+static hipError_t proj_rank(const ApolloArgs& a, hipStream_t s) {
+    switch (a.rank * 1000 + a.tile_ch) {
+        case 64032: return proj_launch<G, 64, 32>(a, s);
+        case 64128: return proj_launch<G, 64, 128>(a, s);
+        case 128032: return proj_launch<G, 128, 32>(a, s);
+        case 128064: return proj_launch<G, 128, 64>(a, s);
+        case 256032: return proj_launch<G, 256, 32>(a, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_apollo_proj(const ApolloArgs& a, int grad_dtype, hipStream_t s) {
     if (a.total_tiles == 0) return hipSuccess;
-    return grad_dtype == G_BF16 ? proj_launch<G_BF16>(a, s) : proj_launch<G_F32>(a, s);
+    return grad_dtype == G_BF16 ? proj_rank<G_BF16>(a, s) : proj_rank<G_F32>(a, s);
 }
 
 // ------------------------------------------------------------ channel scales
