@@ -128,7 +128,7 @@ al_status check_ws(void* ws, size_t ws_bytes, size_t need, const char* who) {
 
 struct FacPlan {
     std::vector<al::FacRec> rec;  // 2-D tensors first, then 1-D
-    int n2 = 0, n1 = 0;
+    int n2 = 0, n1 = 0, lead = 0;
     int64_t total_units = 0, total_ach = 0, total_mt = 0, whole_ach = 0, rows_ach = 0;
     int32_t ur = 256, any_whole = 0, any_edge = 0;
     int64_t total_blk[2] = {0, 0};
@@ -172,8 +172,8 @@ struct FacReserve {
 
 // Validate the tensor list and lay out the workspace: descriptor table, RMS
 // partials, then per-tensor regions (offsets from its start).
-al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& ms, const al_state_spec& vs,
-                   const al_state_spec& cs, FacPlan& P) {
+al_status fac_plan(const al_tensor* ts, int nt, bool came, int32_t grad_dtype, const al_state_spec& ms,
+                   const al_state_spec& vs, const al_state_spec& cs, FacPlan& P) {
     const char* who = came ? "al_came_step" : "al_adafactor_step";
     if (nt < 0) return fail(AL_EINVAL, "%s: nt < 0", who);
     if (nt > 0 && !ts) return fail(AL_EINVAL, "%s: tensors is NULL", who);
@@ -222,6 +222,14 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, const al_state_spec& 
     P.n1 = (int)oned.size();
     const int ntot = P.n2 + P.n1;
     P.rec.resize(ntot);
+    // The 1-D tensors go beside the marginal sums, where short ones are hidden. A workgroup there takes up to 16% longer
+    // than in a kernel of its own (4096 elements 27.7 and 25.6 us, a million 9.7 and 8.2 ms; fp32 gradients 2% at a
+    // million), and holds the pass up if it is long. us per Adafactor step beside and alone: 16384 elements with sixteen
+    // 4096 x 4096 775 and 760 (fp32 1013 and 1060), 20000 with ten 2048 x 2048 286 and 280 (fp32 303 and 315), 50257 with
+    // twelve 4096 x 4096 1065 and 918 (fp32 1166 and 1158).
+    int64_t longest = 0;
+    for (int i : oned) longest = std::max(longest, ts[i].cols);
+    if (P.n2 > 0 && longest <= (grad_dtype == AL_DTYPE_BF16 ? 16384 : 32768)) P.lead = P.n1;
     // Unit rows: 256, halved down to 32 while the list has fewer than kFacMinUnits units (one wavefront
     // each): a short list's passes are bound by the longest wavefront, not by memory. More, shorter units
     // cost column partials (8 bytes per column and unit row), which a short list hardly notices.
@@ -306,6 +314,7 @@ al::FacArgs fac_args(const FacPlan& P, char* ws) {
     a.rmspart = reinterpret_cast<double*>(ws + P.rms_off);
     a.n2 = P.n2;
     a.n1 = P.n1;
+    a.lead = P.lead;
     a.total_units = P.total_units;
     a.total_ach = P.total_ach;
     a.total_mt = P.total_mt;
@@ -832,7 +841,7 @@ al_status al_adafactor_workspace_bytes(const al_tensor* tensors, int32_t nt, con
     al_status st = check_adafactor_cfg(cfg);
     if (st != AL_OK) return st;
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, false, kNoSpec, cfg->v, kNoSpec, P)) != AL_OK) return st;
+    if ((st = fac_plan(tensors, nt, false, cfg->grad_dtype, kNoSpec, cfg->v, kNoSpec, P)) != AL_OK) return st;
     *bytes = P.bytes;
     return AL_OK;
 }
@@ -844,7 +853,7 @@ al_status al_came_workspace_bytes(const al_tensor* tensors, int32_t nt, const al
     al_status st = check_came_cfg(cfg);
     if (st != AL_OK) return st;
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, true, cfg->m, cfg->v, cfg->conf, P)) != AL_OK) return st;
+    if ((st = fac_plan(tensors, nt, true, cfg->grad_dtype, cfg->m, cfg->v, cfg->conf, P)) != AL_OK) return st;
     *bytes = P.bytes;
     return AL_OK;
 }
@@ -856,7 +865,7 @@ al_status al_adafactor_step(const al_tensor* tensors, int32_t nt, const al_adafa
     if (st != AL_OK) return st;
     if (step < 1) return fail(AL_EINVAL, "al_adafactor_step: step must be >= 1");
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, false, kNoSpec, cfg->v, kNoSpec, P)) != AL_OK) return st;
+    if ((st = fac_plan(tensors, nt, false, cfg->grad_dtype, kNoSpec, cfg->v, kNoSpec, P)) != AL_OK) return st;
     if (P.rec.empty()) return AL_OK;
     if ((st = check_ws(ws, ws_bytes, P.bytes, "al_adafactor_step")) != AL_OK) return st;
 
@@ -889,7 +898,7 @@ al_status al_came_step(const al_tensor* tensors, int32_t nt, const al_came_cfg* 
     if (st != AL_OK) return st;
     if (step < 1) return fail(AL_EINVAL, "al_came_step: step must be >= 1");
     FacPlan P;
-    if ((st = fac_plan(tensors, nt, true, cfg->m, cfg->v, cfg->conf, P)) != AL_OK) return st;
+    if ((st = fac_plan(tensors, nt, true, cfg->grad_dtype, cfg->m, cfg->v, cfg->conf, P)) != AL_OK) return st;
     if (P.rec.empty()) return AL_OK;
     if ((st = check_ws(ws, ws_bytes, P.bytes, "al_came_step")) != AL_OK) return st;
 

@@ -211,6 +211,7 @@ struct FacArgs {
     const int64_t *unit_begins, *ach_begins, *mt_begins, *blk_begins[2];
     double* rmspart;      // [total_units] (hi, lo): partial sums of u^2
     int32_t n2, n1;       // 2-D tensors, 1-D tensors (D[n2 .. n2 + n1))
+    int32_t lead;         // n1: the marginal kernel's first workgroups step the 1-D tensors; 0: a launch of their own does
     int64_t total_units, total_ach, total_mt;
     // apply chunks [0, whole_ach): tensors of whole units, listed first; [whole_ach, rows_ach): the other widths that
     // are a multiple of 256; the rest: flattened chunks

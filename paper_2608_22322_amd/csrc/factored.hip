@@ -794,9 +794,8 @@ __device__ __forceinline__ void came_vec1d(const FacArgs& a, const FacDesc& d, D
     vec_encode(a.m_codec, a.m_block, d.ctmp, n, 0.0f, d.m, d.mm, wave, 4, lane);
 }
 
-// The first a.n1 workgroups of the first launch (lead = a.n1) step a 1-D tensor each: one workgroup is
-// latency-bound (4096 elements take 85 us, as a pass of its own at the end of the step), and beside the
-// streaming units it is hidden.
+// The first a.lead workgroups of the first launch (lead = a.lead) step a 1-D tensor each: one workgroup is
+// latency-bound, and beside the streaming units it is hidden.
 template <int G, bool CAME>
 __global__ __launch_bounds__(256) void fac_marg_kernel(const FacArgs a, int64_t base, int lead) {
     __shared__ __attribute__((aligned(16))) double stages[4][2 * MargTerms<G>::NR * kWStride];
@@ -829,10 +828,27 @@ __global__ __launch_bounds__(256) void fac_marg_kernel(const FacArgs a, int64_t 
     }
 }
 
+// 1-D tensors that the marginal kernel's workgroups do not take (fac_plan).
+template <int G, bool CAME>
+__global__ __launch_bounds__(256) void fac_vec1d_kernel(const FacArgs a) {
+    __shared__ DD sh[4];
+    __shared__ double clip_s;
+    const FacDesc& d = a.D[a.n2 + blockIdx.x];
+    if constexpr (CAME)
+        came_vec1d<G>(a, d, sh, clip_s);
+    else
+        ada_vec1d<G>(a, d, sh, clip_s);
+}
+
 template <int G, bool CAME>
 static hipError_t marg_launch(const FacArgs& a, hipStream_t s) {
+    if (a.lead < a.n1) {
+        hipLaunchKernelGGL((fac_vec1d_kernel<G, CAME>), dim3((unsigned)a.n1), dim3(256), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     constexpr int64_t kMaxGrid = int64_t(1) << 30;
-    int lead = a.n1;
+    int lead = a.lead;
     for (int64_t base = 0; base < a.total_units || lead > 0; base += 4 * kMaxGrid) {
         const int64_t left = (a.total_units - base + 3) / 4;
         const int64_t grid = (left < kMaxGrid ? left : kMaxGrid) + lead;
