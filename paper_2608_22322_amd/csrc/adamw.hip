@@ -704,12 +704,16 @@ __device__ __forceinline__ void adamw_compute(const AdamWLaunch& a, const DescG&
 // states get exactly 2 (8 layers of 2048 / 5632, bf16, us per step with all that the
 // registers allow, 4, 3 and 2: 1652, 1631, 1580, 1540), an fp32 second moment alone 3
 // (1248, 1207, 1218; fp32 gradients 1349, 1314, 1294), fp32 momentum with AL8 4 (1212
-// free, 1164 at 4, 1206 at 3). AL16 with fp32 momentum is best left free (1403; 1414
-// at 4, 1502 at 3).
+// free, 1164 at 4, 1206 at 3; one tensor of 128M, at 4 and 3: B_V 64 429 and 448, 128 418 and 430, 256 418 and
+// 426, 512 415 and 419, 1024 444 and 437 but 15.8 and 16.2 at 4M), except B_V 2048, whose chunks need 145-149
+// registers and would spill: 3 (460 and 456; fp32 gradients 520 and 511, at 32M 136 and 130). AL16 with fp32 momentum is
+// best left free (1403; 1414 at 4, 1502 at 3). The 2048-element chunks of a long list at B_V 128 and 256
+// spill 2 registers at 4 and are still faster there (B_V 128, bf16, one tensor of 1000M: 2675 at 4, 2699 at 3).
 template <int MC, int VC, int BV, int CE>
 constexpr int adamw_min_waves() {
     if (VC == FP32) return MC == FP32 ? 2 : 3;
-    if (MC == UF8 || VC == AL8) return 4;
+    if (MC == UF8) return 4;
+    if (VC == AL8) return CE >= 2048 ? 3 : 4;
     return CE >= 2048 ? 2 : 3;
 }
 template <int MC, int VC, int BV, int CE>
