@@ -104,7 +104,10 @@ __host__ __device__ constexpr int long_chunk_elems(int g, int mc, int vc, int bv
 }
 
 // Chunks of a short list (kAdamWSmall): a wavefront's chain of sub-tiles is what
-// its step takes, so it is cut into more and shorter ones.
+// its step takes, so it is cut into more and shorter ones. The line is where that stops to pay for bf16
+// gradients (us per step of one tensor with ordinary and short chunks; UF8 momentum, B_V 256: 1M 8.3 and 7.1, 2M 10.3 and
+// 9.8, 3.5M 15.3 and 14.4, 4M 15.2 and 15.4, 8M 25.8 and 25.9; fp32 gradients 15.6 and 14.3 at 3.5M, 27.3 and
+// 26.5 at 8M; AL16 B_V 128 17.4 and 15.5 at 3.5M, 31.3 and 30.8 at 8M).
 __host__ __device__ constexpr int small_chunk_elems(int vc, int bv) { return vc == FP32 || bv < 512 ? 512 : bv; }
 
 template <int MC, int VC, int BV, int CE>

@@ -83,7 +83,7 @@ constexpr int kMaxDevices = 64;
 hipError_t adamw_static_table(void** table);
 
 // Elements per chunk of a list of `total` elements (exact below kAdamWLong).
-constexpr int64_t kAdamWSmall = 3 << 20, kAdamWLong = int64_t(1) << 28;
+constexpr int64_t kAdamWSmall = 1 << 22, kAdamWLong = int64_t(1) << 28;
 int adamw_tile_elems(int grad_dtype, int m_codec, int v_codec, int v_block, int64_t total);
 hipError_t launch_adamw(const AdamWLaunch& a, const AdamWInline& in, int grad_dtype, int m_codec, int v_codec, int v_block,
                         hipStream_t s, bool apollo = false);

@@ -1,4 +1,4 @@
-"""AdamW's chunk lengths and descriptor routes: a list under 3 * 2^20 elements is cut into short chunks, one of 2^28
+"""AdamW's chunk lengths and descriptor routes: a list under 2^22 elements is cut into short chunks, one of 2^28
 and more into long ones (bf16 gradients, AL8 blocks of 128-1024), up to 8 tensors travel in the kernel arguments. The same tensors stepped in a short list, in a long one (with a large tensor
 beside them) and in a list of more than 8 must give the same parameters, codes and metadata bit for bit (the short
 route is held to the oracle in test_gpu_adamw.py)."""
