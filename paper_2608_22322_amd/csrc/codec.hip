@@ -29,7 +29,7 @@ struct BlockEnc {
 
 // One chunk of K sub-tiles from element e0, the first `valid` elements inside the
 // array (FULL: all).
-template <int C, int B, int K, bool FULL>
+template <int C, int B, int K, bool NT, bool FULL>
 __device__ __forceinline__ void quantize_chunk(gp<const float> x, int64_t e0, int valid, int lane, float log_floor,
                                                gp<uint8_t> codes, gp<float> meta, uint2* skey, BlockEnc* senc) {
     constexpr int NB = 256 * K / B;               // blocks
@@ -41,7 +41,7 @@ __device__ __forceinline__ void quantize_chunk(gp<const float> x, int64_t e0, in
     for (int k = 0; k < K; ++k) {
         const int rel = k * kSub + 4 * lane;
         if constexpr (FULL) {
-            const float4 t = ld_f4<true>(x + e0 + rel);
+            const float4 t = ld_f4<NT>(x + e0 + rel);
             xv[k][0] = t.x, xv[k][1] = t.y, xv[k][2] = t.z, xv[k][3] = t.w;
         } else {
 #pragma unroll
@@ -145,9 +145,13 @@ __device__ __forceinline__ int64_t codec_chunk() {
     return xcd_order(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
+// Loads. UF8 and AL16 codes are decoded with plain loads: a state that the last-level cache holds is read from it
+// (20M values, UF8 18.3 us non-temporal, 15.8 plain; AL16 25.8 and 23.2; 300M no difference). UF8 encodes with
+// plain loads while the input fits that cache (kCodecCached: 20M 17.6 and 16.2 us, 40M 33.8 and 29.1, but 100M 80 and 87); the
+// other codes' arithmetic bounds them.
 // Four waves per SIMD in both directions: the registers allow 7-8, but the streams mix less (50M values AL8
 // B2048 -> fp32 -> AL16 B128: 109 us at 7-8, 107 at 4, 110 at 3, 125 at 2).
-template <int C, int B, int K>
+template <int C, int B, int K, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void quantize_kernel(const float* __restrict__ x, int64_t n, int64_t base,
                                                         float log_floor, void* codes, float* meta) {
     constexpr int E = 256 * K;
@@ -159,9 +163,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const gp<const float> xg = to_g(x);
     const gp<uint8_t> cg = (gp<uint8_t>)to_g(codes);
     if (left >= E)
-        quantize_chunk<C, B, K, true>(xg, e0, E, lane, log_floor, cg, to_g(meta), skey[w], senc[w]);
+        quantize_chunk<C, B, K, NT, true>(xg, e0, E, lane, log_floor, cg, to_g(meta), skey[w], senc[w]);
     else if (left > 0)
-        quantize_chunk<C, B, K, false>(xg, e0, (int)left, lane, log_floor, cg, to_g(meta), skey[w], senc[w]);
+        quantize_chunk<C, B, K, NT, false>(xg, e0, (int)left, lane, log_floor, cg, to_g(meta), skey[w], senc[w]);
 }
 
 // AL8 blocks of 512 and more decode through a table of the block's levels in LDS
@@ -180,9 +184,9 @@ __device__ __forceinline__ void dequantize_chunk(gp<const uint8_t> codes, gp<con
         const int rel = k * kSub + 4 * lane;
         if constexpr (FULL) {
             if constexpr (C == AL16)
-                w[k] = ld_u2<true>(g_as<const void>(codes + 2 * (e0 + rel)));
+                w[k] = ld_u2<false>(g_as<const void>(codes + 2 * (e0 + rel)));
             else
-                w[k] = ld_u1<true>(g_as<const void>(codes + e0 + rel));
+                w[k] = ld_u1<C == AL8>(g_as<const void>(codes + e0 + rel));
         } else {  // only the codes of the n elements are read
             uint32_t q[4];
 #pragma unroll
@@ -508,6 +512,7 @@ hipError_t launch_diag_stream(int mode, float* p, const uint16_t* g, uint8_t* m,
 // Chunks of 2048 elements (K = 8), or of max(B, 256) where the array has too few
 // of those to give every SIMD a wavefront.
 constexpr int64_t kCodecLong = 2048 * 1024;
+constexpr int64_t kCodecCached = int64_t(1) << 26;  // 256 MB of fp32
 
 // One wavefront per chunk, 4 per workgroup; launches beyond 2^32 chunks are split.
 template <class F>
@@ -523,16 +528,20 @@ static hipError_t codec_launch(int64_t n, int64_t elems, F launch) {
     return hipSuccess;
 }
 
+template <int C, int B, int K, bool NT>
+static hipError_t quant_k(const float* x, int64_t n, float lf, void* codes, float* meta, hipStream_t s) {
+    return codec_launch(n, K * kSub, [&](dim3 g, int64_t base) {
+        hipLaunchKernelGGL((quantize_kernel<C, B, K, NT>), g, dim3(256), 0, s, x, n, base, lf, codes, meta);
+    });
+}
+
 template <int C, int B>
 static hipError_t quant_t(const float* x, int64_t n, float lf, void* codes, float* meta, hipStream_t s) {
     constexpr int KS = B > kSub ? B / kSub : 1;
-    if (n >= kCodecLong)
-        return codec_launch(n, 2048, [&](dim3 g, int64_t base) {
-            hipLaunchKernelGGL((quantize_kernel<C, B, 8>), g, dim3(256), 0, s, x, n, base, lf, codes, meta);
-        });
-    return codec_launch(n, KS * kSub, [&](dim3 g, int64_t base) {
-        hipLaunchKernelGGL((quantize_kernel<C, B, KS>), g, dim3(256), 0, s, x, n, base, lf, codes, meta);
-    });
+    constexpr bool NT = C != UF8;
+    if (n < kCodecLong) return quant_k<C, B, KS, NT>(x, n, lf, codes, meta, s);
+    if (n < kCodecCached) return quant_k<C, B, 8, NT>(x, n, lf, codes, meta, s);
+    return quant_k<C, B, 8, true>(x, n, lf, codes, meta, s);
 }
 
 template <int C, int B>

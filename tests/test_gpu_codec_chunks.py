@@ -56,3 +56,24 @@ def test_long_and_short_chunks_agree(dev, codec, block, tail):
         assert torch.equal(sc, codes[lo: lo + nb * block])
         assert torch.equal(sm[: per * nb], meta[per * (lo // block): per * (lo // block + nb)])
         assert torch.equal(so, out[lo:hi])
+
+
+@pytest.mark.parametrize("block", [64, 2048])
+def test_uf8_arrays_past_the_cache_agree_with_shorter_ones(dev, block):
+    """2^26 values and more are read past the last-level cache: the same codes as their parts, a ragged end included."""
+    import torch
+
+    import paper_2608_22322_amd as al
+
+    n = (1 << 26) + 700
+    x = torch.randn(n, generator=torch.Generator(device=dev).manual_seed(block), device=dev)
+    spec = al.Spec(al.UF8, block)
+    codes, meta = al.alloc_state(n, spec, dev)
+    al.quantize(al.UF8, x, block, 0.0, codes, meta)
+    for lo, hi in ((0, 1 << 22), (n // 2048 * 2048 - (1 << 21), n)):
+        part = x[lo:hi].clone()
+        sc, sm = al.alloc_state(hi - lo, spec, dev)
+        al.quantize(al.UF8, part, block, 0.0, sc, sm)
+        nb = (hi - lo + block - 1) // block
+        assert torch.equal(sc[: nb * block], codes[lo: lo + nb * block])
+        assert torch.equal(sm[:nb], meta[lo // block: lo // block + nb])
