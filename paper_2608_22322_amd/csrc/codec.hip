@@ -510,8 +510,13 @@ hipError_t launch_diag_stream(int mode, float* p, const uint16_t* g, uint8_t* m,
 }
 
 // Chunks of 2048 elements (K = 8), or of max(B, 256) where the array has too few
-// of those to give every SIMD a wavefront.
-constexpr int64_t kCodecLong = 2048 * 1024;
+// of those to give every SIMD a wavefront: below 2^21 elements. AL16's arithmetic per element wants more wavefronts
+// for longer: short chunks are faster up to about 4M elements encoding (us at 2.2M and 4M with long and short ones: B 128
+// 10.8 and 8.1, 11.4 and 12.3; B 1024 9.6 and 7.7, 10.5 and 9.6), 7M decoding (5M and 8M: B 128 8.9 and 8.5, 12.1 and
+// 12.9; B 512 8.5 and 7.5, 11.6 and 10.4). AL8 at 4M: encoding 7.2 and 8.7, decoding 7.0 and 7.7.
+constexpr int64_t codec_long(int c, bool encode) {
+    return c == AL16 ? (encode ? int64_t(1) << 22 : int64_t(7) << 20) : int64_t(1) << 21;
+}
 constexpr int64_t kCodecCached = int64_t(1) << 26;  // 256 MB of fp32
 
 // One wavefront per chunk, 4 per workgroup; launches beyond 2^32 chunks are split.
@@ -539,7 +544,7 @@ template <int C, int B>
 static hipError_t quant_t(const float* x, int64_t n, float lf, void* codes, float* meta, hipStream_t s) {
     constexpr int KS = B > kSub ? B / kSub : 1;
     constexpr bool NT = C != UF8;
-    if (n < kCodecLong) return quant_k<C, B, KS, NT>(x, n, lf, codes, meta, s);
+    if (n < codec_long(C, true)) return quant_k<C, B, KS, NT>(x, n, lf, codes, meta, s);
     if (n < kCodecCached) return quant_k<C, B, 8, NT>(x, n, lf, codes, meta, s);
     return quant_k<C, B, 8, true>(x, n, lf, codes, meta, s);
 }
@@ -547,7 +552,7 @@ static hipError_t quant_t(const float* x, int64_t n, float lf, void* codes, floa
 template <int C, int B>
 static hipError_t dequant_t(const void* codes, const float* meta, int64_t n, float* out, hipStream_t s) {
     constexpr int KS = B > kSub ? B / kSub : 1;
-    if (n >= kCodecLong)
+    if (n >= codec_long(C, false))
         return codec_launch(n, 2048, [&](dim3 g, int64_t base) {
             hipLaunchKernelGGL((dequantize_kernel<C, B, 8>), g, dim3(256), 0, s, codes, meta, n, base, out);
         });

@@ -1,5 +1,5 @@
-"""The codecs' two chunk lengths: arrays of 2^21 and more elements take 2048-element chunks, shorter ones
-max(block, 256). The same values must give the same codes, metadata and decoded values through both (the short
+"""The codecs' two chunk lengths: arrays of 2^21 and more elements (AL16: 2^22 encoding, 7 * 2^20 decoding) take
+2048-element chunks, shorter ones max(block, 256). The same values must give the same codes, metadata and decoded values through both (the short
 path is held to the oracle in test_gpu_codec.py), ragged ends included."""
 import pytest
 
@@ -22,12 +22,21 @@ def dev():
 @pytest.mark.parametrize("block", [64, 128, 256, 512, 1024, 2048])
 @pytest.mark.parametrize("tail", [0, 1, 2047, 700])
 def test_long_and_short_chunks_agree(dev, codec, block, tail):
+    _long_and_short(dev, codec, block, LONG + tail, tail)
+
+
+@pytest.mark.parametrize("block", [64, 128, 256, 512, 1024, 2048])
+@pytest.mark.parametrize("tail", [0, 1, 700])
+def test_al16_long_and_short_chunks_agree(dev, block, tail):
+    _long_and_short(dev, "AL16", block, (7 << 20) + tail, tail)
+
+
+def _long_and_short(dev, codec, block, n, tail):
     import torch
 
     import paper_2608_22322_amd as al
 
     c = getattr(al, codec)
-    n = LONG + tail
     gen = torch.Generator(device=dev)
     gen.manual_seed(block + tail)
     x = torch.randn(n, generator=gen, device=dev)
