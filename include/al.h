@@ -190,7 +190,9 @@ typedef struct al_came_cfg {
  *         lam = 1 and *norm_state = fl32(||G~||);
  *   param = fl32(param (1 - lr wd) - lr g (s_c / lam)), binary64.
  * The token embedding, LM head and 1-D tensors are not projected: they take
- * al_adamw_step with the same codes. */
+ * al_adamw_step with the same codes. With more columns than rows,
+ * min(rows - 1, 15) rows of the gradient must span less than 4 GiB (about 71
+ * million fp32 columns; AL_EUNSUPPORTED beyond). */
 typedef struct al_apollo_tensor {
     float* param;
     const void* grad;

@@ -383,6 +383,12 @@ al_status apollo_plan(const al_apollo_tensor* ts, int nt, const al_apollo_cfg* c
         if (t.rows < 0 || t.cols < 0) return fail(AL_EINVAL, "tensor %d: negative shape", i);
         if (t.rows > 0 && t.cols > (int64_t(1) << 40) / t.rows) return fail(AL_EINVAL, "tensor %d: shape too large", i);
         if (t.rows * t.cols == 0) continue;
+        // the projection reaches the 16 inputs of a slice from its base with 32-bit byte offsets: 15 rows of G and a
+        // tile's 128 channels when the channels are columns (128 rows otherwise, of at most 2^20 columns each)
+        if (t.cols > t.rows && (std::min<int64_t>(t.rows - 1, 15) * t.cols + 128) * (cfg->grad_dtype == AL_DTYPE_BF16 ? 2 : 4) >
+                                   (int64_t(1) << 32))
+            return fail(AL_EUNSUPPORTED, "tensor %d: %lld columns are too many for the projection's offsets", i,
+                        (long long)t.cols);
         if (!t.param || !t.grad || !t.proj) return fail(AL_EINVAL, "tensor %d: param, grad or proj is NULL", i);
         if (!aligned16(t.param) || !aligned16(t.grad) || !aligned16(t.proj))
             return fail(AL_EALIGN, "tensor %d: param, grad or proj not 16-byte aligned", i);

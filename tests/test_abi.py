@@ -447,6 +447,25 @@ def test_apollo_workspace_layout():
     assert _ap_ws([_at(rows=0)]) == 0 and _ap_ws([]) == 0
 
 
+@pytest.mark.parametrize("bf16", [True, False])
+def test_apollo_rejects_rows_past_the_projection_offsets(bf16):
+    """Channels along the columns: a slice's inputs lie up to 15 rows from its base, in 32-bit byte offsets."""
+    size = 2 if bf16 else 4
+    cfg = al.apollo_cfg(rank=64, grad_bf16=bf16)
+
+    def status(rows, cols):
+        arr, out = (al.ApolloTensor * 1)(_at(rows=rows, cols=cols)), ctypes.c_size_t(0)
+        return al.lib().al_apollo_workspace_bytes(arr, 1, ctypes.byref(cfg), ctypes.byref(out))
+
+    for rows in (2, 9, 16, 4000):
+        far = min(rows - 1, 15)
+        most = (2 ** 32 // size - 128) // far
+        assert status(rows, most) == 0 and status(rows, most + 1) == 4, (rows, most)
+        assert status(rows, 1000) == 0
+    assert status(1, 2 ** 32) == 0  # one row: no offset
+    assert status(2 ** 20, 2 ** 20) == 0 and status(2 ** 20, 10) == 0  # channels along the rows
+
+
 def test_apollo_validation():
     assert _status(lambda: _ap_step([_at()], step=0)) == 1
     assert _status(lambda: _ap_step([_at()], nt=-1)) == 1
