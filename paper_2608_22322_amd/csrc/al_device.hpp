@@ -302,22 +302,6 @@ __device__ __forceinline__ float div_to_f32(double x, double d, double rd) {
     return (float)(x / d);
 }
 
-// Four quotients at once, with one (rarely taken) branch for the fallbacks.
-__device__ __forceinline__ void div4_to_f32(const double x[4], double d, double rd, float out[4]) {
-    bool ok[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const double q = x[j] * rd;
-        out[j] = (float)q;
-        ok[j] = quotient_ok(q, out[j]);
-    }
-    if (__builtin_expect(!(ok[0] & ok[1] & ok[2] & ok[3]), 0)) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (!ok[j]) out[j] = (float)(x[j] / d);
-    }
-}
-
 // fp32 roundings of N approximate quotients. Each q_j lies within 8 binary64
 // ulps of the binary64 quotient fl64(x_j / d) whose fp32 rounding is wanted
 // (q_j = fl64(fl64(fl64(r * fl64(1 / d)) * c_j) * g_j) against x_j =
@@ -408,16 +392,6 @@ __device__ __forceinline__ double dd_value(DD a) { return a.hi + a.lo; }
 
 __device__ __forceinline__ DD dd_shfl_xor(DD a, int m) { return DD{__shfl_xor(a.hi, m), __shfl_xor(a.lo, m)}; }
 
-// Double-double of the partner lane within a quad (DPP, no LDS traffic):
-// CTRL = kDppQuadXor1 or kDppQuadXor2.
-template <int CTRL>
-__device__ __forceinline__ DD dd_quad_xor(DD a) {
-    const uint64_t h = __builtin_bit_cast(uint64_t, a.hi), l = __builtin_bit_cast(uint64_t, a.lo);
-    const uint64_t h2 = ((uint64_t)dpp<CTRL>((uint32_t)(h >> 32)) << 32) | dpp<CTRL>((uint32_t)h);
-    const uint64_t l2 = ((uint64_t)dpp<CTRL>((uint32_t)(l >> 32)) << 32) | dpp<CTRL>((uint32_t)l);
-    return DD{__builtin_bit_cast(double, h2), __builtin_bit_cast(double, l2)};
-}
-
 // A binary64 value of another lane of the same DPP row (CTRL: a quad
 // permutation or a row mirror).
 template <int CTRL>
@@ -440,16 +414,6 @@ __device__ __forceinline__ DD dd_wave_sum(DD a) {
 // addition in place of a rounding and a conversion.
 __device__ __forceinline__ uint32_t rint_low_bits(double y) {
     return (uint32_t)__builtin_bit_cast(uint64_t, y + 0x1.8p52);
-}
-
-// Encode with r = 127 / absmax (binary64), y = x * r, round to nearest even,
-// clamp to [-127, 127].
-__device__ __forceinline__ int32_t uf8_encode(float x, double r) {
-    double y = (double)x * r;
-    double q = __builtin_rint(y);
-    q = q > 127.0 ? 127.0 : q;
-    q = q < -127.0 ? -127.0 : q;
-    return (int32_t)q;
 }
 
 // fl64(x / 127) without a division, for x a finite fp32 value held in
@@ -494,65 +458,7 @@ __device__ __forceinline__ uint32_t pos_max_key(float x) {
     return (b & 0x80000000u) ? 0u : b;
 }
 
-// ------------------------------------------------------- packed 4-wide I/O
-struct F4 {
-    float v[4];
-};
-
-__device__ __forceinline__ F4 load_f4(const float* p) {
-    float4 t = *reinterpret_cast<const float4*>(p);
-    return F4{{t.x, t.y, t.z, t.w}};
-}
-__device__ __forceinline__ void store_f4(float* p, const F4& x) {
-    *reinterpret_cast<float4*>(p) = make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
-}
-
-// Gradients: 4 consecutive elements as fp32.
-template <int G>
-__device__ __forceinline__ F4 load_grad4(const void* g, int64_t e) {
-    if constexpr (G == G_BF16) {
-        uint2 w = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(g) + e);
-        return F4{{bf16_to_f32(w.x & 0xFFFFu), bf16_to_f32(w.x >> 16), bf16_to_f32(w.y & 0xFFFFu),
-                   bf16_to_f32(w.y >> 16)}};
-    } else {
-        return load_f4(reinterpret_cast<const float*>(g) + e);
-    }
-}
-
-template <int G>
-__device__ __forceinline__ float load_grad1(const void* g, int64_t e) {
-    if constexpr (G == G_BF16)
-        return bf16_to_f32(reinterpret_cast<const uint16_t*>(g)[e]);
-    else
-        return reinterpret_cast<const float*>(g)[e];
-}
-
-// Codes: 4 consecutive codes as unsigned (AL) or signed (UF8) integers.
-template <int C>
-__device__ __forceinline__ void load_codes4(const void* c, int64_t e, uint32_t q[4]) {
-    if constexpr (C == AL8 || C == UF8) {
-        uint32_t w = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(c) + e);
-        q[0] = w & 0xFFu;
-        q[1] = (w >> 8) & 0xFFu;
-        q[2] = (w >> 16) & 0xFFu;
-        q[3] = w >> 24;
-    } else {
-        uint2 w = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(c) + e);
-        q[0] = w.x & 0xFFFFu;
-        q[1] = w.x >> 16;
-        q[2] = w.y & 0xFFFFu;
-        q[3] = w.y >> 16;
-    }
-}
-
-template <int C>
-__device__ __forceinline__ uint32_t load_code1(const void* c, int64_t e) {
-    if constexpr (C == AL8 || C == UF8)
-        return reinterpret_cast<const uint8_t*>(c)[e];
-    else
-        return reinterpret_cast<const uint16_t*>(c)[e];
-}
-
+// ------------------------------------------------- streaming order and I/O
 // Workgroup id -> work unit for streaming kernels. The dispatcher hands
 // workgroups to the 8 XCDs round-robin (workgroup i to XCD i mod 8); this
 // gives each XCD a contiguous eighth of the units instead of every eighth
@@ -569,7 +475,6 @@ __device__ __forceinline__ int64_t xcd_order(uint32_t wg, uint32_t grid) {
 typedef float nt_f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t nt_u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t nt_u4 __attribute__((ext_vector_type(4)));
-typedef double nt_d2 __attribute__((ext_vector_type(2)));
 
 template <bool NT>
 __device__ __forceinline__ float4 ld_f4(const float* p) {
@@ -602,13 +507,6 @@ __device__ __forceinline__ void st_f4(float* p, const float4& x) {
         __builtin_nontemporal_store(nt_f4{x.x, x.y, x.z, x.w}, reinterpret_cast<nt_f4*>(p));
     else
         *reinterpret_cast<float4*>(p) = x;
-}
-template <bool NT>
-__device__ __forceinline__ void st_u2(void* p, const uint2& x) {
-    if constexpr (NT)
-        __builtin_nontemporal_store(nt_u2{x.x, x.y}, reinterpret_cast<nt_u2*>(p));
-    else
-        *reinterpret_cast<uint2*>(p) = x;
 }
 template <bool NT>
 __device__ __forceinline__ void st_u1(void* p, uint32_t x) {
@@ -679,9 +577,6 @@ __device__ __forceinline__ uint4 ld_u4(gp<const void> p) {
         return make_uint4(x.x, x.y, x.z, x.w);
     }
 }
-// Two binary64 values to 16-byte aligned global memory.
-__device__ __forceinline__ void st_d2(gp<double> p, double x, double y) { *g_as<nt_d2>(p) = nt_d2{x, y}; }
-
 template <bool NT>
 __device__ __forceinline__ uint32_t ld_u1(gp<const void> p) {
     if constexpr (NT)
@@ -737,14 +632,6 @@ __device__ __forceinline__ void store_codes4(gp<uint8_t> c, int64_t e, const uin
 }
 
 template <int C>
-__device__ __forceinline__ void store_code1(void* c, int64_t e, uint32_t q) {
-    if constexpr (C == AL8 || C == UF8)
-        reinterpret_cast<uint8_t*>(c)[e] = (uint8_t)q;
-    else
-        reinterpret_cast<uint16_t*>(c)[e] = (uint16_t)q;
-}
-
-template <int C>
 constexpr int levels_of() {
     return C == AL16 ? 65534 : 254;
 }
@@ -770,8 +657,7 @@ __device__ __forceinline__ void load_g4(gp<const void> g, int64_t e, float gv[4]
 }
 
 // Rows and columns of a lane's 4 consecutive elements of the flattening, one
-// 256-element sub-tile after another. step256: the way from a lane's element to
-// the one 256 further on.
+// 256-element sub-tile after another (next: 256 elements further on).
 struct FlatPos {
     int64_t rows, cols;
     int i, j;        // of the lane's first element (wide = false)

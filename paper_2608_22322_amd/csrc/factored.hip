@@ -86,14 +86,6 @@ __device__ __forceinline__ double res_diff(const FacArgs& a, float mh, float uh)
     return (double)uh - (double)m;
 }
 
-template <int G>
-__device__ __forceinline__ float grad1(const void* g, int64_t e) {
-    if constexpr (G == G_BF16)
-        return bf16_to_f32(reinterpret_cast<const uint16_t*>(g)[e]);
-    else
-        return reinterpret_cast<const float*>(g)[e];
-}
-
 // Decode element i of a vector state (runtime codec / block).
 __device__ __forceinline__ float vec_decode(int codec, int B, const void* codes, const float* meta, int64_t i,
                                             const Exp2Coef& cf) {
@@ -719,7 +711,7 @@ __device__ __forceinline__ void ada_vec1d(const FacArgs& a, const FacDesc& d, DD
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n = d.rows * d.cols;
     for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double gi = (double)grad1<G>(d.g, i);
+        const double gi = (double)grad_at_g<G>(to_g(d.g), i);
         const float old = vec_decode(a.v_codec, a.v_block, d.v, d.vm, i, a.cf);
         d.rtmp[i] = (float)(a.beta * (double)old + a.omb * (gi * gi + a.eps1));
     }
@@ -727,7 +719,7 @@ __device__ __forceinline__ void ada_vec1d(const FacArgs& a, const FacDesc& d, DD
     vec_encode(a.v_codec, a.v_block, d.rtmp, n, a.v_floor, d.v, d.vm, wave, 4, lane);
     DD s{0.0, 0.0};
     for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad_at_g<G>(to_g(d.g), i);
         dd_add(s, uu * uu);
     }
     s = block_dd_sum(s, sh);
@@ -738,7 +730,7 @@ __device__ __forceinline__ void ada_vec1d(const FacArgs& a, const FacDesc& d, DD
     __syncthreads();
     const double clip = clip_s;
     for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad_at_g<G>(to_g(d.g), i);
         const double pd = (double)d.p[i] * a.decay;
         d.p[i] = (float)(pd - a.lr * (uu / clip));
     }
@@ -764,7 +756,7 @@ __device__ __forceinline__ void came_vec1d(const FacArgs& a, const FacDesc& d, D
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n = d.rows * d.cols;
     for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double gi = (double)grad1<G>(d.g, i);
+        const double gi = (double)grad_at_g<G>(to_g(d.g), i);
         const float old = vec_decode(a.v_codec, a.v_block, d.v, d.vm, i, a.cf);
         d.rtmp[i] = (float)(a.beta * (double)old + a.omb * (gi * gi + a.eps1));
     }
@@ -772,7 +764,7 @@ __device__ __forceinline__ void came_vec1d(const FacArgs& a, const FacDesc& d, D
     vec_encode(a.v_codec, a.v_block, d.rtmp, n, a.v_floor, d.v, d.vm, wave, 4, lane);
     DD s{0.0, 0.0};
     for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad_at_g<G>(to_g(d.g), i);
         dd_add(s, uu * uu);
     }
     s = block_dd_sum(s, sh);
@@ -783,7 +775,7 @@ __device__ __forceinline__ void came_vec1d(const FacArgs& a, const FacDesc& d, D
     __syncthreads();
     const double clip = clip_s;
     for (int64_t i = tid; i < n; i += blockDim.x) {
-        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad1<G>(d.g, i);
+        const double uu = (1.0 / sqrt((double)d.rtmp[i])) * (double)grad_at_g<G>(to_g(d.g), i);
         const float uh = (float)(uu / clip);
         const float m = came_momentum(a, d, i, uh);
         d.ctmp[i] = m;
