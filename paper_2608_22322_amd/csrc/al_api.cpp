@@ -138,9 +138,15 @@ struct FacPlan {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Two wavefronts per SIMD. Measured on CAME over a 4-layer width-500 list (280 units of 256 rows, 2240 of
-// 32): 162 us with 1024 to 8192, 182 with 512; on Adafactor over a 12-layer width-768 list (2900 units of 256
-// rows): 501 us up to 2048, 521 with 4096 (units of 128 rows).
+// Two wavefronts per SIMD. us per step at unit heights of 256, 128, 64 and 32 rows:
+//   CAME, 4 layers of width 500, fp32 gradients (280 units of 256 rows): 32 rows 162, 64 rows 182
+//   Adafactor, bf16, 4096 x 4096 (256 units): - 83 68 67; CAME, 8192 x 4096 (512): 201 190 181 188
+//   Adafactor, bf16, 6 layers of 640 / 1750 twice over (1236): 245 229 217 219; 20000 x 6000 (1896): 335 333 338 354
+//   Adafactor, bf16, 16384 x 8192 (2048): 302 334 340; 12 layers of width 768 (2900): 501 521
+// Lists of whole units with bf16 gradients keep 256 rows from one wavefront per SIMD (kFacMinWhole): fewer rows
+// leave the whole units' layout, whose passes are the faster ones (6 layers of 1024 / 2816, 1032 units: Adafactor
+// 187 213 202 201, CAME 334 366 339 336; fp32 gradients 253 260 248 250 and 446 419 397 397).
+constexpr int64_t kFacMinWhole = 1024;
 constexpr int64_t kFacMinUnits = 2048;
 // A list cut into units of fewer than 256 rows has fewer than kFacMinUnits of twice the height, so at most this many
 // units, and fewer than kFacMinUnits tensors: its column partials (2048 bytes a unit, each tensor's region aligned)
@@ -230,13 +236,14 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, int32_t grad_dtype, c
     int64_t longest = 0;
     for (int i : oned) longest = std::max(longest, ts[i].cols);
     if (P.n2 > 0 && longest <= (grad_dtype == AL_DTYPE_BF16 ? 16384 : 32768)) P.lead = P.n1;
-    // Unit rows: 256, halved down to 32 while the list has fewer than kFacMinUnits units (one wavefront
+    // Unit rows: 256, halved down to 32 while the list has fewer than kFacMinUnits (kFacMinWhole) units (one wavefront
     // each): a short list's passes are bound by the longest wavefront, not by memory. More, shorter units
     // cost column partials (8 bytes per column and unit row), which a short list hardly notices.
+    const bool all_whole = grad_dtype == AL_DTYPE_BF16 && others == twod.end();
     for (;; P.ur /= 2) {
         int64_t units = 0;
         for (int i : twod) units += ((ts[i].rows + P.ur - 1) / P.ur) * ((ts[i].cols + 255) / 256);
-        if (units >= kFacMinUnits || P.ur == 32) break;
+        if (units >= (all_whole && P.ur == 256 ? kFacMinWhole : kFacMinUnits) || P.ur == 32) break;
     }
     size_t off = align256((size_t)ntot * sizeof(al::FacDesc));
     P.index_off = off;
