@@ -130,7 +130,7 @@ struct FacPlan {
     std::vector<al::FacRec> rec;  // 2-D tensors first, then 1-D
     int n2 = 0, n1 = 0, lead = 0;
     int64_t total_units = 0, total_ach = 0, total_mt = 0, whole_ach = 0, rows_ach = 0;
-    int32_t ur = 256, any_whole = 0, any_edge = 0;
+    int32_t ur = 256, any_whole = 0, any_edge = 0, any_ragged = 0;
     int64_t total_blk[2] = {0, 0};
     size_t bytes = 0;
     size_t index_off = 0, rms_off = 0;
@@ -259,6 +259,7 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, int32_t grad_dtype, c
         if (by_rows(t)) P.rows_ach = P.total_ach;
         if (whole(t)) P.whole_ach = P.total_ach;
         if (by_rows(t) && P.ur == 256 && t.rows >= 256) P.any_whole = 1;
+        if (!whole(t)) P.any_ragged = 1;
         if (!whole(t) || P.ur != 256) P.any_edge = 1;
         r[al::kRecMt] = (uint64_t)P.total_mt;
         P.total_mt += (t.rows + 63) / 64 + (t.cols + 63) / 64;
@@ -329,6 +330,7 @@ al::FacArgs fac_args(const FacPlan& P, char* ws) {
     a.rows_ach = P.rows_ach;
     a.any_whole = P.any_whole;
     a.any_edge = P.any_edge;
+    a.any_ragged = P.any_ragged;
     a.ur = P.ur;
     a.total_blk[0] = P.total_blk[0];
     a.total_blk[1] = P.total_blk[1];

@@ -217,7 +217,9 @@ struct FacArgs {
     // are a multiple of 256; the rest: flattened chunks
     int64_t whole_ach, rows_ach;
     int32_t ur;           // unit rows: 256, or 128 / 64 / 32 for lists of few units
-    int32_t any_whole, any_edge;  // some units are whole 256 x 256 units of a width that is a multiple of 256; some are not, or their matrix is not made of them
+    // some units are whole 256 x 256 units of a width that is a multiple of 256; some are not; some matrix has rows or
+    // columns that are not a multiple of 256
+    int32_t any_whole, any_edge, any_ragged;
     int64_t total_blk[2];  // code blocks over all 2-D tensors' R and C, per role
     double beta, omb;     // second-moment EMA: Adafactor beta2_t / CAME beta2, and 1 - beta
     double beta1, omb1;   // CAME momentum

@@ -1126,15 +1126,17 @@ hipError_t launch_fac_fin(const FacArgs& a, int role, int grad_dtype, hipStream_
 // u_ij = (r_i c_j) g_ij, exactly the oracle's operation order. One wave per unit.
 //
 // Edge units (see edge_unit_sums): left-out elements have g = 0 (and row
-// factor 0 past the last row). Every term u^2 is added double-double, so a unit's
-// partial is its exact sum to about 2^-100.
+// factor 0 past the last row). TERMS (lists with a ragged matrix): every
+// term u^2 is added double-double, so a unit's partial is its exact sum to about
+// 2^-100. Otherwise the 8 terms of a lane's row are added pairwise first, as in the
+// whole units' layout below.
 template <int G>
 struct EdgeRmsBatch {
     Raw8<G> r[kEdgeNR / 2];
     double ri[kEdgeNR / 2];
 };
 
-template <int G>
+template <int G, bool TERMS>
 __device__ __forceinline__ DD edge_unit_rms(const GD& d, const EdgeLane& w) {
     constexpr int NR = kEdgeNR, NP = NR / 2;
     const int nr = w.nr, sh = w.sh;
@@ -1160,11 +1162,14 @@ __device__ __forceinline__ DD edge_unit_rms(const GD& d, const EdgeLane& w) {
                 const double ri = ok ? b.ri[k] : 0.0;
                 float gv[8];
                 unpack8<G>(b.r[k], gv);
+                double t[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const double uu = (ri * cf[j]) * (double)(((j >= sh) & ok) ? gv[j] : 0.0f);
-                    dd_add(acc, uu * uu);
+                    t[j] = uu * uu;
+                    if constexpr (TERMS) dd_add(acc, t[j]);
                 }
+                if constexpr (!TERMS) dd_add(acc, sum8(t));
             }
         });
     return acc;
@@ -1246,22 +1251,27 @@ __device__ __forceinline__ DD whole_unit_rms(const GD& d, int64_t ru, int64_t cu
     return acc;
 }
 
-// WHOLE: a list of whole units alone, without the term-by-term bodies, whose registers cost a wavefront per SIMD
-// (the 1.1B list's step 2617 us with the kernel below, 2627 with the other).
-template <int G, bool WHOLE>
+// By what the list holds, so that a list pays for no other body's registers: matrices of whole units, cut 256 rows
+// high (kRmsWhole: the 1.1B list's step 2617 us, 2627 with kRmsMixed's kernel) or less (kRmsShort), or some ragged
+// matrix (kRmsMixed; whole matrices cut less than 256 rows high are then summed term by term too).
+enum RmsKind { kRmsWhole, kRmsShort, kRmsMixed };
+
+template <int G, int KIND>
 __global__ __launch_bounds__(256) void fac_rms_kernel(const FacArgs a, int64_t base) {
     const int64_t unit = unit_of_wave(base);
     if (unit >= a.total_units) return;
     const GD d = gview(a.D[locate(a.unit_begins, a.n2, unit)]);
     const int64_t u = unit - d.unit_begin, ru = u / d.ncu, cu = u % d.ncu;
     DD acc;
-    if constexpr (WHOLE) {
+    if constexpr (KIND == kRmsWhole) {
         acc = whole_unit_rms<G, false>(d, ru, cu);
+    } else if constexpr (KIND == kRmsShort) {
+        acc = edge_unit_rms<G, false>(d, edge_lane(d, a.ur, ru, cu));
     } else {
         if (whole_unit(a, d, ru))
             acc = (d.rows & 255) == 0 ? whole_unit_rms<G, false>(d, ru, cu) : whole_unit_rms<G, true>(d, ru, cu);
         else if (d.cols >= 8)
-            acc = edge_unit_rms<G>(d, edge_lane(d, a.ur, ru, cu));
+            acc = edge_unit_rms<G, true>(d, edge_lane(d, a.ur, ru, cu));
         else
             acc = narrow_unit_rms<G>(d, a.ur, ru);
     }
@@ -1272,13 +1282,15 @@ __global__ __launch_bounds__(256) void fac_rms_kernel(const FacArgs a, int64_t b
     }
 }
 
+template <int G>
+static hipError_t rms_launch(const FacArgs& a, hipStream_t s) {
+    if (a.any_ragged) return launch_wave_per_unit(fac_rms_kernel<G, kRmsMixed>, a, s);
+    return a.ur == 256 ? launch_wave_per_unit(fac_rms_kernel<G, kRmsWhole>, a, s)
+                       : launch_wave_per_unit(fac_rms_kernel<G, kRmsShort>, a, s);
+}
+
 hipError_t launch_fac_rms(const FacArgs& a, int grad_dtype, hipStream_t s) {
-    const bool bf = grad_dtype == G_BF16;
-    if (!a.any_edge)
-        return bf ? launch_wave_per_unit(fac_rms_kernel<G_BF16, true>, a, s)
-                  : launch_wave_per_unit(fac_rms_kernel<G_F32, true>, a, s);
-    return bf ? launch_wave_per_unit(fac_rms_kernel<G_BF16, false>, a, s)
-              : launch_wave_per_unit(fac_rms_kernel<G_F32, false>, a, s);
+    return grad_dtype == G_BF16 ? rms_launch<G_BF16>(a, s) : rms_launch<G_F32>(a, s);
 }
 
 // ------------------------------------------ clip divisor (workgroup / tensor)
