@@ -9,7 +9,7 @@ steps with HIP events on the launch stream. The headline is B_V = 2048, the
 second-moment block of the paper's AdamW configuration (Table 4); the
 block-size sweep {64, 128, 256, 512, 1024, 2048} is reported alongside, as are the
 measured streaming rates of the same byte mix (al_diag_stream: the step's access
-shape, and the fastest shape found for the mix).
+shape at B_V 2048, and the fastest shape found for the mix).
 
 Prints ONE JSON line on stdout (progress goes to stderr).
 """
@@ -122,7 +122,7 @@ def time_adamw(states, block_v, steps, warmup):
 
 def copy_ceiling(n, steps=10):
     """Streaming rates of the AdamW byte mix (al_diag_stream: read p/g/m/v, write p/m/v, no arithmetic) on flat
-    buffers of n elements: the step's own access shape (ordinary and non-temporal) and the fastest shape found
+    buffers of n elements: the step's access shape at B_V 2048 (ordinary and non-temporal) and the fastest shape found
     for the mix (4096-element chunks, 16 bytes per lane from every stream, all loads before any store)."""
     import torch
 

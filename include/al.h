@@ -357,9 +357,9 @@ al_status al_diff_norms(const float* a, const float* b, int64_t n, double* out, 
 /* Diagnostic: streaming rates of the fused AdamW byte mix. Reads p (n fp32),
  * g (n bf16), m and v (n bytes each) and writes p, m, v with no optimizer
  * arithmetic. mode selects the access shape:
- *   0, 1  the shape of al_adamw_step (one 2048-element chunk per wavefront in
- *         two load phases, 4 consecutive elements per lane, XCD-contiguous
- *         workgroup order); mode 1 uses non-temporal loads and stores. Writes
+ *   0, 1  the shape of al_adamw_step at block 2048 (one 2048-element chunk per
+ *         wavefront in two load phases, 4 consecutive elements per lane,
+ *         XCD-contiguous workgroup order); mode 1 uses non-temporal loads and stores. Writes
  *         p[4i] += g[4i], p[4i+3] += g[4i+3] (g as bf16), m ^= v, v += 1 per
  *         byte. n must be a multiple of 2048.
  *   2, 3  the fastest shape found for the mix (one 4096-element chunk per

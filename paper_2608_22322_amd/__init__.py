@@ -213,7 +213,7 @@ def diag_levels(kind: int, meta, nblocks: int, out, stream=None) -> None:
 
 
 def diag_stream(nontemporal: bool, p, g, m, v, stream=None, wide: bool = False) -> None:
-    """Streaming rate probe of the AdamW byte mix (al_diag_stream): the step's access shape, or with wide=True
+    """Streaming rate probe of the AdamW byte mix (al_diag_stream): the step's access shape at B_V 2048, or with wide=True
     the fastest shape found for the mix (4096-element chunks, 16 bytes per lane from every stream)."""
     mode = (2 | 1) if wide else int(bool(nontemporal))
     check(lib().al_diag_stream(mode, _ptr(p), _ptr(g), _ptr(m), _ptr(v), p.numel(), _stream(stream)))

@@ -235,8 +235,8 @@ __device__ __forceinline__ ALEnc al_enc_params(double lmin, double inv) {
 // guard of a rounding boundary is recomputed with the binary64 log2 of the fp32
 // value, so the rounding decision is the binary64 one. The position is rounded by
 // adding 1.5 2^52 (the low word of the sum is the code's offset). An AL16 block
-// rechecks about one element in 500 at a width of 15 bits, so most wavefronts
-// take that branch for some of their elements: fit_log2 costs half the general
+// rechecks about one element in 240 at a width of 15 bits (twice the guard, 65534 / 15 2^-21), so most
+// wavefronts take that branch for some of their elements: fit_log2 costs half the general
 // logarithm there.
 template <int LEVELS>
 __device__ __forceinline__ uint32_t al_encode_fast(float x, const ALEnc& p) {

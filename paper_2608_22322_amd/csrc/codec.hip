@@ -414,9 +414,10 @@ hipError_t launch_diff_norms(const float* a, const float* b, int64_t n, double* 
 
 // Streaming ceiling of the fused AdamW access pattern: per element read p
 // (fp32), g (bf16), m and v (1 byte each), write p, m, v -- the same bytes,
-// lane mapping and launch shape as the AdamW kernel (one 2048-element chunk
+// lane mapping and launch shape as the AdamW kernel at B_V 2048 (one 2048-element chunk
 // per wavefront in two load phases of four 256-element sub-tiles, 4
-// consecutive elements per lane, XCD-contiguous workgroup order), with no
+// consecutive elements per lane, XCD-contiguous workgroup order; smaller blocks take
+// chunks of 512 or 1024 in one phase but in long lists), with no
 // optimizer arithmetic. NT selects non-temporal loads and stores.
 template <bool NT>
 __global__ __launch_bounds__(256) void stream_kernel(float* __restrict__ p, const uint16_t* __restrict__ g,
