@@ -129,8 +129,8 @@ al_status check_ws(void* ws, size_t ws_bytes, size_t need, const char* who) {
 struct FacPlan {
     std::vector<al::FacRec> rec;  // 2-D tensors first, then 1-D
     int n2 = 0, n1 = 0, lead = 0;
-    int64_t total_units = 0, total_ach = 0, total_mt = 0, whole_ach = 0, rows_ach = 0;
-    int32_t ur = 256, any_whole = 0, any_edge = 0, any_ragged = 0;
+    int64_t total_units = 0, total_ach = 0, total_mt = 0, rows_ach = 0;
+    int32_t ur = 256, any_whole = 0, any_edge = 0, any_ragged = 0, rows_ragged = 0;
     int64_t total_blk[2] = {0, 0};
     size_t bytes = 0;
     size_t index_off = 0, rms_off = 0;
@@ -218,12 +218,11 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, int32_t grad_dtype, c
             if ((st = check_unused(t.m, t.m_meta, "m", i)) != AL_OK) return st;
         }
     }
-    // whole units first, then the other widths that are a multiple of 256 (the apply passes take both by rows;
-    // CAME's update of p is fp32 in the former, binary64 in the latter), in list order within each group
+    // widths that are a multiple of 256 first (the apply passes take them by rows), in list order within
+    // each group
     const auto by_rows = [](const al_tensor& t) { return t.cols % 256 == 0; };
     const auto whole = [](const al_tensor& t) { return t.rows % 256 == 0 && t.cols % 256 == 0; };
-    const auto others = std::stable_partition(twod.begin(), twod.end(), [&](int i) { return whole(ts[i]); });
-    std::stable_partition(others, twod.end(), [&](int i) { return by_rows(ts[i]); });
+    std::stable_partition(twod.begin(), twod.end(), [&](int i) { return by_rows(ts[i]); });
     P.n2 = (int)twod.size();
     P.n1 = (int)oned.size();
     const int ntot = P.n2 + P.n1;
@@ -239,7 +238,7 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, int32_t grad_dtype, c
     // Unit rows: 256, halved down to 32 while the list has fewer than kFacMinUnits (kFacMinWhole) units (one wavefront
     // each): a short list's passes are bound by the longest wavefront, not by memory. More, shorter units
     // cost column partials (8 bytes per column and unit row), which a short list hardly notices.
-    const bool all_whole = grad_dtype == AL_DTYPE_BF16 && others == twod.end();
+    const bool all_whole = grad_dtype == AL_DTYPE_BF16 && std::all_of(twod.begin(), twod.end(), [&](int i) { return whole(ts[i]); });
     for (;; P.ur /= 2) {
         int64_t units = 0;
         for (int i : twod) units += ((ts[i].rows + P.ur - 1) / P.ur) * ((ts[i].cols + 255) / 256);
@@ -257,9 +256,9 @@ al_status fac_plan(const al_tensor* ts, int nt, bool came, int32_t grad_dtype, c
         r[al::kRecAch] = (uint64_t)P.total_ach;
         P.total_ach += by_rows(t) ? ((t.rows + 255) / 256) * ncu * 32 : (t.rows * t.cols + al::kFacFlatChunk - 1) / al::kFacFlatChunk;
         if (by_rows(t)) P.rows_ach = P.total_ach;
-        if (whole(t)) P.whole_ach = P.total_ach;
         if (by_rows(t) && P.ur == 256 && t.rows >= 256) P.any_whole = 1;
         if (!whole(t)) P.any_ragged = 1;
+        if (by_rows(t) && !whole(t)) P.rows_ragged = 1;
         if (!whole(t) || P.ur != 256) P.any_edge = 1;
         r[al::kRecMt] = (uint64_t)P.total_mt;
         P.total_mt += (t.rows + 63) / 64 + (t.cols + 63) / 64;
@@ -326,11 +325,11 @@ al::FacArgs fac_args(const FacPlan& P, char* ws) {
     a.total_units = P.total_units;
     a.total_ach = P.total_ach;
     a.total_mt = P.total_mt;
-    a.whole_ach = P.whole_ach;
     a.rows_ach = P.rows_ach;
     a.any_whole = P.any_whole;
     a.any_edge = P.any_edge;
     a.any_ragged = P.any_ragged;
+    a.rows_ragged = P.rows_ragged;
     a.ur = P.ur;
     a.total_blk[0] = P.total_blk[0];
     a.total_blk[1] = P.total_blk[1];

@@ -213,13 +213,12 @@ struct FacArgs {
     int32_t n2, n1;       // 2-D tensors, 1-D tensors (D[n2 .. n2 + n1))
     int32_t lead;         // n1: the marginal kernel's first workgroups step the 1-D tensors; 0: a launch of their own does
     int64_t total_units, total_ach, total_mt;
-    // apply chunks [0, whole_ach): tensors of whole units, listed first; [whole_ach, rows_ach): the other widths that
-    // are a multiple of 256; the rest: flattened chunks
-    int64_t whole_ach, rows_ach;
+    int64_t rows_ach;     // apply chunks [0, rows_ach): the tensors of widths that are a multiple of 256, listed first
     int32_t ur;           // unit rows: 256, or 128 / 64 / 32 for lists of few units
     // some units are whole 256 x 256 units of a width that is a multiple of 256; some are not; some matrix has rows or
     // columns that are not a multiple of 256
     int32_t any_whole, any_edge, any_ragged;
+    int32_t rows_ragged;  // some matrix of a width that is a multiple of 256 has rows that are not
     int64_t total_blk[2];  // code blocks over all 2-D tensors' R and C, per role
     double beta, omb;     // second-moment EMA: Adafactor beta2_t / CAME beta2, and 1 - beta
     double beta1, omb1;   // CAME momentum

@@ -2019,18 +2019,29 @@ __device__ __forceinline__ void came_apply_rows(const FacArgs& a, const GD& d, i
     }
 }
 
+// Chunk c of a matrix, of which `left` rows start in the chunk or after it.
 template <int G, bool UF, bool WHOLE>
-__global__ __launch_bounds__(256) void came_apply_kernel(const FacArgs a, int64_t base) {
-    const int64_t chunk = chunk_of_wave(base);
-    if (chunk >= (WHOLE ? a.whole_ach : a.rows_ach)) return;
-    const GD d = gview(a.D[locate(a.ach_begins, a.n2, chunk)]);
-    const RowChunk c = row_chunk<kCameApplyW>(d, chunk - d.ach_begin);
-    const int64_t left = d.rows - c.row0;
-    if (left <= 0) return;
+__device__ __forceinline__ void came_apply_chunk(const FacArgs& a, const GD& d, const RowChunk& c, int64_t left) {
     if (c.full)
         came_apply_rows<G, UF, kCameApplyW, WHOLE>(a, d, c.row0, c.col0, left < 8 / kCameApplyW ? (int)left : 8 / kCameApplyW);
     else
         came_apply_rows<G, UF, 1, WHOLE>(a, d, c.row0, c.col0, left < 8 ? (int)left : 8);
+}
+
+// MIXED: some width that is a multiple of 256 has ragged rows (the binary64 body's registers cost lists of whole
+// units 0.4% of a step; a launch of its own would cost short lists more).
+template <int G, bool UF, bool MIXED>
+__global__ __launch_bounds__(256) void came_apply_kernel(const FacArgs a, int64_t base) {
+    const int64_t chunk = chunk_of_wave(base);
+    if (chunk >= a.rows_ach) return;
+    const GD d = gview(a.D[locate(a.ach_begins, a.n2, chunk)]);
+    const RowChunk c = row_chunk<kCameApplyW>(d, chunk - d.ach_begin);
+    const int64_t left = d.rows - c.row0;
+    if (left <= 0) return;
+    if (!MIXED || (d.rows & 255) == 0)
+        came_apply_chunk<G, UF, true>(a, d, c, left);
+    else
+        came_apply_chunk<G, UF, false>(a, d, c, left);
 }
 
 template <int G, bool UF>
@@ -2047,8 +2058,8 @@ __global__ __launch_bounds__(256) void came_apply_flat_kernel(const FacArgs a, i
 
 template <int G, bool UF>
 static hipError_t came_apply_launch(const FacArgs& a, hipStream_t s) {
-    hipError_t e = launch_per_chunk(came_apply_kernel<G, UF, true>, a, 0, a.whole_ach, s);
-    if (e == hipSuccess) e = launch_per_chunk(came_apply_kernel<G, UF, false>, a, a.whole_ach, a.rows_ach, s);
+    const hipError_t e = a.rows_ragged ? launch_per_chunk(came_apply_kernel<G, UF, true>, a, 0, a.rows_ach, s)
+                                       : launch_per_chunk(came_apply_kernel<G, UF, false>, a, 0, a.rows_ach, s);
     return e != hipSuccess ? e : launch_per_chunk(came_apply_flat_kernel<G, UF>, a, a.rows_ach, a.total_ach, s);
 }
 
