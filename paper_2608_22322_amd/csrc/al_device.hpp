@@ -379,6 +379,30 @@ __device__ __forceinline__ void dd_add(DD& a, double x) {
     a.lo += e;
 }
 
+// Eight non-negative terms one after another, as dd_add would: where none of them
+// exceeds the running sum on any lane (after the first few, all but outliers) the
+// error of each addition is Fast2Sum's (Dekker: exact for a.hi >= x), half the
+// operations. The comparison takes the high words, so a.hi >= x wherever it holds.
+__device__ __forceinline__ void dd_add8(DD& a, const double x[8]) {
+    uint32_t top = 0u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t h = (uint32_t)(__builtin_bit_cast(uint64_t, x[j]) >> 32);
+        top = h > top ? h : top;
+    }
+    if (__builtin_expect(__all(top < (uint32_t)(__builtin_bit_cast(uint64_t, a.hi) >> 32)), 1)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const double s = a.hi + x[j];
+            a.lo += x[j] - (s - a.hi);
+            a.hi = s;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dd_add(a, x[j]);
+    }
+}
+
 __device__ __forceinline__ DD dd_merge(DD a, DD b) {
     const double s = a.hi + b.hi;
     const double bp = s - a.hi;

@@ -1167,9 +1167,11 @@ __device__ __forceinline__ DD edge_unit_rms(const GD& d, const EdgeLane& w) {
                 for (int j = 0; j < 8; ++j) {
                     const double uu = (ri * cf[j]) * (double)(((j >= sh) & ok) ? gv[j] : 0.0f);
                     t[j] = uu * uu;
-                    if constexpr (TERMS) dd_add(acc, t[j]);
                 }
-                if constexpr (!TERMS) dd_add(acc, sum8(t));
+                if constexpr (TERMS)
+                    dd_add8(acc, t);
+                else
+                    dd_add(acc, sum8(t));
             }
         });
     return acc;
@@ -1226,9 +1228,11 @@ __device__ __forceinline__ DD whole_unit_rms(const GD& d, int64_t ru, int64_t cu
             for (int j = 0; j < 8; ++j) {
                 const double uu = (ri[k] * cf[j]) * (double)gv[j];
                 t[j] = uu * uu;
-                if constexpr (TERMS) dd_add(acc, t[j]);
             }
-            if constexpr (!TERMS) dd_add(acc, sum8(t));
+            if constexpr (TERMS)
+                dd_add8(acc, t);
+            else
+                dd_add(acc, sum8(t));
         }
     };
     constexpr int NB = 256 / NR;
