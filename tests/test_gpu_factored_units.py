@@ -72,3 +72,29 @@ def test_unit_heights_fast_sums_equal_exact(dev, rows, cols, came, uf8, grad_bf1
                 x, y = getattr(a, name), getattr(b, name)
                 assert x is None or torch.equal(x, y), f"step {t} tensor {i} {name}: exact-sums path differs"
     log(f"{rows}x{cols} came={came} uf8={uf8} bf16={grad_bf16}: fast sums equal exact sums")
+
+
+# lists of whole units alone: 1025 units of 256 rows stay whole with bf16 gradients and are cut to 128 rows with
+# fp32 ones; 260 units are cut to 32 rows with either
+@pytest.mark.parametrize("rows,cols", [(8192, 8192), (4096, 4096)])
+@pytest.mark.parametrize("came,grad_bf16", [(False, True), (False, False), (True, True), (True, False)])
+def test_whole_lists_fast_sums_equal_exact(dev, rows, cols, came, grad_bf16):
+    import torch
+
+    import paper_2608_22322_amd as al
+
+    shapes = [Shape("w", rows, cols), Shape("x", 256, 256), Shape("y", 512, 256), Shape("norm", 1, 515)]
+    w = Workload("whole", shapes, grad_bf16=grad_bf16, zero_frac=0.02, steps=2)
+    kw = _kw(al, came, True)
+    v = kw.pop("vspec")
+    fast = FacPair(dev, shapes, w, came, v, sample=[1, 2, 3], **kw)
+    exact = FacPair(dev, shapes, w, came, v, exact=True, sample=[], **kw)
+    for t in (1, 2):
+        fast.step(t)
+        exact.step(t)
+        fast.compare(t, 1e-5 * t)
+        for i, (a, b) in enumerate(zip(fast.states, exact.states)):
+            for name in ("param", "m", "m_meta", "v", "v_meta", "vr", "vr_meta", "vc", "vc_meta", "cr", "cr_meta",
+                         "cc", "cc_meta"):
+                x, y = getattr(a, name), getattr(b, name)
+                assert x is None or torch.equal(x, y), f"step {t} tensor {i} {name}: exact-sums path differs"
